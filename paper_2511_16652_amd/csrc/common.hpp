@@ -100,6 +100,15 @@ egg_status validate_shape(eggroll_ctx* c, const egg_shape* s, bool need_rows, bo
 // entry points implemented per translation unit (kernel launchers)
 egg_status launch_noise(eggroll_ctx* c, const StreamKey& k, uint32_t member_begin, int64_t members, int64_t n,
                         egg_dtype dtype, egg_dist dist, int int_bound, void* out);
+// several vectors of the same members and type (the factors of a layer's matrices): one launch for those made of whole
+// 16-byte pieces, of up to 20 vectors
+struct NoiseJob {
+    StreamKey key;
+    int64_t n;  // values per member
+    void* out;
+};
+egg_status launch_noise_jobs(eggroll_ctx* c, const NoiseJob* jobs, int count, uint32_t member_begin, int64_t members, egg_dtype dtype,
+                             egg_dist dist, int int_bound);
 egg_status launch_project(eggroll_ctx* c, const StreamKey& kb, const egg_shape& s, egg_dtype io, const void* X,
                           float* t, void* B_cache, bool panel);
 // A layer whose output feeds the next perturbed layer directly (up-projection -> down-projection) can form that

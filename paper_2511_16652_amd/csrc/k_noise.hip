@@ -1,10 +1,12 @@
 // eggroll_noise_gen: materialise factor entries [member][n] from the counter-based stream
 // (Sec. 1: the factors are reconstructed on demand rather than kept; Alg. 1 sampling lines).
-// One thread expands one Threefry block: two normals, two raw words, or eight bounded integers.
-// Integer-ALU bound; stores are contiguous per wave.
+// Vectors made of whole 16-byte pieces (every multiple of 16 bytes: what the models use) go through noise_pieces_kernel;
+// noise_gen_kernel takes any length, one Threefry block a thread: two normals, two raw words, or eight bounded integers.
 #include "common.hpp"
 
 namespace egg {
+
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 enum NoiseMode { NM_F32 = 0, NM_BF16 = 1, NM_I8 = 2, NM_RAW = 3, NM_I8_TABLE = 4 };
 
@@ -74,19 +76,76 @@ __global__ __launch_bounds__(256) void noise_gen_kernel(StreamKey key, uint32_t 
     }
 }
 
-egg_status launch_noise(eggroll_ctx* c, const StreamKey& k, uint32_t member_begin, int64_t members, int64_t n,
+// The same values by whole 16-byte pieces of the output, for vectors that are made of them (n * element size a multiple of
+// 16; the output is then one run of pieces).  A thread expands the 2 or 4 Threefry blocks of one piece -- independent
+// chains that fill each other's latency -- and stores it once; the member of a piece comes from a multiply instead of the
+// 64-bit division that the general kernel spends on every block, which was as long as the generator itself.
+// Several vectors of the same members (the factors of a layer's matrices) go out in one launch: a workgroup looks up its
+// vector by its number.  Vector-ALU bound.
+struct NoisePiece {
+    StreamKey key;
+    FastDiv per_member;   // pieces per member
+    uint32_t total;       // pieces
+    uint32_t first_wg;    // first workgroup of the vector
+    u32x4_t* out;
+};
+constexpr int NOISE_JOBS = 20;
+struct NoisePieces {
+    int count;
+    NoisePiece job[NOISE_JOBS];
+};
+
+template <int MODE>
+__global__ __launch_bounds__(256) void noise_pieces_kernel(NoisePieces jobs, uint32_t member_begin, IntMap im,
+                                                           const int8_t* __restrict__ table)
+{
+    constexpr int BPP = (MODE == NM_BF16 || MODE == NM_I8_TABLE) ? 4 : 2;  // Threefry blocks per piece
+    int j = 0;
+    while (j + 1 < jobs.count && blockIdx.x >= jobs.job[j + 1].first_wg) ++j;
+    const NoisePiece& J = jobs.job[j];
+    const uint32_t i = (blockIdx.x - J.first_wg) * 256u + threadIdx.x;
+    if (i >= J.total) return;
+    const uint32_t m = fast_div(J.per_member, i);
+    const uint32_t blk = (i - m * J.per_member.d) * BPP;
+    uint32_t w[2 * BPP];
+#pragma unroll
+    for (int b = 0; b < BPP; ++b) noise_words(J.key, member_begin + m, blk + b, w[2 * b], w[2 * b + 1]);
+    uint32_t o[4];
+    if constexpr (MODE == NM_BF16) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            float z0, z1;
+            normal_pair<false>(w[2 * b], w[2 * b + 1], z0, z1);
+            o[b] = pack_bf16x2(z0, z1);
+        }
+    } else if constexpr (MODE == NM_F32) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            float z0, z1;
+            normal_pair<true>(w[2 * b], w[2 * b + 1], z0, z1);
+            o[2 * b] = __float_as_uint(z0);
+            o[2 * b + 1] = __float_as_uint(z1);
+        }
+    } else if constexpr (MODE == NM_RAW) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) o[b] = w[b];
+    } else if constexpr (MODE == NM_I8_TABLE) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+            o[b] = (uint32_t)(uint8_t)table[w[2 * b] & 0xFFFFu] | ((uint32_t)(uint8_t)table[w[2 * b] >> 16] << 8) |
+                   ((uint32_t)(uint8_t)table[w[2 * b + 1] & 0xFFFFu] << 16) | ((uint32_t)(uint8_t)table[w[2 * b + 1] >> 16] << 24);
+    } else {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) o[b] = int4_from_word(im, w[b]);
+    }
+    J.out[i] = u32x4_t{o[0], o[1], o[2], o[3]};
+}
+
+static egg_status launch_noise_general(eggroll_ctx* c, const StreamKey& k, uint32_t member_begin, int64_t members, int64_t n,
                         egg_dtype dtype, egg_dist dist, int int_bound, void* out)
 {
     const bool table = dist == EGG_NORMAL_INT16 || (dist == EGG_UNIFORM_INT && int_bound == EGG_INT_NOISE_NORMAL16);
     const int vpb = table ? 4 : (dist == EGG_UNIFORM_INT ? 8 : 2);
-    if (table && !c->norm_tab.p) {
-        // first use on this context: build the table on the host and upload it (a blocking copy)
-        std::vector<int8_t> h(65536);
-        normal_int_table(h.data());
-        egg_status st = reserve(c, c->norm_tab, 65536);
-        if (st != EGG_OK) return st;
-        if ((st = check_hip(c, hipMemcpy(c->norm_tab.p, h.data(), 65536, hipMemcpyHostToDevice), "upload of the integer normal table")) != EGG_OK) return st;
-    }
     const int64_t bpm = (n + vpb - 1) / vpb;
     if (bpm > (int64_t(1) << 32)) return fail(c, EGG_EUNSUPPORTED, "factor vector too long");
     const int64_t total = members * bpm;
@@ -107,6 +166,62 @@ egg_status launch_noise(eggroll_ctx* c, const StreamKey& k, uint32_t member_begi
     else
         hipLaunchKernelGGL(noise_gen_kernel<NM_BF16>, g, b, 0, c->stream, k, member_begin, members, n, bpm, im, tab, out);
     return check_hip(c, hipGetLastError(), "noise_gen launch");
+}
+
+egg_status launch_noise_jobs(eggroll_ctx* c, const NoiseJob* jobs, int count, uint32_t member_begin, int64_t members, egg_dtype dtype,
+                             egg_dist dist, int int_bound)
+{
+    const bool table = dist == EGG_NORMAL_INT16 || (dist == EGG_UNIFORM_INT && int_bound == EGG_INT_NOISE_NORMAL16);
+    if (table && !c->norm_tab.p) {
+        // first use on this context: build the table on the host and upload it (a blocking copy)
+        std::vector<int8_t> h(65536);
+        normal_int_table(h.data());
+        egg_status st = reserve(c, c->norm_tab, 65536);
+        if (st != EGG_OK) return st;
+        if ((st = check_hip(c, hipMemcpy(c->norm_tab.p, h.data(), 65536, hipMemcpyHostToDevice), "upload of the integer normal table")) != EGG_OK) return st;
+    }
+    const int per_piece = dist == EGG_RAW ? 4 : (table || dist == EGG_UNIFORM_INT ? 16 : (dtype == EGG_F32 ? 4 : 8));  // values
+    const IntMap im = make_int_map(dist == EGG_UNIFORM_INT && !table ? int_bound : 0);
+    const int8_t* tab = (const int8_t*)c->norm_tab.p;
+    NoisePieces np{};
+    uint32_t wgs = 0;
+    auto flush = [&]() -> egg_status {
+        if (np.count == 0) return EGG_OK;
+        KernelScope ks(c, "noise_gen");
+        const dim3 g(wgs), b(256);
+        if (dist == EGG_RAW) hipLaunchKernelGGL(noise_pieces_kernel<NM_RAW>, g, b, 0, c->stream, np, member_begin, im, tab);
+        else if (table) hipLaunchKernelGGL(noise_pieces_kernel<NM_I8_TABLE>, g, b, 0, c->stream, np, member_begin, im, tab);
+        else if (dist == EGG_UNIFORM_INT) hipLaunchKernelGGL(noise_pieces_kernel<NM_I8>, g, b, 0, c->stream, np, member_begin, im, tab);
+        else if (dtype == EGG_F32) hipLaunchKernelGGL(noise_pieces_kernel<NM_F32>, g, b, 0, c->stream, np, member_begin, im, tab);
+        else hipLaunchKernelGGL(noise_pieces_kernel<NM_BF16>, g, b, 0, c->stream, np, member_begin, im, tab);
+        np.count = 0;
+        wgs = 0;
+        return check_hip(c, hipGetLastError(), "noise_gen launch");
+    };
+    egg_status st;
+    for (int q = 0; q < count; ++q) {
+        const NoiseJob& J = jobs[q];
+        const int64_t ppm = J.n / per_piece;
+        // whole pieces, 32-bit piece numbers (the exact division needs them below 2^31): everything else goes value by value
+        if (J.n % per_piece || !aligned16(J.out) || ppm >= (int64_t(1) << 31) || members > ((int64_t(1) << 31) - 256) / std::max<int64_t>(ppm, 1)) {
+            if ((st = launch_noise_general(c, J.key, member_begin, members, J.n, dtype, dist, int_bound, J.out)) != EGG_OK) return st;
+            continue;
+        }
+        if (ppm == 0 || members <= 0) continue;
+        const uint32_t total = (uint32_t)(members * ppm), n_wg = (total + 255u) / 256u;
+        if (np.count == NOISE_JOBS || wgs > 0x7FFFFFFFu - n_wg)
+            if ((st = flush()) != EGG_OK) return st;
+        np.job[np.count++] = NoisePiece{J.key, make_fast_div((uint32_t)ppm), total, wgs, (u32x4_t*)J.out};
+        wgs += n_wg;
+    }
+    return flush();
+}
+
+egg_status launch_noise(eggroll_ctx* c, const StreamKey& k, uint32_t member_begin, int64_t members, int64_t n,
+                        egg_dtype dtype, egg_dist dist, int int_bound, void* out)
+{
+    const NoiseJob job{k, n, out};
+    return launch_noise_jobs(c, &job, 1, member_begin, members, dtype, dist, int_bound);
 }
 
 }  // namespace egg

@@ -22,7 +22,7 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
     const int tid = threadIdx.x;
     const int64_t ml = blockIdx.x;  // local member
     const uint32_t member = member_begin + (uint32_t)ml;
-    constexpr int EPC = BF16 ? 8 : 4;  // elements per 16-byte chunk of X
+    constexpr int EPC = BF16 ? 8 : 4;  // elements per 16-byte chunk of X (d_in is a multiple of it)
     // bf16 with more than one rank term: the panel sits in LDS rank-major ([l][column]), so that a 16-byte read holds the
     // same 8 columns as the chunk of the row and each pair of columns is one packed dot product (v_dot2c_f32_bf16)
     // instead of two unpacked multiply-adds: the pass was vector-ALU bound on unpacking (2.5 TB/s at rank 4).
@@ -35,26 +35,52 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
         const int first = k0 * RANK;              // flat index of the panel's first factor entry (even)
         if (k0) __syncthreads();                  // every wave is done with the previous panel
         // ---- phase 1: B_i panel -> LDS (storage dtype), optional cache ---------------------------
-        for (int b = tid; b < (n >> 1); b += 256) {
-            const int gb = (first >> 1) + b;      // Threefry block of the member's vector
-            uint32_t w0, w1;
-            noise_words(kb, member, (uint32_t)gb, w0, w1);
-            float z0, z1;
-            normal_pair<!BF16>(w0, w1, z0, z1);
-            if constexpr (BF16) {
-                const uint32_t pk = pack_bf16x2(z0, z1);
-                if constexpr (TRANSPOSED) {
-                    // flat entries 2b, 2b+1 = (column 2b / RANK, rank terms l, l+1): rank-major in LDS, columns contiguous
-                    const int col = (2 * b) / RANK, l = (2 * b) % RANK;
-                    ((uint16_t*)smem)[l * kn + col] = (uint16_t)(pk & 0xFFFFu);
-                    ((uint16_t*)smem)[(l + 1) * kn + col] = (uint16_t)(pk >> 16);
-                } else {
-                    ((uint32_t*)smem)[b] = pk;
+        // A thread expands several independent Threefry blocks and writes 16-byte pieces.
+        if constexpr (TRANSPOSED) {
+            // one piece of two neighbouring rank terms: flat entries (column, l), (column, l + 1) are one block, so 8 columns
+            // are 8 blocks and give 8 contiguous columns of rows l and l + 1 of the rank-major panel
+            constexpr int LP = RANK / 2;
+            for (int i = tid; i < (kn >> 3) * LP; i += 256) {
+                const int c8 = i / LP, l = (i % LP) * 2;
+                uint32_t pk[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int gb = (first + (c8 * 8 + e) * RANK + l) >> 1;  // Threefry block of the member's vector
+                    uint32_t w0, w1;
+                    noise_words(kb, member, (uint32_t)gb, w0, w1);
+                    float z0, z1;
+                    normal_pair<false>(w0, w1, z0, z1);
+                    pk[e] = pack_bf16x2(z0, z1);
+                    if (B_cache) ((uint32_t*)B_cache)[ml * (int64_t)((d_in * RANK) >> 1) + gb] = pk[e];
                 }
-                if (B_cache) ((uint32_t*)B_cache)[ml * (int64_t)((d_in * RANK) >> 1) + gb] = pk;
-            } else {
-                ((float2*)smem)[b] = make_float2(z0, z1);
-                if (B_cache) ((float2*)B_cache)[ml * (int64_t)((d_in * RANK) >> 1) + gb] = make_float2(z0, z1);
+                u32x4 r0, r1;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    r0[e] = (pk[2 * e] & 0xFFFFu) | (pk[2 * e + 1] << 16);
+                    r1[e] = (pk[2 * e] >> 16) | (pk[2 * e + 1] & 0xFFFF0000u);
+                }
+                *(u32x4*)((uint16_t*)smem + (int64_t)l * kn + c8 * 8) = r0;
+                *(u32x4*)((uint16_t*)smem + (int64_t)(l + 1) * kn + c8 * 8) = r1;
+            }
+        } else {
+            constexpr int BPP = BF16 ? 4 : 2;     // blocks per 16-byte piece of the flat vector
+            for (int i = tid; i < (n >> 1) / BPP; i += 256) {
+                u32x4 o;
+#pragma unroll
+                for (int e = 0; e < BPP; ++e) {
+                    uint32_t w0, w1;
+                    noise_words(kb, member, (uint32_t)((first >> 1) + i * BPP + e), w0, w1);
+                    float z0, z1;
+                    normal_pair<!BF16>(w0, w1, z0, z1);
+                    if constexpr (BF16) {
+                        o[e] = pack_bf16x2(z0, z1);
+                    } else {
+                        o[2 * e] = __float_as_uint(z0);
+                        o[2 * e + 1] = __float_as_uint(z1);
+                    }
+                }
+                ((u32x4*)smem)[i] = o;
+                if (B_cache) *(u32x4*)((char*)B_cache + (ml * (int64_t)d_in * RANK + first) * (BF16 ? 2 : 4) + (int64_t)i * 16) = o;
             }
         }
         __syncthreads();
@@ -175,6 +201,83 @@ __global__ __launch_bounds__(256) void project_row_kernel(StreamKey kb, uint32_t
     if (tid == 0) t[ml] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
+// One row per member (NR = 1) or a pair of them (NR = 2, antithetic: the second at -sigma), rank >= 2.  As above nothing is
+// shared, so B_i does not go through LDS: a thread expands a 16-byte piece of the flat vector -- EPP consecutive entries, a few
+// columns times the rank, or part of one column -- and multiplies it with the matching x at once, all 256 threads; the LDS form
+// left the row to one wave of four.  Vector-ALU bound (the generator).  Measured at 1024 members x 8192 x rank 4 (bf16): 64 us
+// in the LDS form.
+template <bool BF16, int RANK, int NR>
+__global__ __launch_bounds__(256) void project_rows_rank_kernel(StreamKey kb, uint32_t member_begin, int d_in, const void* __restrict__ X,
+                                                                float* __restrict__ t, void* __restrict__ B_cache)
+{
+    constexpr int EPP = BF16 ? 8 : 4, BPP = EPP / 2;
+    constexpr int NL = RANK < EPP ? RANK : EPP;         // rank terms a thread meets
+    constexpr int PPC = RANK > EPP ? RANK / EPP : 1;    // pieces per column
+    constexpr int CPP = RANK < EPP ? EPP / RANK : 1;    // columns per piece
+    static_assert(RANK >= 2 && 256 % PPC == 0, "a thread keeps its rank terms from one piece to the next");
+    __shared__ float red[4][NR][RANK];
+    const int tid = threadIdx.x;
+    const int64_t ml = blockIdx.x;
+    const uint32_t member = member_begin + (uint32_t)ml;
+    const int pieces = d_in * RANK / EPP;
+    float acc[NR][NL];
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+        for (int l = 0; l < NL; ++l) acc[r][l] = 0.f;
+    for (int p = tid; p < pieces; p += 256) {
+        const int col = PPC > 1 ? p / PPC : p * CPP;
+        float x[NR][CPP];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const int64_t at = (ml * NR + r) * d_in + col;
+#pragma unroll
+            for (int k = 0; k < CPP; ++k) {
+                if constexpr (BF16) x[r][k] = bf16_bits_to_f32(((const uint16_t*)X)[at + k]);
+                else x[r][k] = ((const float*)X)[at + k];
+            }
+        }
+        float z[EPP];
+        u32x4 o;
+#pragma unroll
+        for (int b = 0; b < BPP; ++b) {
+            uint32_t w0, w1;
+            noise_words(kb, member, (uint32_t)(p * BPP + b), w0, w1);
+            normal_pair<!BF16>(w0, w1, z[2 * b], z[2 * b + 1]);
+            if constexpr (BF16) {
+                const uint32_t pk = pack_bf16x2(z[2 * b], z[2 * b + 1]);
+                o[b] = pk;
+                z[2 * b] = bf16_lo(pk);
+                z[2 * b + 1] = bf16_hi(pk);
+            } else {
+                o[2 * b] = __float_as_uint(z[2 * b]);
+                o[2 * b + 1] = __float_as_uint(z[2 * b + 1]);
+            }
+        }
+        if (B_cache) ((u32x4*)B_cache)[ml * pieces + p] = o;
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+            for (int f = 0; f < EPP; ++f) acc[r][f % NL] = fmaf(x[r][PPC > 1 ? 0 : f / RANK], z[f], acc[r][f % NL]);
+    }
+    const int l0 = PPC > 1 ? (tid % PPC) * EPP : 0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+            float v = acc[r][l];
+#pragma unroll
+            for (int off = 32; off >= PPC; off >>= 1) v += __shfl_xor(v, off, 64);  // lanes that hold the same rank terms
+            if ((tid & 63) < PPC) red[tid >> 6][r][l0 + l] = v;
+        }
+    __syncthreads();
+    if (tid < NR * RANK) {
+        const int r = tid / RANK, l = tid % RANK;
+        const float v = (red[0][r][l] + red[1][r][l]) + (red[2][r][l] + red[3][r][l]);
+        t[(ml * NR + r) * RANK + l] = r == 1 ? -v : v;
+    }
+}
+
 // The same projection for 8 consecutive members per workgroup, with B leaving the kernel as the K-packed fp16
 // panel the update contracts ([member / 8][k][member % 8]).  512 threads: thread (b, half) generates the column
 // pair (2b, 2b+1) of members 4 half .. 4 half + 3 and stores its 8 bytes of the two 16-byte chunks, which are
@@ -272,6 +375,17 @@ static egg_status launch_project_t(eggroll_ctx* c, const StreamKey& kb, const eg
     if (s.rank == 1 && s.rows_per_member == 1) {
         KernelScope ks(c, "project");
         hipLaunchKernelGGL(project_row_kernel<BF16>, g, b, 0, c->stream, kb, mb, s.d_in, X, t, B_cache);
+        return check_hip(c, hipGetLastError(), "project launch");
+    }
+    if (shape.rows_per_member == 1 && s.rank >= 2) {
+        KernelScope ks(c, "project");
+#define EGG_ROWS(R)                                                                                                                       \
+    if (s.rank == R) {                                                                                                                    \
+        if (shape.antithetic) hipLaunchKernelGGL((project_rows_rank_kernel<BF16, R, 2>), g, b, 0, c->stream, kb, mb, s.d_in, X, t, B_cache); \
+        else hipLaunchKernelGGL((project_rows_rank_kernel<BF16, R, 1>), g, b, 0, c->stream, kb, mb, s.d_in, X, t, B_cache);               \
+    }
+        EGG_ROWS(2) EGG_ROWS(4) EGG_ROWS(8) EGG_ROWS(16)
+#undef EGG_ROWS
         return check_hip(c, hipGetLastError(), "project launch");
     }
 #define EGG_LAUNCH_PROJECT(R)                                                                                        \

@@ -16,6 +16,18 @@
 
 namespace egg {
 
+// 2^ceil(log2(max|f|)) of the maximum, 1 where that is zero or not finite
+__device__ __forceinline__ float fitness_pow2(float mx)
+{
+    float p = 1.f;
+    if (mx > 0.f && mx < 3.0e38f) {
+        int e;
+        (void)frexpf(mx, &e);  // mx = frac * 2^e, frac in [0.5, 1)
+        p = ldexpf(1.f, e);
+    }
+    return p;
+}
+
 // fnorm[0] = 2^ceil(log2(max|f|)) (1 if all zero), fnorm[1] = 1/fnorm[0].  Folding f/fnorm[0] into the
 // fp16 panel and fnorm[0] into the epilogue scale is exact (a power of two) and keeps f_i*a inside
 // the fp16 range whatever the magnitude of the fitness values.
@@ -23,7 +35,15 @@ __global__ __launch_bounds__(1024) void fitness_norm_kernel(const float* __restr
 {
     __shared__ float red[16];
     float m = 0.f;
-    for (int64_t i = threadIdx.x; i < n; i += 1024) m = fmaxf(m, fabsf(f[i]));
+    // eight loads in flight per thread (clamped: a value counted twice changes no maximum), so that 8192 members cost one
+    // memory round trip; one load per iteration made the pass 9 us at 16384 members
+    for (int64_t i = threadIdx.x; i < n; i += 8 * 1024) {
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = f[min(i + k * 1024, n - 1)];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) m = fmaxf(m, fabsf(v[k]));
+    }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
@@ -32,12 +52,7 @@ __global__ __launch_bounds__(1024) void fitness_norm_kernel(const float* __restr
         float mx = red[0];
 #pragma unroll
         for (int w = 1; w < 16; ++w) mx = fmaxf(mx, red[w]);
-        float p = 1.f;
-        if (mx > 0.f && mx < 3.0e38f) {
-            int e;
-            (void)frexpf(mx, &e);  // mx = frac * 2^e, frac in [0.5, 1)
-            p = ldexpf(1.f, e);
-        }
+        const float p = fitness_pow2(mx);
         fnorm[0] = p;
         fnorm[1] = 1.f / p;
     }
@@ -197,49 +212,185 @@ __global__ __launch_bounds__(256) void pack_r1_kernel(const void* __restrict__ s
     }
 }
 
-// Rank-1 bf16 factors without caches: regenerate straight into the K-packed fp16 panel.  A thread owns
-// one column pair (2jp, 2jp+1) of 8 consecutive members -- eight Threefry blocks, the same (member,
-// block) addressing every other kernel uses -- and writes the two finished 16-byte chunks, which are
-// neighbours in the panel: no [member][d] intermediate is written or re-read.
-__global__ __launch_bounds__(256) void gen_pack_r1_kernel(StreamKey key, uint32_t member_begin, const float* __restrict__ fitness,
-                                                          const float* __restrict__ fnorm, int64_t members, int d,
-                                                          int64_t kgroups, u32x4* __restrict__ out)
+// Factors without caches: regenerated straight into the K-packed panels, A (with the fitness) and B in one launch; no
+// [member][d][rank] intermediate is written or re-read.  The (member, block) addressing and the roundings are those of every
+// other kernel: bf16 factors, the product with f_i / fnorm in fp32, then fp16; fp32 factors stay fp32.
+//   rank 1:  a thread owns one column pair of EPC consecutive members -- one Threefry block per member -- and writes the two
+//            finished 16-byte chunks, which are neighbours in the panel;
+//   rank >= 2: a thread owns one chunk, EPC consecutive kappa = i r + l of one column: EPC / 2 blocks.
+// The blocks of a thread are independent chains.  Vector-ALU bound: about 87 issue slots per block and the conversion.
+// Measured at 16384 members x (8192 + 2048) x rank 4 (bf16): noise kernel 2 x 640 us + pack pass 2 x 240 us before.
+struct GenPackJob {
+    StreamKey key;
+    FastDiv div;          // work items per K group: d / 2 at rank 1, d otherwise
+    uint32_t total;       // work items
+    uint32_t first_wg;
+    int64_t kg0;          // first K group
+    int d;
+    const float* fitness; // NULL: the B panel
+    u32x4* out;
+};
+struct GenPackArgs {
+    GenPackJob job[2];
+    uint32_t member_begin;
+    int64_t members;
+    const float* fnorm;   // NULL: every workgroup of the A panel finds the norm itself (few members) ...
+    float* fnorm_out;     // ... and the first one leaves it for the contraction's epilogue
+};
+constexpr int INLINE_NORM_MEMBERS = 1024;  // up to here the maximum over the fitness costs a workgroup less than a launch does
+
+template <bool BF16, int RANK>
+__global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
 {
-    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-    const int pairs = d >> 1;
-    const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (gid >= kgroups * pairs) return;
-    const int64_t kg = gid / pairs;
-    const int jp = (int)(gid - kg * pairs);
-    const float finv = fitness ? fnorm[1] : 1.f;
-    float lo[8], hi[8];  // columns 2jp and 2jp+1 of the 8 members
+    constexpr int EPC = BF16 ? 8 : 4;
+    const GenPackJob& J = g.job[blockIdx.x >= g.job[1].first_wg ? 1 : 0];
+    const bool fit = J.fitness != nullptr;
+    float finv = 1.f;
+    if (fit) {
+        if (g.fnorm) {
+            finv = g.fnorm[1];
+        } else {
+            __shared__ float red[4];
+            float m = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const int64_t i = kg * 8 + e;
-        lo[e] = hi[e] = 0.f;
-        if (i < members) {
-            uint32_t w0, w1;
-            noise_words(key, member_begin + (uint32_t)i, (uint32_t)jp, w0, w1);
-            float z0, z1;
-            normal_pair<false>(w0, w1, z0, z1);
-            const uint32_t pk = pack_bf16x2(z0, z1);  // the factors are bf16 values
-            const float fs = fitness ? fitness[i] * finv : 1.f;
-            lo[e] = bf16_lo(pk) * fs;
-            hi[e] = bf16_hi(pk) * fs;
+            for (int k = 0; k < INLINE_NORM_MEMBERS / 256; ++k) m = fmaxf(m, fabsf(J.fitness[min((int64_t)(k * 256 + threadIdx.x), g.members - 1)]));
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+            __syncthreads();
+            const float p = fitness_pow2(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
+            finv = 1.f / p;
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                g.fnorm_out[0] = p;
+                g.fnorm_out[1] = finv;
+            }
         }
     }
-    u32x4 c0, c1;
+    const uint32_t i = (blockIdx.x - J.first_wg) * 256u + threadIdx.x;
+    if (i >= J.total) return;
+    const uint32_t q = fast_div(J.div, i);
+    const int u = (int)(i - q * J.div.d);
+    const int64_t kg = J.kg0 + q;
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    // fitness of a member of this K group (members past the end count with 0: their entries of the A panel are zero)
+    auto fs_of = [&](int64_t m) __attribute__((always_inline)) {
+        if (!fit) return 1.f;
+        const float v = J.fitness[min(m, g.members - 1)];  // unconditional, from a clamped index
+        return m < g.members ? v * finv : 0.f;
+    };
+    if constexpr (RANK == 1) {
+        float lo[EPC], hi[EPC];  // columns 2u and 2u + 1 of the members
+        float fs[EPC];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        h2 p, q;
-        p[0] = (_Float16)lo[2 * w]; p[1] = (_Float16)lo[2 * w + 1];  // round to nearest even
-        q[0] = (_Float16)hi[2 * w]; q[1] = (_Float16)hi[2 * w + 1];
-        c0[w] = __builtin_bit_cast(uint32_t, p);
-        c1[w] = __builtin_bit_cast(uint32_t, q);
+        for (int e = 0; e < EPC; ++e) fs[e] = fs_of(kg * EPC + e);
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) {
+            uint32_t w0, w1;
+            noise_words(J.key, g.member_begin + (uint32_t)(kg * EPC + e), (uint32_t)u, w0, w1);
+            normal_pair<!BF16>(w0, w1, lo[e], hi[e]);
+            if constexpr (BF16) {
+                const uint32_t pk = pack_bf16x2(lo[e], hi[e]);  // the factors are bf16 values
+                lo[e] = bf16_lo(pk);
+                hi[e] = bf16_hi(pk);
+            }
+            if (fit) {
+                lo[e] *= fs[e];
+                hi[e] *= fs[e];
+            }
+        }
+        u32x4 c0, c1;
+        if constexpr (BF16) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                h2 a, b;
+                a[0] = (_Float16)lo[2 * w]; a[1] = (_Float16)lo[2 * w + 1];  // round to nearest even
+                b[0] = (_Float16)hi[2 * w]; b[1] = (_Float16)hi[2 * w + 1];
+                c0[w] = __builtin_bit_cast(uint32_t, a);
+                c1[w] = __builtin_bit_cast(uint32_t, b);
+            }
+        } else {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                c0[w] = __float_as_uint(lo[w]);
+                c1[w] = __float_as_uint(hi[w]);
+            }
+        }
+        u32x4* o = J.out + kg * J.d + 2 * u;
+        o[0] = c0;
+        o[1] = c1;
+    } else {
+        constexpr int NB = EPC / 2;
+        float fs[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) fs[b] = fs_of((kg * EPC + 2 * b) / RANK);
+        u32x4 o;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int64_t kappa = kg * EPC + 2 * b;
+            const int64_t m = kappa / RANK;
+            const int l = (int)(kappa - m * RANK);
+            uint32_t w0, w1;
+            noise_words(J.key, g.member_begin + (uint32_t)m, ((uint32_t)u * RANK + l) >> 1, w0, w1);
+            float z0, z1;
+            normal_pair<!BF16>(w0, w1, z0, z1);
+            if constexpr (BF16) {
+                const uint32_t pk = pack_bf16x2(z0, z1);
+                z0 = bf16_lo(pk);
+                z1 = bf16_hi(pk);
+            }
+            if (fit) {
+                z0 *= fs[b];
+                z1 *= fs[b];
+            }
+            if constexpr (BF16) {
+                h2 p;
+                p[0] = (_Float16)z0;
+                p[1] = (_Float16)z1;
+                o[b] = __builtin_bit_cast(uint32_t, p);
+            } else {
+                o[2 * b] = __float_as_uint(z0);
+                o[2 * b + 1] = __float_as_uint(z1);
+            }
+        }
+        J.out[kg * J.d + u] = o;
     }
-    u32x4* o = out + kg * d + 2 * jp;
-    o[0] = c0;
-    o[1] = c1;
+}
+
+// panels of the A and (out_b != NULL) the B factors
+static egg_status launch_gen_pack(eggroll_ctx* c, bool bf, const StreamKey& ka, const StreamKey& kb, const egg_shape& s, const float* fitness,
+                                  float* fnorm, bool inline_norm, int64_t kgroups, void* out_a, void* out_b)
+{
+    const int ua = s.rank == 1 ? s.d_out / 2 : s.d_out, ub = s.rank == 1 ? s.d_in / 2 : s.d_in;
+    // work items are numbered in 31 bits: a launch takes as many K groups as fit
+    const int64_t slab = std::max<int64_t>(1, ((int64_t(1) << 30) - 256) / std::max(ua, ub));
+    for (int64_t kg0 = 0; kg0 < kgroups; kg0 += slab) {
+        const int64_t nkg = std::min(slab, kgroups - kg0);
+        GenPackArgs g{};
+        g.member_begin = (uint32_t)s.member_begin;
+        g.members = s.member_count;
+        g.fnorm = inline_norm ? nullptr : fnorm;
+        g.fnorm_out = fnorm;
+        const uint32_t ta = (uint32_t)(nkg * ua), tb = out_b ? (uint32_t)(nkg * ub) : 0u;
+        const uint32_t wa = (ta + 255u) / 256u, wb = (tb + 255u) / 256u;
+        g.job[0] = GenPackJob{ka, make_fast_div((uint32_t)ua), ta, 0u, kg0, s.d_out, fitness, (u32x4*)out_a};
+        g.job[1] = GenPackJob{kb, make_fast_div((uint32_t)ub), tb, wa, kg0, s.d_in, nullptr, (u32x4*)out_b};
+        KernelScope ks(c, "update_pack");
+#define EGG_GEN_PACK(B, R) hipLaunchKernelGGL((gen_pack_kernel<B, R>), dim3(wa + wb), dim3(256), 0, c->stream, g); break
+#define EGG_GEN_PACK_RANKS(B)         \
+    switch (s.rank) {                 \
+        case 1: EGG_GEN_PACK(B, 1);   \
+        case 2: EGG_GEN_PACK(B, 2);   \
+        case 4: EGG_GEN_PACK(B, 4);   \
+        case 8: EGG_GEN_PACK(B, 8);   \
+        default: EGG_GEN_PACK(B, 16); \
+    }
+        if (bf) EGG_GEN_PACK_RANKS(true) else EGG_GEN_PACK_RANKS(false)
+#undef EGG_GEN_PACK_RANKS
+#undef EGG_GEN_PACK
+        const egg_status st = check_hip(c, hipGetLastError(), "update_pack launch");
+        if (st != EGG_OK) return st;
+    }
+    return EGG_OK;
 }
 
 struct UpdArgs {
@@ -341,31 +492,34 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
     if (kgroups > 0x7FFFFFFF) return fail(c, EGG_EUNSUPPORTED, "population * rank too large");
     egg_status st;
 
-    // factors in [member][d][r] layout: the caller's caches, or regenerated into scratch
-    // (rank-1 bf16 without caches regenerates straight into the packed panels instead)
-    const bool gen_packed = !A_cache && bf && s.rank == 1 && s.d_out % 2 == 0 && s.d_in % 2 == 0;
-    const void* A_src = A_cache;
-    const void* B_src = B_cache;
-    if (!A_src && !gen_packed) {
-        const size_t na = (size_t)s.member_count * s.d_out * s.rank * esz, nb = (size_t)s.member_count * s.d_in * s.rank * esz;
-        if ((st = reserve(c, c->a_buf, na)) != EGG_OK) return st;
-        if ((st = reserve(c, c->b_buf, nb)) != EGG_OK) return st;
-        if ((st = launch_noise(c, ka, (uint32_t)s.member_begin, s.member_count, (int64_t)s.d_out * s.rank, noise_dtype, EGG_NORMAL, 0, c->a_buf.p)) != EGG_OK) return st;
-        if ((st = launch_noise(c, kb, (uint32_t)s.member_begin, s.member_count, (int64_t)s.d_in * s.rank, noise_dtype, EGG_NORMAL, 0, c->b_buf.p)) != EGG_OK) return st;
-        A_src = c->a_buf.p;
-        B_src = c->b_buf.p;
-    }
-
     if ((st = reserve(c, c->fnorm, 256)) != EGG_OK) return st;
     float* fnorm = (float*)c->fnorm.p;
-    {
-        KernelScope ks(c, "fitness_norm");
-        hipLaunchKernelGGL(fitness_norm_kernel, dim3(1), dim3(1024), 0, c->stream, fitness, s.member_count, fnorm);
-    }
     if ((st = reserve(c, c->pack_a, (size_t)kgroups * s.d_out * 16)) != EGG_OK) return st;
     // b_panel: the caller's B_cache already is the packed panel (written by the forward pass); only A is generated
     if (!b_panel && (st = reserve(c, c->pack_b, (size_t)kgroups * s.d_in * 16)) != EGG_OK) return st;
-    {
+    // Without caches the factors are generated straight into the panels (a rank-1 work item is a column pair: an odd width goes
+    // through the noise kernel and the pack pass, like the caches).
+    const bool gen_packed = !A_cache && (s.rank > 1 || (s.d_out % 2 == 0 && s.d_in % 2 == 0));
+    const bool inline_norm = gen_packed && s.member_count <= INLINE_NORM_MEMBERS;
+    if (!inline_norm) {
+        KernelScope ks(c, "fitness_norm");
+        hipLaunchKernelGGL(fitness_norm_kernel, dim3(1), dim3(1024), 0, c->stream, fitness, s.member_count, fnorm);
+    }
+    if (gen_packed) {
+        if ((st = launch_gen_pack(c, bf, ka, kb, s, fitness, fnorm, inline_norm, kgroups, c->pack_a.p, b_panel ? nullptr : c->pack_b.p)) != EGG_OK) return st;
+    } else {
+        // factors in [member][d][r] layout: the caller's caches, or regenerated into scratch
+        const void* A_src = A_cache;
+        const void* B_src = B_cache;
+        if (!A_src) {
+            const size_t na = (size_t)s.member_count * s.d_out * s.rank * esz, nb = (size_t)s.member_count * s.d_in * s.rank * esz;
+            if ((st = reserve(c, c->a_buf, na)) != EGG_OK) return st;
+            if ((st = reserve(c, c->b_buf, nb)) != EGG_OK) return st;
+            if ((st = launch_noise(c, ka, (uint32_t)s.member_begin, s.member_count, (int64_t)s.d_out * s.rank, noise_dtype, EGG_NORMAL, 0, c->a_buf.p)) != EGG_OK) return st;
+            if ((st = launch_noise(c, kb, (uint32_t)s.member_begin, s.member_count, (int64_t)s.d_in * s.rank, noise_dtype, EGG_NORMAL, 0, c->b_buf.p)) != EGG_OK) return st;
+            A_src = c->a_buf.p;
+            B_src = c->b_buf.p;
+        }
         const int64_t ta = kgroups * s.d_out, tb = kgroups * s.d_in;
         if ((ta + 255) / 256 > 0x7FFFFFFF || (tb + 255) / 256 > 0x7FFFFFFF) return fail(c, EGG_EUNSUPPORTED, "pack grid too large");
         KernelScope ks(c, "update_pack");
@@ -382,18 +536,8 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
                 else hipLaunchKernelGGL(pack_kernel<false>, g, b, 0, c->stream, src, fit, fnorm, s.member_count, d, s.rank, kgroups, dst);
             }
         };
-        auto gen_pack = [&](const StreamKey& k, const float* fit, int d, void* dst) {
-            const int64_t n = kgroups * (d / 2);
-            hipLaunchKernelGGL(gen_pack_r1_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, k,
-                               (uint32_t)s.member_begin, fit, fnorm, s.member_count, d, kgroups, (u32x4*)dst);
-        };
-        if (gen_packed) {
-            gen_pack(ka, fitness, s.d_out, c->pack_a.p);
-            if (!b_panel) gen_pack(kb, nullptr, s.d_in, c->pack_b.p);
-        } else {
-            pack(A_src, fitness, s.d_out, c->pack_a.p);
-            pack(B_src, nullptr, s.d_in, c->pack_b.p);
-        }
+        pack(A_src, fitness, s.d_out, c->pack_a.p);
+        pack(B_src, nullptr, s.d_in, c->pack_b.p);
         if ((st = check_hip(c, hipGetLastError(), "pack launch")) != EGG_OK) return st;
     }
 

@@ -55,10 +55,13 @@ __device__ __forceinline__ void noise_words(const StreamKey& k, uint32_t member,
     threefry2x32_20(k.k0, k.k1, k.k2, block, member, w0, w1);
 }
 
-// u = ((w >> 9) + 1/2) * 2^-23, exact in fp32 (24 significant bits)
+// u = ((w >> 9) + 1/2) * 2^-23, exact in fp32 (24 significant bits).  The 23 bits become the mantissa of a number in
+// [1, 2) with one alignbit (the word 0x7F : w shifted right by 9 is 0x3F800000 | w >> 9); subtracting 1 - 2^-24 leaves
+// (2k + 1) 2^-24, which fp32 holds, so the subtraction is exact.  Two instructions; shift, or, convert and multiply
+// (the integer (w >> 9) * 2 + 1 scaled by 2^-24) were four, of about 88 per pair of normals.
 __device__ __forceinline__ float word_to_unit(uint32_t w)
 {
-    return (float)((w >> 9) * 2u + 1u) * 5.9604644775390625e-08f;  // (2k+1) * 2^-24
+    return __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, w, 9)) - 0.999999940395355224609375f;
 }
 
 // Box-Muller pair from one block.  PRECISE: library log/sincospi (few-ulp), used where the factors
@@ -81,6 +84,30 @@ __device__ __forceinline__ void normal_pair(uint32_t w0, uint32_t w1, float& z0,
         z0 = rho * __builtin_amdgcn_cosf(u2);
         z1 = rho * __builtin_amdgcn_sinf(u2);
     }
+}
+
+// Exact division of x < 2^31 by a divisor chosen on the host: x / d = mulhi(x, mul) >> shift (d > 1; mul = 0 stands for
+// d = 1).  With s = ceil(log2 d) and mul = ceil(2^(31+s) / d) the excess mul d - 2^(31+s) is below d <= 2^s, so x times it
+// stays below 2^(31+s) and the quotient is exact.
+struct FastDiv {
+    uint32_t d, mul, shift;
+};
+
+inline FastDiv make_fast_div(uint32_t d)
+{
+    FastDiv f{d, 0u, 0u};
+    if (d > 1) {
+        uint32_t s = 1;
+        while (s < 31 && (uint64_t(1) << s) < d) ++s;
+        f.mul = (uint32_t)(((uint64_t(1) << (31 + s)) + d - 1) / d);
+        f.shift = s - 1;
+    }
+    return f;
+}
+
+__host__ __device__ __forceinline__ uint32_t fast_div(const FastDiv& f, uint32_t x)
+{
+    return f.mul ? (uint32_t)(((uint64_t)x * f.mul) >> 32) >> f.shift : x;
 }
 
 // byte -> integer on {-b..b}: m = 2b+1, q = 256/m; byte < q*m ? byte/q - b : 0.
