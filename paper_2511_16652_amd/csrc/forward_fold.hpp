@@ -1,0 +1,56 @@
+// Pieces of the forward layer shared by its translation units: the bf16-grade GELU, the flags of the store-only epilogues and
+// the launch interface of the folded layer (k_forward_fold.hip).
+#pragma once
+#include "common.hpp"
+
+namespace egg {
+
+// What a store-only epilogue does behind the accumulators, fixed at compile time (LEAN_PROJ: k_forward.hip)
+enum { LEAN_ON = 1, LEAN_GELU = 2, LEAN_RESID = 4, LEAN_PROJ = 8 };
+
+// gelu(x) = x Phi(x) for outputs that are rounded to bf16.  Every vector-ALU slot of the epilogue is exposed time
+// (one slot per element costs about 1 % of a K = 2048 tile), and the library erff costs about 27 of them.  Here
+// Phi(x) - 1/2 is an odd degree-17 polynomial on [-4, 4] (least squares on Chebyshev nodes, pinned to 1/2 at the
+// ends so that the clamp continues it with Phi = 0 and Phi = 1): 12 slots.  |error of gelu| <= 2e-5 inside
+// (-3.8, 3.8) and <= 1.3e-4 at |x| = 4 (the neglected tail 4 Phi(-4)); a bf16 ulp of gelu is larger than that
+// wherever |gelu(x)| > 0.03.  fp32 outputs keep erff.
+// Four values at a time, step by step, so that the four Horner chains are independent neighbours in the
+// instruction stream (a dependent fma cannot issue back to back).
+__device__ __forceinline__ void gelu_bf16_grade4(float (&y)[4])
+{
+    float xc[4], x2[4], p[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) xc[e] = __builtin_amdgcn_fmed3f(y[e], -4.0f, 4.0f);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x2[e] = xc[e] * xc[e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) p[e] = fmaf(8.809068429e-11f, x2[e], -7.454938351e-09f);
+#define EGG_GELU_STEP(C) _Pragma("unroll") for (int e = 0; e < 4; ++e) p[e] = fmaf(p[e], x2[e], C);
+    EGG_GELU_STEP(2.826503707e-07f)
+    EGG_GELU_STEP(-6.433988670e-06f)
+    EGG_GELU_STEP(9.985887631e-05f)
+    EGG_GELU_STEP(-1.137293224e-03f)
+    EGG_GELU_STEP(9.882503528e-03f)
+    EGG_GELU_STEP(-6.641100396e-02f)
+    EGG_GELU_STEP(3.989198364e-01f)
+#undef EGG_GELU_STEP
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] *= fmaf(xc[e], p[e], 0.5f);
+}
+
+// One bf16 layer whose correction is folded into the accumulators as a few more MFMAs (or is off: c = 0), for every shape
+// that the parked form of k_forward.hip does not take: S not a multiple of 64, rank 16, ragged K, few tiles.
+struct FoldLayer {
+    int S;            // rows per noise id (a pair's 2S rows count as one member's); at least FOLD_MIN_ROWS when c != 0
+    int d_out, d_in, rank;
+    int64_t R;
+    float c;          // sigma / sqrt(rank)
+    bool gelu;
+    const void *W, *X, *A, *resid;  // A: materialised factors [id][d_out][rank] bf16; resid may be NULL
+    void* Y;
+    const float* t;
+};
+constexpr int FOLD_MIN_ROWS = 15;  // 16 neighbouring rows then belong to at most two members
+egg_status launch_forward_fold(eggroll_ctx* c, const FoldLayer& l);
+
+}  // namespace egg

@@ -562,8 +562,9 @@ struct RowStagerSwz {
 // and nothing waits for a workgroup to drain its stores, be retired and be replaced.  (Measured at K = 2048: the
 // one-tile kernel spends 3 us of a tile on its prologue and 7 us from the first store to the next workgroup's
 // first MFMA.)
-template <class MT, int BM, int BN, int WM, int WN, class Epi>
-__global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_persistent_kernel(Operand P, Operand Q, int kchunks, int tiles_m,
+// TAIL: K need not be a whole number of stages.  WG_PER_CU: smaller tiles run several workgroups per compute unit.
+template <class MT, int BM, int BN, int WM, int WN, class Epi, bool TAIL = false, int WG_PER_CU = 1>
+__global__ __launch_bounds__(WM* WN * 64, WG_PER_CU) void gemm_nt_persistent_kernel(Operand P, Operand Q, int kchunks, int tiles_m,
                                                                       int tiles_n, const char* zero_page,
                                                                       typename Epi::Args ea)
 {
@@ -594,8 +595,8 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_persistent_kernel(Oper
     const int a_base = wm * WTM * PITCH;
     const int b_base = BM * PITCH + wn * WTN * PITCH;
 
-    DmaLoader<BM, NT, false, false> lp;  // K is a whole number of stages (checked on the host)
-    DmaLoader<BN, NT, false, false> lq;
+    DmaLoader<BM, NT, false, TAIL> lp;  // TAIL = false: K is a whole number of stages (checked on the host)
+    DmaLoader<BN, NT, false, TAIL> lq;
 
     int tile = blockIdx.x;
     if (tile >= total) return;

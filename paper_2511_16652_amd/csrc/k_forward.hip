@@ -5,38 +5,9 @@
 // the correction in fp32, optionally keeps A_i for the update, applies the activation and stores.
 #include "common.hpp"
 #include "gemm_core.hpp"
+#include "forward_fold.hpp"
 
 namespace egg {
-
-// gelu(x) = x Phi(x) for outputs that are rounded to bf16.  Every vector-ALU slot of the epilogue is exposed time
-// (one slot per element costs about 1 % of a K = 2048 tile), and the library erff costs about 27 of them.  Here
-// Phi(x) - 1/2 is an odd degree-17 polynomial on [-4, 4] (least squares on Chebyshev nodes, pinned to 1/2 at the
-// ends so that the clamp continues it with Phi = 0 and Phi = 1): 12 slots.  |error of gelu| <= 2e-5 inside
-// (-3.8, 3.8) and <= 1.3e-4 at |x| = 4 (the neglected tail 4 Phi(-4)); a bf16 ulp of gelu is larger than that
-// wherever |gelu(x)| > 0.03.  fp32 outputs keep erff.
-// Four values at a time, step by step, so that the four Horner chains are independent neighbours in the
-// instruction stream (a dependent fma cannot issue back to back).
-__device__ __forceinline__ void gelu_bf16_grade4(float (&y)[4])
-{
-    float xc[4], x2[4], p[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) xc[e] = __builtin_amdgcn_fmed3f(y[e], -4.0f, 4.0f);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) x2[e] = xc[e] * xc[e];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) p[e] = fmaf(8.809068429e-11f, x2[e], -7.454938351e-09f);
-#define EGG_GELU_STEP(C) _Pragma("unroll") for (int e = 0; e < 4; ++e) p[e] = fmaf(p[e], x2[e], C);
-    EGG_GELU_STEP(2.826503707e-07f)
-    EGG_GELU_STEP(-6.433988670e-06f)
-    EGG_GELU_STEP(9.985887631e-05f)
-    EGG_GELU_STEP(-1.137293224e-03f)
-    EGG_GELU_STEP(9.882503528e-03f)
-    EGG_GELU_STEP(-6.641100396e-02f)
-    EGG_GELU_STEP(3.989198364e-01f)
-#undef EGG_GELU_STEP
-#pragma unroll
-    for (int e = 0; e < 4; ++e) y[e] *= fmaf(xc[e], p[e], 0.5f);
-}
 
 // Arguments of the forward epilogue (the same for every instantiation).
 struct FwdArgs {
@@ -74,7 +45,6 @@ struct FwdArgs {
 // t'[n] = sum_m Y[n][m] B'[m] is formed here from the very bf16 values that are stored, so that Y is not read again
 // by a projection pass: a lane adds its 4 x 8 products per column, the four lane groups of a column are summed by two
 // shuffles, and the sum over the wave tile's 128 rows goes to a slab-partial that a small pass adds up in fixed order.
-enum { LEAN_ON = 1, LEAN_GELU = 2, LEAN_RESID = 4, LEAN_PROJ = 8 };
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
 // sum over the 16 lanes of a DPP row, left in every lane of the row
@@ -687,6 +657,12 @@ static egg_status launch_forward_t(eggroll_ctx* c, const StreamKey& ka, const eg
                           nullptr, nullptr};
     if constexpr (BF16) {
         const int64_t big_tiles = ((s.d_out + 255) / 256) * ((R + 255) / 256);
+        // bf16 out and no correction, or one that 16 neighbouring rows share among at most two members: folded into the
+        // accumulators, store-only epilogue.  The parked form below is the faster one where it applies (big tiles, S a multiple
+        // of 64, whole K stages).
+        const bool parked = big_tiles >= 192 && kchunks % 8 == 0 && (ea.c == 0.f || (!REGEN && Epi::RANK_ELEMS_BYTES <= 16 && ea.S % Epi::CORR_COLS == 0));
+        if (!next && yd == EGG_BF16 && !parked && (ea.c == 0.f || (!REGEN && ea.S >= FOLD_MIN_ROWS)))
+            return launch_forward_fold(c, FoldLayer{ea.S, s.d_out, s.d_in, s.rank, R, ea.c, act == EGG_ACT_GELU, W, X, A_buf, resid, Y, t});
         if (big_tiles >= 192) {
             // bf16 out and nothing left to correct in the epilogue (unperturbed, or the correction folds into the
             // accumulators): the store-only epilogue with the activation and the residual fixed at compile time

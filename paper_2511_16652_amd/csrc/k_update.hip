@@ -108,8 +108,12 @@ __global__ __launch_bounds__(256) void pack_kernel(const void* __restrict__ src,
 #pragma unroll
             for (int h = 0; h < 4; ++h) {
                 h2 p;
-                p[0] = (_Float16)(in[h] ? bf16_lo(w[h]) * fs[h] : 0.f);  // round to nearest even; past the last member: +0
-                p[1] = (_Float16)(in[h] ? bf16_hi(w[h]) * fs[h] : 0.f);
+                // the product in fp32, then round to nearest even, as gen_pack_kernel has it (fused into one rounding, entries in
+                // a few thousand would differ from the regenerated panel's by an fp16 ulp); past the last member: +0
+                float lo = bf16_lo(w[h]) * fs[h], hi = bf16_hi(w[h]) * fs[h];
+                asm volatile("" : "+v"(lo), "+v"(hi));
+                p[0] = (_Float16)(in[h] ? lo : 0.f);
+                p[1] = (_Float16)(in[h] ? hi : 0.f);
                 o[h] = __builtin_bit_cast(uint32_t, p);
             }
             ((u32x4*)out)[gid] = o;

@@ -1,0 +1,73 @@
+"""GPU: the bf16 layer whose correction is folded into the accumulators for row groups of any length, at the edges of its
+dispatch: both sides of the smallest row group (15 rows of one noise id; a pair counts its 2S rows), blocks that straddle two
+members, rank 16's second pass, ragged K, d_out and row counts, both tile sizes.
+
+Reference in 64 bits from the factors that eggroll_noise_gen writes.  Per entry: one bf16 rounding (2^-9 of the value), the
+fp32 sums and the hi/lo split of c t (2^-16 of the correction, of the size of the row) and the polynomial GELU (1.3e-4)."""
+import math
+
+import pytest
+
+from paper_2511_16652_amd import binding as eb
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    c = eb.Context(0)
+    yield c
+    torch.cuda.synchronize()
+    c.close()
+
+
+CASES = [  # d_out, d_in, members, S, rank, antithetic, gelu, residual
+    (132, 72, 9, 15, 1, 0, 0, 0),
+    (132, 72, 9, 14, 1, 0, 0, 0),      # below the rule: the general epilogue
+    (260, 136, 7, 16, 2, 0, 1, 0),
+    (124, 200, 6, 17, 4, 0, 0, 1),
+    (388, 64, 5, 31, 8, 0, 1, 1),
+    (136, 72, 9, 15, 16, 0, 0, 0),
+    (136, 72, 4, 100, 16, 0, 0, 1),
+    (200, 264, 8, 8, 2, 1, 0, 0),      # pairs: 16 rows share their factors
+    (200, 264, 8, 7, 2, 1, 0, 0),      # 14: the general epilogue
+    (64, 8, 1, 1, 1, 0, 0, 0),
+    (4096, 72, 31, 100, 4, 0, 1, 0),   # 256 x 256 tiles, ragged K
+    (4100, 128, 195, 17, 8, 0, 0, 1),
+    (4096, 64, 205, 15, 16, 0, 0, 0),
+    (4096, 128, 62, 51, 1, 0, 0, 0),
+    (4096, 72, 50, 64, 2, 0, 0, 0),    # S a multiple of 64, ragged K
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("sigma", [0.0, 0.7])
+def test_folded_layer(ctx, case, sigma):
+    import torch
+    d_out, d_in, N, S, rank, anti, gelu, resid = case
+    R, ids, per = N * S, N // (2 if anti else 1), S * (2 if anti else 1)
+    g = torch.Generator("cuda").manual_seed(d_out + S)
+    draw = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)  # noqa: E731
+    W, X, Rin = draw(d_out, d_in) * d_in ** -0.5, draw(R, d_in), draw(R, d_out)
+    Y = torch.full((R, d_out), float("nan"), dtype=torch.bfloat16, device="cuda")
+    key, shape = eb.make_key(3, 2, 5), eb.make_shape(4, N, S, d_out, d_in, rank, anti)
+    act = eb.EGG_ACT_GELU if gelu else eb.EGG_ACT_NONE
+    if resid:
+        ctx.eggroll_perturbed_forward_add(key, shape, sigma, act, W, X, Rin, Y)
+    else:
+        ctx.eggroll_perturbed_forward(key, shape, sigma, act, W, X, Y)
+    A = torch.empty((ids, d_out, rank), dtype=torch.bfloat16, device="cuda")
+    B = torch.empty((ids, d_in, rank), dtype=torch.bfloat16, device="cuda")
+    ctx.eggroll_noise_gen(key, eb.make_shape(4 // (2 if anti else 1), ids, 1, d_out, d_in, rank), eb.EGG_BF16, eb.EGG_NORMAL, 0, A, B)
+    t = torch.bmm(X.double().view(ids, per, d_in), B.double())
+    if anti:
+        t[:, S:] *= -1
+    corr = torch.bmm(t, A.double().transpose(1, 2).contiguous()).view(R, d_out) * (sigma / math.sqrt(rank))
+    pre = X.double() @ W.double().t().contiguous() + corr
+    ref = 0.5 * pre * (1 + torch.erf(pre * math.sqrt(0.5))) if gelu else pre
+    if resid:
+        ref = ref + Rin.double()
+    tol = 2.0 ** -8 * ref.abs() + 1e-4 * (1 + corr.abs().amax(1, keepdim=True)) + (2e-4 if gelu else 0)
+    err = (Y.double() - ref).abs()
+    assert torch.isfinite(Y.float()).all() and (err <= tol).all(), (err - tol).max()
