@@ -536,23 +536,21 @@ egg_status eggroll_egg_update_i8(eggroll_ctx* c, egg_key key, const egg_shape* s
     if (shape->member_count * (int64_t)noise_max(int_bound) * noise_max(int_bound) > 0x7FFFFFFFLL)
         return fail(c, EGG_EUNSUPPORTED, "population too large for int32 accumulation");
     if (hipSetDevice(c->device) != hipSuccess) return fail(c, EGG_EHIP, "hipSetDevice");
+    std::vector<I8UpdateJob> jobs;
+    jobs.reserve(6 * (size_t)layers + 2);
     auto one = [&](uint32_t layer, int d_out, int d_in, int8_t* theta) {
-        egg_shape sh = *shape;
-        sh.d_out = d_out;
-        sh.d_in = d_in;
-        return launch_update_i8(c, make_stream_key(key.seed, key.step, layer, 0), make_stream_key(key.seed, key.step, layer, 1), sh,
-                                int_bound, fitness, threshold, theta, nullptr);
+        jobs.push_back(I8UpdateJob{make_stream_key(key.seed, key.step, layer, 0), make_stream_key(key.seed, key.step, layer, 1), d_out, d_in, theta, nullptr});
     };
-    if ((s = one(key.layer, 256, D, model->emb)) != EGG_OK) return s;
+    one(key.layer, 256, D, model->emb);
     const size_t DD = (size_t)D * D;
     for (int i = 0; i < layers; ++i) {
         const uint32_t base = key.layer + 1u + 6u * (uint32_t)i;
-        for (int m = 0; m < 4; ++m)
-            if ((s = one(base + m, D, D, model->gru_w + ((size_t)i * 4 + m) * DD)) != EGG_OK) return s;
-        if ((s = one(base + 4, 4 * D, D, model->mlp1 + (size_t)i * 4 * DD)) != EGG_OK) return s;
-        if ((s = one(base + 5, D, 4 * D, model->mlp2 + (size_t)i * 4 * DD)) != EGG_OK) return s;
+        for (int m = 0; m < 4; ++m) one(base + m, D, D, model->gru_w + ((size_t)i * 4 + m) * DD);
+        one(base + 4, 4 * D, D, model->mlp1 + (size_t)i * 4 * DD);
+        one(base + 5, D, 4 * D, model->mlp2 + (size_t)i * 4 * DD);
     }
-    return one(key.layer + 1u + 6u * (uint32_t)layers, 256, D, model->head);
+    one(key.layer + 1u + 6u * (uint32_t)layers, 256, D, model->head);
+    return launch_update_i8_jobs(c, jobs.data(), (int)jobs.size(), (uint32_t)shape->member_begin, shape->member_count, int_bound, fitness, threshold);
 }
 
 egg_status eggroll_update(eggroll_ctx* c, egg_key key, const egg_shape* shape, egg_dtype noise_dtype,
@@ -600,9 +598,8 @@ egg_status eggroll_update_i8(eggroll_ctx* c, egg_key key, const egg_shape* shape
     if (shape->member_count * (int64_t)noise_max(int_bound) * noise_max(int_bound) > 0x7FFFFFFFLL)
         return fail(c, EGG_EUNSUPPORTED, "population too large for int32 accumulation");
     if (hipSetDevice(c->device) != hipSuccess) return fail(c, EGG_EHIP, "hipSetDevice");
-    return launch_update_i8(c, make_stream_key(key.seed, key.step, key.layer, 0),
-                            make_stream_key(key.seed, key.step, key.layer, 1), *shape, int_bound, fitness, threshold,
-                            theta, E_out);
+    const I8UpdateJob job{make_stream_key(key.seed, key.step, key.layer, 0), make_stream_key(key.seed, key.step, key.layer, 1), shape->d_out, shape->d_in, theta, E_out};
+    return launch_update_i8_jobs(c, &job, 1, (uint32_t)shape->member_begin, shape->member_count, int_bound, fitness, threshold);
 }
 
 void eggroll_normal_int_table(int8_t* out)

@@ -100,6 +100,7 @@ egg_status validate_shape(eggroll_ctx* c, const egg_shape* s, bool need_rows, bo
 // entry points implemented per translation unit (kernel launchers)
 egg_status launch_noise(eggroll_ctx* c, const StreamKey& k, uint32_t member_begin, int64_t members, int64_t n,
                         egg_dtype dtype, egg_dist dist, int int_bound, void* out);
+egg_status ensure_normal_table(eggroll_ctx* c);  // c->norm_tab holds the table of round(16 z)
 // several vectors of the same members and type (the factors of a layer's matrices): one launch for those made of whole
 // 16-byte pieces, of up to 20 vectors
 struct NoiseJob {
@@ -203,7 +204,14 @@ egg_status launch_egg_forward_i8(eggroll_ctx* c, egg_key key, const egg_shape& s
                                  const egg_model_i8& P, const uint8_t* tokens, const int8_t* S_in, int8_t* S_out,
                                  int8_t* logits);
 egg_status launch_loglik_i8(eggroll_ctx* c, int64_t rows, const int8_t* logits, const uint8_t* targets, int accumulate, int32_t* out);
-egg_status launch_update_i8(eggroll_ctx* c, const StreamKey& ka, const StreamKey& kb, const egg_shape& s,
-                            int int_bound, const int8_t* F, int32_t threshold, int8_t* theta, int32_t* E_out);
+// integer updates of several matrices of one population
+struct I8UpdateJob {
+    StreamKey ka, kb;
+    int d_out, d_in;
+    int8_t* theta;
+    int32_t* E_out;  // optional
+};
+egg_status launch_update_i8_jobs(eggroll_ctx* c, const I8UpdateJob* jobs, int count, uint32_t member_begin, int64_t N, int int_bound,
+                                 const int8_t* F, int32_t threshold);
 
 }  // namespace egg

@@ -271,10 +271,10 @@ __device__ __forceinline__ void epi_column(E& e, int n, bool valid)
     else e.column(n, valid);
 }
 
-template <class MT, int BM, int BN, int WM, int WN, bool KMAJOR, class Epi, int WG_PER_CU = 1>
-__global__ __launch_bounds__(WM* WN * 64, WG_PER_CU) void gemm_nt_kernel(Operand P, Operand Q, int kchunks, int tiles_m,
-                                                                   int tiles_n, int ksplit, const char* zero_page,
-                                                                   typename Epi::Args ea)
+// One tile of the product, by all threads of a workgroup: K-chunks kbeg .. kbeg + kchunks - 1.
+template <class MT, int BM, int BN, int WM, int WN, bool KMAJOR, class Epi>
+__device__ __forceinline__ void gemm_nt_tile(const Operand& P, const Operand& Q, int tile_id, int kbeg, int kchunks, int tiles_m,
+                                             int tiles_n, const char* zero_page, const typename Epi::Args& ea)
 {
     constexpr int NT = WM * WN * 64;
     constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -294,16 +294,6 @@ __global__ __launch_bounds__(WM* WN * 64, WG_PER_CU) void gemm_nt_kernel(Operand
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM, wn = wave / WM;
 
-    // split-K (ksplit > 0): consecutive groups of tiles_m * tiles_n workgroups own consecutive ranges of
-    // ksplit K-chunks; the epilogue stores partial tiles that a later pass combines
-    int tile_id = blockIdx.x, kbeg = 0;
-    if (ksplit > 0) {
-        const int tiles = tiles_m * tiles_n;
-        const int sp = tile_id / tiles;
-        tile_id -= sp * tiles;
-        kbeg = sp * ksplit;
-        kchunks = min(kchunks - kbeg, ksplit);
-    }
     int tm, tn;
     tile_coords(tile_id, tiles_m, tiles_n, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
@@ -473,6 +463,13 @@ __global__ __launch_bounds__(WM* WN * 64, WG_PER_CU) void gemm_nt_kernel(Operand
         });
         epi.template flush<WTM>(m0 + wm * WTM, n0 + wn * WTN + j * BLK, Q.rows);
     });
+}
+
+template <class MT, int BM, int BN, int WM, int WN, bool KMAJOR, class Epi, int WG_PER_CU = 1>
+__global__ __launch_bounds__(WM* WN * 64, WG_PER_CU) void gemm_nt_kernel(Operand P, Operand Q, int kchunks, int tiles_m, int tiles_n,
+                                                                   const char* zero_page, typename Epi::Args ea)
+{
+    gemm_nt_tile<MT, BM, BN, WM, WN, KMAJOR, Epi>(P, Q, blockIdx.x, 0, kchunks, tiles_m, tiles_n, zero_page, ea);
 }
 
 // Staging helper for epilogues whose output is row-major [n][m] with 2-byte elements: store4 parks a

@@ -56,12 +56,14 @@ egg_status launch_gru_i8(eggroll_ctx* c, egg_key key, const egg_shape& s, int in
     if ((st = reserve(c, c->gru, 8 * fac + 6 * act + 5 * dots)) != EGG_OK) return st;
     char* base = (char*)c->gru.p;
     int8_t *A[4], *B[4];
+    NoiseJob noise[8];
     for (int m = 0; m < 4; ++m) {
         A[m] = (int8_t*)(base + (2 * m) * fac);
         B[m] = (int8_t*)(base + (2 * m + 1) * fac);
-        if ((st = launch_noise(c, make_stream_key(key.seed, key.step, key.layer + m, 0), first_id, ids, D, EGG_I8, EGG_UNIFORM_INT, int_bound, A[m])) != EGG_OK) return st;
-        if ((st = launch_noise(c, make_stream_key(key.seed, key.step, key.layer + m, 1), first_id, ids, D, EGG_I8, EGG_UNIFORM_INT, int_bound, B[m])) != EGG_OK) return st;
+        noise[2 * m] = NoiseJob{make_stream_key(key.seed, key.step, key.layer + m, 0), D, A[m]};
+        noise[2 * m + 1] = NoiseJob{make_stream_key(key.seed, key.step, key.layer + m, 1), D, B[m]};
     }
+    if ((st = launch_noise_jobs(c, noise, 8, first_id, ids, EGG_I8, EGG_UNIFORM_INT, int_bound)) != EGG_OK) return st;
     int8_t* buf[6];
     for (int b = 0; b < 6; ++b) buf[b] = (int8_t*)(base + 8 * fac + b * act);
     int* dot[5];

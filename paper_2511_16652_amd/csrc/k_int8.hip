@@ -356,7 +356,8 @@ static egg_status launch_i8_gemm(eggroll_ctx* c, const Operand& P, const Operand
     if (st != EGG_OK) return st;
     KernelScope ks(c, "forward_gemm_i8");
     hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(WM * WN * 64), lds, c->stream, P, Q, kchunks,
-                       tiles_m, tiles_n, 0, (const char*)c->zero_page.p, ea);
+                       tiles_m, tiles_n,
+                       (const char*)c->zero_page.p, ea);
     return check_hip(c, hipGetLastError(), "forward_gemm_i8");
 }
 
@@ -605,8 +606,8 @@ egg_status launch_forward_i8(eggroll_ctx* c, const StreamKey& ka, const StreamKe
     int8_t* scratch[2] = {(int8_t*)c->i8_h.p, (int8_t*)c->i8_h.p + ((obytes + 255) & ~size_t(255))};
     char* dots_base = (char*)c->t_buf.p;
 
-    if ((st = launch_noise(c, ka, first_id, noise_ids, d_out, EGG_I8, EGG_UNIFORM_INT, int_bound, A)) != EGG_OK) return st;
-    if ((st = launch_noise(c, kb, first_id, noise_ids, d_in, EGG_I8, EGG_UNIFORM_INT, int_bound, B)) != EGG_OK) return st;
+    const NoiseJob noise[2] = {{ka, d_out, A}, {kb, d_in, B}};
+    if ((st = launch_noise_jobs(c, noise, 2, first_id, noise_ids, EGG_I8, EGG_UNIFORM_INT, int_bound)) != EGG_OK) return st;
     if (steps > 1) {   // a fill kernel rather than a memset node, so that the call can sit inside a captured graph
         const int64_t nz = (int64_t)(dot_row / sizeof(int)) * (steps + 1);
         KernelScope ks(c, "zero_dots");

@@ -168,17 +168,24 @@ static egg_status launch_noise_general(eggroll_ctx* c, const StreamKey& k, uint3
     return check_hip(c, hipGetLastError(), "noise_gen launch");
 }
 
+// first use on this context: build the table on the host and upload it (a blocking copy)
+egg_status ensure_normal_table(eggroll_ctx* c)
+{
+    if (c->norm_tab.p) return EGG_OK;
+    std::vector<int8_t> h(65536);
+    normal_int_table(h.data());
+    const egg_status st = reserve(c, c->norm_tab, 65536);
+    if (st != EGG_OK) return st;
+    return check_hip(c, hipMemcpy(c->norm_tab.p, h.data(), 65536, hipMemcpyHostToDevice), "upload of the integer normal table");
+}
+
 egg_status launch_noise_jobs(eggroll_ctx* c, const NoiseJob* jobs, int count, uint32_t member_begin, int64_t members, egg_dtype dtype,
                              egg_dist dist, int int_bound)
 {
     const bool table = dist == EGG_NORMAL_INT16 || (dist == EGG_UNIFORM_INT && int_bound == EGG_INT_NOISE_NORMAL16);
-    if (table && !c->norm_tab.p) {
-        // first use on this context: build the table on the host and upload it (a blocking copy)
-        std::vector<int8_t> h(65536);
-        normal_int_table(h.data());
-        egg_status st = reserve(c, c->norm_tab, 65536);
+    if (table) {
+        const egg_status st = ensure_normal_table(c);
         if (st != EGG_OK) return st;
-        if ((st = check_hip(c, hipMemcpy(c->norm_tab.p, h.data(), 65536, hipMemcpyHostToDevice), "upload of the integer normal table")) != EGG_OK) return st;
     }
     const int per_piece = dist == EGG_RAW ? 4 : (table || dist == EGG_UNIFORM_INT ? 16 : (dtype == EGG_F32 ? 4 : 8));  // values
     const IntMap im = make_int_map(dist == EGG_UNIFORM_INT && !table ? int_bound : 0);
