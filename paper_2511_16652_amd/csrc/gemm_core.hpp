@@ -63,6 +63,15 @@ struct MmaBf16Blk16 {
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
     }
 };
+struct MmaF16Blk16 {
+    static constexpr int MFMA_PER_MMA = 1;
+    static constexpr int BLK = 16;
+    typedef f32x4 acc_t;
+    static __device__ __forceinline__ void mma(const u32x4& a, const u32x4& b, acc_t& c)
+    {
+        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+    }
+};
 struct MmaF16 {
     static constexpr int MFMA_PER_MMA = 1;
     static constexpr int BLK = 32;
@@ -187,13 +196,13 @@ constexpr size_t gemm_lds_bytes()
 // may overwrite the buffer.  (The macros use the kernels' local names.)
 #define EGG_READ_A(BUF, STAGE, KS_, H_)                                                                        \
     {                                                                                                          \
-        const char* sa_ = lds + (STAGE)*STAGE_BYTES + a_base + foff[KS_] + (H_)*HB * BLK * PITCH;              \
-        _Pragma("unroll") for (int i = 0; i < HB; ++i) fa[BUF][i] = *(const u32x4*)(sa_ + i * BLK * PITCH);    \
+        const char* sa_ = lds + (STAGE)*STAGE_BYTES + a_base + foffa[KS_] + (H_)*HB * BLK_STEP;                \
+        _Pragma("unroll") for (int i = 0; i < HB; ++i) fa[BUF][i] = *(const u32x4*)(sa_ + i * BLK_STEP);       \
     }
 #define EGG_READ_B(BUF, STAGE, KS_)                                                                            \
     {                                                                                                          \
-        const char* sb_ = lds + (STAGE)*STAGE_BYTES + b_base + foff[KS_];                                      \
-        _Pragma("unroll") for (int j = 0; j < NB; ++j) fb[BUF][j] = *(const u32x4*)(sb_ + j * BLK * PITCH);    \
+        const char* sb_ = lds + (STAGE)*STAGE_BYTES + b_base + foffb[KS_];                                     \
+        _Pragma("unroll") for (int j = 0; j < NB; ++j) fb[BUF][j] = *(const u32x4*)(sb_ + j * BLK_STEP);       \
     }
 #define EGG_MMA_UNIT(ABUF, BBUF, H_, I0, I1)                                                                   \
     _Pragma("unroll") for (int i = I0; i < I1; ++i) _Pragma("unroll") for (int j = 0; j < NB; ++j)             \
@@ -285,7 +294,6 @@ __device__ __forceinline__ void gemm_nt_tile(const Operand& P, const Operand& Q,
     static_assert(BM * 8 % NT == 0 && BN * 8 % NT == 0, "stage rows must divide over the threads");
     static_assert(BLK == 32 || BLK == 16, "MFMA block shapes: 32x32 (K = 16 per step) or 16x16 (K = 32 per step)");
     static_assert(WTM % 32 == 0 && WTN % 32 == 0 && MB % 2 == 0, "wave tiles are made of whole MFMA blocks");
-    static_assert(BLK == 32 || !KMAJOR, "the 16x16 form is written for row-major operands");
 
     extern __shared__ __attribute__((aligned(1024))) char lds[];
 
@@ -319,13 +327,17 @@ __device__ __forceinline__ void gemm_nt_tile(const Operand& P, const Operand& Q,
     constexpr int CPS = 8 / KSTEPS;                    // 16-byte chunks per k-step and row
     const int frow = lane & (BLK - 1);
     const int fsw = (frow >> 1) & 7;
-    int foff[KSTEPS];
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) foff[ks] = frow * PITCH + (((CPS * ks + lane / BLK) ^ fsw) << 4);
-    const int a_base = wm * WTM * PITCH;
-    const int b_base = BM * PITCH + wn * WTN * PITCH;
     // chunk-major stages: chunk c of row r at (c * ROWS + r) * 16 inside the operand's half of the stage
-    const int a_row16 = (wm * WTM + frow) * 16, b_row16 = BM * PITCH + (wn * WTN + frow) * 16;
+    constexpr int BLK_STEP = KMAJOR ? BLK * 16 : BLK * PITCH;  // bytes from one block of rows to the next
+    int foffa[KSTEPS], foffb[KSTEPS];
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) {
+        const int ch = CPS * ks + lane / BLK;
+        foffa[ks] = KMAJOR ? (ch * BM + frow) * 16 : frow * PITCH + ((ch ^ fsw) << 4);
+        foffb[ks] = KMAJOR ? (ch * BN + frow) * 16 : foffa[ks];
+    }
+    const int a_base = wm * WTM * (KMAJOR ? 16 : PITCH);
+    const int b_base = BM * PITCH + wn * WTN * (KMAJOR ? 16 : PITCH);
 
     typename MT::acc_t acc[MB][NB];
 #pragma unroll
@@ -341,12 +353,10 @@ __device__ __forceinline__ void gemm_nt_tile(const Operand& P, const Operand& Q,
 
 #define EGG_READ_FRAGS(BUF, STAGE, KS_)                                                                        \
     {                                                                                                          \
-        const int c_ = 2 * (KS_) + (lane >> 5);                                                                \
-        const char* sa_ = lds + (STAGE)*STAGE_BYTES + (KMAJOR ? a_row16 + c_ * BM * 16 : a_base + foff[KS_]);  \
-        const char* sb_ = lds + (STAGE)*STAGE_BYTES + (KMAJOR ? b_row16 + c_ * BN * 16 : b_base + foff[KS_]);  \
-        constexpr int BLK_ = KMAJOR ? 32 * 16 : 32 * PITCH;                                                    \
-        _Pragma("unroll") for (int i = 0; i < MB; ++i) fa[BUF][i] = *(const u32x4*)(sa_ + i * BLK_);           \
-        _Pragma("unroll") for (int j = 0; j < NB; ++j) fb[BUF][j] = *(const u32x4*)(sb_ + j * BLK_);           \
+        const char* sa_ = lds + (STAGE)*STAGE_BYTES + a_base + foffa[KS_];                                     \
+        const char* sb_ = lds + (STAGE)*STAGE_BYTES + b_base + foffb[KS_];                                     \
+        _Pragma("unroll") for (int i = 0; i < MB; ++i) fa[BUF][i] = *(const u32x4*)(sa_ + i * BLK_STEP);       \
+        _Pragma("unroll") for (int j = 0; j < NB; ++j) fb[BUF][j] = *(const u32x4*)(sb_ + j * BLK_STEP);       \
     }
 #define EGG_MMA_ROWS(BUF, I0, I1)                                                                              \
     _Pragma("unroll") for (int i = I0; i < I1; ++i) _Pragma("unroll") for (int j = 0; j < NB; ++j)             \
@@ -586,9 +596,11 @@ __global__ __launch_bounds__(WM* WN * 64, WG_PER_CU) void gemm_nt_persistent_ker
     constexpr int KSTEPS = 2, CPS = 4;
     const int frow = lane & (BLK - 1);
     const int fsw = (frow >> 1) & 7;
-    int foff[KSTEPS];
+    constexpr int BLK_STEP = BLK * PITCH;
+    int foffa[KSTEPS];
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) foff[ks] = frow * PITCH + (((CPS * ks + lane / BLK) ^ fsw) << 4);
+    for (int ks = 0; ks < KSTEPS; ++ks) foffa[ks] = frow * PITCH + (((CPS * ks + lane / BLK) ^ fsw) << 4);
+    const int(&foffb)[KSTEPS] = foffa;
     const int a_base = wm * WTM * PITCH;
     const int b_base = BM * PITCH + wn * WTN * PITCH;
 
@@ -675,6 +687,169 @@ __global__ __launch_bounds__(WM* WN * 64, WG_PER_CU) void gemm_nt_persistent_ker
         tile = next;
     }
 #undef EGG_FIRST_STAGES
+}
+
+// s_waitcnt immediate: at most n vector-memory operations outstanding, no LDS operation outstanding
+constexpr int vm_lds_imm(int n) { return 0x0070 | (n & 15) | ((n >> 4) << 14); }
+
+// One tile per workgroup, for products whose tiles leave compute units empty.  With a workgroup of four waves to itself a SIMD
+// has nothing to put beside a wave that waits for a fragment.  A wave alone on its SIMD has 512 registers: here it holds the
+// fragments of a whole stage twice and reads the next stage's under the 32 MFMAs of this one, and the LDS that a second workgroup
+// would take holds four stages, waited for by count.  What bounds it now is the rate at which one CU can load (32 KB per stage at
+// about 65 bytes/ns, the rate the chip reaches per CU with all of them loading): 128 x 128 stages take 0.57 us, 0.66 in the
+// two-stage loop.  Layers of 1024 x 2048 rows, 1024 -> .. (us, before / now): K = 256 16.8 / 15.7, 1024 24.3 / 22.9, 4096 51.3 / 49.2.
+// K-packed or row-major operands; epilogues as in the persistent kernel.
+template <class MT, int BM, int BN, int WM, int WN, bool KMAJOR, class Epi>
+__global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P, Operand Q, int kchunks, int tiles_m, int tiles_n,
+                                                                 const char* zero_page, typename Epi::Args ea)
+{
+    constexpr int NT = WM * WN * 64, DEPTH = 4;
+    constexpr int WTM = BM / WM, WTN = BN / WN;
+    constexpr int BLK = MT::BLK;
+    static_assert(BLK == 16, "written for the 16x16x32 form");
+    constexpr int MB = WTM / BLK, NB = WTN / BLK;
+    constexpr int PITCH = 128;
+    constexpr int STAGE_BYTES = (BM + BN) * PITCH;
+    static_assert(BM * 8 % NT == 0 && BN * 8 % NT == 0, "tile shape");
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % WM, wn = wave / WM;
+    const int64_t pstep = 8 * P.kc_stride, qstep = 8 * Q.kc_stride;
+    const int KT = (kchunks + 7) >> 3;
+
+    constexpr int KSTEPS = 2, CPS = 4;
+    const int frow = lane & (BLK - 1);
+    const int fsw = (frow >> 1) & 7;
+    constexpr int BLK_STEP = KMAJOR ? BLK * 16 : BLK * PITCH;
+    int foffa[KSTEPS], foffb[KSTEPS];
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) {
+        const int ch = CPS * ks + lane / BLK;
+        foffa[ks] = KMAJOR ? (ch * BM + frow) * 16 : frow * PITCH + ((ch ^ fsw) << 4);
+        foffb[ks] = KMAJOR ? (ch * BN + frow) * 16 : foffa[ks];
+    }
+    const int a_base = wm * WTM * (KMAJOR ? 16 : PITCH);
+    const int b_base = BM * PITCH + wn * WTN * (KMAJOR ? 16 : PITCH);
+
+    int tm, tn;
+    tile_coords(blockIdx.x, tiles_m, tiles_n, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    const char* pb = P.base + (int64_t)m0 * P.row_stride;
+    const char* qb = Q.base + (int64_t)n0 * Q.row_stride;
+    DmaLoader<BM, NT, KMAJOR> lp;
+    DmaLoader<BN, NT, KMAJOR> lq;
+    lp.init(P, m0, tid);
+    lq.init(Q, n0, tid);
+    constexpr int LOADS = DmaLoader<BM, NT, KMAJOR>::L + DmaLoader<BN, NT, KMAJOR>::L;  // of a wave per stage
+    static_assert((DEPTH - 1) * LOADS < 64, "the counter holds the loads in flight");
+    auto issue = [&](int kt) __attribute__((always_inline)) {
+        char* dst = lds + (kt & (DEPTH - 1)) * STAGE_BYTES;
+        lp.load(pb + (int64_t)kt * pstep, kt * 8, kchunks, zero_page, dst, wave);
+        lq.load(qb + (int64_t)kt * qstep, kt * 8, kchunks, zero_page, dst + BM * PITCH, wave);
+    };
+    typename MT::acc_t acc[MB][NB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][j][e] = 0;
+    u32x4 fa[2][KSTEPS][MB], fb[2][KSTEPS][NB];
+
+    // the barrier without the memory fence of __syncthreads(), which would wait for every load in flight: what it orders is the
+    // stage that every wave has waited for by count, and the reads of the stage whose buffer is loaded next (lgkmcnt(0))
+#define EGG_DEEP_BARRIER(N_)                               \
+    asm volatile("" ::: "memory");                         \
+    __builtin_amdgcn_s_waitcnt(vm_lds_imm((N_)*LOADS));    \
+    __builtin_amdgcn_s_barrier();                          \
+    asm volatile("" ::: "memory");
+#define EGG_DEEP_READ(SET, KT_)                                                                                \
+    {                                                                                                          \
+        const char* st_ = lds + ((KT_) & (DEPTH - 1)) * STAGE_BYTES;                                           \
+        _Pragma("unroll") for (int ks = 0; ks < KSTEPS; ++ks)                                                  \
+        {                                                                                                      \
+            _Pragma("unroll") for (int j = 0; j < NB; ++j) fb[SET][ks][j] = *(const u32x4*)(st_ + b_base + foffb[ks] + j * BLK_STEP); \
+            _Pragma("unroll") for (int i = 0; i < MB; ++i) fa[SET][ks][i] = *(const u32x4*)(st_ + a_base + foffa[ks] + i * BLK_STEP); \
+        }                                                                                                      \
+    }
+    // stage KT_, its fragments in set SET; IN_FLIGHT: stages issued after stage KT_ + 1 that may still be under way
+#define EGG_ITER_DEEP(KT_, SET, NEXT, LOAD4, IN_FLIGHT)                                                        \
+    {                                                                                                          \
+        EGG_DEEP_BARRIER(IN_FLIGHT) /* stage KT_ + 1 has landed; every wave holds stage KT_ in registers */     \
+        if (LOAD4) issue((KT_) + DEPTH);                                                                       \
+        if (NEXT) EGG_DEEP_READ((SET) ^ 1, (KT_) + 1)                                                          \
+        _Pragma("unroll") for (int ks = 0; ks < KSTEPS; ++ks)                                                  \
+            _Pragma("unroll") for (int i = 0; i < MB; ++i)                                                     \
+                _Pragma("unroll") for (int j = 0; j < NB; ++j) MT::mma(fa[SET][ks][i], fb[SET][ks][j], acc[i][j]); \
+        _Pragma("unroll") for (int r_ = 0; r_ < KSTEPS * MB * NB; ++r_)                                        \
+        {                                                                                                      \
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                 \
+            if ((NEXT) && r_ < KSTEPS * (MB + NB)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);          \
+        }                                                                                                      \
+    }
+    issue(0);
+    if (KT > 1) issue(1);
+    if (KT > 2) issue(2);
+    if (KT > 3) issue(3);
+    if (KT > 3) { EGG_DEEP_BARRIER(3) }
+    else { EGG_DEEP_BARRIER(0) }
+    EGG_DEEP_READ(0, 0)
+    int kt = 0;
+    for (; kt + DEPTH + 1 < KT; kt += 2) {  // stages kt + 2 and kt + 3 may be under way
+        EGG_ITER_DEEP(kt, 0, true, true, DEPTH - 2)
+        EGG_ITER_DEEP(kt + 1, 1, true, true, DEPTH - 2)
+    }
+    if (kt + DEPTH < KT) {
+        EGG_ITER_DEEP(kt, 0, true, true, DEPTH - 2)
+        ++kt;
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) {  // (the sets are named at compile time)
+#pragma unroll
+            for (int i = 0; i < MB; ++i) fa[0][ks][i] = fa[1][ks][i];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) fb[0][ks][j] = fb[1][ks][j];
+        }
+    }
+    // the last stages, nothing more to issue: KT - 2 - kt stages are under way beyond stage kt + 1
+    const int left = KT - kt;  // 1 .. 4
+    if (left == 4) {
+        EGG_ITER_DEEP(kt, 0, true, false, 2)
+        EGG_ITER_DEEP(kt + 1, 1, true, false, 1)
+        EGG_ITER_DEEP(kt + 2, 0, true, false, 0)
+        EGG_ITER_DEEP(kt + 3, 1, false, false, 0)
+    } else if (left == 3) {
+        EGG_ITER_DEEP(kt, 0, true, false, 0)
+        EGG_ITER_DEEP(kt + 1, 1, true, false, 0)
+        EGG_ITER_DEEP(kt + 2, 0, false, false, 0)
+    } else if (left == 2) {
+        EGG_ITER_DEEP(kt, 0, true, false, 0)
+        EGG_ITER_DEEP(kt + 1, 1, false, false, 0)
+    } else {
+        EGG_ITER_DEEP(kt, 0, false, false, 0)
+    }
+#undef EGG_ITER_DEEP
+#undef EGG_DEEP_READ
+#undef EGG_DEEP_BARRIER
+    Epi epi(ea, lds + DEPTH * STAGE_BYTES + wave * Epi::lds_per_wave(WTM), lane);
+    epi.template prefetch<MB, NB>(m0 + wm * WTM, n0 + wn * WTN, lane, Q.rows);
+    epi.template extra_mma<MT, MB, NB>(acc, m0 + wm * WTM, n0 + wn * WTN, lane, Q.rows);
+    static_for<0, NB>([&](auto jc) __attribute__((always_inline)) {
+        constexpr int j = decltype(jc)::value;
+        const int n = n0 + wn * WTN + j * BLK + (lane & (BLK - 1));
+        const bool nvalid = n < Q.rows;
+        epi.template column_at<j>(n, nvalid);
+        static_for<0, MB>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+            const int ml = i * BLK + (lane >> 4) * 4;
+            typename Epi::value_t v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = acc[i][j][e];
+            epi.template store4_at<i, j>(m0 + wm * WTM + ml, n, v, nvalid, ml);
+        });
+        epi.template flush<WTM>(m0 + wm * WTM, n0 + wn * WTN + j * BLK, Q.rows);
+    });
 }
 
 #undef EGG_ITER16

@@ -20,34 +20,57 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ int sat127(int v) { return min(127, max(-127, v)); }
 __device__ __forceinline__ int sbyte(uint32_t w, int b) { return (int)(int8_t)(w >> (8 * b)); }
 
+// sum over the 2^L neighbouring lanes that share a row, left in all of them: within 16 lanes by DPP (each level adds the other
+// half of a group whose lanes already agree), beyond by shuffles
+template <int L>
+__device__ __forceinline__ int row_sum(int x)
+{
+#define EGG_DPP_ADD(CTRL) x += __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true);
+    if constexpr (L >= 1) EGG_DPP_ADD(0xB1)   // quad_perm [1, 0, 3, 2]
+    if constexpr (L >= 2) EGG_DPP_ADD(0x4E)   // quad_perm [2, 3, 0, 1]
+    if constexpr (L >= 3) EGG_DPP_ADD(0x141)  // row_half_mirror: the other quad of the half row
+    if constexpr (L >= 4) EGG_DPP_ADD(0x140)  // row_mirror: the other half row
+#undef EGG_DPP_ADD
+    if constexpr (L >= 5) x += __shfl_xor(x, 16, 64);
+    if constexpr (L >= 6) x += __shfl_xor(x, 32, 64);
+    return x;
+}
+
 // y[row] = I8(y[row] + add[row]) when add != nullptr (written back), then u[row] = LN(ln, y[row]).
 // By-products (LnExtras): dot products of the normalised row with the row of up to two factor arrays (the
 // u . B of the matmuls that read u; the odd member of an antithetic pair uses -B), and two int32 vectors
 // cleared for epilogues that accumulate into them later.
+// L: log2 of the lanes per row.  Bandwidth work; every load goes out before the first use (the weights and the factor rows
+// used to be asked for behind the row sum, two more memory round trips in a row).
+template <int L>
 __global__ __launch_bounds__(256) void resid_ln_kernel(const int8_t* __restrict__ add, int8_t* __restrict__ y,
                                                        const int8_t* __restrict__ ln, int8_t* __restrict__ u,
-                                                       int64_t rows, int lpr_log2, int d_log2, LnExtras ex)
+                                                       int64_t rows, LnExtras ex)
 {
+    constexpr int d_log2 = L + 4;
     const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t row = gid >> lpr_log2;
-    const int part = (int)(gid & ((1 << lpr_log2) - 1));
-    const bool live = row < rows;   // dead lanes run the shuffles with zeros
-    const size_t off = ((size_t)row << d_log2) + (size_t)part * 16;
-    u32x4 yv = {0, 0, 0, 0};
-    if (live) {
-        yv = *(const u32x4*)(y + off);
-        if (add) {
-            const u32x4 av = *(const u32x4*)(add + off);
+    const int64_t row = gid >> L;
+    const int part = (int)(gid & ((1 << L) - 1));
+    const bool live = row < rows;   // dead lanes (whole rows of them) run the shuffles on a copy of the last row
+    const int64_t rl = live ? row : rows - 1;
+    const size_t off = ((size_t)rl << d_log2) + (size_t)part * 16;
+    const size_t foff = ((size_t)(ex.anti ? rl >> 1 : rl) << d_log2) + (size_t)part * 16;
+    u32x4 yv = *(const u32x4*)(y + off);
+    u32x4 av = {0, 0, 0, 0}, b0 = av, b1 = av;
+    if (add) av = *(const u32x4*)(add + off);
+    const u32x4 lv = *(const u32x4*)(ln + (size_t)part * 16);
+    if (ex.dot[0]) b0 = *(const u32x4*)(ex.B[0] + foff);
+    if (ex.dot[1]) b1 = *(const u32x4*)(ex.B[1] + foff);
+    if (add) {
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const uint32_t yw = yv[w], aw = av[w];
-                uint32_t o = 0;
+        for (int w = 0; w < 4; ++w) {
+            const uint32_t yw = yv[w], aw = av[w];
+            uint32_t o = 0;
 #pragma unroll
-                for (int b = 0; b < 4; ++b) o |= (uint32_t)(sat127(sbyte(yw, b) + sbyte(aw, b)) & 0xFF) << (8 * b);
-                yv[w] = o;
-            }
-            *(u32x4*)(y + off) = yv;
+            for (int b = 0; b < 4; ++b) o |= (uint32_t)(sat127(sbyte(yw, b) + sbyte(aw, b)) & 0xFF) << (8 * b);
+            yv[w] = o;
         }
+        if (live) *(u32x4*)(y + off) = yv;
     }
     int sum = 0;
 #pragma unroll
@@ -56,11 +79,9 @@ __global__ __launch_bounds__(256) void resid_ln_kernel(const int8_t* __restrict_
 #pragma unroll
         for (int b = 0; b < 4; ++b) sum += abs(sbyte(yw, b));
     }
-    for (int o = 1; o < (1 << lpr_log2); o <<= 1) sum += __shfl_xor(sum, o, 64);
-    if (!live) return;
+    sum = row_sum<L>(sum);
     const uint32_t mav = (uint32_t)max(sum >> d_log2, 1);
     const uint32_t magic = ((1u << 21) + mav - 1u) / mav;
-    const u32x4 lv = *(const u32x4*)(ln + (size_t)part * 16);
     u32x4 ov;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -74,30 +95,23 @@ __global__ __launch_bounds__(256) void resid_ln_kernel(const int8_t* __restrict_
         }
         ov[w] = o;
     }
-    *(u32x4*)(u + off) = ov;
+    if (live) *(u32x4*)(u + off) = ov;
     if (ex.dot[0]) {
-        const size_t foff = ((size_t)(ex.anti ? row >> 1 : row) << d_log2) + (size_t)part * 16;
-        const u32x4 b0 = *(const u32x4*)(ex.B[0] + foff);
         int d0 = 0, d1 = 0;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) d0 = __builtin_amdgcn_sdot4((int)ov[w], (int)b0[w], d0, false);
-        if (ex.dot[1]) {
-            const u32x4 b1 = *(const u32x4*)(ex.B[1] + foff);
-#pragma unroll
-            for (int w = 0; w < 4; ++w) d1 = __builtin_amdgcn_sdot4((int)ov[w], (int)b1[w], d1, false);
+        for (int w = 0; w < 4; ++w) {
+            d0 = __builtin_amdgcn_sdot4((int)ov[w], (int)b0[w], d0, false);
+            d1 = __builtin_amdgcn_sdot4((int)ov[w], (int)b1[w], d1, false);
         }
-        // every lane of a live row is live (rows are whole groups of lanes), so the shuffles stay inside the row
-        for (int o = 1; o < (1 << lpr_log2); o <<= 1) {
-            d0 += __shfl_xor(d0, o, 64);
-            d1 += __shfl_xor(d1, o, 64);
-        }
-        if (part == 0) {
+        d0 = row_sum<L>(d0);
+        if (ex.dot[1]) d1 = row_sum<L>(d1);
+        if (part == 0 && live) {
             const bool neg = ex.anti && (row & 1);
             ex.dot[0][row] = neg ? -d0 : d0;
             if (ex.dot[1]) ex.dot[1][row] = neg ? -d1 : d1;
         }
     }
-    if (part == 0) {
+    if (part == 0 && live) {
         if (ex.zero[0]) ex.zero[0][row] = 0;
         if (ex.zero[1]) ex.zero[1][row] = 0;
     }
@@ -209,9 +223,14 @@ egg_status launch_layernorm_i8(eggroll_ctx* c, const int8_t* add, int8_t* y, con
     if (rows == 0) return EGG_OK;
     KernelScope ks(c, "resid_layernorm_i8");
     const int lpr = ilog2(D / 16);
-    const int64_t threads = rows << lpr;
-    hipLaunchKernelGGL(resid_ln_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, c->stream, add, y, ln, u, rows, lpr, ilog2(D),
-                       extras ? *extras : LnExtras());
+    const dim3 g((unsigned)(((rows << lpr) + 255) / 256)), b(256);
+    const LnExtras ex = extras ? *extras : LnExtras();
+    switch (lpr) {
+#define EGG_LN(L) case L: hipLaunchKernelGGL(resid_ln_kernel<L>, g, b, 0, c->stream, add, y, ln, u, rows, ex); break;
+        EGG_LN(0) EGG_LN(1) EGG_LN(2) EGG_LN(3) EGG_LN(4) EGG_LN(5)
+#undef EGG_LN
+        default: hipLaunchKernelGGL(resid_ln_kernel<6>, g, b, 0, c->stream, add, y, ln, u, rows, ex); break;
+    }
     return check_hip(c, hipGetLastError(), "resid_layernorm_i8 launch");
 }
 

@@ -6,6 +6,7 @@
 #include "common.hpp"
 #include "gemm_core.hpp"
 #include "forward_fold.hpp"
+#include "gemm_small.hpp"
 
 namespace egg {
 
@@ -557,6 +558,101 @@ struct FwdEpi {
     }
 };
 
+// Epilogue of the small kernel: the general one, for 4 consecutive outputs of a row that a thread has read back from LDS (so
+// that they are stored directly, and the cache of regenerated factors too).
+template <bool BF16, int RANK, bool REGEN>
+struct FwdSmallEpi {
+    typedef float value_t;
+    typedef FwdArgs Args;
+    const Args a;
+    __device__ __forceinline__ FwdSmallEpi(const Args& a_) : a(a_) {}
+    __device__ __forceinline__ void apply4(int m, int n, const float (&v)[4])
+    {
+        float y[4] = {v[0], v[1], v[2], v[3]};
+        if (a.c != 0.f) {
+            const int64_t ml = n / a.S;
+            const int64_t aoff = (ml * a.d_out + m) * RANK;  // element offset of A_i[m][0]
+            float z[4 * RANK];
+            if constexpr (REGEN) {
+                static_assert(RANK == 1, "in-register regeneration is the rank-1 path");
+                uint32_t pk[2];
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    uint32_t w0, w1;
+                    noise_words(a.ka, a.member_begin + (uint32_t)ml, ((uint32_t)m >> 1) + b, w0, w1);
+                    normal_pair<!BF16>(w0, w1, z[2 * b], z[2 * b + 1]);
+                    if constexpr (BF16) {
+                        pk[b] = pack_bf16x2(z[2 * b], z[2 * b + 1]);
+                        z[2 * b] = bf16_lo(pk[b]);
+                        z[2 * b + 1] = bf16_hi(pk[b]);
+                    }
+                }
+                if (a.A_buf) {  // (with pairs a kept cache goes the materialised way: here a row is a member)
+                    if constexpr (BF16) *(uint2*)((uint16_t*)a.A_buf + aoff) = make_uint2(pk[0], pk[1]);
+                    else *(float4*)((float*)a.A_buf + aoff) = make_float4(z[0], z[1], z[2], z[3]);
+                }
+            } else if constexpr (BF16) {
+                const uint2* src = (const uint2*)((const uint16_t*)a.A_buf + aoff);
+#pragma unroll
+                for (int k = 0; k < RANK; ++k) {
+                    const uint2 p = src[k];
+                    z[4 * k] = bf16_lo(p.x); z[4 * k + 1] = bf16_hi(p.x);
+                    z[4 * k + 2] = bf16_lo(p.y); z[4 * k + 3] = bf16_hi(p.y);
+                }
+            } else {
+                const float4* src = (const float4*)((const float*)a.A_buf + aoff);
+#pragma unroll
+                for (int k = 0; k < RANK; ++k) {
+                    const float4 p = src[k];
+                    z[4 * k] = p.x; z[4 * k + 1] = p.y; z[4 * k + 2] = p.z; z[4 * k + 3] = p.w;
+                }
+            }
+            float tc[RANK];
+#pragma unroll
+            for (int l = 0; l < RANK; ++l) tc[l] = a.c * a.t[(int64_t)n * RANK + l];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float corr = 0.f;
+#pragma unroll
+                for (int l = 0; l < RANK; ++l) corr = fmaf(tc[l], z[e * RANK + l], corr);
+                y[e] += corr;
+            }
+        }
+        if (a.act == EGG_ACT_GELU) {
+            if (a.y_bf16) gelu_bf16_grade4(y);
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] = 0.5f * y[e] * (1.0f + erff(y[e] * 0.70710678118654752f));
+        }
+        const int64_t at = (int64_t)n * a.d_out + m;  // d_out is a multiple of 4: whole groups
+        if (a.y_bf16) {
+            if (a.resid) {
+                const uint2 rv = *(const uint2*)((const uint16_t*)a.resid + at);
+                y[0] += bf16_lo(rv.x); y[1] += bf16_hi(rv.x);
+                y[2] += bf16_lo(rv.y); y[3] += bf16_hi(rv.y);
+            }
+            *(uint2*)((uint16_t*)a.Y + at) = make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+        } else {
+            if (a.resid) {
+                const float4 rv = *(const float4*)((const float*)a.resid + at);
+                y[0] += rv.x; y[1] += rv.y; y[2] += rv.z; y[3] += rv.w;
+            }
+            *(float4*)((float*)a.Y + at) = make_float4(y[0], y[1], y[2], y[3]);
+        }
+    }
+};
+
+template <class MT, class Epi>
+static egg_status launch_gemm_small(eggroll_ctx* c, const char* name, const Operand& P, const Operand& Q, int kchunks, int tile,
+                                    const typename Epi::Args& ea)
+{
+    const int tm = (P.rows + tile - 1) / tile, tn = (Q.rows + tile - 1) / tile;
+    KernelScope ks(c, shaped_name(c, name, P.rows, kchunks * 16 / (ea.y_bf16 ? 2 : 4)));
+    if (std::is_same_v<MT, MmaBf16> || tile == 32) hipLaunchKernelGGL((gemm_small_kernel<MT, false, 32, Epi>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
+    else if constexpr (!std::is_same_v<MT, MmaBf16>) hipLaunchKernelGGL((gemm_small_kernel<MT, false, 64, Epi>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
+    return check_hip(c, hipGetLastError(), name);
+}
+
 template <class MT, int BM, int BN, int WM, int WN, class Epi>
 static egg_status launch_gemm(eggroll_ctx* c, const char* name, const Operand& P, const Operand& Q, int kchunks,
                               typename Epi::Args ea)
@@ -655,6 +751,8 @@ static egg_status launch_forward_t(eggroll_ctx* c, const StreamKey& ka, const eg
     typename Epi::Args ea{ka, (uint32_t)(s.member_begin / anti), s.rows_per_member * anti, s.d_out, sigma / sqrtf((float)s.rank),
                           (int)act, yd == EGG_BF16 ? 1 : 0, Y, t, A_buf, 0, 0, 0, (REGEN && s.antithetic) ? 1 : 0, resid,
                           nullptr, nullptr};
+    const int small = next ? 0 : small_tile(s.d_out, R, !BF16);
+    if (small) return launch_gemm_small<std::conditional_t<BF16, MmaBf16, MmaF32>, FwdSmallEpi<BF16, RANK, REGEN>>(c, BF16 ? "forward_gemm_bf16_small" : "forward_gemm_f32", P, Q, kchunks, small, ea);
     if constexpr (BF16) {
         const int64_t big_tiles = ((s.d_out + 255) / 256) * ((R + 255) / 256);
         // bf16 out and no correction, or one that 16 neighbouring rows share among at most two members: folded into the

@@ -198,6 +198,24 @@ static egg_status launch_fold_t(eggroll_ctx* c, const char* name, const Operand&
     return check_hip(c, hipGetLastError(), name);
 }
 
+// tiles that do not fill the chip: one workgroup per CU with four stages in flight
+template <int AW, int LEAN>
+static egg_status launch_fold_deep(eggroll_ctx* c, const Operand& P, const Operand& Q, int kchunks, const FoldArgs& ea)
+{
+    constexpr int BM = 128, BN = 128, WM = 2, WN = 2;
+    typedef FoldEpi<AW, LEAN, BM / WM / 16> Epi;
+    auto kern = gemm_nt_deep_kernel<MmaBf16Blk16, BM, BN, WM, WN, false, Epi>;
+    const int tiles_m = (P.rows + BM - 1) / BM, tiles_n = (Q.rows + BN - 1) / BN;
+    const size_t lds = 2 * gemm_lds_bytes<BM, BN>() + (size_t)WM * WN * Epi::lds_per_wave(BM / WM);
+    if (!operand_offsets_fit(P, BM) || !operand_offsets_fit(Q, BN)) return fail(c, EGG_EUNSUPPORTED, "operand strides too large for 32-bit tile offsets");
+    const egg_status st = ensure_dynamic_lds(c, (const void*)kern, lds, "gemm smem attr");
+    if (st != EGG_OK) return st;
+    KernelScope ks(c, shaped_name(c, "forward_gemm_bf16_small", P.rows, kchunks * 8));
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(WM * WN * 64), lds, c->stream, P, Q, kchunks, tiles_m, tiles_n,
+                       (const char*)c->zero_page.p, ea);
+    return check_hip(c, hipGetLastError(), "forward_gemm_bf16_small");
+}
+
 template <int AW, int LEAN>
 static egg_status launch_fold_aw(eggroll_ctx* c, const Operand& P, const Operand& Q, int kchunks, const FoldArgs& ea)
 {
@@ -209,6 +227,7 @@ static egg_status launch_fold_aw(eggroll_ctx* c, const Operand& P, const Operand
             if (kchunks % 8 == 0) return launch_fold_t<256, 256, 2, 4, 1, false, AW, LEAN>(c, "forward_gemm_bf16", P, Q, kchunks, ea);
         return launch_fold_t<256, 256, 2, 4, 1, true, AW, LEAN>(c, "forward_gemm_bf16", P, Q, kchunks, ea);
     }
+    if (((P.rows + 127) / 128) * (((int64_t)Q.rows + 127) / 128) <= c->compute_units) return launch_fold_deep<AW, LEAN>(c, P, Q, kchunks, ea);
     return launch_fold_t<128, 128, 2, 2, 2, true, AW, LEAN>(c, "forward_gemm_bf16_small", P, Q, kchunks, ea);
 }
 

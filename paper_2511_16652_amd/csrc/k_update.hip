@@ -13,6 +13,7 @@
 // and a fixed summation order, so the result is run-to-run identical.
 #include "common.hpp"
 #include "gemm_core.hpp"
+#include "gemm_small.hpp"
 
 namespace egg {
 
@@ -468,6 +469,65 @@ struct UpdEpiT {
     }
 };
 
+// Epilogue of the small kernel: rows of the product are the columns k of G (P = B panel), its columns the rows j, so that the 4
+// consecutive values of a thread are neighbours in G.
+struct UpdSmallEpi {
+    typedef float value_t;
+    typedef UpdArgs Args;
+    const Args a;
+    float scale;
+    __device__ __forceinline__ UpdSmallEpi(const Args& a_) : a(a_) { scale = a.scale * a.fnorm[0]; }
+    __device__ __forceinline__ void apply4(int m, int n, const float (&v)[4])
+    {
+        const int64_t at = (int64_t)n * a.d_in + m;
+        float g[4];
+        if (a.d_in % 4 == 0) {
+            if (a.accumulate) {
+                const float4 o = *(const float4*)(a.G + at);
+                g[0] = fmaf(scale, v[0], o.x); g[1] = fmaf(scale, v[1], o.y); g[2] = fmaf(scale, v[2], o.z); g[3] = fmaf(scale, v[3], o.w);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) g[e] = scale * v[e];
+            }
+            *(float4*)(a.G + at) = make_float4(g[0], g[1], g[2], g[3]);
+            if (a.W && a.w_bf16) {
+                uint2* w = (uint2*)((uint16_t*)a.W + at);
+                const uint2 o = *w;
+                *w = make_uint2(pack_bf16x2(fmaf(a.lr, g[0], bf16_lo(o.x)), fmaf(a.lr, g[1], bf16_hi(o.x))),
+                                pack_bf16x2(fmaf(a.lr, g[2], bf16_lo(o.y)), fmaf(a.lr, g[3], bf16_hi(o.y))));
+            } else if (a.W) {
+                float4* w = (float4*)((float*)a.W + at);
+                const float4 o = *w;
+                *w = make_float4(fmaf(a.lr, g[0], o.x), fmaf(a.lr, g[1], o.y), fmaf(a.lr, g[2], o.z), fmaf(a.lr, g[3], o.w));
+            }
+            return;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (m + e >= a.d_in) break;
+            g[e] = a.accumulate ? fmaf(scale, v[e], a.G[at + e]) : scale * v[e];
+            a.G[at + e] = g[e];
+            if (a.W && a.w_bf16) {
+                uint16_t* w = (uint16_t*)a.W + at + e;
+                *w = f32_to_bf16_bits(fmaf(a.lr, g[e], bf16_bits_to_f32(*w)));
+            } else if (a.W) {
+                float* w = (float*)a.W + at + e;
+                *w = fmaf(a.lr, g[e], *w);
+            }
+        }
+    }
+};
+
+template <class MT>
+static egg_status launch_upd_small(eggroll_ctx* c, const char* name, const Operand& P, const Operand& Q, int kchunks, int tile, const UpdArgs& ea)
+{
+    const int tm = (P.rows + tile - 1) / tile, tn = (Q.rows + tile - 1) / tile;
+    KernelScope ks(c, name);
+    if (tile == 32) hipLaunchKernelGGL((gemm_small_kernel<MT, true, 32, UpdSmallEpi>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
+    else hipLaunchKernelGGL((gemm_small_kernel<MT, true, 64, UpdSmallEpi>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
+    return check_hip(c, hipGetLastError(), name);
+}
+
 template <class MT, int BM, int BN, int WM, int WN>
 static egg_status launch_upd_gemm(eggroll_ctx* c, const char* name, const Operand& P, const Operand& Q, int kchunks,
                                   const UpdArgs& ea)
@@ -549,6 +609,10 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
     Operand P{(const char*)c->pack_a.p, 16, (int64_t)s.d_out * 16, s.d_out};
     Operand Q{(const char*)(b_panel ? B_cache : c->pack_b.p), 16, (int64_t)s.d_in * 16, s.d_in};
     UpdArgs ea{G, W, fnorm, s.d_out, s.d_in, scale, lr, accumulate, w_dtype == EGG_BF16 ? 1 : 0};
+    if (const int small = small_tile(s.d_in, s.d_out, true)) {
+        return bf ? launch_upd_small<MmaF16>(c, "update_gemm_f16_small", Q, P, (int)kgroups, small, ea)
+                  : launch_upd_small<MmaF32>(c, "update_gemm_f32", Q, P, (int)kgroups, small, ea);
+    }
     if (bf) {
         const int64_t big_tiles = ((s.d_out + 255) / 256) * (int64_t)((s.d_in + 255) / 256);
         if (big_tiles >= 192) return launch_upd_gemm<MmaF16, 256, 256, 2, 4>(c, "update_gemm_f16", P, Q, (int)kgroups, ea);

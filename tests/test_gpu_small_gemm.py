@@ -1,0 +1,84 @@
+"""GPU: products too small for the chip-filling tiles (32 and 64 tiles with K split over four waves; one 128 x 128 tile per CU with
+four stages in flight), at the edges of their K ranges and of the rule between them.
+
+References in 64 bits from the library's own factors; fp32: 1e-5 of |value| + rms (sums of up to 2064 products in another order);
+bf16 outputs: one rounding, 2^-8; update panels in fp16: 2^-11 per term, random sign, so 2e-3 of the rms covers every entry."""
+import math
+
+import pytest
+
+from paper_2511_16652_amd import binding as eb
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    c = eb.Context(0)
+    yield c
+    torch.cuda.synchronize()
+    c.close()
+
+
+def factors(ctx, key, ids, n, rank, which, tdt, code):
+    import torch
+    F = torch.empty((ids, n, rank), dtype=tdt, device="cuda")
+    shape = eb.make_shape(0, ids, 1, n, n, rank)
+    ctx.eggroll_noise_gen(key, shape, code, eb.EGG_NORMAL, 0, *((F, None) if which == 0 else (None, F)))
+    return F
+
+
+@pytest.mark.parametrize("dtype,d_out,d_in,N,S,rank,cache", [
+    ("f32", 4, 4, 1, 1, 1, 0), ("f32", 36, 12, 33, 1, 1, 1), ("f32", 100, 68, 9, 3, 4, 0), ("f32", 256, 2064, 5, 7, 2, 0),
+    ("f32", 1028, 132, 260, 2, 1, 0),       # 33 x 17 tiles of 32: the 64 form
+    ("bf16", 4, 8, 1, 1, 1, 0), ("bf16", 36, 24, 33, 1, 1, 1), ("bf16", 100, 520, 9, 3, 4, 0), ("bf16", 132, 2056, 5, 7, 16, 0),
+    ("bf16", 520, 64, 33, 16, 2, 0),        # 17 x 17 tiles of 32
+    ("bf16", 1028, 64, 33, 16, 2, 0),       # 33 x 17: past the 32 form; one stage of K
+    ("bf16", 1028, 136, 33, 16, 4, 0), ("bf16", 1028, 200, 33, 16, 8, 0), ("bf16", 1028, 256, 33, 16, 1, 0),   # two, three and four stages
+    ("bf16", 1028, 328, 33, 16, 1, 0), ("bf16", 1028, 392, 33, 16, 1, 0), ("bf16", 1028, 456, 33, 16, 1, 0),   # five, six, seven
+])
+def test_small_forward(ctx, dtype, d_out, d_in, N, S, rank, cache):
+    import torch
+    tdt, code = (torch.bfloat16, eb.EGG_BF16) if dtype == "bf16" else (torch.float32, eb.EGG_F32)
+    g = torch.Generator("cuda").manual_seed(d_in)
+    W = (torch.randn((d_out, d_in), generator=g, device="cuda") * d_in ** -0.5).to(tdt)
+    X = torch.randn((N * S, d_in), generator=g, device="cuda").to(tdt)
+    Y = torch.full((N * S, d_out), float("nan"), dtype=tdt, device="cuda")
+    key, sigma = eb.make_key(1, 2, 3), 0.5
+    A, B = factors(ctx, key, N, d_out, rank, 0, tdt, code), factors(ctx, key, N, d_in, rank, 1, tdt, code)
+    Ac, Bc = (torch.empty_like(A), torch.empty_like(B)) if cache else (None, None)
+    ctx.eggroll_perturbed_forward(key, eb.make_shape(0, N, S, d_out, d_in, rank), sigma, eb.EGG_ACT_NONE, W, X, Y, Ac, Bc)
+    if cache:
+        assert torch.equal(A, Ac) and torch.equal(B, Bc)
+    t = torch.bmm(X.double().view(N, S, d_in), B.double())
+    corr = torch.bmm(t, A.double().transpose(1, 2).contiguous()).view(N * S, d_out) * (sigma / math.sqrt(rank))
+    ref = X.double() @ W.double().t().contiguous() + corr
+    rms = ref.square().mean(1, keepdim=True).sqrt()
+    tol = 1e-5 * (ref.abs() + rms) if dtype == "f32" else 2.0 ** -8 * ref.abs() + 1e-4 * (rms + corr.abs().amax(1, keepdim=True))
+    assert ((Y.double() - ref).abs() <= tol).all()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d_out,d_in,N,rank", [(4, 2, 1, 1), (36, 7, 9, 2), (260, 130, 33, 1), (256, 256, 257, 8), (1028, 1056, 64, 1),
+                                              (1028, 1056, 65, 4), (2052, 1030, 40, 1)])  # the 32 form, the 64 form, past both
+@pytest.mark.parametrize("w", [None, "bf16", "f32"])
+def test_small_update(ctx, dtype, d_out, d_in, N, rank, w):
+    import torch
+    tdt, code = (torch.bfloat16, eb.EGG_BF16) if dtype == "bf16" else (torch.float32, eb.EGG_F32)
+    g = torch.Generator("cuda").manual_seed(d_in)
+    key = eb.make_key(1, 2, 3)
+    A, B = factors(ctx, key, N, d_out, rank, 0, tdt, code), factors(ctx, key, N, d_in, rank, 1, tdt, code)
+    f = torch.randn(N, generator=g, device="cuda")
+    G0 = torch.randn((d_out, d_in), generator=g, device="cuda")
+    G, W = G0.clone(), None
+    if w:
+        W0 = torch.randn((d_out, d_in), generator=g, device="cuda").to(torch.bfloat16 if w == "bf16" else torch.float32)
+        W = W0.clone()
+    ctx.eggroll_update(key, eb.make_shape(0, N, 1, d_out, d_in, rank), code, f, 0.25, 1, G, W, 0.125)
+    ref = torch.einsum("nor,nir->oi", (A.double() * f.double()[:, None, None]).cpu(), B.double().cpu()).cuda() * 0.25 + G0.double()
+    rms = ref.square().mean().sqrt()
+    assert ((G.double() - ref).abs() <= (1e-5 * (ref.abs() + rms) if dtype == "f32" else 2e-3 * (ref.abs() + rms))).all()
+    if w:
+        want = W0.double() + 0.125 * G.double()
+        assert ((W.double() - want).abs() <= (2.0 ** -8 if w == "bf16" else 1e-6) * (want.abs() + 1e-3)).all()
