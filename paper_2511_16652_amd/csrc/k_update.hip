@@ -469,6 +469,94 @@ struct UpdEpiT {
     }
 };
 
+// Epilogue of the f16 contraction.  Rows of the product are the columns k of G (P = B panel), its columns the rows j (Q = A
+// panel): a lane of a 16 x 16 block owns 4 consecutive k of one j.  A block of 16 rows of G is parked in the wave's LDS slice and
+// read back so that the wave writes whole runs of WTM floats of a row in 16-byte pieces (and reads W and, when accumulating, G the
+// same way, in one batch per block, unconditionally from clamped addresses).
+template <int WTM>
+struct UpdEpi16 {
+    typedef float value_t;
+    typedef UpdArgs Args;
+    const Args a;
+    char* const stage;
+    const int lane;
+    static constexpr int P = WTM * 4 + 16, CPR = WTM / 4, PASSES = 16 * CPR / 64;
+    static constexpr __host__ __device__ int lds_per_wave(int) { return 16 * P; }
+    __device__ __forceinline__ UpdEpi16(const Args& a_, char* slice, int lane_) : a(a_), stage(slice), lane(lane_) {}
+    __device__ __forceinline__ void column(int, bool) {}
+    template <int J>
+    __device__ __forceinline__ void column_at(int, bool) {}
+    template <int NT, int BM, int BN>
+    __device__ __forceinline__ bool tile_begin(char*, int, int, int, int) { return false; }
+    template <class MT, int MB, int NB>
+    __device__ __forceinline__ void extra_mma(typename MT::acc_t (&)[MB][NB], int, int, int, int) {}
+    template <int MB, int NB>
+    __device__ __forceinline__ void prefetch(int, int, int, int) {}
+    template <int I, int J>
+    __device__ __forceinline__ void store4_at(int m, int n, const float (&v)[4], bool valid, int ml) { store4(m, n, v, valid, ml); }
+    __device__ __forceinline__ void store4(int, int, const float (&v)[4], bool, int ml)
+    {
+        *(float4*)(stage + (lane & 15) * P + ml * 4) = make_float4(v[0], v[1], v[2], v[3]);
+    }
+    template <int W_>
+    __device__ __forceinline__ void flush(int mw0, int nb0, int n_rows)
+    {
+        static_assert(W_ == WTM, "wave tile of the launched kernel");
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's own LDS writes have landed
+        __builtin_amdgcn_wave_barrier();
+        const float scale = a.scale * a.fnorm[0];
+        if (a.d_in % 4 == 0) {
+            float4 g[PASSES], old[PASSES], wf[PASSES];
+            uint2 wb[PASSES];
+            auto at = [&](int it, bool& in) __attribute__((always_inline)) {
+                const int c = it * 64 + lane, j = nb0 + c / CPR, k = mw0 + (c % CPR) * 4;
+                in = j < n_rows && k < a.d_in;
+                return (int64_t)min(j, n_rows - 1) * a.d_in + min(k, a.d_in - 4);
+            };
+            bool in;
+#pragma unroll
+            for (int it = 0; it < PASSES; ++it) {
+                const int c = it * 64 + lane;
+                g[it] = *(const float4*)(stage + (c / CPR) * P + (c % CPR) * 16);
+                if (a.accumulate) old[it] = *(const float4*)(a.G + at(it, in));
+                if (a.W && a.w_bf16) wb[it] = *(const uint2*)((const uint16_t*)a.W + at(it, in));
+                else if (a.W) wf[it] = *(const float4*)((const float*)a.W + at(it, in));
+            }
+#pragma unroll
+            for (int it = 0; it < PASSES; ++it) {
+                const int64_t idx = at(it, in);
+                float v[4] = {scale * g[it].x, scale * g[it].y, scale * g[it].z, scale * g[it].w};
+                if (a.accumulate) { v[0] += old[it].x; v[1] += old[it].y; v[2] += old[it].z; v[3] += old[it].w; }
+                if (!in) continue;
+                *(float4*)(a.G + idx) = make_float4(v[0], v[1], v[2], v[3]);
+                if (a.W && a.w_bf16)
+                    *(uint2*)((uint16_t*)a.W + idx) = make_uint2(pack_bf16x2(fmaf(a.lr, v[0], bf16_lo(wb[it].x)), fmaf(a.lr, v[1], bf16_hi(wb[it].x))),
+                                                                 pack_bf16x2(fmaf(a.lr, v[2], bf16_lo(wb[it].y)), fmaf(a.lr, v[3], bf16_hi(wb[it].y))));
+                else if (a.W)
+                    *(float4*)((float*)a.W + idx) = make_float4(fmaf(a.lr, v[0], wf[it].x), fmaf(a.lr, v[1], wf[it].y), fmaf(a.lr, v[2], wf[it].z), fmaf(a.lr, v[3], wf[it].w));
+            }
+        } else {
+            // rows of G that are not made of whole 16-byte pieces: entry by entry
+            for (int c = lane; c < 16 * WTM; c += 64) {
+                const int j = nb0 + c / WTM, k = mw0 + c % WTM;
+                if (j >= n_rows || k >= a.d_in) continue;
+                const int64_t idx = (int64_t)j * a.d_in + k;
+                float v = scale * *(const float*)(stage + (c / WTM) * P + (c % WTM) * 4);
+                if (a.accumulate) v += a.G[idx];
+                a.G[idx] = v;
+                if (a.W && a.w_bf16) {
+                    uint16_t* w = (uint16_t*)a.W + idx;
+                    *w = f32_to_bf16_bits(fmaf(a.lr, v, bf16_bits_to_f32(*w)));
+                } else if (a.W) {
+                    float* w = (float*)a.W + idx;
+                    *w = fmaf(a.lr, v, *w);
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();  // the slice is reused by the next row block
+    }
+};
+
 // Epilogue of the small kernel: rows of the product are the columns k of G (P = B panel), its columns the rows j, so that the 4
 // consecutive values of a thread are neighbours in G.
 struct UpdSmallEpi {
@@ -525,6 +613,26 @@ static egg_status launch_upd_small(eggroll_ctx* c, const char* name, const Opera
     KernelScope ks(c, name);
     if (tile == 32) hipLaunchKernelGGL((gemm_small_kernel<MT, true, 32, UpdSmallEpi>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
     else hipLaunchKernelGGL((gemm_small_kernel<MT, true, 64, UpdSmallEpi>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
+    return check_hip(c, hipGetLastError(), name);
+}
+
+// DEEP: one tile per CU with four stages in flight
+template <int BM, int BN, int WM, int WN, bool DEEP>
+static egg_status launch_upd_gemm16(eggroll_ctx* c, const char* name, const Operand& P, const Operand& Q, int kchunks, const UpdArgs& ea)
+{
+    typedef UpdEpi16<BM / WM> Epi;
+    const int tiles_m = (P.rows + BM - 1) / BM, tiles_n = (Q.rows + BN - 1) / BN;
+    const size_t stages = gemm_lds_bytes<BM, BN>(), epi = (size_t)WM * WN * Epi::lds_per_wave(BM / WM);
+    if (!operand_offsets_fit(P, BM) || !operand_offsets_fit(Q, BN)) return fail(c, EGG_EUNSUPPORTED, "operand strides too large for 32-bit tile offsets");
+    void (*kern)(Operand, Operand, int, int, int, const char*, UpdArgs);
+    if constexpr (DEEP) kern = gemm_nt_deep_kernel<MmaF16Blk16, BM, BN, WM, WN, true, Epi>;
+    else kern = gemm_nt_kernel<MmaF16Blk16, BM, BN, WM, WN, true, Epi>;
+    const size_t lds = DEEP ? 2 * stages + epi : std::max(stages, epi);
+    egg_status st = ensure_dynamic_lds(c, (const void*)kern, lds, "gemm smem attr");
+    if (st != EGG_OK) return st;
+    KernelScope ks(c, name);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(WM * WN * 64), lds, c->stream, P, Q, kchunks, tiles_m, tiles_n,
+                       (const char*)c->zero_page.p, ea);
     return check_hip(c, hipGetLastError(), name);
 }
 
@@ -615,7 +723,9 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
     }
     if (bf) {
         const int64_t big_tiles = ((s.d_out + 255) / 256) * (int64_t)((s.d_in + 255) / 256);
-        if (big_tiles >= 192) return launch_upd_gemm<MmaF16, 256, 256, 2, 4>(c, "update_gemm_f16", P, Q, (int)kgroups, ea);
+        if (big_tiles >= 192) return launch_upd_gemm16<256, 256, 2, 4, false>(c, "update_gemm_f16", Q, P, (int)kgroups, ea);
+        if (((s.d_out + 127) / 128) * (int64_t)((s.d_in + 127) / 128) <= c->compute_units)
+            return launch_upd_gemm16<128, 128, 2, 2, true>(c, "update_gemm_f16_small", Q, P, (int)kgroups, ea);
         return launch_upd_gemm<MmaF16, 128, 128, 2, 2>(c, "update_gemm_f16_small", P, Q, (int)kgroups, ea);
     }
     return launch_upd_gemm<MmaF32, 128, 128, 2, 2>(c, "update_gemm_f32", P, Q, (int)kgroups, ea);
