@@ -116,7 +116,7 @@ egg_status validate_shape(eggroll_ctx* c, const egg_shape* s, bool need_rows, bo
 // projection pre-pass + shared GEMM with the correction epilogue for one validated linear layer
 egg_status forward_linear(eggroll_ctx* c, egg_key key, const egg_shape& shape, egg_dtype io_dtype, egg_dtype y_dtype, float sigma,
                           egg_act act, const void* W, const void* X, void* Y, void* A_cache, void* B_cache, const void* resid,
-                          float* t_fixed, const float* t_ready, const NextProjection* next)
+                          float* t_fixed, const float* t_ready, const NextProjection* next, const void* A_ready)
 {
     const bool panel = c->cache_layout == EGG_CACHE_PANEL;
     const int64_t R = shape.member_count * (int64_t)shape.rows_per_member;
@@ -136,7 +136,7 @@ egg_status forward_linear(eggroll_ctx* c, egg_key key, const egg_shape& shape, e
         if (s != EGG_OK) return s;
     }
     return launch_forward_gemm(c, make_stream_key(key.seed, key.step, key.layer, 0), shape, io_dtype, y_dtype, sigma, act, W, X, Y,
-                               t, A_cache, resid, next);
+                               t, A_cache, resid, next, A_ready);
 }
 
 // validation shared by the forward entry points; t_fixed != NULL: the projections go to that buffer of t_capacity

@@ -60,6 +60,18 @@ struct eggroll_ctx {
 
 namespace egg {
 
+// sum over the 16 lanes of a DPP row, left in every lane of the row
+__device__ __forceinline__ float row_sum16(float x)
+{
+#define EGG_DPP_ADD(CTRL) x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+    EGG_DPP_ADD(0xB1)   // quad_perm [1, 0, 3, 2]
+    EGG_DPP_ADD(0x4E)   // quad_perm [2, 3, 0, 1]
+    EGG_DPP_ADD(0x141)  // row_half_mirror: the other quad of the half row
+    EGG_DPP_ADD(0x140)  // row_mirror: the other half row
+#undef EGG_DPP_ADD
+    return x;
+}
+
 egg_status fail(eggroll_ctx* c, egg_status s, const char* fmt, ...);
 egg_status check_hip(eggroll_ctx* c, hipError_t e, const char* what);
 egg_status reserve(eggroll_ctx* c, eggroll_ctx::Buf& b, size_t bytes);
@@ -121,15 +133,17 @@ struct NextProjection {
     float* t;
 };
 bool forward_fuses_next_projection(const egg_shape& s, egg_dtype io, egg_dtype yd, float sigma, egg_act act, bool resid);
+// A_ready: the factors A that eggroll_noise_gen would write for this layer, already drawn by the caller (NULL: drawn here)
 egg_status launch_forward_gemm(eggroll_ctx* c, const StreamKey& ka, const egg_shape& s, egg_dtype io, egg_dtype yd,
                                float sigma, egg_act act, const void* W, const void* X, void* Y, const float* t,
-                               void* A_cache, const void* resid = nullptr, const NextProjection* next = nullptr);
+                               void* A_cache, const void* resid = nullptr, const NextProjection* next = nullptr, const void* A_ready = nullptr);
 egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& kb, const egg_shape& s,
                          egg_dtype noise_dtype, const float* fitness, float scale, int accumulate, float* G, void* W,
                          egg_dtype w_dtype, float lr, const void* A_cache, const void* B_cache, bool b_panel);
 egg_status forward_linear(eggroll_ctx* c, egg_key key, const egg_shape& shape, egg_dtype io_dtype, egg_dtype y_dtype, float sigma,
                           egg_act act, const void* W, const void* X, void* Y, void* A_cache, void* B_cache, const void* resid,
-                          float* t_fixed = nullptr, const float* t_ready = nullptr, const NextProjection* next = nullptr);
+                          float* t_fixed = nullptr, const float* t_ready = nullptr, const NextProjection* next = nullptr,
+                          const void* A_ready = nullptr);
 egg_status checked_forward(eggroll_ctx* c, egg_key key, const egg_shape* shape, egg_dtype io_dtype, egg_dtype y_dtype,
                            float sigma, egg_act act, const void* W, const void* X, const void* R_in, bool need_r, void* Y,
                            void* A_cache, void* B_cache, float* t_fixed, size_t t_capacity, const float* t_in = nullptr,

@@ -115,6 +115,12 @@ __device__ __forceinline__ void static_for(F&& f)
     }
 }
 
+// Products with more than this many 256 x 256 tiles take them: up to it, four times as many tiles of 128 x 128 fit two workgroups
+// on each of 256 CUs at once; beyond, they need a second wave where one of the large tiles still does.  Measured between 128 and
+// 192 tiles (us, 128 x 128 / 256 x 256): forward 2048 x 8192, 5760 rows 240 / 215; 3072^2, 3000 rows (S = 1) 119 / 105; 2048^2,
+// 4608 rows 69.4 / 63.6; update 4096 x 2560, K = 4096 153 / 128.
+constexpr int64_t BIG_TILES_ABOVE = 128;
+
 // XCD-aware tile order: workgroup ids go round-robin over the 8 XCDs, so ids that are congruent
 // mod 8 share an L2.  Give each XCD a contiguous run of tiles, and walk tiles in groups of GM rows
 // so that a run covers a compact block of C (few distinct P and Q panels per L2).
@@ -280,6 +286,77 @@ __device__ __forceinline__ void epi_column(E& e, int n, bool valid)
     else e.column(n, valid);
 }
 
+// An epilogue may ask for the parked form instead (static constexpr int PARKED = groups in flight):
+//   struct Side;  __device__ Epi(const Args&);
+//   __device__ void side(int m, int n, Side&);                 loads the side data of 4 consecutive rows m .. m + 3 of column n
+//   __device__ void finish(int m, int n, const float (&v)[4], const Side&, bool valid);
+// The wave parks 32 columns of its tile in LDS and walks them in a rolled loop in which neighbouring lanes hold neighbouring rows
+// m: stores, and loads of side data, are contiguous.  Unrolled over the accumulators instead, an epilogue that draws factors or
+// applies a correction is some 80 KB of code, more than the instruction cache two compute units share, run once per tile.
+template <class E, class = void>
+struct is_parked : std::false_type {};
+template <class E>
+struct is_parked<E, std::void_t<decltype(E::PARKED)>> : std::true_type {};
+template <int WTM>
+constexpr int parked_bytes_per_wave() { return 32 * (WTM * 4 + 16); }
+
+// acc: the wave tile's accumulators; C rows mw0.., columns nw0..
+template <class Epi, int WTM, int WTN, int BLK, int MB, int NB, class Acc>
+__device__ __forceinline__ void parked_epilogue(const typename Epi::Args& ea, Acc (&acc)[MB][NB], char* slice, int mw0, int nw0, int lane,
+                                                int m_rows, int n_rows)
+{
+    constexpr int PITCH_P = WTM * 4 + 16;
+    constexpr int LPR = WTM / 4, RPI = 64 / LPR, ITS = 32 / RPI, U = Epi::PARKED;
+    static_assert(ITS % (2 * U) == 0 || ITS == U, "whole batches");
+    Epi epi(ea);
+    const int mo = (lane % LPR) * 4, no = lane / LPR;
+    static_for<0, WTN / 32>([&](auto hc) __attribute__((always_inline)) {
+        constexpr int h = decltype(hc)::value;
+        const int nb0 = nw0 + h * 32;
+        typename Epi::Side s0[U], s1[U];
+        auto fetch = [&](typename Epi::Side(&s)[U], int it) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) epi.side(min(mw0 + mo, m_rows - 4), min(nb0 + (it + u) * RPI + no, n_rows - 1), s[u]);  // clamped, unconditional
+        };
+        fetch(s0, 0);
+        static_for<0, 32 / BLK>([&](auto jc) __attribute__((always_inline)) {
+            constexpr int j = h * (32 / BLK) + decltype(jc)::value;
+            static_for<0, MB>([&](auto ic) __attribute__((always_inline)) {
+                constexpr int i = decltype(ic)::value;
+                static_for<0, (BLK == 32 ? 4 : 1)>([&](auto qc) __attribute__((always_inline)) {
+                    constexpr int q = decltype(qc)::value;
+                    const int ml = i * BLK + (BLK == 32 ? q * 8 + (lane >> 5) * 4 : (lane >> 4) * 4);
+                    *(float4*)(slice + (decltype(jc)::value * BLK + (lane & (BLK - 1))) * PITCH_P + ml * 4) =
+                        make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+                });
+            });
+        });
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave's own LDS writes have landed
+        __builtin_amdgcn_wave_barrier();
+        auto finish = [&](const typename Epi::Side(&s)[U], int it) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int nl = (it + u) * RPI + no, n = nb0 + nl, m = mw0 + mo;
+                const float4 x = *(const float4*)(slice + nl * PITCH_P + mo * 4);
+                const float v[4] = {x.x, x.y, x.z, x.w};
+                epi.finish(m, n, v, s[u], m < m_rows && n < n_rows);
+            }
+        };
+        if constexpr (ITS == U) {
+            finish(s0, 0);
+        } else {
+#pragma unroll 1
+            for (int it = 0; it < ITS; it += 2 * U) {
+                fetch(s1, it + U);
+                finish(s0, it);
+                fetch(s0, min(it + 2 * U, ITS - U));
+                finish(s1, it + U);
+            }
+        }
+        __builtin_amdgcn_wave_barrier();  // the slice is reused by the next 32 columns
+    });
+}
+
 // One tile of the product, by all threads of a workgroup: K-chunks kbeg .. kbeg + kchunks - 1.
 template <class MT, int BM, int BN, int WM, int WN, bool KMAJOR, class Epi>
 __device__ __forceinline__ void gemm_nt_tile(const Operand& P, const Operand& Q, int tile_id, int kbeg, int kchunks, int tiles_m,
@@ -308,8 +385,13 @@ __device__ __forceinline__ void gemm_nt_tile(const Operand& P, const Operand& Q,
 
     // The epilogue may fetch small per-tile side data ahead of time instead of paying global-memory
     // latency behind the last MFMA: its prefetch hook runs before the last K-stage.
-    Epi epi(ea, lds + wave * Epi::lds_per_wave(WTM), lane);
-#define EGG_EPI_PREFETCH epi.template prefetch<MB, NB>(m0 + wm * WTM, n0 + wn * WTN, lane, Q.rows);
+    struct NoEpi {};
+    auto make_epi = [&]() __attribute__((always_inline)) {
+        if constexpr (is_parked<Epi>::value) return NoEpi{};
+        else return Epi(ea, lds + wave * Epi::lds_per_wave(WTM), lane);
+    };
+    auto epi = make_epi();
+#define EGG_EPI_PREFETCH if constexpr (!is_parked<Epi>::value) epi.template prefetch<MB, NB>(m0 + wm * WTM, n0 + wn * WTN, lane, Q.rows);
 
     const char* pb = P.base + (int64_t)m0 * P.row_stride + (int64_t)kbeg * P.kc_stride;
     const char* qb = Q.base + (int64_t)n0 * Q.row_stride + (int64_t)kbeg * Q.kc_stride;
@@ -449,6 +531,9 @@ __device__ __forceinline__ void gemm_nt_tile(const Operand& P, const Operand& Q,
     // an epilogue can turn the MFMA layout (a lane owns 4 consecutive rows of one column) into
     // row-contiguous 16-byte stores.
     __syncthreads();
+  if constexpr (is_parked<Epi>::value) {
+    parked_epilogue<Epi, WTM, WTN, BLK, MB, NB>(ea, acc, lds + wave * parked_bytes_per_wave<WTM>(), m0 + wm * WTM, n0 + wn * WTN, lane, P.rows, Q.rows);
+  } else {
     // an epilogue may fold per-column-block rank-r terms into the accumulators with a few more MFMAs
     epi.template extra_mma<MT, MB, NB>(acc, m0 + wm * WTM, n0 + wn * WTN, lane, Q.rows);
     // workgroup-level hook: an epilogue may pull per-tile side data into the LDS behind the wave slices
@@ -473,6 +558,7 @@ __device__ __forceinline__ void gemm_nt_tile(const Operand& P, const Operand& Q,
         });
         epi.template flush<WTM>(m0 + wm * WTM, n0 + wn * WTN + j * BLK, Q.rows);
     });
+  }
 }
 
 template <class MT, int BM, int BN, int WM, int WN, bool KMAJOR, class Epi, int WG_PER_CU = 1>

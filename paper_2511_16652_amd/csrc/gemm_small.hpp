@@ -12,15 +12,13 @@ namespace egg {
 
 // Tile of the small kernel for an M x N product, 0 where the tiles of gemm_core.hpp do better.  Measured over 256 .. 4096 rows and
 // columns and K of 64 .. 4096 (us, this kernel against theirs; the lines lie where the last listed shape still gains):
-//   32: up to 512 tiles   bf16 forward 512 x 512 x 1024: 16.7 / 21.1, 1024 x 512 x 4096: 45 / 51 (1024 x 1024: 77 / 51);
-//                         fp32 256 x 64 x 256: 14 / 31, 1024 x 512 x 1024: 29 / 80; update 256 x 256 x 4096: 26 / 56
-//   64: up to 512 tiles, fp32 and the update's panels (whose fragments are contiguous; row-major bf16 fragments are not, and the
-//                         LDS kernel is faster there)   update 2048 x 1024 x 4096: 57 / 68 (2048 x 2048: 86 / 78);
-//                         fp32 2048 x 1024 x 1024: 67 / 81 (2048 x 2048: 118 / 83)
-inline int small_tile(int64_t M, int64_t N, bool use64)
+//   32: up to 512 tiles   fp32 forward 256 x 64 x 256: 14 / 31, 1024 x 512 x 1024: 29 / 80; update 256 x 256 x 4096: 26 / 56
+//   64: up to 512 tiles   update 2048 x 1024 x 4096: 57 / 68 (2048 x 2048: 86 / 78); fp32 forward 2048 x 1024 x 1024: 67 / 81
+//                         (2048 x 2048: 118 / 83)
+inline int small_tile(int64_t M, int64_t N)
 {
     if (((M + 31) / 32) * ((N + 31) / 32) <= 512) return 32;
-    return use64 && ((M + 63) / 64) * ((N + 63) / 64) <= 512 ? 64 : 0;
+    return ((M + 63) / 64) * ((N + 63) / 64) <= 512 ? 64 : 0;
 }
 
 // Epi requirements: struct Args; __device__ Epi(const Args&); value_t; __device__ void apply4(int m, int n, const value_t (&v)[4]),
@@ -130,5 +128,73 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(Operand P, Operand Q
         if (m < P.rows && n < Q.rows) epi.apply4(m, n, v);
     }
 }
+
+// The same for the bf16 forward layer, whose outputs must not depend on how many rows a call has (a population may be walked in
+// chunks): K is not split, every output is the one ascending chain of 16x16x32 MFMAs that the large tiles run.  A workgroup owns
+// 32 x 32 outputs, a wave a 16 x 16 block of them over all of K, its fragments straight from memory, two batches of eight k-steps
+// in flight; the chain itself is short (16 cycles a step).
+// Epi: struct Args; Epi(const Args&); extra<MT>(acc, m0, n0, lane, n_rows) adds to the block's accumulators; apply4 as above.
+template <class MT, class Epi>
+__global__ __launch_bounds__(256, 2) void gemm_small16_kernel(Operand P, Operand Q, int kchunks, int tiles_m, typename Epi::Args ea)
+{
+    static_assert(MT::BLK == 16, "16x16 MFMA blocks");
+    constexpr int U = 8;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m0 = (int)(blockIdx.x % tiles_m) * 32 + (wave & 1) * 16, n0 = (int)(blockIdx.x / tiles_m) * 32 + (wave >> 1) * 16;
+    if (m0 >= P.rows || n0 >= Q.rows) return;  // (no barrier in this kernel)
+    const int fr = lane & 15, fc = lane >> 4;  // a k-step is four 16-byte chunks
+    const char* pa = P.base + (int64_t)min(m0 + fr, P.rows - 1) * P.row_stride;  // rows past the end re-read the last one
+    const char* qa = Q.base + (int64_t)min(n0 + fr, Q.rows - 1) * Q.row_stride;
+    typename MT::acc_t acc;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] = 0;
+    struct Batch {
+        u32x4 a[U], b[U];
+    };
+    auto load = [&](Batch& f, int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t c = min((s + u) * 4 + fc, kchunks - 1);  // unconditional, from a clamped chunk
+            f.a[u] = *(const u32x4*)(pa + c * P.kc_stride);
+            f.b[u] = *(const u32x4*)(qa + c * Q.kc_stride);
+        }
+    };
+    auto mul = [&](Batch& f, int s, bool tail) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (tail) {
+                const bool in = (s + u) * 4 + fc < kchunks;
+                f.a[u] = in ? f.a[u] : u32x4{0u, 0u, 0u, 0u};
+                f.b[u] = in ? f.b[u] : u32x4{0u, 0u, 0u, 0u};
+            }
+            MT::mma(f.a[u], f.b[u], acc);
+        }
+    };
+    const int steps = (kchunks + 3) / 4;
+    Batch f0, f1;
+    load(f0, 0);
+    int s = 0;
+    for (; (s + 2 * U) * 4 <= kchunks; s += 2 * U) {  // two whole batches: nothing to mask
+        load(f1, s + U);
+        mul(f0, s, false);
+        load(f0, s + 2 * U);  // (past the end: clamped, and masked below or never used)
+        mul(f1, s + U, false);
+    }
+    for (; s < steps; s += U) {
+        load(f1, s + U);
+        mul(f0, s, true);
+        f0 = f1;
+    }
+    Epi epi(ea);
+    epi.template extra<MT>(acc, m0, n0, lane, Q.rows);
+    const int m = m0 + fc * 4, n = n0 + fr;
+    const float v[4] = {acc[0], acc[1], acc[2], acc[3]};
+    if (m < P.rows && n < Q.rows) epi.apply4(m, n, v);
+}
+// Up to so many tiles of 32 x 32 the bf16 layer takes it (us, this kernel / 128 x 128 tiles): 16 rows per member 256 x 64 x 4096
+// 41 / 46, 512 x 512 x 1024 19.7 / 20.6 (1024 x 512 x 1024: 28 / 21); one row per member 512 x 256 x 1024 14 / 24.
+constexpr int64_t SMALL16_TILES = 256;
+inline bool small16(int64_t M, int64_t N) { return ((M + 31) / 32) * ((N + 31) / 32) <= SMALL16_TILES; }
 
 }  // namespace egg

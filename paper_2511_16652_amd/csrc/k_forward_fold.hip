@@ -14,6 +14,7 @@
 // under this block's MFMAs); 16 rows x r entries of A are neighbours, so a load instruction touches few lines.
 #include "forward_fold.hpp"
 #include "gemm_core.hpp"
+#include "gemm_small.hpp"
 
 namespace egg {
 
@@ -91,8 +92,8 @@ struct FoldEpi {
             }
         }
     }
-    template <class MT>
-    __device__ __forceinline__ void fold(const Frag& f, typename MT::acc_t (&acc)[MB][NB], int j, int mw0, int lane) const
+    template <class MT, int NB_>
+    __device__ __forceinline__ void fold(const Frag& f, typename MT::acc_t (&acc)[MB][NB_], int j, int mw0, int lane) const
     {
         if constexpr (AW > 0) {
             const int g = lane >> 4;
@@ -140,14 +141,14 @@ struct FoldEpi {
             static_for<0, NB>([&](auto jc) __attribute__((always_inline)) {
                 constexpr int j = decltype(jc)::value;
                 if constexpr (j + 1 < NB) fetch(f[(j + 1) & 1], mw0, nw0 + (j + 1) * BLK, lane, n_rows, 0);
-                fold<MT>(f[j & 1], acc, j, mw0, lane);
+                fold<MT, NB>(f[j & 1], acc, j, mw0, lane);
             });
             if (AW == 4 && a.rank == 16) {
                 // the second member of the blocks that have one (others multiply by zero)
                 static_for<0, NB>([&](auto jc) __attribute__((always_inline)) {
                     constexpr int j = decltype(jc)::value;
                     fetch(f[0], mw0, nw0 + j * BLK, lane, n_rows, 1);
-                    fold<MT>(f[0], acc, j, mw0, lane);
+                    fold<MT, NB>(f[0], acc, j, mw0, lane);
                 });
             }
         }
@@ -175,6 +176,43 @@ struct FoldEpi {
     {
         static_assert(W == WTM, "wave tile of the launched kernel");
         sty.template flush<WTM, BLK>((uint16_t*)a.Y, a.d_out, mw0, nb0, n_rows, a.d_out);
+    }
+};
+
+// the same for one 16 x 16 block whose 4-row groups are stored straight from registers
+template <int AW, int LEAN>
+struct FoldSmallEpi {
+    typedef float value_t;
+    typedef FoldArgs Args;
+    const Args a;
+    __device__ __forceinline__ FoldSmallEpi(const Args& a_) : a(a_) {}
+    template <class MT>
+    __device__ __forceinline__ void extra(typename MT::acc_t& acc, int m0, int n0, int lane, int n_rows) const
+    {
+        if constexpr (AW > 0) {
+            const FoldEpi<AW, LEAN_ON, 1> e(a, nullptr, lane);
+            typename FoldEpi<AW, LEAN_ON, 1>::Frag f;
+            typename MT::acc_t one[1][1] = {{acc}};
+            e.fetch(f, m0, n0, lane, n_rows, 0);
+            e.template fold<MT, 1>(f, one, 0, m0, lane);
+            if (AW == 4 && a.rank == 16) {
+                e.fetch(f, m0, n0, lane, n_rows, 1);
+                e.template fold<MT, 1>(f, one, 0, m0, lane);
+            }
+            acc = one[0][0];
+        }
+    }
+    __device__ __forceinline__ void apply4(int m, int n, const float (&v)[4]) const
+    {
+        float y[4] = {v[0], v[1], v[2], v[3]};
+        const int64_t at = (int64_t)n * a.d_out + m;  // d_out is a multiple of 4: whole groups
+        if constexpr ((LEAN & LEAN_GELU) != 0) gelu_bf16_grade4(y);
+        if constexpr ((LEAN & LEAN_RESID) != 0) {
+            const uint2 r = *(const uint2*)((const uint16_t*)a.resid + at);
+            y[0] += bf16_lo(r.x); y[1] += bf16_hi(r.x);
+            y[2] += bf16_lo(r.y); y[3] += bf16_hi(r.y);
+        }
+        *(uint2*)((uint16_t*)a.Y + at) = make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
     }
 };
 
@@ -219,10 +257,15 @@ static egg_status launch_fold_deep(eggroll_ctx* c, const Operand& P, const Opera
 template <int AW, int LEAN>
 static egg_status launch_fold_aw(eggroll_ctx* c, const Operand& P, const Operand& Q, int kchunks, const FoldArgs& ea)
 {
-    // 256 x 256 tiles while they fill three quarters of the chip (the rule of the parked form); below that four times as many
-    // tiles of 128 x 128, two workgroups per CU.  K that is not made of whole stages takes the loaders with the zero page.
+    // 256 x 256 tiles or four times as many of 128 x 128, two workgroups per CU or, where that leaves CUs empty, one.  K that is not made of whole stages takes the loaders with the zero page.
     const int64_t big_tiles = ((P.rows + 255) / 256) * (((int64_t)Q.rows + 255) / 256);
-    if (big_tiles >= 192) {
+    if (small16(P.rows, Q.rows)) {
+        const int tm = (P.rows + 31) / 32, tn = (Q.rows + 31) / 32;
+        KernelScope ks(c, shaped_name(c, "forward_gemm_bf16_small", P.rows, kchunks * 8));
+        hipLaunchKernelGGL((gemm_small16_kernel<MmaBf16Blk16, FoldSmallEpi<AW, LEAN>>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
+        return check_hip(c, hipGetLastError(), "forward_gemm_bf16_small");
+    }
+    if (big_tiles > BIG_TILES_ABOVE) {
         if constexpr (AW > 0)  // (whole stages and nothing to correct: the parked form's kernel)
             if (kchunks % 8 == 0) return launch_fold_t<256, 256, 2, 4, 1, false, AW, LEAN>(c, "forward_gemm_bf16", P, Q, kchunks, ea);
         return launch_fold_t<256, 256, 2, 4, 1, true, AW, LEAN>(c, "forward_gemm_bf16", P, Q, kchunks, ea);

@@ -124,7 +124,12 @@ egg_status launch_decoder_forward(eggroll_ctx* c, egg_key key, const egg_shape& 
     // rank 1: the normalisation passes form the projections of the layers that read their output (q, k, v; up; head),
     // so those layers' inputs are not read a second time by a projection pass
     const bool fuse_proj = sigma != 0.0f && s.rank == 1;
-    if (fuse_proj) need += 3 * (pad((size_t)cm * d * 2) + pad(rows_max * sizeof(float))) + pad((size_t)cm * ff * 2) + pad(rows_max * sizeof(float));
+    // ... from factors that one launch draws per layer, the A of its six matrices with them (a launch each was 4 us times 26 in a
+    // two-layer call over 32 members; at 2^18 rows the generator's work is the same)
+    const size_t fD = pad((size_t)cm * d * 2), fF = pad((size_t)cm * ff * 2), fV = pad((size_t)cm * V * 2), fT = pad(rows_max * sizeof(float));
+    const bool draw_A = fuse_proj && S > 1;  // with one row per member the layers regenerate A in registers
+    const size_t fA = draw_A ? std::max(5 * fD + fF, fV) : 0;
+    if (fuse_proj) need += 5 * fD + fF + fA + 4 * fT;
     egg_status st = reserve(c, c->model, need);
     if (st != EGG_OK) return st;
     const size_t dd = (size_t)d * d * 2, dff = (size_t)d * ff * 2;
@@ -140,23 +145,24 @@ egg_status launch_decoder_forward(eggroll_ctx* c, egg_key key, const egg_shape& 
         void* v = cv.take(rows_max * d * 2);
         void* u = cv.take(rows_max * ff * 2);
         void* lg = logits ? (void*)((char*)logits + r0 * V * 2) : cv.take(rows_max * V * 2);
-        void* Bf[3] = {nullptr, nullptr, nullptr};
-        float* tf[3] = {nullptr, nullptr, nullptr};
-        if (fuse_proj)
-            for (int j = 0; j < 3; ++j) {
-                Bf[j] = cv.take((size_t)cm * d * 2);
-                tf[j] = (float*)cv.take(rows_max * sizeof(float));
-            }
-        void* Bdn = nullptr;   // the down-projection's factors over d_ff and its projections, formed by the up-projection's epilogue
-        float* tdn = nullptr;
+        // factors of the layer at hand: B of q, k, v, o, up (over d) and down (over ff), A of the same six; the head's go in the same
+        // places, its A over the whole vocabulary
+        void *B[6] = {}, *A[6] = {};
+        float *tf[3] = {}, *tdn = nullptr;
         if (fuse_proj) {
-            Bdn = cv.take((size_t)cm * ff * 2);
-            tdn = (float*)cv.take(rows_max * sizeof(float));
+            for (int j = 0; j < 6; ++j) B[j] = cv.take(j == 5 ? fF : fD);
+            char* a0 = (char*)cv.take(fA);
+            for (int j = 0; draw_A && j < 6; ++j) {
+                A[j] = a0;
+                a0 += j == 4 ? fF : fD;
+            }
+            for (int j = 0; j < 3; ++j) tf[j] = (float*)cv.take(fT);
+            tdn = (float*)cv.take(fT);
         }
-        // factors B_i of the layer with noise id `layer` for this chunk's members, as the projection pass would draw them
-        auto gen_b = [&](uint32_t layer, void* out, int len) {
-            return launch_noise(c, make_stream_key(key.seed, key.step, layer, 1), (uint32_t)(s.member_begin + m0), n, len, EGG_BF16, EGG_NORMAL, 0, out);
+        auto draw = [&](const NoiseJob* jobs, int count) {
+            return launch_noise_jobs(c, jobs, count, (uint32_t)(s.member_begin + m0), n, EGG_BF16, EGG_NORMAL, 0);
         };
+        auto stream = [&](uint32_t layer, int which) { return make_stream_key(key.seed, key.step, layer, which); };
         egg_shape sq = s;
         sq.member_begin = s.member_begin + m0;
         sq.member_count = n;
@@ -170,35 +176,40 @@ egg_status launch_decoder_forward(eggroll_ctx* c, egg_key key, const egg_shape& 
         for (int l = 0; l < L; ++l) {
             const uint32_t lid = key.layer + 6u * (uint32_t)l;
             auto kk = [&](uint32_t j) { return egg_key{key.seed, key.step, lid + j}; };
-            if (fuse_proj) {
-                for (uint32_t j = 0; j < 3; ++j)
-                    if ((st = gen_b(lid + j, Bf[j], d)) != EGG_OK) return st;
-                if ((st = launch_rmsnorm_proj(c, rows, S, d, cfg.rms_eps, (const char*)w.norm1 + (size_t)l * d * 2, x, h, 3, Bf, tf)) != EGG_OK) return st;
-            } else if ((st = launch_rmsnorm(c, rows, d, cfg.rms_eps, (const char*)w.norm1 + (size_t)l * d * 2, x, h)) != EGG_OK) return st;
-            if ((st = forward_linear(c, kk(0), sq, EGG_BF16, EGG_BF16, sigma, EGG_ACT_NONE, (const char*)w.wq + l * dd, h, q, nullptr, nullptr, nullptr, nullptr, tf[0])) != EGG_OK) return st;
-            if ((st = forward_linear(c, kk(1), sq, EGG_BF16, EGG_BF16, sigma, EGG_ACT_NONE, (const char*)w.wk + l * dd, h, k, nullptr, nullptr, nullptr, nullptr, tf[1])) != EGG_OK) return st;
-            if ((st = forward_linear(c, kk(2), sq, EGG_BF16, EGG_BF16, sigma, EGG_ACT_NONE, (const char*)w.wv + l * dd, h, v, nullptr, nullptr, nullptr, nullptr, tf[2])) != EGG_OK) return st;
-            // the attention kernel forms the o-projection's projections of the rows it writes
-            if (fuse_proj && (st = gen_b(lid + 3, Bf[0], d)) != EGG_OK) return st;
-            if ((st = launch_attention(c, n, S, cfg.heads, hd, q, k, v, h, fuse_proj ? Bf[0] : nullptr, fuse_proj ? tf[0] : nullptr)) != EGG_OK) return st;
-            if ((st = forward_linear(c, kk(3), sq, EGG_BF16, EGG_BF16, sigma, EGG_ACT_NONE, (const char*)w.wo + l * dd, h, x, nullptr, nullptr, x, nullptr, fuse_proj ? tf[0] : nullptr)) != EGG_OK) return st;
-            if (fuse_proj) {
-                if ((st = gen_b(lid + 4, Bf[0], d)) != EGG_OK) return st;
-                if ((st = launch_rmsnorm_proj(c, rows, S, d, cfg.rms_eps, (const char*)w.norm2 + (size_t)l * d * 2, x, h, 1, Bf, tf)) != EGG_OK) return st;
-            } else if ((st = launch_rmsnorm(c, rows, d, cfg.rms_eps, (const char*)w.norm2 + (size_t)l * d * 2, x, h)) != EGG_OK) return st;
             // the up-projection's epilogue also projects what it stores onto the down-projection's factors, where it can
             const bool fuse_dn = fuse_proj && forward_fuses_next_projection(sup, EGG_BF16, EGG_BF16, sigma, EGG_ACT_GELU, false);
-            NextProjection np{Bdn, tdn};
-            if (fuse_dn && (st = gen_b(lid + 5, Bdn, ff)) != EGG_OK) return st;
-            if ((st = forward_linear(c, kk(4), sup, EGG_BF16, EGG_BF16, sigma, EGG_ACT_GELU, (const char*)w.w_up + l * dff, h, u, nullptr, nullptr, nullptr, nullptr, tf[0], fuse_dn ? &np : nullptr)) != EGG_OK) return st;
-            if ((st = forward_linear(c, kk(5), sdn, EGG_BF16, EGG_BF16, sigma, EGG_ACT_NONE, (const char*)w.w_down + l * dff, u, x, nullptr, nullptr, x, nullptr, fuse_dn ? tdn : nullptr)) != EGG_OK) return st;
+            if (fuse_proj) {
+                NoiseJob jobs[12];
+                int nj = 0;
+                for (uint32_t j = 0; j < 6; ++j) {
+                    if (j < 5 || fuse_dn) jobs[nj++] = NoiseJob{stream(lid + j, 1), j == 5 ? ff : d, B[j]};
+                    if (draw_A) jobs[nj++] = NoiseJob{stream(lid + j, 0), j == 4 ? ff : d, A[j]};
+                }
+                if ((st = draw(jobs, nj)) != EGG_OK) return st;
+            }
+            if (fuse_proj) {
+                if ((st = launch_rmsnorm_proj(c, rows, S, d, cfg.rms_eps, (const char*)w.norm1 + (size_t)l * d * 2, x, h, 3, B, tf)) != EGG_OK) return st;
+            } else if ((st = launch_rmsnorm(c, rows, d, cfg.rms_eps, (const char*)w.norm1 + (size_t)l * d * 2, x, h)) != EGG_OK) return st;
+            if ((st = forward_linear(c, kk(0), sq, EGG_BF16, EGG_BF16, sigma, EGG_ACT_NONE, (const char*)w.wq + l * dd, h, q, nullptr, nullptr, nullptr, nullptr, tf[0], nullptr, A[0])) != EGG_OK) return st;
+            if ((st = forward_linear(c, kk(1), sq, EGG_BF16, EGG_BF16, sigma, EGG_ACT_NONE, (const char*)w.wk + l * dd, h, k, nullptr, nullptr, nullptr, nullptr, tf[1], nullptr, A[1])) != EGG_OK) return st;
+            if ((st = forward_linear(c, kk(2), sq, EGG_BF16, EGG_BF16, sigma, EGG_ACT_NONE, (const char*)w.wv + l * dd, h, v, nullptr, nullptr, nullptr, nullptr, tf[2], nullptr, A[2])) != EGG_OK) return st;
+            // the attention kernel forms the o-projection's projections of the rows it writes
+            if ((st = launch_attention(c, n, S, cfg.heads, hd, q, k, v, h, fuse_proj ? B[3] : nullptr, fuse_proj ? tf[0] : nullptr)) != EGG_OK) return st;
+            if ((st = forward_linear(c, kk(3), sq, EGG_BF16, EGG_BF16, sigma, EGG_ACT_NONE, (const char*)w.wo + l * dd, h, x, nullptr, nullptr, x, nullptr, fuse_proj ? tf[0] : nullptr, nullptr, A[3])) != EGG_OK) return st;
+            if (fuse_proj) {
+                if ((st = launch_rmsnorm_proj(c, rows, S, d, cfg.rms_eps, (const char*)w.norm2 + (size_t)l * d * 2, x, h, 1, &B[4], tf)) != EGG_OK) return st;
+            } else if ((st = launch_rmsnorm(c, rows, d, cfg.rms_eps, (const char*)w.norm2 + (size_t)l * d * 2, x, h)) != EGG_OK) return st;
+            const NextProjection np{B[5], tdn};
+            if ((st = forward_linear(c, kk(4), sup, EGG_BF16, EGG_BF16, sigma, EGG_ACT_GELU, (const char*)w.w_up + l * dff, h, u, nullptr, nullptr, nullptr, nullptr, tf[0], fuse_dn ? &np : nullptr, A[4])) != EGG_OK) return st;
+            if ((st = forward_linear(c, kk(5), sdn, EGG_BF16, EGG_BF16, sigma, EGG_ACT_NONE, (const char*)w.w_down + l * dff, u, x, nullptr, nullptr, x, nullptr, fuse_dn ? tdn : nullptr, nullptr, A[5])) != EGG_OK) return st;
         }
         const egg_key kh{key.seed, key.step, key.layer + 6u * (uint32_t)L};
         if (fuse_proj) {
-            if ((st = gen_b(kh.layer, Bf[0], d)) != EGG_OK) return st;
-            if ((st = launch_rmsnorm_proj(c, rows, S, d, cfg.rms_eps, w.norm_f, x, h, 1, Bf, tf)) != EGG_OK) return st;
+            const NoiseJob jobs[2] = {{stream(kh.layer, 1), d, B[0]}, {stream(kh.layer, 0), V, A[0]}};
+            if ((st = draw(jobs, draw_A ? 2 : 1)) != EGG_OK) return st;
+            if ((st = launch_rmsnorm_proj(c, rows, S, d, cfg.rms_eps, w.norm_f, x, h, 1, B, tf)) != EGG_OK) return st;
         } else if ((st = launch_rmsnorm(c, rows, d, cfg.rms_eps, w.norm_f, x, h)) != EGG_OK) return st;
-        if ((st = forward_linear(c, kh, shd, EGG_BF16, EGG_BF16, sigma, EGG_ACT_NONE, w.head, h, lg, nullptr, nullptr, nullptr, nullptr, tf[0])) != EGG_OK) return st;
+        if ((st = forward_linear(c, kh, shd, EGG_BF16, EGG_BF16, sigma, EGG_ACT_NONE, w.head, h, lg, nullptr, nullptr, nullptr, nullptr, tf[0], nullptr, A[0])) != EGG_OK) return st;
         if (loglik && (st = launch_token_loglik(c, n, S, V, lg, tok, loglik + r0)) != EGG_OK) return st;
     }
     return EGG_OK;

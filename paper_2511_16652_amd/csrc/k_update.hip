@@ -717,13 +717,13 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
     Operand P{(const char*)c->pack_a.p, 16, (int64_t)s.d_out * 16, s.d_out};
     Operand Q{(const char*)(b_panel ? B_cache : c->pack_b.p), 16, (int64_t)s.d_in * 16, s.d_in};
     UpdArgs ea{G, W, fnorm, s.d_out, s.d_in, scale, lr, accumulate, w_dtype == EGG_BF16 ? 1 : 0};
-    if (const int small = small_tile(s.d_in, s.d_out, true)) {
+    if (const int small = small_tile(s.d_in, s.d_out)) {
         return bf ? launch_upd_small<MmaF16>(c, "update_gemm_f16_small", Q, P, (int)kgroups, small, ea)
                   : launch_upd_small<MmaF32>(c, "update_gemm_f32", Q, P, (int)kgroups, small, ea);
     }
     if (bf) {
         const int64_t big_tiles = ((s.d_out + 255) / 256) * (int64_t)((s.d_in + 255) / 256);
-        if (big_tiles >= 192) return launch_upd_gemm16<256, 256, 2, 4, false>(c, "update_gemm_f16", Q, P, (int)kgroups, ea);
+        if (big_tiles > BIG_TILES_ABOVE) return launch_upd_gemm16<256, 256, 2, 4, false>(c, "update_gemm_f16", Q, P, (int)kgroups, ea);
         if (((s.d_out + 127) / 128) * (int64_t)((s.d_in + 127) / 128) <= c->compute_units)
             return launch_upd_gemm16<128, 128, 2, 2, true>(c, "update_gemm_f16_small", Q, P, (int)kgroups, ea);
         return launch_upd_gemm<MmaF16, 128, 128, 2, 2>(c, "update_gemm_f16_small", P, Q, (int)kgroups, ea);

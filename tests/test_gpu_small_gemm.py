@@ -82,3 +82,34 @@ def test_small_update(ctx, dtype, d_out, d_in, N, rank, w):
     if w:
         want = W0.double() + 0.125 * G.double()
         assert ((W.double() - want).abs() <= (2.0 ** -8 if w == "bf16" else 1e-6) * (want.abs() + 1e-3)).all()
+
+
+@pytest.mark.parametrize("d_out,d_in,S,rank,members", [
+    (256, 264, 64, 1, (1, 8, 64, 700)), (256, 328, 100, 4, (1, 8, 64, 500)), (512, 200, 16, 8, (3, 40, 300, 2500)), (256, 72, 31, 16, (2, 20, 200, 1600)),
+    (384, 136, 1, 1, (2, 300, 4000, 30000)), (384, 136, 3, 4, (2, 100, 1300, 10000)), (256, 520, 14, 2, (2, 30, 300, 2500))])
+@pytest.mark.parametrize("sigma,form", [(0.0, "plain"), (0.5, "plain"), (0.5, "gelu"), (0.5, "residual")])
+def test_bf16_rows_do_not_depend_on_the_call(ctx, d_out, d_in, S, rank, members, sigma, form):
+    """A member's outputs are the same bits in a call of one member and in one of thousands: every kernel runs the same chain of
+    MFMAs (16 x 16 blocks from memory, 128 x 128 tiles with two and four stages, 256 x 256 tiles)."""
+    import torch
+    N = max(members)
+    g = torch.Generator("cuda").manual_seed(S)
+    W = (torch.randn((d_out, d_in), generator=g, device="cuda") * d_in ** -0.5).to(torch.bfloat16)
+    X = torch.randn((N * S, d_in), generator=g, device="cuda").to(torch.bfloat16)
+    R = torch.randn((N * S, d_out), generator=g, device="cuda").to(torch.bfloat16)
+    key = eb.make_key(1, 2, 3)
+
+    def run(first, n):
+        x, r = X[first * S:(first + n) * S].contiguous(), R[first * S:(first + n) * S].contiguous()
+        y = torch.empty((n * S, d_out), dtype=torch.bfloat16, device="cuda")
+        args = (key, eb.make_shape(first, n, S, d_out, d_in, rank), sigma, eb.EGG_ACT_GELU if form == "gelu" else eb.EGG_ACT_NONE, W, x)
+        if form == "residual":
+            ctx.eggroll_perturbed_forward_add(*args, r, y)
+        else:
+            ctx.eggroll_perturbed_forward(*args, y)
+        return y
+
+    whole = run(0, N)
+    for n in members[:-1]:
+        for first in (0, N - n, (N - n) // 2):
+            assert torch.equal(run(first, n), whole[first * S:(first + n) * S]), (first, n)
