@@ -129,175 +129,197 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const uint4* __restrict__ 
 }
 
 // ---- causal softmax attention ------------------------------------------------------------------------
-// One workgroup (8 waves) per (member, head): K [S][HD] and V transposed [HD][S] of the head sit in LDS, wave w
-// owns 32 query rows and walks the key blocks 0 .. its own (the causal triangle).  The two waves of a SIMD get
-// query blocks b and 7 - b, so every SIMD does the same number of key blocks.
+// One workgroup of four waves per (member, head).  K and V of up to 128 keys sit in LDS as they are in memory, brought there by
+// direct-to-LDS loads (no registers, no writes); rows of 256 / 128 / 64 bytes with their 16-byte chunks XOR-swizzled by the row
+// number -- the permutation is applied on the global side, a row stays one contiguous run.  Wave w owns query blocks (32 rows) w
+// and 7 - w, which together see nine key blocks whatever w is: block w and the first half of the keys of block 7 - w from the
+// first 128 keys, then the second 128 keys take their place for the rest of block 7 - w.  64 KB of LDS at head_dim 128 let two
+// workgroups share a CU, so one loads while the other multiplies (with all 256 keys of a head in one workgroup of 136 KB the
+// phases of a CU added up.  512 members x 16 heads x 256 x 128: 680 us then, 478 now, of which the four tensors are 420 at
+// 5.1 TB/s; 64 rows: 200 / 144; head_dim 64: 368 / 311).
 //   scores^T = K Q^T      as MFMA C[m = key][n = query]: a lane holds 16 scores of ONE query, so the row
 //                         maximum and sum are in-lane reductions plus one exchange between the lane halves;
 //   O^T     += V^T P^T    as MFMA C[m = hd][n = query]: the P operand is the lane's own 16 probabilities
-//                         (bf16), the V^T operand reads the keys in the same order from LDS.
+//                         (bf16); the V^T operand comes from the row-major V by transposing LDS reads
+//                         (ds_read_b64_tr_b16: 16 lanes read 4 keys x 16 columns, lane i receives column i of the 4 keys).
 // Online softmax in base 2 (running maximum and sum per query, fp32).  S <= 256.
 template <int HD>
 struct AttnCfg {
-    static constexpr int SMAX = 256;
-    static constexpr int KP = HD * 2 + 16;    // K row pitch in bytes (68 dwords at HD = 128: 16 lanes cover all banks)
-    static constexpr int VP = SMAX * 2 + 8;   // V^T row pitch in bytes (130 dwords: 32 lanes x 8 bytes cover all banks)
-    static constexpr int LDS = SMAX * KP + HD * VP;
+    static constexpr int TILE = 128;        // keys in LDS at a time
+    static constexpr int ROW = HD * 2;      // bytes of a row
+    static constexpr int CPR = HD / 8;      // 16-byte chunks of a row
+    static_assert(HD == 32 || HD == 64 || HD == 128, "swizzles below");
+    // K: the 16 rows that neighbouring lanes read at one chunk fall on the 16 chunk columns of 256 bytes
+    static __device__ __forceinline__ int swz_k(int row) { return HD == 128 ? row & 15 : (HD == 64 ? (row >> 1) & 7 : (row >> 2) & 3); }
+    // V: a transposing read of a wave touches 8 rows x 4 chunks, two on each chunk column
+    static __device__ __forceinline__ int swz_v(int row) { return HD == 128 ? (row & 3) << 2 : (HD == 64 ? ((row >> 1) & 1) << 2 : 0); }
 };
 
 template <int HD>
-__global__ __launch_bounds__(512) void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
-                                                        const uint16_t* __restrict__ V, uint16_t* __restrict__ O, int S,
-                                                        int heads, int64_t ld, float scale_log2,
-                                                        const uint16_t* __restrict__ Bo, float* __restrict__ part, int64_t rows_total)
+__global__ __launch_bounds__(256, 2) void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+                                                           const uint16_t* __restrict__ V, uint16_t* __restrict__ O, int S,
+                                                           int heads, int64_t ld, float scale_log2, int tile_rows, const char* zero_page,
+                                                           const uint16_t* __restrict__ Bo, float* __restrict__ part, int64_t rows_total)
 {
     // Bo != NULL: the rows written here feed a perturbed layer (the o-projection) whose rank-1 factors are Bo[member][heads * HD];
     // the head's share of that layer's projections, sum over its HD columns of O[row][col] * Bo[col] (from the bf16 values stored),
     // goes to part[head][row] and a small pass adds the heads in order -- so the attention output is not read a second time.
     typedef AttnCfg<HD> C;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
     char* sK = smem;
-    char* sV = smem + C::SMAX * C::KP;
-    char* sB = smem + C::LDS;  // HD bf16 of Bo for this (member, head)
+    char* sV = smem + tile_rows * C::ROW;      // tile_rows: min(128, S rounded up to 32)
+    char* sB = sV + tile_rows * C::ROW;        // HD bf16 of Bo for this (member, head)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t member = blockIdx.x / heads;
     const int head = (int)(blockIdx.x - member * heads);
     const int64_t base = member * S * ld + (int64_t)head * HD;
     const uint16_t *Qg = Q + base, *Kg = K + base, *Vg = V + base;
-    const int SP = (S + 31) & ~31;
-    constexpr int CPR = HD / 8;  // 16-byte chunks per row
-
-    // The wave's query rows first (they are needed last): 32 rows, the lane's half of every 16 columns.
-    const int nqb = SP / 32;
-    const int qb = wave < 4 ? wave : 11 - wave;
+    const int nqb = (S + 31) >> 5;
     const int n = lane & 31, h = lane >> 5;
-    const int qrow = qb * 32 + n;
-    u32x4 qf[HD / 16];
-#pragma unroll
-    for (int ks = 0; ks < HD / 16; ++ks) {
-        qf[ks] = u32x4{0u, 0u, 0u, 0u};
-        if (qb < nqb && qrow < S) qf[ks] = *(const u32x4*)(Qg + (int64_t)qrow * ld + (2 * ks + h) * 8);
-    }
-    if (Bo && tid < CPR) *(uint4*)(sB + tid * 16) = *(const uint4*)(Bo + (member * heads + head) * (int64_t)HD + tid * 8);
-    // K and V of the head pass through registers on their way to LDS.  Every load of a thread is issued before the first
-    // LDS write (fixed trip counts for S = SMAX, predicated), so the workgroup pays the memory latency once, not per 16 bytes.
-    constexpr int KIT = C::SMAX * CPR / 512, VIT = (C::SMAX / 64) * CPR / 8;
-    static_assert(C::SMAX * CPR % 512 == 0 && (C::SMAX / 64) * CPR % 8 == 0, "whole passes of the workgroup");
-    uint4 kreg[KIT], vreg[VIT];
-#pragma unroll
-    for (int i = 0; i < KIT; ++i) {
-        const int idx = i * 512 + tid;
-        const int row = idx / CPR, ch = idx - row * CPR;
-        kreg[i] = make_uint4(0, 0, 0, 0);
-        if (row < S) kreg[i] = *(const uint4*)(Kg + (int64_t)row * ld + ch * 8);
-    }
-    // V: a wave's 64 lanes take 64 consecutive keys of one 8-column chunk, so each 2-byte transposed store
-    // instruction writes 128 contiguous bytes of one V^T row
-#pragma unroll
-    for (int i = 0; i < VIT; ++i) {
-        const int it = i * 8 + wave;
-        const int kg = it / CPR, ch = it - kg * CPR;
-        const int key = kg * 64 + lane;
-        vreg[i] = make_uint4(0, 0, 0, 0);
-        if (key < S) vreg[i] = *(const uint4*)(Vg + (int64_t)key * ld + ch * 8);
-    }
-#pragma unroll
-    for (int i = 0; i < KIT; ++i) {
-        const int idx = i * 512 + tid;
-        const int row = idx / CPR, ch = idx - row * CPR;
-        if (row < SP) *(uint4*)(sK + row * C::KP + ch * 16) = kreg[i];
-    }
-#pragma unroll
-    for (int i = 0; i < VIT; ++i) {
-        const int it = i * 8 + wave;
-        const int kg = it / CPR, ch = it - kg * CPR;
-        const int key = kg * 64 + lane;
-        if (key < SP) {
-            const uint32_t w[4] = {vreg[i].x, vreg[i].y, vreg[i].z, vreg[i].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                *(uint16_t*)(sV + (ch * 8 + 2 * e) * C::VP + key * 2) = (uint16_t)(w[e] & 0xFFFFu);
-                *(uint16_t*)(sV + (ch * 8 + 2 * e + 1) * C::VP + key * 2) = (uint16_t)(w[e] >> 16);
-            }
-        }
-    }
-    __syncthreads();
-    if (qb >= nqb) return;  // no barrier follows
-    f32x16 oacc[HD / 32];
-#pragma unroll
-    for (int mb = 0; mb < HD / 32; ++mb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) oacc[mb][e] = 0.f;
-    float mrun = -INFINITY, lrun = 0.f;
 
-    for (int kb = 0; kb <= qb; ++kb) {
-        f32x16 s;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) s[e] = 0.f;
-        const char* kp = sK + (kb * 32 + n) * C::KP + h * 16;
-#pragma unroll
-        for (int ks = 0; ks < HD / 16; ++ks) {
-            const u32x4 a = *(const u32x4*)(kp + ks * 32);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, qf[ks]), s, 0, 0, 0);
+    // keys key0 .. key0 + rows - 1 (whole blocks of 32) into LDS.  Rows past S are zeros (their scores are masked, and a zero
+    // probability times a copy of an infinite value would not be).
+    auto load_tile = [&](int key0, int rows) __attribute__((always_inline)) {
+        const int slots = rows * C::CPR;  // a multiple of 64 for every head_dim
+        for (int s0 = wave * 64; s0 < slots; s0 += 256) {
+            const int slot = s0 + lane, row = slot / C::CPR, cp = slot % C::CPR;
+            const int64_t g = (int64_t)min(key0 + row, S - 1) * ld;
+            const char *kg = (const char*)(Kg + g + ((cp ^ C::swz_k(row)) << 3)), *vg = (const char*)(Vg + g + ((cp ^ C::swz_v(row)) << 3));
+            if (key0 + row >= S) kg = vg = zero_page;
+            __builtin_amdgcn_global_load_lds((egg_glb_void*)kg, (egg_lds_void*)(sK + s0 * 16), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((egg_glb_void*)vg, (egg_lds_void*)(sV + s0 * 16), 16, 0, 0);
         }
-        float p[16];
-        float mx = -INFINITY;
+    };
+    // the wave's query rows: 32 of each of its two blocks, the lane's half of every 16 columns
+    u32x4 qf[2][HD / 16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int key = kb * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
-            p[i] = (kb == qb && key > qrow) ? -INFINITY : s[i] * scale_log2;
-            mx = fmaxf(mx, p[i]);
-        }
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        const float mnew = fmaxf(mrun, mx);  // finite: key 0 of the member is visible to every query
-        const float alpha = __builtin_amdgcn_exp2f(mrun - mnew);
-        float lsum = 0.f;
+    for (int z = 0; z < 2; ++z) {
+        const int qrow = min((z ? 7 - wave : wave) * 32 + n, S - 1);  // (rows past the end: a copy, never stored)
+        if (z == 0 || nqb > 4)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            p[i] = __builtin_amdgcn_exp2f(p[i] - mnew);
-            lsum += p[i];
-        }
-        lrun = lrun * alpha + lsum;
-        mrun = mnew;
+            for (int ks = 0; ks < HD / 16; ++ks) qf[z][ks] = *(const u32x4*)(Qg + (int64_t)qrow * ld + (2 * ks + h) * 8);
+    }
+    if (Bo && tid < C::CPR) *(uint4*)(sB + tid * 16) = *(const uint4*)(Bo + (member * heads + head) * (int64_t)HD + tid * 8);
+    load_tile(0, tile_rows);
+
+    // fragment addresses: K row n of a block, chunk 2 ks + h; V keys 4 h + (s >> 2) (+ 8) of 16, columns 16 (group & 1) + 4 (s & 3)
+    const int s = lane & 15;
+    const char* kp = sK + n * C::ROW;
+    const int kx = h ^ C::swz_k(n);
+    const char* vp = sV + (4 * h + (s >> 2)) * C::ROW + (s & 1) * 8;
+    int vc[HD / 32];
+#pragma unroll
+    for (int mb = 0; mb < HD / 32; ++mb) vc[mb] = ((mb * 4 + ((lane >> 4) & 1) * 2 + ((s & 3) >> 1)) ^ C::swz_v(s >> 2)) << 4;
+
+    f32x16 oacc[HD / 32];
+    float mrun, lrun;
+    auto begin = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int mb = 0; mb < HD / 32; ++mb)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) oacc[mb][e] *= alpha;
+            for (int e = 0; e < 16; ++e) oacc[mb][e] = 0.f;
+        mrun = -INFINITY;
+        lrun = 0.f;
+    };
+    // key blocks kb0 .. kb1 - 1 (their first one in LDS is block kt) for query block qb
+    auto attend = [&](const u32x4(&q)[HD / 16], int qb, int kb0, int kb1, int kt) __attribute__((always_inline)) {
+        const int qrow = qb * 32 + n;
+        for (int kb = kb0; kb < kb1; ++kb) {
+            f32x16 sc;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const u32x4 pb = {pack_bf16x2(p[8 * t], p[8 * t + 1]), pack_bf16x2(p[8 * t + 2], p[8 * t + 3]),
-                              pack_bf16x2(p[8 * t + 4], p[8 * t + 5]), pack_bf16x2(p[8 * t + 6], p[8 * t + 7])};
+            for (int e = 0; e < 16; ++e) sc[e] = 0.f;
+            const int at = (kb - kt) * 32 * C::ROW;
 #pragma unroll
-            for (int mb = 0; mb < HD / 32; ++mb) {
-                // K-slots j < 4: keys kb*32 + 16t + 4h + j;  j >= 4: the same + 8 -- the order of the lane's p values
-                const char* vp = sV + (mb * 32 + n) * C::VP + (kb * 32 + 16 * t + 4 * h) * 2;
-                const uint2 lo = *(const uint2*)vp, hi = *(const uint2*)(vp + 16);
-                const u32x4 a = {lo.x, lo.y, hi.x, hi.y};
-                oacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, pb), oacc[mb], 0, 0, 0);
+            for (int ks = 0; ks < HD / 16; ++ks) {
+                const u32x4 a = *(const u32x4*)(kp + at + ((kx ^ (2 * ks)) << 4));
+                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, q[ks]), sc, 0, 0, 0);
+            }
+            float p[16];
+            float mx = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int key = kb * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
+                p[i] = (kb == qb && key > qrow) ? -INFINITY : sc[i] * scale_log2;
+                mx = fmaxf(mx, p[i]);
+            }
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            const float mnew = fmaxf(mrun, mx);  // finite: key 0 of the member is visible to every query
+            const float alpha = __builtin_amdgcn_exp2f(mrun - mnew);
+            float lsum = 0.f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                p[i] = __builtin_amdgcn_exp2f(p[i] - mnew);
+                lsum += p[i];
+            }
+            lrun = lrun * alpha + lsum;
+            mrun = mnew;
+#pragma unroll
+            for (int mb = 0; mb < HD / 32; ++mb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) oacc[mb][e] *= alpha;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const u32x4 pb = {pack_bf16x2(p[8 * t], p[8 * t + 1]), pack_bf16x2(p[8 * t + 2], p[8 * t + 3]),
+                                  pack_bf16x2(p[8 * t + 4], p[8 * t + 5]), pack_bf16x2(p[8 * t + 6], p[8 * t + 7])};
+#pragma unroll
+                for (int mb = 0; mb < HD / 32; ++mb) {
+                    // K-slots j < 4: keys kb*32 + 16t + 4h + j;  j >= 4: the same + 8 -- the order of the lane's p values
+                    const char* v0 = vp + at + 16 * t * C::ROW + vc[mb];
+                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)v0);
+                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(v0 + 8 * C::ROW));
+                    const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+                    const u32x4 a = {l2.x, l2.y, h2.x, h2.y};
+                    oacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, pb), oacc[mb], 0, 0, 0);
+                }
             }
         }
+    };
+    auto finish = [&](int qb) __attribute__((always_inline)) {
+        const int qrow = qb * 32 + n;
+        const float inv = 1.0f / (lrun + __shfl_xor(lrun, 32, 64));
+        uint16_t* orow = O + base + (int64_t)qrow * ld;
+        float tp = 0.f;
+#pragma unroll
+        for (int mb = 0; mb < HD / 32; ++mb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint2 o = make_uint2(pack_bf16x2(oacc[mb][4 * q] * inv, oacc[mb][4 * q + 1] * inv),
+                                           pack_bf16x2(oacc[mb][4 * q + 2] * inv, oacc[mb][4 * q + 3] * inv));
+                if (qrow < S) *(uint2*)(orow + mb * 32 + 8 * q + 4 * h) = o;
+                if (Bo) {
+                    const uint2 bv = *(const uint2*)(sB + (mb * 32 + 8 * q + 4 * h) * 2);
+                    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+                    tp = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, o.x), __builtin_bit_cast(bf16x2_t, bv.x), tp, false);
+                    tp = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, o.y), __builtin_bit_cast(bf16x2_t, bv.y), tp, false);
+                }
+            }
+        if (Bo) {
+            tp += __shfl_xor(tp, 32, 64);  // the two lane halves hold the two halves of every 8 columns
+            if (h == 0 && qrow < S) part[(int64_t)head * rows_total + member * S + qrow] = tp;
+        }
+    };
+
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's direct-to-LDS loads have landed
+    __syncthreads();
+    if (wave < nqb) {
+        begin();
+        attend(qf[0], wave, 0, wave + 1, 0);
+        finish(wave);
     }
-    const float inv = 1.0f / (lrun + __shfl_xor(lrun, 32, 64));
-    uint16_t* orow = O + base + (int64_t)qrow * ld;
-    float tp = 0.f;
-#pragma unroll
-    for (int mb = 0; mb < HD / 32; ++mb)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint2 o = make_uint2(pack_bf16x2(oacc[mb][4 * q] * inv, oacc[mb][4 * q + 1] * inv),
-                                       pack_bf16x2(oacc[mb][4 * q + 2] * inv, oacc[mb][4 * q + 3] * inv));
-            if (qrow < S) *(uint2*)(orow + mb * 32 + 8 * q + 4 * h) = o;
-            if (Bo) {
-                const uint2 bv = *(const uint2*)(sB + (mb * 32 + 8 * q + 4 * h) * 2);
-                typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-                tp = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, o.x), __builtin_bit_cast(bf16x2_t, bv.x), tp, false);
-                tp = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, o.y), __builtin_bit_cast(bf16x2_t, bv.y), tp, false);
-            }
-        }
-    if (Bo) {
-        tp += __shfl_xor(tp, 32, 64);  // the two lane halves hold the two halves of every 8 columns
-        if (h == 0 && qrow < S) part[(int64_t)head * rows_total + member * S + qrow] = tp;
+    if (nqb <= 4) return;  // (uniform: every wave of the workgroup leaves here, or none)
+    const int qb = 7 - wave;
+    begin();
+    if (qb < nqb) attend(qf[1], qb, 0, 4, 0);
+    __syncthreads();  // every wave is done with the first keys
+    load_tile(C::TILE, (nqb - 4) * 32);
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();
+    if (qb < nqb) {
+        attend(qf[1], qb, 4, qb + 1, 4);
+        finish(qb);
     }
 }
 
@@ -412,15 +434,17 @@ template <int HD>
 static egg_status launch_attention_t(eggroll_ctx* c, int64_t members, int S, int heads, const void* Q, const void* K,
                                      const void* V, void* O, const void* Bo, float* part)
 {
+    typedef AttnCfg<HD> C;
     auto kern = attention_kernel<HD>;
-    constexpr size_t LDS = (size_t)AttnCfg<HD>::LDS + HD * 2;
-    egg_status st = ensure_dynamic_lds(c, (const void*)kern, LDS, "attention smem attr");
+    const int tile_rows = std::min(C::TILE, (S + 31) & ~31);
+    const size_t lds = (size_t)2 * tile_rows * C::ROW + HD * 2;
+    egg_status st = ensure_dynamic_lds(c, (const void*)kern, lds, "attention smem attr");
     if (st != EGG_OK) return st;
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
     KernelScope ks(c, "attention");
-    hipLaunchKernelGGL(kern, dim3((unsigned)(members * heads)), dim3(512), LDS, c->stream, (const uint16_t*)Q,
-                       (const uint16_t*)K, (const uint16_t*)V, (uint16_t*)O, S, heads, (int64_t)heads * HD, scale_log2,
-                       (const uint16_t*)Bo, part, members * S);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(members * heads)), dim3(256), lds, c->stream, (const uint16_t*)Q,
+                       (const uint16_t*)K, (const uint16_t*)V, (uint16_t*)O, S, heads, (int64_t)heads * HD, scale_log2, tile_rows,
+                       (const char*)c->zero_page.p, (const uint16_t*)Bo, part, members * S);
     return check_hip(c, hipGetLastError(), "attention launch");
 }
 
