@@ -174,6 +174,11 @@ egg_status launch_forward_i8(eggroll_ctx* c, const StreamKey& ka, const StreamKe
                              int int_bound, int corr_shift, int out_shift, int steps, const int8_t* W,
                              const int8_t* H_in, int8_t* H_out);
 
+// many time steps in one kernel (k_recur_i8.hip), for the shapes that recur_i8_applies accepts
+bool recur_i8_applies(int d_out, int d_in, int64_t rows, int steps);
+egg_status launch_recur_i8(eggroll_ctx* c, const int8_t* A, const int8_t* B, int anti, int64_t rows, int d, int int_bound, int corr_shift,
+                           int out_shift, int steps, const int8_t* W, const int8_t* H_in, int8_t* H_out);
+
 // GRU gating fused into the epilogue of an integer matmul (see I8Args in k_int8.hip)
 struct I8Gate {
     int mode;  // 1: f and f^,  2: h

@@ -596,18 +596,19 @@ egg_status launch_forward_i8(eggroll_ctx* c, const StreamKey& ka, const StreamKe
     egg_status st;
     if ((st = reserve(c, c->i8_a, (size_t)noise_ids * d_out)) != EGG_OK) return st;
     if ((st = reserve(c, c->i8_b, (size_t)noise_ids * d_in)) != EGG_OK) return st;
+    int8_t* A = (int8_t*)c->i8_a.p;
+    int8_t* B = (int8_t*)c->i8_b.p;
+    const NoiseJob noise[2] = {{ka, d_out, A}, {kb, d_in, B}};
+    if ((st = launch_noise_jobs(c, noise, 2, first_id, noise_ids, EGG_I8, EGG_UNIFORM_INT, int_bound)) != EGG_OK) return st;
+    if (recur_i8_applies(d_out, d_in, rows, steps)) return launch_recur_i8(c, A, B, anti, rows, d_in, int_bound, corr_shift, out_shift, steps, W, H_in, H_out);
     if ((st = reserve(c, c->i8_h, 2 * ((obytes + 255) & ~size_t(255)))) != EGG_OK) return st;
     // one row of dot products per step: step t reads row t (filled by the dot kernel for t = 0, by the
     // previous step's epilogue otherwise) and accumulates row t+1
     const size_t dot_row = ((size_t)rows * sizeof(int) + 255) & ~size_t(255);
     if ((st = reserve(c, c->t_buf, dot_row * (size_t)(steps + 1))) != EGG_OK) return st;
-    int8_t* A = (int8_t*)c->i8_a.p;
-    int8_t* B = (int8_t*)c->i8_b.p;
     int8_t* scratch[2] = {(int8_t*)c->i8_h.p, (int8_t*)c->i8_h.p + ((obytes + 255) & ~size_t(255))};
     char* dots_base = (char*)c->t_buf.p;
 
-    const NoiseJob noise[2] = {{ka, d_out, A}, {kb, d_in, B}};
-    if ((st = launch_noise_jobs(c, noise, 2, first_id, noise_ids, EGG_I8, EGG_UNIFORM_INT, int_bound)) != EGG_OK) return st;
     if (steps > 1) {   // a fill kernel rather than a memset node, so that the call can sit inside a captured graph
         const int64_t nz = (int64_t)(dot_row / sizeof(int)) * (steps + 1);
         KernelScope ks(c, "zero_dots");
