@@ -461,15 +461,13 @@ __global__ __launch_bounds__(64) void sum_slabs_kernel(const float* __restrict__
     const int64_t n = (int64_t)blockIdx.x * 64 + threadIdx.x;
     if (n >= R) return;
     float acc = 0.f;
-    int p = 0;
-    for (; p + 16 <= slabs; p += 16) {
+    for (int p = 0; p < slabs; p += 16) {
         float v[16];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) v[k] = part[(int64_t)(p + k) * R + n];
+        for (int k = 0; k < 16; ++k) v[k] = part[(int64_t)min(p + k, slabs - 1) * R + n];  // clamped, unconditional
 #pragma unroll
-        for (int k = 0; k < 16; ++k) acc += v[k];
+        for (int k = 0; k < 16; ++k) acc = p + k < slabs ? acc + v[k] : acc;
     }
-    for (; p < slabs; ++p) acc += part[(int64_t)p * R + n];
     t[n] = acc;
 }
 

@@ -96,8 +96,8 @@ struct NoisePieces {
 };
 
 template <int MODE>
-__global__ __launch_bounds__(256) void noise_pieces_kernel(NoisePieces jobs, uint32_t member_begin, IntMap im,
-                                                           const int8_t* __restrict__ table)
+__global__ __launch_bounds__(256) void noise_pieces_kernel(uint32_t member_begin, IntMap im, const int8_t* __restrict__ table,
+                                                           NoisePieces jobs)
 {
     constexpr int BPP = (MODE == NM_BF16 || MODE == NM_I8_TABLE) ? 4 : 2;  // Threefry blocks per piece
     int j = 0;
@@ -196,11 +196,11 @@ egg_status launch_noise_jobs(eggroll_ctx* c, const NoiseJob* jobs, int count, ui
         if (np.count == 0) return EGG_OK;
         KernelScope ks(c, "noise_gen");
         const dim3 g(wgs), b(256);
-        if (dist == EGG_RAW) hipLaunchKernelGGL(noise_pieces_kernel<NM_RAW>, g, b, 0, c->stream, np, member_begin, im, tab);
-        else if (table) hipLaunchKernelGGL(noise_pieces_kernel<NM_I8_TABLE>, g, b, 0, c->stream, np, member_begin, im, tab);
-        else if (dist == EGG_UNIFORM_INT) hipLaunchKernelGGL(noise_pieces_kernel<NM_I8>, g, b, 0, c->stream, np, member_begin, im, tab);
-        else if (dtype == EGG_F32) hipLaunchKernelGGL(noise_pieces_kernel<NM_F32>, g, b, 0, c->stream, np, member_begin, im, tab);
-        else hipLaunchKernelGGL(noise_pieces_kernel<NM_BF16>, g, b, 0, c->stream, np, member_begin, im, tab);
+        if (dist == EGG_RAW) hipLaunchKernelGGL(noise_pieces_kernel<NM_RAW>, g, b, 0, c->stream, member_begin, im, tab, np);
+        else if (table) hipLaunchKernelGGL(noise_pieces_kernel<NM_I8_TABLE>, g, b, 0, c->stream, member_begin, im, tab, np);
+        else if (dist == EGG_UNIFORM_INT) hipLaunchKernelGGL(noise_pieces_kernel<NM_I8>, g, b, 0, c->stream, member_begin, im, tab, np);
+        else if (dtype == EGG_F32) hipLaunchKernelGGL(noise_pieces_kernel<NM_F32>, g, b, 0, c->stream, member_begin, im, tab, np);
+        else hipLaunchKernelGGL(noise_pieces_kernel<NM_BF16>, g, b, 0, c->stream, member_begin, im, tab, np);
         np.count = 0;
         wgs = 0;
         return check_hip(c, hipGetLastError(), "noise_gen launch");
