@@ -121,6 +121,15 @@ __device__ __forceinline__ void static_for(F&& f)
 // 4608 rows 69.4 / 63.6; update 4096 x 2560, K = 4096 153 / 128.
 constexpr int64_t BIG_TILES_ABOVE = 128;
 
+// fp32 products are bound by the MFMAs of the busiest CU: 128 x 64 tiles where they leave it less to do than 128 x 128 tiles.
+// Measured (us, 128 x 128 / 128 x 64): forward 1024 x 2048, 8255 rows (520 tiles on 256 CUs) 422 / 378; update 3000 x 2000, K = 1000
+// 155 / 128; level where the tiles fill the CUs evenly (2048^2, 2048 rows: 156 / 160), so those keep the larger one.
+inline bool narrow_f32_tiles(int64_t M, int64_t N, int compute_units)
+{
+    const int64_t tm = (M + 127) / 128, wide = tm * ((N + 127) / 128), narrow = tm * ((N + 63) / 64);
+    return (narrow + compute_units - 1) / compute_units < 2 * ((wide + compute_units - 1) / compute_units);
+}
+
 // XCD-aware tile order: workgroup ids go round-robin over the 8 XCDs, so ids that are congruent
 // mod 8 share an L2.  Give each XCD a contiguous run of tiles, and walk tiles in groups of GM rows
 // so that a run covers a compact block of C (few distinct P and Q panels per L2).

@@ -145,7 +145,6 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const uint4* __restrict__ 
 // Online softmax in base 2 (running maximum and sum per query, fp32).  S <= 256.
 template <int HD>
 struct AttnCfg {
-    static constexpr int TILE = 128;        // keys in LDS at a time
     static constexpr int ROW = HD * 2;      // bytes of a row
     static constexpr int CPR = HD / 8;      // 16-byte chunks of a row
     static_assert(HD == 32 || HD == 64 || HD == 128, "swizzles below");
@@ -155,8 +154,11 @@ struct AttnCfg {
     static __device__ __forceinline__ int swz_v(int row) { return HD == 128 ? (row & 3) << 2 : (HD == 64 ? ((row >> 1) & 1) << 2 : 0); }
 };
 
-template <int HD>
-__global__ __launch_bounds__(256, 2) void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+// NW: waves.  Four as above; eight -- one query block each (b and 7 - b on a SIMD), all keys in LDS at once -- where there are no
+// more workgroups than CUs and the chain of one wave is what the call waits for (kernel
+// alone, us, four / eight waves: 32 members x 4 heads x 200 x 64 10.4 / 7.9; 20 x 2 x 256 x 128 15.1 / 12.3; 32 x 8 x 256 x 128 20.4 / 18.5).
+template <int HD, int NW>
+__global__ __launch_bounds__(NW * 64, 8 / NW) void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
                                                            const uint16_t* __restrict__ V, uint16_t* __restrict__ O, int S,
                                                            int heads, int64_t ld, float scale_log2, int tile_rows, const char* zero_page,
                                                            const uint16_t* __restrict__ Bo, float* __restrict__ part, int64_t rows_total)
@@ -165,11 +167,12 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const uint16_t* __res
     // the head's share of that layer's projections, sum over its HD columns of O[row][col] * Bo[col] (from the bf16 values stored),
     // goes to part[head][row] and a small pass adds the heads in order -- so the attention output is not read a second time.
     typedef AttnCfg<HD> C;
+    constexpr int TILE = NW * 32;
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     char* sK = smem;
-    char* sV = smem + tile_rows * C::ROW;      // tile_rows: min(128, S rounded up to 32)
+    char* sV = smem + tile_rows * C::ROW;      // tile_rows: min(TILE, S rounded up to 32)
     char* sB = sV + tile_rows * C::ROW;        // HD bf16 of Bo for this (member, head)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -184,7 +187,7 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const uint16_t* __res
     // probability times a copy of an infinite value would not be).
     auto load_tile = [&](int key0, int rows) __attribute__((always_inline)) {
         const int slots = rows * C::CPR;  // a multiple of 64 for every head_dim
-        for (int s0 = wave * 64; s0 < slots; s0 += 256) {
+        for (int s0 = wave * 64; s0 < slots; s0 += NW * 64) {
             const int slot = s0 + lane, row = slot / C::CPR, cp = slot % C::CPR;
             const int64_t g = (int64_t)min(key0 + row, S - 1) * ld;
             const char *kg = (const char*)(Kg + g + ((cp ^ C::swz_k(row)) << 3)), *vg = (const char*)(Vg + g + ((cp ^ C::swz_v(row)) << 3));
@@ -194,10 +197,12 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const uint16_t* __res
         }
     };
     // the wave's query rows: 32 of each of its two blocks, the lane's half of every 16 columns
-    u32x4 qf[2][HD / 16];
+    const int qb0 = NW == 4 || wave < 4 ? wave : 11 - wave;
+    constexpr int NZ = NW == 4 ? 2 : 1;
+    u32x4 qf[NZ][HD / 16];
 #pragma unroll
-    for (int z = 0; z < 2; ++z) {
-        const int qrow = min((z ? 7 - wave : wave) * 32 + n, S - 1);  // (rows past the end: a copy, never stored)
+    for (int z = 0; z < NZ; ++z) {
+        const int qrow = min((z ? 7 - wave : qb0) * 32 + n, S - 1);  // (rows past the end: a copy, never stored)
         if (z == 0 || nqb > 4)
 #pragma unroll
             for (int ks = 0; ks < HD / 16; ++ks) qf[z][ks] = *(const u32x4*)(Qg + (int64_t)qrow * ld + (2 * ks + h) * 8);
@@ -214,6 +219,15 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const uint16_t* __res
 #pragma unroll
     for (int mb = 0; mb < HD / 32; ++mb) vc[mb] = ((mb * 4 + ((lane >> 4) & 1) * 2 + ((s & 3) >> 1)) ^ C::swz_v(s >> 2)) << 4;
 
+    constexpr bool EARLY_V = HD <= 64;
+    // K-slots j < 4: keys 16t + 4h + j of the block;  j >= 4: the same + 8 -- the order of the lane's p values
+    auto read_v = [&](int at, int t, int mb) __attribute__((always_inline)) {
+        const char* v0 = vp + at + 16 * t * C::ROW + vc[mb];
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)v0);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(v0 + 8 * C::ROW));
+        const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+        return u32x4{l2.x, l2.y, h2.x, h2.y};
+    };
     f32x16 oacc[HD / 32];
     float mrun, lrun;
     auto begin = [&]() __attribute__((always_inline)) {
@@ -236,6 +250,14 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const uint16_t* __res
             for (int ks = 0; ks < HD / 16; ++ks) {
                 const u32x4 a = *(const u32x4*)(kp + at + ((kx ^ (2 * ks)) << 4));
                 sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, q[ks]), sc, 0, 0, 0);
+            }
+            // asked for here the V fragments arrive under the softmax (at head_dim 128 the registers are taken)
+            u32x4 va[EARLY_V ? 2 : 1][EARLY_V ? HD / 32 : 1];
+            if constexpr (EARLY_V) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int mb = 0; mb < HD / 32; ++mb) va[t][mb] = read_v(at, t, mb);
             }
             float p[16];
             float mx = -INFINITY;
@@ -266,12 +288,7 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const uint16_t* __res
                                   pack_bf16x2(p[8 * t + 4], p[8 * t + 5]), pack_bf16x2(p[8 * t + 6], p[8 * t + 7])};
 #pragma unroll
                 for (int mb = 0; mb < HD / 32; ++mb) {
-                    // K-slots j < 4: keys kb*32 + 16t + 4h + j;  j >= 4: the same + 8 -- the order of the lane's p values
-                    const char* v0 = vp + at + 16 * t * C::ROW + vc[mb];
-                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)v0);
-                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(v0 + 8 * C::ROW));
-                    const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-                    const u32x4 a = {l2.x, l2.y, h2.x, h2.y};
+                    const u32x4 a = EARLY_V ? va[EARLY_V ? t : 0][EARLY_V ? mb : 0] : read_v(at, t, mb);
                     oacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, pb), oacc[mb], 0, 0, 0);
                 }
             }
@@ -304,22 +321,24 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(const uint16_t* __res
 
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's direct-to-LDS loads have landed
     __syncthreads();
-    if (wave < nqb) {
+    if (qb0 < nqb) {
         begin();
-        attend(qf[0], wave, 0, wave + 1, 0);
-        finish(wave);
+        attend(qf[0], qb0, 0, qb0 + 1, 0);
+        finish(qb0);
     }
-    if (nqb <= 4) return;  // (uniform: every wave of the workgroup leaves here, or none)
-    const int qb = 7 - wave;
-    begin();
-    if (qb < nqb) attend(qf[1], qb, 0, 4, 0);
-    __syncthreads();  // every wave is done with the first keys
-    load_tile(C::TILE, (nqb - 4) * 32);
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    __syncthreads();
-    if (qb < nqb) {
-        attend(qf[1], qb, 4, qb + 1, 4);
-        finish(qb);
+    if constexpr (NW == 4) {
+        if (nqb <= 4) return;  // (uniform: every wave of the workgroup leaves here, or none)
+        const int qb = 7 - wave;
+        begin();
+        if (qb < nqb) attend(qf[1], qb, 0, 4, 0);
+        __syncthreads();  // every wave is done with the first keys
+        load_tile(TILE, (nqb - 4) * 32);
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();
+        if (qb < nqb) {
+            attend(qf[1], qb, 4, qb + 1, 4);
+            finish(qb);
+        }
     }
 }
 
@@ -435,14 +454,16 @@ static egg_status launch_attention_t(eggroll_ctx* c, int64_t members, int S, int
                                      const void* V, void* O, const void* Bo, float* part)
 {
     typedef AttnCfg<HD> C;
-    auto kern = attention_kernel<HD>;
-    const int tile_rows = std::min(C::TILE, (S + 31) & ~31);
+    const bool eight = S > 128 && members * heads <= c->compute_units;
+    void (*kern)(const uint16_t*, const uint16_t*, const uint16_t*, uint16_t*, int, int, int64_t, float, int, const char*, const uint16_t*, float*, int64_t) =
+        eight ? attention_kernel<HD, 8> : attention_kernel<HD, 4>;
+    const int tile_rows = std::min(eight ? 256 : 128, (S + 31) & ~31);
     const size_t lds = (size_t)2 * tile_rows * C::ROW + HD * 2;
     egg_status st = ensure_dynamic_lds(c, (const void*)kern, lds, "attention smem attr");
     if (st != EGG_OK) return st;
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)HD);
     KernelScope ks(c, "attention");
-    hipLaunchKernelGGL(kern, dim3((unsigned)(members * heads)), dim3(256), lds, c->stream, (const uint16_t*)Q,
+    hipLaunchKernelGGL(kern, dim3((unsigned)(members * heads)), dim3(eight ? 512 : 256), lds, c->stream, (const uint16_t*)Q,
                        (const uint16_t*)K, (const uint16_t*)V, (uint16_t*)O, S, heads, (int64_t)heads * HD, scale_log2, tile_rows,
                        (const char*)c->zero_page.p, (const uint16_t*)Bo, part, members * S);
     return check_hip(c, hipGetLastError(), "attention launch");

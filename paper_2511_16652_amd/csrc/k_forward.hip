@@ -586,6 +586,7 @@ static egg_status launch_forward_t(eggroll_ctx* c, const StreamKey& ka, const eg
         if (next) return fail(c, EGG_EINVAL, "this layer cannot form the next layer's projections (ask forward_fuses_next_projection first)");
         if (const int tile = small_tile(s.d_out, R)) return launch_gemm_small<FwdRowEpi<false, RANK, REGEN>>(c, "forward_gemm_f32", P, Q, kchunks, tile, ea);
         ea.pair_share = pairs;
+        if (narrow_f32_tiles(s.d_out, R, c->compute_units)) return launch_gemm<MmaF32, 128, 64, 2, 2, Epi>(c, "forward_gemm_f32", P, Q, kchunks, ea);
         return launch_gemm<MmaF32, 128, 128, 2, 2, Epi>(c, "forward_gemm_f32", P, Q, kchunks, ea);
     }
 }

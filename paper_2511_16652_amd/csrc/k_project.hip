@@ -184,24 +184,38 @@ __global__ __launch_bounds__(256) void project_row_kernel(StreamKey kb, uint32_t
     const uint32_t member = member_begin + (uint32_t)ml;
     const int pairs = d_in >> 1;
     float acc = 0.f;
-    for (int b = tid; b < pairs; b += 256) {
+    // one column pair; the order of the additions is that of b
+    auto pair = [&](int b, uint2 xv) __attribute__((always_inline)) {
         uint32_t w0, w1;
         noise_words(kb, member, (uint32_t)b, w0, w1);
         float z0, z1;
         normal_pair<!BF16>(w0, w1, z0, z1);
         if constexpr (BF16) {
             const uint32_t pk = pack_bf16x2(z0, z1);
-            const uint32_t xv = ((const uint32_t*)X)[ml * pairs + b];
-            acc = fmaf(bf16_lo(xv), bf16_lo(pk), acc);
-            acc = fmaf(bf16_hi(xv), bf16_hi(pk), acc);
+            acc = fmaf(bf16_lo(xv.x), bf16_lo(pk), acc);
+            acc = fmaf(bf16_hi(xv.x), bf16_hi(pk), acc);
             if (B_cache) ((uint32_t*)B_cache)[ml * pairs + b] = pk;
         } else {
-            const float2 xv = ((const float2*)X)[ml * pairs + b];
-            acc = fmaf(xv.x, z0, acc);
-            acc = fmaf(xv.y, z1, acc);
+            acc = fmaf(__uint_as_float(xv.x), z0, acc);
+            acc = fmaf(__uint_as_float(xv.y), z1, acc);
             if (B_cache) ((float2*)B_cache)[ml * pairs + b] = make_float2(z0, z1);
         }
+    };
+    auto xload = [&](int b) __attribute__((always_inline)) {
+        if constexpr (BF16) return make_uint2(((const uint32_t*)X)[ml * pairs + b], 0u);
+        else return ((const uint2*)X)[ml * pairs + b];
+    };
+    int b = tid;
+    // four at a time: their loads and their generator chains are independent (one at a time, 4096 members x 4096 columns took
+    // 32 us, of which the generator's issue slots are 19)
+    for (; b + 768 < pairs; b += 1024) {
+        uint2 xv[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xv[k] = xload(b + 256 * k);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pair(b + 256 * k, xv[k]);
     }
+    for (; b < pairs; b += 256) pair(b, xload(b));
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
     if ((tid & 63) == 0) red[tid >> 6] = acc;

@@ -728,6 +728,7 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
             return launch_upd_gemm16<128, 128, 2, 2, true>(c, "update_gemm_f16_small", Q, P, (int)kgroups, ea);
         return launch_upd_gemm<MmaF16, 128, 128, 2, 2>(c, "update_gemm_f16_small", P, Q, (int)kgroups, ea);
     }
+    if (narrow_f32_tiles(s.d_out, s.d_in, c->compute_units)) return launch_upd_gemm<MmaF32, 128, 64, 2, 2>(c, "update_gemm_f32", P, Q, (int)kgroups, ea);
     return launch_upd_gemm<MmaF32, 128, 128, 2, 2>(c, "update_gemm_f32", P, Q, (int)kgroups, ea);
 }
 
