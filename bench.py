@@ -281,7 +281,7 @@ def decoder_workload(args):
                         "step_frac_of_bf16_peak": (fwd_flops + upd_flops) / t_step["median"] / 1e12 / peak},
         "roofline": {"bound": "mfma", "kernel": "forward_gemm_bf16 (all %d launches of one step)" % gemm["launches"],
                      "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
-                     "traffic": profiled_traffic("cfg5", ("MmaBf16", "FwdEpi"))},
+                     "traffic": profiled_traffic("cfg5", ("MmaBf16", "Epi"))},
         "measured_ceilings": ceil,
         "mean_token_loglik": loglik_mean,
         "kernels": kernels,
@@ -418,7 +418,7 @@ def mlp_stack_workload(args):
                         "step_frac_of_bf16_peak": (fwd_flops + upd_flops) / t_step["median"] / 1e12 / peak},
         "roofline": {"bound": "mfma", "kernel": "forward_gemm_bf16 (all %d launches of one step)" % gemm["launches"],
                      "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
-                     "traffic": profiled_traffic("cfg4", ("MmaBf16", "FwdEpi"))},
+                     "traffic": profiled_traffic("cfg4", ("MmaBf16", "Epi"))},
         "measured_ceilings": ceil,
         "kernels": kernels,
     }
@@ -619,7 +619,7 @@ def linear_workload(args):
         "measured_ceilings": measured_ceilings(),
         "roofline": {"bound": "mfma", "kernel": gemm_name, "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak,
-                     "traffic": profiled_traffic(args.workload, ("MmaBf16" if wl.dtype == "bf16" else "MmaF32", "FwdEpi"))},
+                     "traffic": profiled_traffic(args.workload, ("MmaBf16" if wl.dtype == "bf16" else "MmaF32", "Epi"))},
         "update_roofline": {"bound": "mfma", "kernel": upd_name, "achieved": upd_tflops, "peak": peak,
                             "unit": "TFLOP/s", "frac": upd_tflops / peak},
         "kernels": kernels,
@@ -723,7 +723,7 @@ def int8_workload(args):
     ctx.profile_enable(False)
     kernels = {k: {"launches": n, "avg_us": 1e3 * ms / n} for k, (n, ms) in prof.items()}
     ops = 2.0 * wl.N * wl.d * wl.d
-    achieved = ops / (kernels["forward_gemm_i8"]["avg_us"] * 1e-6) / 1e12
+    achieved = ops * wl.steps / (kernels["forward_recur_i8"]["avg_us"] * 1e-6) / 1e12   # one launch runs all time steps
 
     # the integer parameter update over the same population (not part of the timed step: the metric is
     # the recurrence), ternary fitness, threshold for about 20 % moves
@@ -748,10 +748,10 @@ def int8_workload(args):
         "warmup": args.warmup, "ms_per_step": 1e3 * t_step, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "i8", "data": "synthetic",
         "config": {"workload": wl.name, "d": wl.d, "population": wl.N, "time_steps": wl.steps, "bound": wl.bound},
-        "roofline": {"bound": "mfma", "kernel": "forward_gemm_i8", "achieved": achieved,
+        "roofline": {"bound": "mfma", "kernel": "forward_recur_i8", "achieved": achieved,
                      "peak": roofline.MFMA_PEAK_TFLOPS["i8"], "unit": "TOP/s",
                      "frac": achieved / roofline.MFMA_PEAK_TFLOPS["i8"],
-                     "traffic": profiled_traffic(args.workload, ("MmaI8",))},
+                     "traffic": profiled_traffic(args.workload, ("recur_i8_kernel",))},
         "kernels": kernels,
         "integer_update": {"ms": 1e3 * t_upd, "TOP/s": ops / t_upd / 1e12, "threshold": tau, "kernels": uk},
     }

@@ -41,16 +41,7 @@ struct Operand {
     int rows;            // valid rows
 };
 
-struct MmaBf16 {
-    static constexpr int MFMA_PER_MMA = 1;
-    static constexpr int BLK = 32;
-    typedef f32x16 acc_t;
-    static __device__ __forceinline__ void mma(const u32x4& a, const u32x4& b, acc_t& c)
-    {
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-    }
-};
-// The same contraction from 16x16x32 blocks.  Both shapes retire 1024 flops per cycle and CU and read the same
+// bf16 from 16x16x32 blocks rather than 32x32x16.  Both shapes retire 1024 flops per cycle and CU and read the same
 // fragment bytes from LDS, but on ordinary (non-constant) operands the chip clocks higher under the 16x16x32 form:
 // measured with MFMAs alone 2.0 PFLOP/s against 1.7, and 1.40 against 1.22 inside this kernel's loop structure
 // (fragment reads, one barrier and 64 KB of direct-to-LDS loads per stage).
@@ -264,8 +255,6 @@ constexpr size_t gemm_lds_bytes()
 //   template <int WTM> __device__ void flush(int mw0, int nb0, int n_rows);   after each 32-column block
 //   template <int MB, int NB> __device__ void prefetch(int mw0, int nw0, int lane, int n_rows);   late in the main loop
 //   template <class MT, int MB, int NB> __device__ void extra_mma(acc_t (&acc)[MB][NB], int mw0, int nw0, int lane, int n_rows);
-//   template <int NT, int BM, int BN> __device__ bool tile_begin(char* lds_tail, int m0, int n0, int tid, int n_rows);
-//       called by all threads before the per-wave part; returns whether a barrier is needed
 //
 // Main loop, per K-stage (4 MFMA k-steps): the fragments of k-step s+1 are read from LDS while the
 // MFMAs of k-step s run (two fragment register sets).  The single barrier of the stage sits in the
@@ -545,8 +534,6 @@ __device__ __forceinline__ void gemm_nt_tile(const Operand& P, const Operand& Q,
   } else {
     // an epilogue may fold per-column-block rank-r terms into the accumulators with a few more MFMAs
     epi.template extra_mma<MT, MB, NB>(acc, m0 + wm * WTM, n0 + wn * WTN, lane, Q.rows);
-    // workgroup-level hook: an epilogue may pull per-tile side data into the LDS behind the wave slices
-    if (epi.template tile_begin<NT, BM, BN>(lds + WM * WN * Epi::lds_per_wave(WTM), m0, n0, tid, Q.rows)) __syncthreads();
     // (a compile-time loop: were the optimiser to leave it rolled, acc would be indexed at run time and live in scratch)
     static_for<0, NB>([&](auto jc) __attribute__((always_inline)) {
         constexpr int j = decltype(jc)::value;
@@ -577,47 +564,9 @@ __global__ __launch_bounds__(WM* WN * 64, WG_PER_CU) void gemm_nt_kernel(Operand
     gemm_nt_tile<MT, BM, BN, WM, WN, KMAJOR, Epi>(P, Q, blockIdx.x, 0, kchunks, tiles_m, tiles_n, zero_page, ea);
 }
 
-// Staging helper for epilogues whose output is row-major [n][m] with 2-byte elements: store4 parks a
-// lane's 4 consecutive m-values of column n in the wave's LDS slice as row (n mod block size); flush writes
-// the ROWS x WTM block out with 16-byte stores, 16 lanes per 256 contiguous bytes.
-struct RowStager2B {
-    char* base;
-    int lane;
-    int row;  // the lane's column of the MFMA block = row of the staged block: lane & (block size - 1)
-    static constexpr __host__ __device__ int pitch(int wtm) { return wtm * 2 + 16; }
-    static constexpr __host__ __device__ int bytes(int wtm) { return 32 * pitch(wtm); }
-    __device__ __forceinline__ void put(int wtm_pitch, int ml, uint32_t lo, uint32_t hi) const
-    {
-        *(uint2*)(base + row * wtm_pitch + ml * 2) = make_uint2(lo, hi);
-    }
-    // out: element pointer of the row-major destination with `ld` elements per row; rows nb0..nb0+31
-    // (valid below n_rows), columns mw0..mw0+WTM-1 (valid below m_cols, a multiple of 4)
-    template <int WTM, int ROWS = 32>
-    __device__ __forceinline__ void flush(uint16_t* out, int64_t ld, int mw0, int nb0, int n_rows, int m_cols) const
-    {
-        constexpr int P = pitch(WTM), CPR = WTM / 8;  // 16-byte chunks per row
-        static_assert(ROWS * CPR % 64 == 0, "whole wave passes");
-        __builtin_amdgcn_s_waitcnt(0xC07F);           // lgkmcnt(0): the wave's own LDS writes have landed
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int it = 0; it < ROWS * CPR / 64; ++it) {
-            const int c = it * 64 + lane;
-            const int row = c / CPR, cc = c % CPR;
-            const int n = nb0 + row, m = mw0 + cc * 8;
-            if (n < n_rows && m < m_cols) {
-                const u32x4 v = *(const u32x4*)(base + row * P + cc * 16);
-                uint16_t* dst = out + (int64_t)n * ld + m;
-                if (m + 8 <= m_cols) *(u32x4*)dst = v;
-                else *(uint2*)dst = make_uint2(v[0], v[1]);
-            }
-        }
-        __builtin_amdgcn_wave_barrier();  // the slice is reused by the next column block
-    }
-};
-
-
-// The same staging in half the space: 16 rows (one 16x16 column block) of WTM 2-byte elements without padding,
-// the 16-byte chunks of a row XOR-swizzled by the row number instead.  A store4 of 16 rows x 2 lane groups then
+// Staging helper for epilogues whose output is row-major [n][m] with 2-byte elements: store4 parks a lane's 4 consecutive
+// m-values of column n in the wave's LDS slice, flush writes the block out with 16-byte stores.  16 rows (one 16x16 column
+// block) of WTM elements without padding, the 16-byte chunks of a row XOR-swizzled by the row number.  A store4 of 16 rows x 2 lane groups then
 // covers 16 distinct chunks (all 64 banks once), and flush reads whole rows.  At WTM = 128 the eight waves of a
 // workgroup need 32 KB: what a 160 KB LDS leaves beside two 64 KB stages, so a persistent kernel can stage one
 // tile's output while the next tile's first stages are already landing.

@@ -168,8 +168,6 @@ struct I8Epi {
     static constexpr __host__ __device__ int pitch(int wtm) { return SWZ ? wtm * 4 : wtm * 4 + 16; }
     static constexpr __host__ __device__ int lds_per_wave(int wtm) { return 32 * pitch(wtm); }
     __device__ __forceinline__ I8Epi(const Args& a_, char* slice, int lane_) : a(a_), stage(slice), lane(lane_), cur_j(-1) {}
-    template <int NT, int BM, int BN>
-    __device__ __forceinline__ bool tile_begin(char*, int, int, int, int) { return false; }
     template <class MT, int MB, int NB>
     __device__ __forceinline__ void extra_mma(typename MT::acc_t (&)[MB][NB], int, int, int, int) {}
 

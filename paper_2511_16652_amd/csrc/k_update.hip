@@ -439,8 +439,6 @@ struct UpdEpiT {
     }
     template <int WTM>
     __device__ __forceinline__ void flush(int, int, int) {}
-    template <int NT, int BM, int BN>
-    __device__ __forceinline__ bool tile_begin(char*, int, int, int, int) { return false; }
     template <class MT, int MB, int NB>
     __device__ __forceinline__ void extra_mma(typename MT::acc_t (&)[MB][NB], int, int, int, int) {}
     template <int MB, int NB>
@@ -486,8 +484,6 @@ struct UpdEpi16 {
     __device__ __forceinline__ void column(int, bool) {}
     template <int J>
     __device__ __forceinline__ void column_at(int, bool) {}
-    template <int NT, int BM, int BN>
-    __device__ __forceinline__ bool tile_begin(char*, int, int, int, int) { return false; }
     template <class MT, int MB, int NB>
     __device__ __forceinline__ void extra_mma(typename MT::acc_t (&)[MB][NB], int, int, int, int) {}
     template <int MB, int NB>

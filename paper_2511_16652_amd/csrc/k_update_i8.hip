@@ -174,8 +174,6 @@ struct I8UpdEpi {
     static constexpr __host__ __device__ int pitch(int wtm) { return wtm * 4 + 16; }
     static constexpr __host__ __device__ int lds_per_wave(int wtm) { return 32 * pitch(wtm); }
     __device__ __forceinline__ I8UpdEpi(const Args& a_, char* slice, int lane_) : a(a_), stage(slice), lane(lane_), row_pitch(0) {}
-    template <int NT, int BM, int BN>
-    __device__ __forceinline__ bool tile_begin(char*, int, int, int, int) { return false; }
     template <class MT, int MB, int NB>
     __device__ __forceinline__ void extra_mma(typename MT::acc_t (&)[MB][NB], int, int, int, int) {}
     template <int MB, int NB>
