@@ -299,8 +299,7 @@ egg_status eggroll_loglik_i8(eggroll_ctx* ctx, int64_t rows, const int8_t* logit
  * eggroll_egg_forward_i8 with the same key: for the embedding table, the four GRU matrices and the two MLP
  * matrices of each layer, and the head, with that parameter's noise layer,
  *   E = sum_i F_i A_i B_i^T (int32),   theta <- clamp(theta + sign(E) [|E| >= threshold], -127, 127)
- * exactly as eggroll_update_i8 does for one matrix (one call of it per parameter, 6 layers + 2 launches of
- * its kernels).  shape: member ids are noise ids (pair ids when the forward ran antithetic pairs; antithetic
+ * exactly as eggroll_update_i8 does for one matrix (several parameters to a launch of its kernels).  shape: member ids are noise ids (pair ids when the forward ran antithetic pairs; antithetic
  * must be 0 here), d_out = d_in = D, rank 1.  fitness: int8 [member_count] in {-1, 0, 1}, one shaped value
  * per noise id (for pairs sign(s+ - s-), "Fitness Shaping").  Normalisation weights and biases are left as
  * they are (the paper perturbs and updates matrices and the embedding only).  Bit-exact.

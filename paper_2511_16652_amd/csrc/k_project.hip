@@ -13,7 +13,15 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // d_in is walked in panels of `panel` columns (a multiple of the 16-byte chunk, all of d_in when B_i fits the LDS budget):
 // per panel B_i[k0 .. k0 + panel) is regenerated into LDS and the member's rows are streamed against it; with more than
 // one panel the partial sums are carried in t itself (a row is always handled by the same wave).
-template <bool BF16, int RANK>
+// NR > 1, rank 8 and 16: phase 2 walks NR rows of a wave at once, so that a factor read from LDS serves them all -- a row alone reads
+// 8 or 16 times its own bytes from there -- and asks for the next step's pieces of the rows before it multiplies this step's, the
+// first step's before the factors are generated.  Rows past the last are repeated, not stored; the order of a row's additions
+// does not depend on NR.  Whole calls of layers with 256 outputs
+// (us, one row at a time / this): bf16 64 members x 128 rows of 4096, rank 16: 244 / 173; 256 x 64 of 8192, rank 8: 172 / 164; fp32
+// 64 x 64 of 2048, rank 8: 143 / 109; 1024 -> 1024, 256 x 16, rank 8: 30.7 / 29.1.
+// Below rank 8, and with one row to a wave, the loop over rows one at a time is as fast or faster (the registers of the deeper
+// form cost more waves than its loads hide: 64 rows of 2048 at rank 4 74.6 us against 68.3).
+template <bool BF16, int RANK, int NR>
 __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t member_begin, int S, int anti_rows, int d_in, int panel,
                                                       const void* __restrict__ X, float* __restrict__ t,
                                                       void* __restrict__ B_cache)
@@ -28,9 +36,24 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
     // instead of two unpacked multiply-adds: the pass was vector-ALU bound on unpacking (2.5 TB/s at rank 4).
     constexpr bool TRANSPOSED = BF16 && RANK >= 2;
     const int lane = tid & 63, wave = tid >> 6;
+    constexpr int U = 2;  // chunks of a row per step (NR > 1)
 
     for (int k0 = 0; k0 < d_in; k0 += panel) {
         const int kn = min(panel, d_in - k0);     // columns of this panel
+        const int chunks = kn / EPC;
+        const int steps = (chunks + 64 * U - 1) / (64 * U);  // per batch of rows
+        // rows s0, s0 + 4, ..; pieces past the end are clamped to the last one and not multiplied
+        auto load = [&](int s0, int ch0, uint4 (&x)[NR][U]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < NR; ++j) {
+                const int64_t row = ml * S + min(s0 + 4 * j, S - 1);
+                const uint4* xr = (const uint4*)((const char*)X + (row * (int64_t)d_in + k0) * (BF16 ? 2 : 4));
+#pragma unroll
+                for (int u = 0; u < U; ++u) x[j][u] = xr[min(ch0 + lane + 64 * u, chunks - 1)];
+            }
+        };
+        uint4 xn[NR][U];
+        if constexpr (NR > 1) load(wave, 0, xn);
         const int n = kn * RANK;                  // even: d_in and panel are multiples of 4
         const int first = k0 * RANK;              // flat index of the panel's first factor entry (even)
         if (k0) __syncthreads();                  // every wave is done with the previous panel
@@ -86,7 +109,31 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
         __syncthreads();
 
         // ---- phase 2: one wave per row ------------------------------------------------------------
-        const int chunks = kn / EPC;
+        // the sums of a row over the wave's lanes
+        auto finish = [&](int s, float (&a)[RANK]) __attribute__((always_inline)) {
+            const int64_t row = ml * S + s;
+#pragma unroll
+            for (int l = 0; l < RANK; ++l) {
+                float v = a[l];
+                if constexpr (RANK >= 2) {
+                    // within 16 lanes by DPP: a shuffle is an LDS round trip, and a row of rank 8 takes 48 of them
+                    v = row_sum16(v);
+                    v += __shfl_xor(v, 16, 64);
+                    v += __shfl_xor(v, 32, 64);
+                } else {
+                    // (rank 1: the order of the normalisation pass, which forms the same projections)
+#pragma unroll
+                    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+                }
+                // antithetic pairs: the workgroup owns both members of a pair (2 x anti_rows rows); the second
+                // member is evaluated at -sigma, which is folded into its projections
+                if (lane == 0) {
+                    const float sv = (anti_rows && s >= anti_rows) ? -v : v;
+                    t[row * RANK + l] = k0 ? t[row * RANK + l] + sv : sv;
+                }
+            }
+        };
+      if constexpr (NR == 1) {
         for (int s = wave; s < S; s += 4) {
             const int64_t row = ml * S + s;
             const uint4* xr = (const uint4*)((const char*)X + (row * (int64_t)d_in + k0) * (BF16 ? 2 : 4));
@@ -146,27 +193,81 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
                     }
                 }
             }
+            finish(s, acc);
+        }
+      } else {
+        for (int s0 = wave; s0 < S; s0 += 4 * NR) {
+            float acc[NR][RANK];
 #pragma unroll
-            for (int l = 0; l < RANK; ++l) {
-                float v = acc[l];
-                if constexpr (RANK >= 2) {
-                    // within 16 lanes by DPP: a shuffle is an LDS round trip, and a row of rank 8 takes 48 of them
-                    v = row_sum16(v);
-                    v += __shfl_xor(v, 16, 64);
-                    v += __shfl_xor(v, 32, 64);
-                } else {
-                    // (rank 1: the order of the normalisation pass, which forms the same projections)
+            for (int j = 0; j < NR; ++j)
 #pragma unroll
-                    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-                }
-                // antithetic pairs: the workgroup owns both members of a pair (2 x anti_rows rows); the second
-                // member is evaluated at -sigma, which is folded into its projections
-                if (lane == 0) {
-                    const float sv = (anti_rows && s >= anti_rows) ? -v : v;
-                    t[row * RANK + l] = k0 ? t[row * RANK + l] + sv : sv;
+                for (int l = 0; l < RANK; ++l) acc[j][l] = 0.f;
+            for (int st = 0; st < steps; ++st) {
+                uint4 xc[NR][U];
+#pragma unroll
+                for (int j = 0; j < NR; ++j)
+#pragma unroll
+                    for (int u = 0; u < U; ++u) xc[j][u] = xn[j][u];
+                if (st + 1 < steps) load(s0, (st + 1) * 64 * U, xn);
+                else if (s0 + 4 * NR < S) load(s0 + 4 * NR, 0, xn);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int ch = (st * U + u) * 64 + lane;
+                    if (ch >= chunks) break;
+                    if constexpr (TRANSPOSED) {
+                        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+                        for (int l = 0; l < RANK; ++l) {
+                            const uint4 q = *(const uint4*)((const uint16_t*)smem + (int64_t)l * kn + (int64_t)ch * 8);
+                            const uint32_t bw[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+                            for (int j = 0; j < NR; ++j) {
+                                const uint32_t xw[4] = {xc[j][u].x, xc[j][u].y, xc[j][u].z, xc[j][u].w};
+#pragma unroll
+                                for (int e = 0; e < 4; ++e)
+                                    acc[j][l] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, xw[e]), __builtin_bit_cast(bf16x2, bw[e]), acc[j][l], false);
+                            }
+                        }
+                    } else {
+                        float x[NR][EPC];
+#pragma unroll
+                        for (int j = 0; j < NR; ++j) {
+                            const uint32_t w[4] = {xc[j][u].x, xc[j][u].y, xc[j][u].z, xc[j][u].w};
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                if constexpr (BF16) {
+                                    x[j][2 * e] = __uint_as_float(w[e] << 16);
+                                    x[j][2 * e + 1] = __uint_as_float(w[e] & 0xFFFF0000u);
+                                } else {
+                                    x[j][e] = __uint_as_float(w[e]);
+                                }
+                            }
+                        }
+                        // B_i[k][l] for the chunk's k range: EPC*RANK consecutive elements = RANK 16-byte reads
+                        const uint4* bp = (const uint4*)smem + (int64_t)ch * RANK;
+#pragma unroll
+                        for (int v = 0; v < RANK; ++v) {
+                            const uint4 q = bp[v];
+                            const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+                            // the 16 bytes hold flat entries v*EPC .. of the chunk: entry f belongs to column f / RANK, rank term f % RANK
+#pragma unroll
+                            for (int e = 0; e < EPC; ++e) {
+                                const int f = v * EPC + e;
+                                float bv;
+                                if constexpr (BF16) bv = (e & 1) ? __uint_as_float(w[e >> 1] & 0xFFFF0000u) : __uint_as_float(w[e >> 1] << 16);
+                                else bv = __uint_as_float(w[e]);
+#pragma unroll
+                                for (int j = 0; j < NR; ++j) acc[j][f % RANK] = fmaf(x[j][f / RANK], bv, acc[j][f % RANK]);
+                            }
+                        }
+                    }
                 }
             }
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+                if (s0 + 4 * j < S) finish(s0 + 4 * j, acc[j]);
         }
+      }
     }
 }
 
@@ -226,8 +327,8 @@ __global__ __launch_bounds__(256) void project_row_kernel(StreamKey kb, uint32_t
 // One row per member (NR = 1) or a pair of them (NR = 2, antithetic: the second at -sigma), rank >= 2.  As above nothing is
 // shared, so B_i does not go through LDS: a thread expands a 16-byte piece of the flat vector -- EPP consecutive entries, a few
 // columns times the rank, or part of one column -- and multiplies it with the matching x at once, all 256 threads; the LDS form
-// left the row to one wave of four.  Vector-ALU bound (the generator).  Measured at 1024 members x 8192 x rank 4 (bf16): 64 us
-// in the LDS form.
+// left the row to one wave of four.  Vector-ALU bound (the generator).  Measured at 1024 members x 8192 x rank 4 (bf16): 55 us,
+// 64 in the LDS form.
 template <bool BF16, int RANK, int NR>
 __global__ __launch_bounds__(256) void project_rows_rank_kernel(StreamKey kb, uint32_t member_begin, int d_in, const void* __restrict__ X,
                                                                 float* __restrict__ t, void* __restrict__ B_cache)
@@ -410,9 +511,18 @@ static egg_status launch_project_t(eggroll_ctx* c, const StreamKey& kb, const eg
 #undef EGG_ROWS
         return check_hip(c, hipGetLastError(), "project launch");
     }
+    // (rank 8 and 16) rows of a wave at once: four, or two, where the repeats this makes are at most an eighth of the rows (with more
+    // the loop over single rows is level or faster: 5, 6, 9, 17 and 33 rows by 1 to 3 %)
+    const int S = s.rows_per_member;
+    auto fits = [&](int k) { return (int64_t)(S + 4 * k - 1) / (4 * k) * (4 * k) * 8 <= (int64_t)S * 9; };
+    const int nr = fits(4) ? 4 : fits(2) ? 2 : 1;
 #define EGG_LAUNCH_PROJECT(R)                                                                                        \
     {                                                                                                                \
-        auto kern = project_kernel<BF16, R>;                                                                         \
+        auto kern = project_kernel<BF16, R, 1>;                                                                      \
+        if constexpr (R >= 8) {                                                                                      \
+            if (nr == 4) kern = project_kernel<BF16, R, 4>;                                                          \
+            if (nr == 2) kern = project_kernel<BF16, R, 2>;                                                          \
+        }                                                                                                            \
         if (lds > 48 * 1024) {                                                                                       \
             egg_status st = ensure_dynamic_lds(c, (const void*)kern, (size_t)lds, "project smem attr"); \
             if (st != EGG_OK) return st;                                                                             \

@@ -224,7 +224,8 @@ __global__ __launch_bounds__(256) void pack_r1_kernel(const void* __restrict__ s
 //            finished 16-byte chunks, which are neighbours in the panel;
 //   rank >= 2: a thread owns one chunk, EPC consecutive kappa = i r + l of one column: EPC / 2 blocks.
 // The blocks of a thread are independent chains.  Vector-ALU bound: about 87 issue slots per block and the conversion.
-// Measured at 16384 members x (8192 + 2048) x rank 4 (bf16): noise kernel 2 x 640 us + pack pass 2 x 240 us before.
+// Measured at 16384 members x (8192 + 2048) x rank 4 (bf16): 926 us (744 are the generator's issue slots); noise kernel
+// 2 x 640 us + pack pass 2 x 240 us before.
 struct GenPackJob {
     StreamKey key;
     FastDiv div;          // work items per K group: d / 2 at rank 1, d otherwise
