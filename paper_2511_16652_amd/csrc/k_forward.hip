@@ -294,9 +294,13 @@ struct FwdRowEpi {
     // groups whose side data is in flight while as many are finished; with REGEN their blocks are independent chains
     static constexpr int PARKED = (REGEN || RANK <= 2) ? 4 : (RANK == 4 ? 2 : 1);
     static constexpr int ZW = REGEN ? 1 : (BF16 ? 2 * RANK : 4 * RANK);  // 32-bit words of the 4 rows' factors
+    // a bf16 residual travels with the side data while registers allow: read at the store, its latency stood behind every group
+    // (512 -> 1024, 3236 rows in antithetic pairs, rank 1: the layer 26.3 us then, 22.3 now; 2048 -> 8192, 512 x 3 rows, rank 4: 99.8 / 94.2)
+    static constexpr bool RESID_AHEAD = BF16 && (REGEN || RANK <= 4);
     struct Side {
         float t[RANK];
         uint32_t z[ZW];
+        uint2 r;
     };
     const Args a;
     __device__ __forceinline__ FwdRowEpi(const Args& a_) : a(a_) {}
@@ -304,6 +308,7 @@ struct FwdRowEpi {
     __device__ __forceinline__ void extra(typename MT::acc_t&, int, int, int, int) const {}
     __device__ __forceinline__ void side(int m, int n, Side& s) const
     {
+        if (RESID_AHEAD && a.resid && a.y_bf16) s.r = *(const uint2*)((const uint16_t*)a.resid + (int64_t)n * a.d_out + m);
         if (a.c == 0.f) return;  // unperturbed: there are no projections (t is NULL)
 #pragma unroll
         for (int l = 0; l < RANK; ++l) s.t[l] = a.t[(int64_t)n * RANK + l];
@@ -395,10 +400,11 @@ struct FwdRowEpi {
                 for (int e = 0; e < 4; ++e) y[e] = 0.5f * y[e] * (1.0f + erff(y[e] * 0.70710678118654752f));
         }
         if (!valid) return;
-        // each output element is read here (residual) and written exactly once, so Y may be the residual buffer itself
+        // each output element is read (residual) and then written by one lane, so Y may be the residual buffer itself (what the lanes
+        // of clamped rows read of it is not used)
         if (a.y_bf16) {
             if (a.resid) {
-                const uint2 rv = *(const uint2*)((const uint16_t*)a.resid + at);
+                const uint2 rv = RESID_AHEAD ? s.r : *(const uint2*)((const uint16_t*)a.resid + at);
                 y[0] += bf16_lo(rv.x); y[1] += bf16_hi(rv.x);
                 y[2] += bf16_lo(rv.y); y[3] += bf16_hi(rv.y);
             }
