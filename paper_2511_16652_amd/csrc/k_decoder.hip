@@ -238,61 +238,69 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void attention_kernel(const uint16
         mrun = -INFINITY;
         lrun = 0.f;
     };
-    // key blocks kb0 .. kb1 - 1 (their first one in LDS is block kt) for query block qb
-    auto attend = [&](const u32x4(&q)[HD / 16], int qb, int kb0, int kb1, int kt) __attribute__((always_inline)) {
+    // One key block for query block qb (at: its place in LDS).  DIAG: the block that the causal edge crosses, kb == qb.
+    // The floating-point operations are written out, none is left to the compiler's contraction, and both widths of the kernel and
+    // all of its loops run this text: a member's bits are the same whatever else is in the call.
+    auto block = [&](auto diag, const u32x4(&q)[HD / 16], int qb, int kb, int at) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
+        constexpr bool DIAG = decltype(diag)::value;
         const int qrow = qb * 32 + n;
-        for (int kb = kb0; kb < kb1; ++kb) {
-            f32x16 sc;
+        f32x16 sc;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) sc[e] = 0.f;
-            const int at = (kb - kt) * 32 * C::ROW;
+        for (int e = 0; e < 16; ++e) sc[e] = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < HD / 16; ++ks) {
-                const u32x4 a = *(const u32x4*)(kp + at + ((kx ^ (2 * ks)) << 4));
-                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, q[ks]), sc, 0, 0, 0);
-            }
-            // asked for here the V fragments arrive under the softmax (at head_dim 128 the registers are taken)
-            u32x4 va[EARLY_V ? 2 : 1][EARLY_V ? HD / 32 : 1];
-            if constexpr (EARLY_V) {
+        for (int ks = 0; ks < HD / 16; ++ks) {
+            const u32x4 a = *(const u32x4*)(kp + at + ((kx ^ (2 * ks)) << 4));
+            sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, q[ks]), sc, 0, 0, 0);
+        }
+        // asked for here the V fragments arrive under the softmax (at head_dim 128 the registers are taken)
+        u32x4 va[EARLY_V ? 2 : 1][EARLY_V ? HD / 32 : 1];
+        if constexpr (EARLY_V) {
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < 2; ++t)
 #pragma unroll
-                    for (int mb = 0; mb < HD / 32; ++mb) va[t][mb] = read_v(at, t, mb);
-            }
-            float p[16];
-            float mx = -INFINITY;
+                for (int mb = 0; mb < HD / 32; ++mb) va[t][mb] = read_v(at, t, mb);
+        }
+        float p[16];
+        float mx = -INFINITY;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int key = kb * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
-                p[i] = (kb == qb && key > qrow) ? -INFINITY : sc[i] * scale_log2;
-                mx = fmaxf(mx, p[i]);
-            }
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-            const float mnew = fmaxf(mrun, mx);  // finite: key 0 of the member is visible to every query
-            const float alpha = __builtin_amdgcn_exp2f(mrun - mnew);
-            float lsum = 0.f;
+        for (int i = 0; i < 16; ++i) {
+            const int key = kb * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
+            p[i] = (DIAG && key > qrow) ? -INFINITY : sc[i] * scale_log2;
+            mx = fmaxf(mx, p[i]);
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float mnew = fmaxf(mrun, mx);  // finite: key 0 of the member is visible to every query
+        const float alpha = __builtin_amdgcn_exp2f(mrun - mnew);
+        float lsum = 0.f;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                p[i] = __builtin_amdgcn_exp2f(p[i] - mnew);
-                lsum += p[i];
-            }
-            lrun = lrun * alpha + lsum;
-            mrun = mnew;
+        for (int i = 0; i < 16; ++i) {
+            // whole blocks: one rounding less; where scores are masked their scaled value is what the mask replaced
+            p[i] = __builtin_amdgcn_exp2f(DIAG ? p[i] - mnew : fmaf(sc[i], scale_log2, -mnew));
+            lsum += p[i];
+        }
+        lrun = fmaf(lrun, alpha, lsum);
+        mrun = mnew;
 #pragma unroll
-            for (int mb = 0; mb < HD / 32; ++mb)
+        for (int mb = 0; mb < HD / 32; ++mb)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) oacc[mb][e] *= alpha;
+            for (int e = 0; e < 16; ++e) oacc[mb][e] *= alpha;
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const u32x4 pb = {pack_bf16x2(p[8 * t], p[8 * t + 1]), pack_bf16x2(p[8 * t + 2], p[8 * t + 3]),
-                                  pack_bf16x2(p[8 * t + 4], p[8 * t + 5]), pack_bf16x2(p[8 * t + 6], p[8 * t + 7])};
+        for (int t = 0; t < 2; ++t) {
+            const u32x4 pb = {pack_bf16x2(p[8 * t], p[8 * t + 1]), pack_bf16x2(p[8 * t + 2], p[8 * t + 3]),
+                              pack_bf16x2(p[8 * t + 4], p[8 * t + 5]), pack_bf16x2(p[8 * t + 6], p[8 * t + 7])};
 #pragma unroll
-                for (int mb = 0; mb < HD / 32; ++mb) {
-                    const u32x4 a = EARLY_V ? va[EARLY_V ? t : 0][EARLY_V ? mb : 0] : read_v(at, t, mb);
-                    oacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, pb), oacc[mb], 0, 0, 0);
-                }
+            for (int mb = 0; mb < HD / 32; ++mb) {
+                const u32x4 a = EARLY_V ? va[EARLY_V ? t : 0][EARLY_V ? mb : 0] : read_v(at, t, mb);
+                oacc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, pb), oacc[mb], 0, 0, 0);
             }
         }
+    };
+    // key blocks kb0 .. kb1 - 1 (their first one in LDS is block kt) for query block qb >= kb1 - 1
+    auto attend = [&](const u32x4(&q)[HD / 16], int qb, int kb0, int kb1, int kt) __attribute__((always_inline)) {
+        const int whole = min(kb1, qb);
+        for (int kb = kb0; kb < whole; ++kb) block(std::false_type{}, q, qb, kb, (kb - kt) * 32 * C::ROW);
+        if (kb1 > qb) block(std::true_type{}, q, qb, qb, (qb - kt) * 32 * C::ROW);
     };
     auto finish = [&](int qb) __attribute__((always_inline)) {
         const int qrow = qb * 32 + n;

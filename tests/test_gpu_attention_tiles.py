@@ -58,3 +58,29 @@ def test_an_infinite_value_stays_where_it_is_visible(ctx):
     keep = torch.ones_like(O, dtype=torch.bool)
     keep[64:S, 3] = False  # the key block of the last token
     assert ((O.double() - ref).abs()[keep] <= 1e-2 * (ref.abs()[keep] + ref.square().mean().sqrt())).all()
+
+
+@pytest.mark.parametrize("hd", [32, 64, 128])
+@pytest.mark.parametrize("S", [128, 129, 161, 200, 223, 256])
+def test_members_do_not_depend_on_the_call(ctx, hd, S):
+    """A member's rows and projections are the same bits whatever else is in the call: few (member, head) pairs run in workgroups of
+    eight waves, more of them than compute units in workgroups of four.  The larger call is also held to the reference: it is the one
+    that brings ragged windows to the kernel of four waves."""
+    import torch
+    N, heads = 90, 4
+    g = torch.Generator("cuda").manual_seed(S + hd)
+    Q, K, V = (torch.randn((N * S, heads * hd), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    key = eb.make_key(3, 1, 4)
+
+    def run(first, n):
+        q, k, v = (t[first * S:(first + n) * S].contiguous() for t in (Q * 2, K, V))
+        o, t_next = torch.empty_like(q), torch.empty(n * S, device="cuda")
+        ctx.eggroll_causal_attention_project_bf16(key, first, n, S, heads, hd, q, k, v, o, t_next)
+        return o, t_next
+
+    O, t = run(0, N)
+    for first, n in ((0, 1), (41, 3), (N - 60, 60)):
+        o, tn = run(first, n)
+        assert torch.equal(o, O[first * S:(first + n) * S]) and torch.equal(tn, t[first * S:(first + n) * S]), (first, n)
+    ref = reference(Q * 2, K, V, N, S, heads)
+    assert ((O.double() - ref).abs() <= 1e-2 * (ref.abs() + ref.square().mean().sqrt())).all()
