@@ -72,6 +72,24 @@ __device__ __forceinline__ float row_sum16(float x)
     return x;
 }
 
+// sum over the wave, left in every lane: lanes 32 apart first, then 16, 8, 4, 2, 1 -- the order, and so the bits, of a butterfly of
+// shuffles, each of which is an LDS round trip (a row of rank 8 takes 48 of them); the swaps and DPP forms stay in the vector ALU
+__device__ __forceinline__ float wave_sum(float x)
+{
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+#define EGG_DPP_ADD(CTRL) x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+    EGG_DPP_ADD(0x128)  // row_ror:8
+    EGG_DPP_ADD(0x124)  // row_ror:4 (lanes 8 apart agree: the lane 4 away in either direction)
+    EGG_DPP_ADD(0x4E)   // quad_perm [2, 3, 0, 1]
+    EGG_DPP_ADD(0xB1)   // quad_perm [1, 0, 3, 2]
+#undef EGG_DPP_ADD
+    return x;
+}
+
 egg_status fail(eggroll_ctx* c, egg_status s, const char* fmt, ...);
 egg_status check_hip(eggroll_ctx* c, hipError_t e, const char* what);
 egg_status reserve(eggroll_ctx* c, eggroll_ctx::Buf& b, size_t bytes);

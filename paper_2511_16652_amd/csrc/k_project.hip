@@ -139,17 +139,7 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
             const int64_t row = ml * S + s;
 #pragma unroll
             for (int l = 0; l < RANK; ++l) {
-                float v = a[l];
-                if constexpr (RANK >= 2) {
-                    // within 16 lanes by DPP: a shuffle is an LDS round trip, and a row of rank 8 takes 48 of them
-                    v = row_sum16(v);
-                    v += __shfl_xor(v, 16, 64);
-                    v += __shfl_xor(v, 32, 64);
-                } else {
-                    // (rank 1: the order of the normalisation pass, which forms the same projections)
-#pragma unroll
-                    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-                }
+                const float v = wave_sum(a[l]);  // (at rank 1 the order of the normalisation pass, which forms the same projections)
                 // antithetic pairs: the workgroup owns both members of a pair (2 x anti_rows rows); the second
                 // member is evaluated at -sigma, which is folded into its projections
                 if (lane == 0) {

@@ -41,3 +41,34 @@ def test_rows_at_once(dtype, S, d_in, rank, anti):
     assert err.max() <= 2e-5
     torch.cuda.synchronize()
     ctx.close()
+
+
+@pytest.mark.parametrize("rank", [1, 2, 4, 8, 16])
+@pytest.mark.parametrize("S", [2, 8, 16])
+def test_the_order_over_lanes(rank, S):
+    """A row's products are added over the 64 lanes as a butterfly does it: lanes 32 apart first, then 16, 8, 4, 2, 1 (fixed, so that a
+    layer's bits stay what they were when the pass is changed).  One column per lane is not zero, so the order of a lane's own sum does
+    not matter; c = 1 and W = 0, so Y is a chain of fused multiply-adds of t and A, emulated with 64 bits of mantissa.  Exact."""
+    import numpy as np
+    import torch
+    N, d_in, d_out = 3, 256, 8
+    ctx = eb.Context(0)
+    key = eb.make_key(21, 22, 23)
+    A, B = (torch.empty((N, d, rank), device="cuda") for d in (d_out, d_in))
+    ctx.eggroll_noise_gen(key, eb.make_shape(0, N, 1, d_out, d_in, rank), eb.EGG_F32, eb.EGG_NORMAL, 0, A, B)
+    X = torch.zeros((N * S, d_in), device="cuda")
+    X[:, ::4] = torch.randn((N * S, 64), generator=torch.Generator("cuda").manual_seed(rank), device="cuda")
+    W, Y = torch.zeros((d_out, d_in), device="cuda"), torch.empty((N * S, d_out), device="cuda")
+    sigma = float(np.sqrt(np.float32(rank)))
+    ctx.eggroll_perturbed_forward(key, eb.make_shape(0, N, S, d_out, d_in, rank), sigma, eb.EGG_ACT_NONE, W, X, Y)
+    a, b, x = A.cpu().numpy(), B.cpu().numpy()[:, ::4], X.cpu().numpy().reshape(N, S, d_in)[:, :, ::4]
+    t = x[:, :, :, None] * b[:, None]            # fp32 products [member][row][lane][rank]
+    while t.shape[2] > 1:
+        half = t.shape[2] // 2
+        t = t[:, :, :half] + t[:, :, half:]
+    want = np.zeros((N, S, d_out), np.float32)
+    for l in range(rank):
+        want = (t[:, :, 0, l, None].astype(np.longdouble) * a[:, None, :, l].astype(np.longdouble) + want).astype(np.float32)
+    assert (Y.cpu().numpy().reshape(N, S, d_out) == want).all()
+    torch.cuda.synchronize()
+    ctx.close()
