@@ -49,6 +49,7 @@ struct MmaBf16Blk16 {
     static constexpr int MFMA_PER_MMA = 1;
     static constexpr int BLK = 16;
     typedef f32x4 acc_t;
+    static __device__ __forceinline__ u32x4 arrange(const u32x4& x) { return x; }
     static __device__ __forceinline__ void mma(const u32x4& a, const u32x4& b, acc_t& c)
     {
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
@@ -58,6 +59,7 @@ struct MmaF16Blk16 {
     static constexpr int MFMA_PER_MMA = 1;
     static constexpr int BLK = 16;
     typedef f32x4 acc_t;
+    static __device__ __forceinline__ u32x4 arrange(const u32x4& x) { return x; }
     static __device__ __forceinline__ void mma(const u32x4& a, const u32x4& b, acc_t& c)
     {
         c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
@@ -105,6 +107,29 @@ __device__ __forceinline__ void static_for(F&& f)
         static_for<FIRST + 1, LAST>(f);
     }
 }
+
+// The same products in the same order from 16x16x4 blocks.  An fp32 MFMA is a chain of fused multiply-adds over its k-values, each
+// rounded, so an output is the same bits from either shape as long as its k-values come in the same order: MmaF32 takes those of 8 in
+// the order 0, 4, 1, 5, 2, 6, 3, 7 (lane halves, then elements).  A k-step is 16 of them, a chunk for each of the four lane groups;
+// arrange() brings them into place: operand e of mma holds, in lane groups 0 .. 3, k-values 8 (e >> 1) + 2 (e & 1) + {0, 4, 1, 5}.
+struct MmaF32Blk16 {
+    static constexpr int MFMA_PER_MMA = 4;
+    static constexpr int BLK = 16;
+    typedef f32x4 acc_t;
+    static __device__ __forceinline__ u32x4 arrange(const u32x4& x)
+    {
+        // (swap: the upper lanes of the first operand for the lower lanes of the second)
+        const auto p = __builtin_amdgcn_permlane32_swap(x[0], x[1], false, false), q = __builtin_amdgcn_permlane32_swap(x[2], x[3], false, false);
+        return u32x4{p[0], q[0], p[1], q[1]};
+    }
+    static __device__ __forceinline__ void mma(const u32x4& a, const u32x4& b, acc_t& c)
+    {
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[0]), __uint_as_float(b[0]), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[1]), __uint_as_float(b[1]), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[2]), __uint_as_float(b[2]), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[3]), __uint_as_float(b[3]), c, 0, 0, 0);
+    }
+};
 
 // Products with more than this many 256 x 256 tiles take them: up to it, four times as many tiles of 128 x 128 fit two workgroups
 // on each of 256 CUs at once; beyond, they need a second wave where one of the large tiles still does.  Measured between 128 and
@@ -742,6 +767,7 @@ constexpr int vm_lds_imm(int n) { return 0x0070 | (n & 15) | ((n >> 4) << 14); }
 // would take holds four stages, waited for by count.  What bounds it now is the rate at which one CU can load (32 KB per stage at
 // about 65 bytes/ns, the rate the chip reaches per CU with all of them loading): 128 x 128 stages take 0.57 us, 0.66 in the
 // two-stage loop.  Layers of 1024 x 2048 rows, 1024 -> .. (us, before / now): K = 256 16.8 / 15.7, 1024 24.3 / 22.9, 4096 51.3 / 49.2.
+// fp32 runs it on 32 x 32 tiles, several workgroups to a CU (k_forward.hip): there the MFMAs are the bound, 256 cycles a stage.
 // K-packed or row-major operands; epilogues as in the persistent kernel.
 template <class MT, int BM, int BN, int WM, int WN, bool KMAJOR, class Epi>
 __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P, Operand Q, int kchunks, int tiles_m, int tiles_n,
@@ -825,9 +851,13 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P,
         if (LOAD4) issue((KT_) + DEPTH);                                                                       \
         if (NEXT) EGG_DEEP_READ((SET) ^ 1, (KT_) + 1)                                                          \
         _Pragma("unroll") for (int ks = 0; ks < KSTEPS; ++ks)                                                  \
+        {                                                                                                      \
+            _Pragma("unroll") for (int i = 0; i < MB; ++i) fa[SET][ks][i] = MT::arrange(fa[SET][ks][i]);       \
+            _Pragma("unroll") for (int j = 0; j < NB; ++j) fb[SET][ks][j] = MT::arrange(fb[SET][ks][j]);       \
             _Pragma("unroll") for (int i = 0; i < MB; ++i)                                                     \
                 _Pragma("unroll") for (int j = 0; j < NB; ++j) MT::mma(fa[SET][ks][i], fb[SET][ks][j], acc[i][j]); \
-        _Pragma("unroll") for (int r_ = 0; r_ < KSTEPS * MB * NB; ++r_)                                        \
+        }                                                                                                      \
+        _Pragma("unroll") for (int r_ = 0; r_ < KSTEPS * MB * NB * MT::MFMA_PER_MMA; ++r_)                     \
         {                                                                                                      \
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                 \
             if ((NEXT) && r_ < KSTEPS * (MB + NB)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);          \

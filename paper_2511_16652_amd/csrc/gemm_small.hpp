@@ -4,7 +4,8 @@
 // reads its MFMA fragments straight from memory into registers (no LDS stages and no barrier in the loop: a wave alone on its
 // SIMD would spend them waiting), and the four partial tiles are added through LDS, from which every thread finishes
 // groups of 4 consecutive m of one n.  What bounds these calls is latency -- the length of a wave's chain of loads and MFMAs --
-// and the number of workgroups: a 256 x 256 x 64 layer is 16 workgroups of a quarter of K here, 2 of all of K at 128 x 128.
+// and the number of workgroups: a 256 x 256 x 4096 update is 64 workgroups of a quarter of K here, 4 of all of K at 128 x 128.
+// Updates only: their K is the population, so that a call's sums are those of its members anyway; a forward layer keeps K whole.
 #pragma once
 #include "gemm_core.hpp"
 
@@ -12,9 +13,8 @@ namespace egg {
 
 // Tile of the small kernel for an M x N product, 0 where the tiles of gemm_core.hpp do better.  Measured over 256 .. 4096 rows and
 // columns and K of 64 .. 4096 (us, this kernel against theirs; the lines lie where the last listed shape still gains):
-//   32: up to 512 tiles   fp32 forward 256 x 64 x 256: 14 / 31, 1024 x 512 x 1024: 29 / 80; update 256 x 256 x 4096: 26 / 56
-//   64: up to 512 tiles   update 2048 x 1024 x 4096: 57 / 68 (2048 x 2048: 86 / 78); fp32 forward 2048 x 1024 x 1024: 67 / 81
-//                         (2048 x 2048: 118 / 83)
+//   32: up to 512 tiles   256 x 256 x 4096: 26 / 56
+//   64: up to 512 tiles   2048 x 1024 x 4096: 57 / 68 (2048 x 2048: 86 / 78)
 inline int small_tile(int64_t M, int64_t N)
 {
     if (((M + 31) / 32) * ((N + 31) / 32) <= 512) return 32;
@@ -23,7 +23,7 @@ inline int small_tile(int64_t M, int64_t N)
 
 // Epi requirements: struct Args; __device__ Epi(const Args&); value_t; __device__ void apply4(int m, int n, const value_t (&v)[4]),
 // rows m .. m + 3 of column n, called once per in-range group (m < P.rows, n < Q.rows; P.rows may end inside the group).
-template <class MT, bool KMAJOR, int T, class Epi>
+template <class MT, int T, class Epi>
 __global__ __launch_bounds__(256, 2) void gemm_small_kernel(Operand P, Operand Q, int kchunks, int tiles_m, typename Epi::Args ea)
 {
     static_assert(MT::BLK == 32 && (T == 32 || T == 64), "32x32 MFMA blocks");

@@ -608,8 +608,8 @@ static egg_status launch_upd_small(eggroll_ctx* c, const char* name, const Opera
 {
     const int tm = (P.rows + tile - 1) / tile, tn = (Q.rows + tile - 1) / tile;
     KernelScope ks(c, name);
-    if (tile == 32) hipLaunchKernelGGL((gemm_small_kernel<MT, true, 32, UpdSmallEpi>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
-    else hipLaunchKernelGGL((gemm_small_kernel<MT, true, 64, UpdSmallEpi>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
+    if (tile == 32) hipLaunchKernelGGL((gemm_small_kernel<MT, 32, UpdSmallEpi>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
+    else hipLaunchKernelGGL((gemm_small_kernel<MT, 64, UpdSmallEpi>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
     return check_hip(c, hipGetLastError(), name);
 }
 

@@ -113,3 +113,32 @@ def test_bf16_rows_do_not_depend_on_the_call(ctx, d_out, d_in, S, rank, members,
     for n in members[:-1]:
         for first in (0, N - n, (N - n) // 2):
             assert torch.equal(run(first, n), whole[first * S:(first + n) * S]), (first, n)
+
+
+@pytest.mark.parametrize("S,rank,anti,members", [(1, 1, 0, (3, 500, 1000, 2048)), (1, 1, 1, (2, 500, 1000, 2048)), (1, 4, 0, (1, 300, 1001, 2000)),
+                                                 (3, 2, 0, (1, 100, 333, 500)), (16, 16, 0, (1, 20, 61, 90))])
+@pytest.mark.parametrize("sigma,form", [(0.0, "plain"), (0.5, "plain"), (0.5, "gelu"), (0.5, "residual"), (0.5, "both")])
+def test_f32_rows_do_not_depend_on_the_call(ctx, S, rank, anti, members, sigma, form):
+    """fp32 members are the same bits in any call, as the bf16 ones: 32 x 32 tiles (up to 1024 of them), 128 x 64 tiles, 128 x 128 tiles
+    (the three larger member counts of each shape, in this order)."""
+    import torch
+    d_out, d_in, N = 2044, 140, max(members)
+    g = torch.Generator("cuda").manual_seed(S)
+    W = torch.randn((d_out, d_in), generator=g, device="cuda") * d_in ** -0.5
+    X, R = (torch.randn((N * S, d), generator=g, device="cuda") for d in (d_in, d_out))
+    key = eb.make_key(1, 2, 3)
+
+    def run(first, n):
+        x, r = X[first * S:(first + n) * S].contiguous(), R[first * S:(first + n) * S].contiguous()
+        y = torch.empty((n * S, d_out), device="cuda")
+        args = (key, eb.make_shape(first, n, S, d_out, d_in, rank, anti), sigma, eb.EGG_ACT_GELU if form in ("gelu", "both") else eb.EGG_ACT_NONE, W, x)
+        if form in ("residual", "both"):
+            ctx.eggroll_perturbed_forward_add(*args, r, y)
+        else:
+            ctx.eggroll_perturbed_forward(*args, y)
+        return y
+
+    whole = run(0, N)
+    for n in members[:-1]:
+        for first in (0, N - n, (N - n) // 4 * 2):
+            assert torch.equal(run(first, n), whole[first * S:(first + n) * S]), (first, n)
