@@ -38,6 +38,36 @@ __device__ __forceinline__ void gelu_bf16_grade4(float (&y)[4])
     for (int e = 0; e < 4; ++e) y[e] *= fmaf(xc[e], p[e], 0.5f);
 }
 
+// The parts of the N products c t that a fold's K-slots hold: the nearest bf16 values or what they leave, which together are c t to about
+// 2^-17.  (The correction is at most of the size of the layer's output, whose own rounding to bf16 is 2^-9; over the ranks and row
+// counts of the layer tests the error against 64 bits is the same as with the correction in fp32.)
+// A finite c t that would round to infinity takes the largest bf16 value, and an infinite one leaves nothing (inf - inf is NaN): the
+// products with the factors are then those of c t itself.  The operations are written out, none is left to contraction: a member's
+// bits are the same in every kernel that folds.
+template <int N>
+__device__ __forceinline__ void bf16_parts(float c, const float (&t)[N], bool rest, float (&out)[N])
+{
+#pragma clang fp contract(off)
+    float top = 0.f;
+#pragma unroll
+    for (int l = 0; l < N; ++l) {
+        const float x = c * t[l], hi = round_bf16(x);
+        out[l] = rest ? fmaf(c, t[l], -hi) : hi;
+        top = fmaxf(top, fabsf(x));
+    }
+    const float most = __uint_as_float(0x7F7F0000u);
+    if (__any(top > most)) {
+#pragma unroll
+        for (int l = 0; l < N; ++l) {
+            const float x = c * t[l];
+            if (fabsf(x) > most) {
+                const float hi = __builtin_isinf(x) ? x : __builtin_copysignf(most, x);
+                out[l] = !rest ? hi : (__builtin_isinf(x) ? 0.f : x - hi);
+            }
+        }
+    }
+}
+
 // One bf16 layer whose correction is folded into the accumulators as a few more MFMAs (or is off: c = 0), for every shape
 // that the parked form of k_forward.hip does not take: S not a multiple of 64, rank 16, ragged K, few tiles.
 struct FoldLayer {

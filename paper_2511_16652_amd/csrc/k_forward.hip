@@ -170,14 +170,9 @@ struct LeanEpi {
         for (int j = 0; j < NB; ++j) {
             uint32_t tb[4] = {0u, 0u, 0u, 0u};
             float ct[RANK];
+            bf16_parts(a.c, pf_t[j], half == 1, ct);
 #pragma unroll
-            for (int l = 0; l < RANK; ++l) {
-                const float v = a.c * pf_t[j][l];
-                const float hi = round_bf16(v);
-                ct[l] = half == 0 ? hi : (half == 1 ? v - hi : 0.f);
-            }
-#pragma unroll
-            for (int l = 0; l < RANK; l += 2) tb[l >> 1] = pack_bf16x2(ct[l], l + 1 < RANK ? ct[l + 1] : 0.f);
+            for (int l = 0; l < RANK; l += 2) tb[l >> 1] = half < 2 ? pack_bf16x2(ct[l], l + 1 < RANK ? ct[l + 1] : 0.f) : 0u;
             const u32x4 bfrag = {tb[0], tb[1], tb[2], tb[3]};
 #pragma unroll
             for (int i = 0; i < MB; ++i) {

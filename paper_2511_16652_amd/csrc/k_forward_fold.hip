@@ -99,15 +99,12 @@ struct FoldEpi {
             const int g = lane >> 4;
             const bool lo_half = (AW == 4 && a.rank == 16) ? (g >> 1) != 0 : (g & 1) != 0;
             uint32_t tb[4] = {0u, 0u, 0u, 0u};
+            float v[2 * AW];
+            bf16_parts(a.c, f.tv, lo_half, v);
 #pragma unroll
             for (int w = 0; w < AW; ++w) {
-                float v[2];
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const float x = a.c * f.tv[2 * w + e], hi = round_bf16(x);
-                    v[e] = f.own ? (lo_half ? x - hi : hi) : 0.f;
-                }
-                tb[w] = pack_bf16x2(v[0], (AW == 1 && a.rank == 1) ? 0.f : v[1]);
+                const uint32_t p = pack_bf16x2(v[2 * w], (AW == 1 && a.rank == 1) ? 0.f : v[2 * w + 1]);
+                tb[w] = f.own ? p : 0u;
             }
             const u32x4 bfrag = {tb[0], tb[1], tb[2], tb[3]};
 #pragma unroll

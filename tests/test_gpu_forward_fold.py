@@ -71,3 +71,63 @@ def test_folded_layer(ctx, case, sigma):
     tol = 2.0 ** -8 * ref.abs() + 1e-4 * (1 + corr.abs().amax(1, keepdim=True)) + (2e-4 if gelu else 0)
     err = (Y.double() - ref).abs()
     assert torch.isfinite(Y.float()).all() and (err <= tol).all(), (err - tol).max()
+
+
+@pytest.mark.parametrize("d_out,d_in,N,S", [(64, 64, 3, 15), (64, 64, 2, 100), (260, 72, 9, 31), (1028, 64, 37, 16), (4096, 64, 130, 64), (4096, 72, 84, 100)])
+@pytest.mark.parametrize("rank", [1, 2, 4, 8, 16])
+def test_an_infinite_projection(ctx, d_out, d_in, N, S, rank):
+    """Two rows whose projections overflow (their products with W do not: the columns are zero there): their outputs are infinite with the
+    sign of the correction, NaN only where infinities of both signs meet; the other rows, of the same blocks too, are untouched."""
+    import torch
+    R, sigma = N * S, 1e-30  # a projection that stays finite contributes next to nothing
+    g = torch.Generator("cuda").manual_seed(rank)
+    W = (torch.randn((d_out, d_in), generator=g, device="cuda") * d_in ** -0.5).to(torch.bfloat16)
+    X = torch.randn((R, d_in), generator=g, device="cuda").to(torch.bfloat16)
+    W[:, :32] = 0
+    rows = [S + 1, R - 2]
+    key = eb.make_key(3, 2, 5)
+    A = torch.empty((N, d_out, rank), dtype=torch.bfloat16, device="cuda")
+    B = torch.empty((N, d_in, rank), dtype=torch.bfloat16, device="cuda")
+    ctx.eggroll_noise_gen(key, eb.make_shape(0, N, 1, d_out, d_in, rank), eb.EGG_BF16, eb.EGG_NORMAL, 0, A, B)
+    for q in rows:
+        b = B[q // S, :32].abs().float().sort(-1).values
+        at = int((b[:, -1] - (b[:, -2] if rank > 1 else 0)).argmax())  # one rank term stands out: it alone overflows
+        X[q, at] = 3.5e38 / b[at, -1].double()
+    Y = torch.empty((R, d_out), dtype=torch.bfloat16, device="cuda")
+    ctx.eggroll_perturbed_forward(key, eb.make_shape(0, N, S, d_out, d_in, rank), sigma, eb.EGG_ACT_NONE, W, X, Y)
+    plain = X.double() @ W.double().t().contiguous()
+    seen = 0
+    for q in rows:
+        t = (X[q].double()[:, None] * B[q // S].double()).sum(0)
+        t = torch.where(t.abs() >= 2.0 ** 128 - 2.0 ** 103, t.sign() * math.inf, t * (sigma / math.sqrt(rank)))  # as fp32 holds it
+        want = plain[q] + (A[q // S].double() * t).sum(-1)
+        seen += int(torch.isinf(want).sum())
+        assert torch.equal(torch.isnan(Y[q]), torch.isnan(want)) and torch.equal(torch.isposinf(Y[q]), torch.isposinf(want)) and torch.equal(
+            torch.isneginf(Y[q]), torch.isneginf(want))
+    assert seen
+    rest = torch.ones(R, dtype=torch.bool)
+    rest[rows] = False
+    assert ((Y.double() - plain).abs() <= 2.0 ** -8 * plain.abs() + 1e-5)[rest].all()
+
+
+@pytest.mark.parametrize("S", [15, 64, 100])
+def test_a_projection_beyond_bf16(ctx, S):
+    """c t between the largest bf16 value and the largest fp32 value (W = 0, rank 1): Y = c t A, not infinity."""
+    import torch
+    d_out, d_in, N, key = 260, 64, 4, eb.make_key(3, 2, 6)
+    A = torch.empty((N, d_out, 1), dtype=torch.bfloat16, device="cuda")
+    B = torch.empty((N, d_in, 1), dtype=torch.bfloat16, device="cuda")
+    ctx.eggroll_noise_gen(key, eb.make_shape(0, N, 1, d_out, d_in, 1), eb.EGG_BF16, eb.EGG_NORMAL, 0, A, B)
+    W, X = torch.zeros((d_out, d_in), dtype=torch.bfloat16, device="cuda"), torch.zeros((N * S, d_in), dtype=torch.bfloat16, device="cuda")
+    b, q, target = B[1].double().view(-1), S + 3, 3.399e38
+    at = int(b.abs().argmax())
+    X[q, at] = (target / b[at]).to(torch.bfloat16)
+    near = int((b.abs() - 0.5).abs().argmin())  # what is left of the target, to 2^-9 of 2^-9
+    X[q, near] = ((target - X[q, at].double() * b[at]) / b[near]).to(torch.bfloat16)
+    t = float((X[q].double() * b).sum())
+    assert 3.3953e38 < t < 3.4028e38
+    Y = torch.empty((N * S, d_out), dtype=torch.bfloat16, device="cuda")
+    ctx.eggroll_perturbed_forward(key, eb.make_shape(0, N, S, d_out, d_in, 1), 1.0, eb.EGG_ACT_NONE, W, X, Y)
+    want = t * A[1].double().view(-1)
+    small = want.abs() < 3.3e38
+    assert small.any() and ((Y[q].double() - want).abs() <= 2.0 ** -8 * want.abs())[small].all()

@@ -85,12 +85,13 @@ def test_small_update(ctx, dtype, d_out, d_in, N, rank, w):
 
 
 @pytest.mark.parametrize("d_out,d_in,S,rank,members", [
-    (256, 264, 64, 1, (1, 8, 64, 700)), (256, 328, 100, 4, (1, 8, 64, 500)), (512, 200, 16, 8, (3, 40, 300, 2500)), (256, 72, 31, 16, (2, 20, 200, 1600)),
+    (256, 264, 64, 1, (1, 8, 64, 700)), (256, 256, 64, 1, (1, 8, 64, 700)), (256, 128, 64, 4, (1, 8, 64, 600)), (256, 64, 128, 8, (1, 300)), (256, 328, 100, 4, (1, 8, 64, 500)), (512, 200, 16, 8, (3, 40, 300, 2500)), (256, 72, 31, 16, (2, 20, 200, 1600)),
     (384, 136, 1, 1, (2, 300, 4000, 30000)), (384, 136, 3, 4, (2, 100, 1300, 10000)), (256, 520, 14, 2, (2, 30, 300, 2500))])
-@pytest.mark.parametrize("sigma,form", [(0.0, "plain"), (0.5, "plain"), (0.5, "gelu"), (0.5, "residual")])
+@pytest.mark.parametrize("sigma,form", [(0.0, "plain"), (0.5, "plain"), (0.5, "gelu"), (0.5, "residual"), (0.5, "both")])
 def test_bf16_rows_do_not_depend_on_the_call(ctx, d_out, d_in, S, rank, members, sigma, form):
     """A member's outputs are the same bits in a call of one member and in one of thousands: every kernel runs the same chain of
-    MFMAs (16 x 16 blocks from memory, 128 x 128 tiles with two and four stages, 256 x 256 tiles)."""
+    MFMAs (16 x 16 blocks from memory, 128 x 128 tiles with two and four stages, 256 x 256 tiles, with
+    the correction's operands from memory or parked)."""
     import torch
     N = max(members)
     g = torch.Generator("cuda").manual_seed(S)
@@ -102,8 +103,8 @@ def test_bf16_rows_do_not_depend_on_the_call(ctx, d_out, d_in, S, rank, members,
     def run(first, n):
         x, r = X[first * S:(first + n) * S].contiguous(), R[first * S:(first + n) * S].contiguous()
         y = torch.empty((n * S, d_out), dtype=torch.bfloat16, device="cuda")
-        args = (key, eb.make_shape(first, n, S, d_out, d_in, rank), sigma, eb.EGG_ACT_GELU if form == "gelu" else eb.EGG_ACT_NONE, W, x)
-        if form == "residual":
+        args = (key, eb.make_shape(first, n, S, d_out, d_in, rank), sigma, eb.EGG_ACT_GELU if form in ("gelu", "both") else eb.EGG_ACT_NONE, W, x)
+        if form in ("residual", "both"):
             ctx.eggroll_perturbed_forward_add(*args, r, y)
         else:
             ctx.eggroll_perturbed_forward(*args, y)
