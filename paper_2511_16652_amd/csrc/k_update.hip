@@ -59,6 +59,15 @@ __global__ __launch_bounds__(1024) void fitness_norm_kernel(const float* __restr
     }
 }
 
+// x f as an entry of an fp16 panel, rounded once (v_fma_mixlo_f16; the statement keeps it from being turned into a product in fp32 and
+// a packed conversion, two roundings).  Rank 2, 4 and 8; the passes of rank 1 and 16 round the fp32 product.
+__device__ __forceinline__ _Float16 f16_product(float x, float f)
+{
+    _Float16 p = (_Float16)(x * f);
+    asm volatile("" : "+v"(p));
+    return p;
+}
+
 // out chunk (kg, col) at (kg*d + col)*16 bytes holds kappa = kg*EPC .. +EPC-1 of column `col`.
 template <bool BF16>
 __global__ __launch_bounds__(256) void pack_kernel(const void* __restrict__ src, const float* __restrict__ fitness,
@@ -109,12 +118,9 @@ __global__ __launch_bounds__(256) void pack_kernel(const void* __restrict__ src,
 #pragma unroll
             for (int h = 0; h < 4; ++h) {
                 h2 p;
-                // the product in fp32, then round to nearest even, as gen_pack_kernel has it (fused into one rounding, entries in
-                // a few thousand would differ from the regenerated panel's by an fp16 ulp); past the last member: +0
-                float lo = bf16_lo(w[h]) * fs[h], hi = bf16_hi(w[h]) * fs[h];
-                asm volatile("" : "+v"(lo), "+v"(hi));
-                p[0] = (_Float16)(in[h] ? lo : 0.f);
-                p[1] = (_Float16)(in[h] ? hi : 0.f);
+                const _Float16 zero = 0;  // past the last member: +0
+                p[0] = in[h] ? f16_product(bf16_lo(w[h]), fs[h]) : zero;
+                p[1] = in[h] ? f16_product(bf16_hi(w[h]), fs[h]) : zero;
                 o[h] = __builtin_bit_cast(uint32_t, p);
             }
             ((u32x4*)out)[gid] = o;
@@ -219,7 +225,7 @@ __global__ __launch_bounds__(256) void pack_r1_kernel(const void* __restrict__ s
 
 // Factors without caches: regenerated straight into the K-packed panels, A (with the fitness) and B in one launch; no
 // [member][d][rank] intermediate is written or re-read.  The (member, block) addressing and the roundings are those of every
-// other kernel: bf16 factors, the product with f_i / fnorm in fp32, then fp16; fp32 factors stay fp32.
+// other kernel: bf16 factors times f_i / fnorm as the pack pass rounds them to fp16; fp32 factors stay fp32.
 //   rank 1:  a thread owns one column pair of EPC consecutive members -- one Threefry block per member -- and writes the two
 //            finished 16-byte chunks, which are neighbours in the panel;
 //   rank >= 2: a thread owns one chunk, EPC consecutive kappa = i r + l of one column: EPC / 2 blocks.
@@ -344,7 +350,15 @@ __global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
                 z0 = bf16_lo(pk);
                 z1 = bf16_hi(pk);
             }
-            if (fit) {
+            if constexpr (BF16 && RANK < 16) {
+                if (fit) {
+                    h2 p;
+                    p[0] = f16_product(z0, fs[b]);
+                    p[1] = f16_product(z1, fs[b]);
+                    o[b] = __builtin_bit_cast(uint32_t, p);
+                    continue;
+                }
+            } else if (fit) {
                 z0 *= fs[b];
                 z1 *= fs[b];
             }

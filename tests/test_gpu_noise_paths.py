@@ -53,6 +53,35 @@ def test_generated_panels_equal_packed(ctx, dtype, rank, members):
     assert G.abs().max() > 0 and torch.equal(G, H)
 
 
+@pytest.mark.parametrize("rank", [1, 2, 4, 8, 16])
+@pytest.mark.parametrize("d_out", [4096, 4092])  # (rank 1: the block form and the general one)
+def test_panel_entries_are_rounded_as_stated(ctx, rank, d_out):
+    """B picks one (member, rank term) per column of G, so G is the A panel itself, times a power of two: the product of the bf16 factor
+    and the fp32 fitness rounded to fp16 once at rank 2, 4 and 8, after a rounding to fp32 at rank 1 and 16.  Exact."""
+    import numpy as np
+    import torch
+    N = 64 // rank
+    g = torch.Generator("cuda").manual_seed(rank)
+    A = torch.randn((N, d_out, rank), generator=g, device="cuda").to(torch.bfloat16)
+    B = torch.zeros((N, 64, rank), dtype=torch.bfloat16, device="cuda")
+    i, l = np.divmod(np.arange(64), rank)
+    B[i, np.arange(64), l] = 1.0
+    # fitness values for which some 8-bit factor's product rounds to another fp16 value by way of fp32 (one in 130)
+    draws = np.random.default_rng(rank).uniform(0.5, 1.0, 20000).astype(np.float32)
+    exact = draws[:, None].astype(np.float64) * np.arange(128, 256)
+    draws = draws[(exact.astype(np.float16) != exact.astype(np.float32).astype(np.float16)).any(1)]
+    f = torch.from_numpy(draws[:N]).cuda()
+    G = torch.empty((d_out, 64), device="cuda")
+    ctx.eggroll_update(eb.make_key(1, 1, 1), eb.make_shape(0, N, 1, d_out, 64, rank), eb.EGG_BF16, f, 1.0, 0, G, None, 0.0, A, B)
+    a, fit = A.float().cpu().numpy(), f.cpu().numpy()
+    norm = 2.0 ** np.ceil(np.log2(np.abs(fit).max()))
+    product = a[i, :, l].T.astype(np.float64) * (fit / norm).astype(np.float64)[i]
+    want = (product if rank in (2, 4, 8) else product.astype(np.float32)).astype(np.float16)
+    if rank in (2, 4, 8):
+        assert (want != product.astype(np.float32).astype(np.float16)).any()  # the two do differ
+    assert (G.cpu().numpy() == want.astype(np.float32) * norm).all()
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("rank", [2, 4, 8, 16])
 @pytest.mark.parametrize("anti", [0, 1])
