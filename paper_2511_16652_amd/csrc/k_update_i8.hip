@@ -273,7 +273,6 @@ static egg_status update_i8_group(eggroll_ctx* c, const I8UpdateJob* jobs, int c
         tiles += ((jobs[q].d_out + 127) / 128) * (int64_t)((jobs[q].d_in + 127) / 128);
         entries += (int64_t)jobs[q].d_out * jobs[q].d_in;
     }
-    if ((st = reserve(c, c->pack_a, panels)) != EGG_OK) return st;
     // K is split so that the group's tiles are at most two workgroups per CU -- one wave of them -- in whole 8-chunk stages
     // (128 members), at least four of them: shorter runs cost more in partial sums than they gain
     const bool big = count == 1 && ((jobs[0].d_out + 255) / 256) * (int64_t)((jobs[0].d_in + 255) / 256) >= 192;
@@ -287,7 +286,9 @@ static egg_status update_i8_group(eggroll_ctx* c, const I8UpdateJob* jobs, int c
             nsplit = (int)((kgroups + per_split - 1) / per_split);
         }
     }
+    // (the partial sums first: they are of much the same size for a smaller group, which is tried where the panels do not fit)
     if (nsplit > 1 && (st = reserve(c, c->t_buf, (size_t)nsplit * entries * sizeof(int32_t))) != EGG_OK) return st;
+    if ((st = reserve(c, c->pack_a, panels)) != EGG_OK) return st;
 
     const bool table = int_bound == EGG_INT_NOISE_NORMAL16;
     if (table && (st = ensure_normal_table(c)) != EGG_OK) return st;
@@ -353,20 +354,27 @@ egg_status launch_update_i8_jobs(eggroll_ctx* c, const I8UpdateJob* jobs, int co
 {
     const int64_t kgroups = (N + 15) / 16;
     if (kgroups > 0x7FFFFFFF) return fail(c, EGG_EUNSUPPORTED, "population too large");
-    // Matrices share a group while their panels stay within 1 GB of scratch: beyond that a single one has work enough for the
-    // chip.  One that fills the chip with 256 x 256 tiles goes alone.
+    // Matrices share a group while their panels stay within GROUP_BYTES of scratch: beyond that a single one has work enough for the
+    // chip.  One that fills the chip with 256 x 256 tiles goes alone.  Where that much scratch is not to be had, smaller groups
+    // do, down to the panels of one matrix.
+    // (256 x 256 and 256 x 1024 matrices, 131072 ids, whole steps of the integer model: 1 GB 8145 us, 256 MB 8520, 64 MB 9545)
     constexpr size_t GROUP_BYTES = size_t(1) << 30;
     auto fills_chip = [](const I8UpdateJob& j) { return ((j.d_out + 255) / 256) * (int64_t)((j.d_in + 255) / 256) >= 192; };
+    int most = I8_BATCH;
     for (int q = 0; q < count;) {
         int n = 0;
         size_t bytes = 0;
-        while (q + n < count && n < I8_BATCH) {
+        while (q + n < count && n < most) {
             const size_t more = (size_t)kgroups * 16 * ((size_t)jobs[q + n].d_out + jobs[q + n].d_in);
             if (n > 0 && (bytes + more > GROUP_BYTES || fills_chip(jobs[q + n]) || fills_chip(jobs[q]))) break;
             bytes += more;
             ++n;
         }
         const egg_status st = update_i8_group(c, jobs + q, n, member_begin, N, int_bound, F, threshold);
+        if (st == EGG_ENOMEM && n > 1) {  // (scratch is reserved before anything is enqueued)
+            most = n / 2;
+            continue;
+        }
         if (st != EGG_OK) return st;
         q += n;
     }

@@ -110,3 +110,45 @@ def test_update_i8_argument_errors(ctx):
         with pytest.raises(eb.EggrollError) as e:
             ctx.eggroll_update_i8(key, shape, bound, F, tau, th)
         assert e.value.status == status
+
+
+def test_model_update_with_little_scratch():
+    """The update of the whole integer model groups its matrices over up to 1 GB of panels; with 700 MB of the card left it takes
+    smaller groups and gives the same bits."""
+    import torch
+    D, L, N = 256, 1, 262144
+    g = torch.Generator("cuda").manual_seed(1)
+    weights = lambda *s: torch.randint(-127, 128, s, generator=g, device="cuda", dtype=torch.int8)  # noqa: E731
+    shapes = {"emb": (256, D), "ln1": (L, D), "gru_w": (L, 4, D, D), "gru_b": (L, 2, D), "ln2": (L, D), "mlp1": (L, 4 * D, D), "mlp2": (L, D, 4 * D),
+              "ln_out": (D,), "head": (256, D)}
+    model = {n: weights(*shapes[n]) for n in eb.EGG_MODEL_FIELDS}
+    F = torch.randint(-1, 2, (N,), generator=g, device="cuda", dtype=torch.int8)
+
+    def update():
+        m = {n: t.clone() for n, t in model.items()}
+        ctx = eb.Context(0)
+        try:
+            ctx.eggroll_egg_update_i8(eb.make_key(SEED, STEP, LAYER), eb.make_shape(0, N, 1, D, D, 1), L, 8, F, 5000, m)
+            torch.cuda.synchronize()
+        finally:
+            ctx.close()
+        return m
+
+    want = update()
+    assert any((want[n] != model[n]).any() for n in want)
+    torch.cuda.empty_cache()
+    fill, piece = [], 32 << 30
+    while piece >= 16 << 20:
+        if torch.cuda.mem_get_info()[0] - piece < 700 << 20:
+            piece //= 2
+            continue
+        try:
+            fill.append(torch.empty(piece, dtype=torch.uint8, device="cuda"))
+        except torch.cuda.OutOfMemoryError:
+            piece //= 2
+    try:
+        got = update()
+    finally:
+        del fill
+        torch.cuda.empty_cache()
+    assert all(torch.equal(got[n], want[n]) for n in want)
