@@ -191,9 +191,10 @@ typedef enum { EGG_CACHE_ROWS = 0, EGG_CACHE_PANEL = 1 } egg_cache_layout;
 egg_status eggroll_set_cache_layout(eggroll_ctx* ctx, egg_cache_layout layout);
 
 /*
- * Diagnostic switch.  The row-streaming integer matmul (used at d_in = 256) keeps loads in flight across its loop
- * iterations and waits for them by count; with on != 0 it waits for every outstanding load instead (slower, no
- * assumption about how many loads are in flight).  Results are identical in both forms; a test holds one against the other.
+ * Diagnostic switch.  The row-streaming integer matmul (used at d_in = 256) and the kernel of products whose tiles leave compute
+ * units empty (fp32 and bf16 layers, bf16 updates) keep loads in flight across their loop iterations and wait for them by count;
+ * with on != 0 they wait for every outstanding load instead (slower, no assumption about how many loads are in flight).  Results
+ * are identical in both forms; tests hold one against the other.
  */
 egg_status eggroll_set_conservative_waits(eggroll_ctx* ctx, int on);
 

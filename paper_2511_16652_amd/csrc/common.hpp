@@ -20,7 +20,7 @@ struct eggroll_ctx {
     std::string err;
     int compute_units = 256;  // of the device (grid size of persistent kernels)
     int cache_layout = 0;  // egg_cache_layout of the forward/update caches
-    bool conservative_waits = false;  // diagnostic: kernels with counted s_waitcnt wait for everything instead
+    bool conservative_waits = false;  // diagnostic: the kernels that count their loads in flight wait for everything instead
 
     // scratch, grown on demand and kept for the life of the context
     struct Buf {

@@ -768,10 +768,11 @@ constexpr int vm_lds_imm(int n) { return 0x0070 | (n & 15) | ((n >> 4) << 14); }
 // about 65 bytes/ns, the rate the chip reaches per CU with all of them loading): 128 x 128 stages take 0.57 us, 0.66 in the
 // two-stage loop.  Layers of 1024 x 2048 rows, 1024 -> .. (us, before / now): K = 256 16.8 / 15.7, 1024 24.3 / 22.9, 4096 51.3 / 49.2.
 // fp32 runs it on 32 x 32 tiles, several workgroups to a CU (k_forward.hip): there the MFMAs are the bound, 256 cycles a stage.
-// K-packed or row-major operands; epilogues as in the persistent kernel.
+// K-packed or row-major operands; epilogues as in the persistent kernel.  wait_all: the context's diagnostic switch, every wait of the
+// main loop is for everything.
 template <class MT, int BM, int BN, int WM, int WN, bool KMAJOR, class Epi>
 __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P, Operand Q, int kchunks, int tiles_m, int tiles_n,
-                                                                 const char* zero_page, typename Epi::Args ea)
+                                                                 const char* zero_page, int wait_all, typename Epi::Args ea)
 {
     constexpr int NT = WM * WN * 64, DEPTH = 4;
     constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -832,6 +833,7 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P,
     // stage that every wave has waited for by count, and the reads of the stage whose buffer is loaded next (lgkmcnt(0))
 #define EGG_DEEP_BARRIER(N_)                               \
     asm volatile("" ::: "memory");                         \
+    if (wait_all) __builtin_amdgcn_s_waitcnt(vm_lds_imm(0)); \
     __builtin_amdgcn_s_waitcnt(vm_lds_imm((N_)*LOADS));    \
     __builtin_amdgcn_s_barrier();                          \
     asm volatile("" ::: "memory");

@@ -463,7 +463,7 @@ static egg_status launch_gemm_f32_deep(eggroll_ctx* c, const Operand& P, const O
     if (st != EGG_OK) return st;
     KernelScope ks(c, shaped_name(c, "forward_gemm_f32", P.rows, kchunks * 4));
     hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(256), lds, c->stream, P, Q, kchunks, tiles_m, tiles_n,
-                       (const char*)c->zero_page.p, ea);
+                       (const char*)c->zero_page.p, c->conservative_waits ? 1 : 0, ea);
     return check_hip(c, hipGetLastError(), "forward_gemm_f32");
 }
 

@@ -247,7 +247,7 @@ static egg_status launch_fold_deep(eggroll_ctx* c, const Operand& P, const Opera
     if (st != EGG_OK) return st;
     KernelScope ks(c, shaped_name(c, "forward_gemm_bf16_small", P.rows, kchunks * 8));
     hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(WM * WN * 64), lds, c->stream, P, Q, kchunks, tiles_m, tiles_n,
-                       (const char*)c->zero_page.p, ea);
+                       (const char*)c->zero_page.p, c->conservative_waits ? 1 : 0, ea);
     return check_hip(c, hipGetLastError(), "forward_gemm_bf16_small");
 }
 

@@ -635,15 +635,21 @@ static egg_status launch_upd_gemm16(eggroll_ctx* c, const char* name, const Oper
     const int tiles_m = (P.rows + BM - 1) / BM, tiles_n = (Q.rows + BN - 1) / BN;
     const size_t stages = gemm_lds_bytes<BM, BN>(), epi = (size_t)WM * WN * Epi::lds_per_wave(BM / WM);
     if (!operand_offsets_fit(P, BM) || !operand_offsets_fit(Q, BN)) return fail(c, EGG_EUNSUPPORTED, "operand strides too large for 32-bit tile offsets");
-    void (*kern)(Operand, Operand, int, int, int, const char*, UpdArgs);
-    if constexpr (DEEP) kern = gemm_nt_deep_kernel<MmaF16Blk16, BM, BN, WM, WN, true, Epi>;
-    else kern = gemm_nt_kernel<MmaF16Blk16, BM, BN, WM, WN, true, Epi>;
     const size_t lds = DEEP ? 2 * stages + epi : std::max(stages, epi);
-    egg_status st = ensure_dynamic_lds(c, (const void*)kern, lds, "gemm smem attr");
-    if (st != EGG_OK) return st;
-    KernelScope ks(c, name);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(WM * WN * 64), lds, c->stream, P, Q, kchunks, tiles_m, tiles_n,
-                       (const char*)c->zero_page.p, ea);
+    const dim3 g((unsigned)(tiles_m * tiles_n)), b(WM * WN * 64);
+    if constexpr (DEEP) {
+        auto kern = gemm_nt_deep_kernel<MmaF16Blk16, BM, BN, WM, WN, true, Epi>;
+        const egg_status st = ensure_dynamic_lds(c, (const void*)kern, lds, "gemm smem attr");
+        if (st != EGG_OK) return st;
+        KernelScope ks(c, name);
+        hipLaunchKernelGGL(kern, g, b, lds, c->stream, P, Q, kchunks, tiles_m, tiles_n, (const char*)c->zero_page.p, c->conservative_waits ? 1 : 0, ea);
+    } else {
+        auto kern = gemm_nt_kernel<MmaF16Blk16, BM, BN, WM, WN, true, Epi>;
+        const egg_status st = ensure_dynamic_lds(c, (const void*)kern, lds, "gemm smem attr");
+        if (st != EGG_OK) return st;
+        KernelScope ks(c, name);
+        hipLaunchKernelGGL(kern, g, b, lds, c->stream, P, Q, kchunks, tiles_m, tiles_n, (const char*)c->zero_page.p, ea);
+    }
     return check_hip(c, hipGetLastError(), name);
 }
 

@@ -143,3 +143,34 @@ def test_f32_rows_do_not_depend_on_the_call(ctx, S, rank, anti, members, sigma, 
     for n in members[:-1]:
         for first in (0, N - n, (N - n) // 4 * 2):
             assert torch.equal(run(first, n), whole[first * S:(first + n) * S]), (first, n)
+
+
+@pytest.mark.parametrize("stages", range(1, 10))
+@pytest.mark.parametrize("kind", ["f32", "bf16", "update"])
+def test_counted_waits_equal_waits_for_everything(ctx, kind, stages):
+    """The kernel that keeps four stages of K in flight waits for them by count; with the diagnostic switch it waits for every load.  The
+    same bits, for row-major operands (32 x 32 tiles in fp32, 128 x 128 in bf16) and the update's K-packed panels, at every length of
+    its loop's ends, whole and ragged last stages."""
+    import torch
+    for part in (0, 1):
+        res = []
+        for on in (0, 1):
+            g = torch.Generator("cuda").manual_seed(stages)
+            ctx.eggroll_set_conservative_waits(on)
+            try:
+                if kind == "update":
+                    N = 64 * stages - 24 * part
+                    f = torch.randn(N, generator=g, device="cuda")
+                    Y = torch.empty((2048, 2040), device="cuda")   # 256 tiles of 128 x 128
+                    ctx.eggroll_update(eb.make_key(1, 2, 3), eb.make_shape(0, N, 1, 2048, 2040, 1), eb.EGG_BF16, f, 1.0, 0, Y)
+                else:
+                    tdt, d_out, N, S = (torch.float32, 260, 30, 4) if kind == "f32" else (torch.bfloat16, 1028, 33, 16)
+                    d_in = (32 if kind == "f32" else 64) * stages - 8 * part
+                    W = torch.randn((d_out, d_in), generator=g, device="cuda").to(tdt)
+                    X = torch.randn((N * S, d_in), generator=g, device="cuda").to(tdt)
+                    Y = torch.empty((N * S, d_out), dtype=tdt, device="cuda")
+                    ctx.eggroll_perturbed_forward(eb.make_key(1, 2, 3), eb.make_shape(0, N, S, d_out, d_in, 2), 0.5, eb.EGG_ACT_NONE, W, X, Y)
+            finally:
+                ctx.eggroll_set_conservative_waits(0)
+            res.append(Y)
+        assert torch.equal(res[0], res[1]) and torch.isfinite(res[0].float()).all()
