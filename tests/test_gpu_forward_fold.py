@@ -38,6 +38,11 @@ CASES = [  # d_out, d_in, members, S, rank, antithetic, gelu, residual
     (4096, 64, 205, 15, 16, 0, 0, 0),
     (4096, 128, 62, 51, 1, 0, 0, 0),
     (4096, 72, 50, 64, 2, 0, 0, 0),    # S a multiple of 64, ragged K
+    (2052, 72, 26, 100, 4, 0, 1, 0),   # 257 to 512 tiles of 128 x 128, two workgroups per CU: ragged K, blocks of two members
+    (2052, 136, 51, 51, 16, 0, 0, 1),
+    (2052, 200, 100, 26, 2, 0, 1, 1),
+    (2052, 64, 41, 64, 1, 0, 0, 1),
+    (2052, 72, 52, 50, 8, 1, 0, 0),
 ]
 
 

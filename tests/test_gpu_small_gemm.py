@@ -1,5 +1,6 @@
-"""GPU: products too small for the chip-filling tiles (32 and 64 tiles with K split over four waves; one 128 x 128 tile per CU with
-four stages in flight), at the edges of their K ranges and of the rule between them.
+"""GPU: products too small for the chip-filling tiles (updates: 32 and 64 tiles with K split over four waves; bf16 layers: 32 tiles from
+memory, one 128 x 128 tile per CU with four stages in flight; fp32 layers: 32 tiles with four stages in flight), at the edges of their
+K ranges and of the rule between them, and the tiles that follow them.
 
 References in 64 bits from the library's own factors; fp32: 1e-5 of |value| + rms (sums of up to 2064 products in another order);
 bf16 outputs: one rounding, 2^-8; update panels in fp16: 2^-11 per term, random sign, so 2e-3 of the rms covers every entry."""
@@ -31,7 +32,7 @@ def factors(ctx, key, ids, n, rank, which, tdt, code):
 
 @pytest.mark.parametrize("dtype,d_out,d_in,N,S,rank,cache", [
     ("f32", 4, 4, 1, 1, 1, 0), ("f32", 36, 12, 33, 1, 1, 1), ("f32", 100, 68, 9, 3, 4, 0), ("f32", 256, 2064, 5, 7, 2, 0),
-    ("f32", 1028, 132, 260, 2, 1, 0),       # 33 x 17 tiles of 32: the 64 form
+    ("f32", 1028, 132, 260, 2, 1, 0),       # 33 x 17 tiles of 32
     ("bf16", 4, 8, 1, 1, 1, 0), ("bf16", 36, 24, 33, 1, 1, 1), ("bf16", 100, 520, 9, 3, 4, 0), ("bf16", 132, 2056, 5, 7, 16, 0),
     ("bf16", 520, 64, 33, 16, 2, 0),        # 17 x 17 tiles of 32
     ("bf16", 1028, 64, 33, 16, 2, 0),       # 33 x 17: past the 32 form; one stage of K
@@ -61,7 +62,8 @@ def test_small_forward(ctx, dtype, d_out, d_in, N, S, rank, cache):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d_out,d_in,N,rank", [(4, 2, 1, 1), (36, 7, 9, 2), (260, 130, 33, 1), (256, 256, 257, 8), (1028, 1056, 64, 1),
-                                              (1028, 1056, 65, 4), (2052, 1030, 40, 1)])  # the 32 form, the 64 form, past both
+                                              (1028, 1056, 65, 4), (2052, 1030, 40, 1),  # the 32 form, the 64 form, past both
+                                              (3004, 2002, 40, 1), (3072, 2048, 33, 4)])  # 384 tiles of 128 x 128; in fp32 128 x 64
 @pytest.mark.parametrize("w", [None, "bf16", "f32"])
 def test_small_update(ctx, dtype, d_out, d_in, N, rank, w):
     import torch
@@ -114,6 +116,38 @@ def test_bf16_rows_do_not_depend_on_the_call(ctx, d_out, d_in, S, rank, members,
     for n in members[:-1]:
         for first in (0, N - n, (N - n) // 2):
             assert torch.equal(run(first, n), whole[first * S:(first + n) * S]), (first, n)
+
+
+@pytest.mark.parametrize("d_out,d_in,N,S,rank,anti,cache", [
+    (2044, 140, 1000, 1, 1, 0, 1), (2044, 140, 1000, 1, 1, 1, 0), (2044, 68, 333, 3, 4, 0, 0), (2044, 36, 60, 16, 16, 0, 1),   # 128 x 64 tiles
+    (2044, 140, 2046, 1, 1, 1, 0), (2044, 140, 2047, 1, 1, 0, 1), (2044, 68, 681, 3, 2, 0, 0), (2044, 36, 60, 33, 8, 0, 0), (2044, 68, 510, 2, 16, 1, 0)])
+@pytest.mark.parametrize("form", ["plain", "gelu", "residual", "both"])
+def test_f32_tiles(ctx, d_out, d_in, N, S, rank, anti, cache, form):
+    """fp32 layers of more than four 32 x 32 tiles per CU (128 x 64 tiles, then 128 x 128): factors regenerated in registers, shared by
+    the lanes of a pair, or read; ragged in every direction.  GELU has a slope of at most 1.13."""
+    import torch
+    ids, per = N // (2 if anti else 1), S * (2 if anti else 1)
+    g = torch.Generator("cuda").manual_seed(N)
+    W = torch.randn((d_out, d_in), generator=g, device="cuda") * d_in ** -0.5
+    X, R = (torch.randn((N * S, d), generator=g, device="cuda") for d in (d_in, d_out))
+    Y = torch.full((N * S, d_out), float("nan"), device="cuda")
+    key, sigma = eb.make_key(1, 2, 3), 0.5
+    A, B = factors(ctx, key, ids, d_out, rank, 0, torch.float32, eb.EGG_F32), factors(ctx, key, ids, d_in, rank, 1, torch.float32, eb.EGG_F32)
+    Ac, Bc = (torch.empty_like(A), torch.empty_like(B)) if cache else (None, None)
+    args = (key, eb.make_shape(0, N, S, d_out, d_in, rank, anti), sigma, eb.EGG_ACT_GELU if form in ("gelu", "both") else eb.EGG_ACT_NONE, W, X)
+    if form in ("residual", "both"):
+        ctx.eggroll_perturbed_forward_add(*args, R, Y, Ac, Bc)
+    else:
+        ctx.eggroll_perturbed_forward(*args, Y, Ac, Bc)
+    if cache:
+        assert torch.equal(A, Ac) and torch.equal(B, Bc)
+    t = torch.bmm(X.double().view(ids, per, d_in), B.double())
+    if anti:
+        t[:, S:] *= -1
+    pre = X.double() @ W.double().t().contiguous() + torch.bmm(t, A.double().transpose(1, 2).contiguous()).view(N * S, d_out) * (sigma / math.sqrt(rank))
+    ref = 0.5 * pre * (1 + torch.erf(pre * math.sqrt(0.5))) if form in ("gelu", "both") else pre
+    ref = ref + R.double() if form in ("residual", "both") else ref
+    assert ((Y.double() - ref).abs() <= 1e-5 * (ref.abs() + pre.square().mean(1, keepdim=True).sqrt())).all()
 
 
 @pytest.mark.parametrize("S,rank,anti,members", [(1, 1, 0, (3, 500, 1000, 2048)), (1, 1, 1, (2, 500, 1000, 2048)), (1, 4, 0, (1, 300, 1001, 2000)),
