@@ -244,19 +244,13 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
                             }
                         }
                     } else {
+                        static_assert(!BF16, "bf16 of rank 2 and more is rank-major");
                         float x[NR][EPC];
 #pragma unroll
                         for (int j = 0; j < NR; ++j) {
                             const uint32_t w[4] = {xc[j][u].x, xc[j][u].y, xc[j][u].z, xc[j][u].w};
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                if constexpr (BF16) {
-                                    x[j][2 * e] = __uint_as_float(w[e] << 16);
-                                    x[j][2 * e + 1] = __uint_as_float(w[e] & 0xFFFF0000u);
-                                } else {
-                                    x[j][e] = __uint_as_float(w[e]);
-                                }
-                            }
+                            for (int e = 0; e < EPC; ++e) x[j][e] = __uint_as_float(w[e]);
                         }
                         // B_i[k][l] for the chunk's k range: EPC*RANK consecutive elements = RANK 16-byte reads
                         const uint4* bp = (const uint4*)smem + (int64_t)ch * RANK;
@@ -268,11 +262,8 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
 #pragma unroll
                             for (int e = 0; e < EPC; ++e) {
                                 const int f = v * EPC + e;
-                                float bv;
-                                if constexpr (BF16) bv = (e & 1) ? __uint_as_float(w[e >> 1] & 0xFFFF0000u) : __uint_as_float(w[e >> 1] << 16);
-                                else bv = __uint_as_float(w[e]);
 #pragma unroll
-                                for (int j = 0; j < NR; ++j) acc[j][f % RANK] = fmaf(x[j][f / RANK], bv, acc[j][f % RANK]);
+                                for (int j = 0; j < NR; ++j) acc[j][f % RANK] = fmaf(x[j][f / RANK], __uint_as_float(w[e]), acc[j][f % RANK]);
                             }
                         }
                     }
