@@ -193,7 +193,7 @@ egg_status launch_forward_i8(eggroll_ctx* c, const StreamKey& ka, const StreamKe
                              const int8_t* H_in, int8_t* H_out);
 
 // many time steps in one kernel (k_recur_i8.hip), for the shapes that recur_i8_applies accepts
-bool recur_i8_applies(int d_out, int d_in, int64_t rows, int steps);
+bool recur_i8_applies(int d_out, int d_in, int64_t rows, int steps, int compute_units);
 egg_status launch_recur_i8(eggroll_ctx* c, const int8_t* A, const int8_t* B, int anti, int64_t rows, int d, int int_bound, int corr_shift,
                            int out_shift, int steps, const int8_t* W, const int8_t* H_in, int8_t* H_out);
 

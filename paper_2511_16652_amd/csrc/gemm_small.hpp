@@ -12,13 +12,13 @@
 namespace egg {
 
 // Tile of the small kernel for an M x N product, 0 where the tiles of gemm_core.hpp do better.  Measured over 256 .. 4096 rows and
-// columns and K of 64 .. 4096 (us, this kernel against theirs; the lines lie where the last listed shape still gains):
-//   32: up to 512 tiles   256 x 256 x 4096: 26 / 56
-//   64: up to 512 tiles   2048 x 1024 x 4096: 57 / 68 (2048 x 2048: 86 / 78)
-inline int small_tile(int64_t M, int64_t N)
+// columns and K of 64 .. 4096 on 256 CUs (us, this kernel against theirs; the lines lie where the last listed shape still gains):
+//   32: up to two tiles per CU   256 x 256 x 4096: 26 / 56
+//   64: up to two tiles per CU   2048 x 1024 x 4096: 57 / 68 (2048 x 2048: 86 / 78)
+inline int small_tile(int64_t M, int64_t N, int compute_units)
 {
-    if (((M + 31) / 32) * ((N + 31) / 32) <= 512) return 32;
-    return ((M + 63) / 64) * ((N + 63) / 64) <= 512 ? 64 : 0;
+    if (((M + 31) / 32) * ((N + 31) / 32) <= 2 * (int64_t)compute_units) return 32;
+    return ((M + 63) / 64) * ((N + 63) / 64) <= 2 * (int64_t)compute_units ? 64 : 0;
 }
 
 // Epi requirements: struct Args; __device__ Epi(const Args&); value_t; __device__ void apply4(int m, int n, const value_t (&v)[4]),
@@ -192,9 +192,8 @@ __global__ __launch_bounds__(256, 2) void gemm_small16_kernel(Operand P, Operand
     const float v[4] = {acc[0], acc[1], acc[2], acc[3]};
     if (m < P.rows && n < Q.rows) epi.apply4(m, n, v);
 }
-// Up to so many tiles of 32 x 32 the bf16 layer takes it (us, this kernel / 128 x 128 tiles): 16 rows per member 256 x 64 x 4096
+// Up to one tile of 32 x 32 per CU the bf16 layer takes it (us, this kernel / 128 x 128 tiles): 16 rows per member 256 x 64 x 4096
 // 41 / 46, 512 x 512 x 1024 19.7 / 20.6 (1024 x 512 x 1024: 28 / 21); one row per member 512 x 256 x 1024 14 / 24.
-constexpr int64_t SMALL16_TILES = 256;
-inline bool small16(int64_t M, int64_t N) { return ((M + 31) / 32) * ((N + 31) / 32) <= SMALL16_TILES; }
+inline bool small16(int64_t M, int64_t N, int compute_units) { return ((M + 31) / 32) * ((N + 31) / 32) <= compute_units; }
 
 }  // namespace egg

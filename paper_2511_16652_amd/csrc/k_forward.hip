@@ -467,7 +467,7 @@ static egg_status launch_gemm_f32_deep(eggroll_ctx* c, const Operand& P, const O
     return check_hip(c, hipGetLastError(), "forward_gemm_f32");
 }
 
-// bf16: at most SMALL16_TILES tiles of 32 x 32
+// bf16, for the products that small16 names
 template <class Epi>
 static egg_status launch_gemm_small16(eggroll_ctx* c, const Operand& P, const Operand& Q, int kchunks, const FwdArgs& ea)
 {
@@ -570,17 +570,17 @@ static egg_status launch_forward_t(eggroll_ctx* c, const StreamKey& ka, const eg
     FwdArgs ea{ka, (uint32_t)(s.member_begin / anti), S, s.d_out, make_fast_div((uint32_t)S), sigma / sqrtf((float)s.rank),
                (int)act, yd == EGG_BF16 ? 1 : 0, Y, t, A_buf, 0, resid, nullptr, nullptr};
     if constexpr (BF16) {
-        const int64_t big_tiles = ((s.d_out + 255) / 256) * ((R + 255) / 256);
+        const bool big = big_tiles(s.d_out, R, c->compute_units);
         // bf16 out and no correction, or one that 16 neighbouring rows share among at most two members: folded into the
         // accumulators, store-only epilogue.  The parked form below is the faster one where it applies (big tiles, S a multiple
         // of 64, whole K stages).
-        const bool parked = big_tiles > BIG_TILES_ABOVE && kchunks % 8 == 0 && (ea.c == 0.f || (!REGEN && RANK <= 8 && S % 64 == 0));
+        const bool parked = big && kchunks % 8 == 0 && (ea.c == 0.f || (!REGEN && RANK <= 8 && S % 64 == 0));
         if (!next && yd == EGG_BF16 && !parked && (ea.c == 0.f || (!REGEN && ea.S >= FOLD_MIN_ROWS)))
             return launch_forward_fold(c, FoldLayer{ea.S, s.d_out, s.d_in, s.rank, R, ea.c, act == EGG_ACT_GELU, W, X, A_buf, resid, Y, t});
         // (the correction per output, here and in the general epilogue: the same bits for any number of rows)
-        if (!next && small16(s.d_out, R) && (REGEN || ea.S < FOLD_MIN_ROWS))
+        if (!next && small16(s.d_out, R, c->compute_units) && (REGEN || ea.S < FOLD_MIN_ROWS))
             return launch_gemm_small16<Epi>(c, P, Q, kchunks, ea);
-        if (big_tiles > BIG_TILES_ABOVE) {
+        if (big) {
             // bf16 out and nothing left to correct in the epilogue (unperturbed, or the correction folds into the
             // accumulators): the store-only epilogue with the activation and the residual fixed at compile time
             const bool folded = !REGEN && RANK <= 8 && ea.c != 0.f && S % 64 == 0;

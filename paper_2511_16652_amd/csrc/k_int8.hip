@@ -598,7 +598,7 @@ egg_status launch_forward_i8(eggroll_ctx* c, const StreamKey& ka, const StreamKe
     int8_t* B = (int8_t*)c->i8_b.p;
     const NoiseJob noise[2] = {{ka, d_out, A}, {kb, d_in, B}};
     if ((st = launch_noise_jobs(c, noise, 2, first_id, noise_ids, EGG_I8, EGG_UNIFORM_INT, int_bound)) != EGG_OK) return st;
-    if (recur_i8_applies(d_out, d_in, rows, steps)) return launch_recur_i8(c, A, B, anti, rows, d_in, int_bound, corr_shift, out_shift, steps, W, H_in, H_out);
+    if (recur_i8_applies(d_out, d_in, rows, steps, c->compute_units)) return launch_recur_i8(c, A, B, anti, rows, d_in, int_bound, corr_shift, out_shift, steps, W, H_in, H_out);
     if ((st = reserve(c, c->i8_h, 2 * ((obytes + 255) & ~size_t(255)))) != EGG_OK) return st;
     // one row of dot products per step: step t reads row t (filled by the dot kernel for t = 0, by the
     // previous step's epilogue otherwise) and accumulates row t+1

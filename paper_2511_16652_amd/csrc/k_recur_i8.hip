@@ -4,7 +4,7 @@
 // A member's row depends on no other member, so a workgroup that owns 32 rows can walk all time steps by itself: state, factors
 // and dot products stay in LDS, and no kernel boundary, no operand tile and no factor row goes through memory between steps.
 // What a step costs then is reading theta: d^2 bytes per workgroup.  Its MFMA fragments are kept in registers as far as they go
-// -- all of them up to d = 512, a quarter at d = 1024 -- and the rest streams from L2 in fragment order (a small kernel lays theta
+// -- all of them up to d = 512, 10 of 24 k blocks at d = 768, 6 of 32 at d = 1024 -- and the rest streams from L2 in fragment order (a small kernel lays theta
 // out so at the start of the call: a fragment of the row-major matrix is 32 pieces of 32 bytes, a row apart).
 // Bound: the MFMAs and one barrier up to d = 512; beyond, the rate at which a CU loads.
 #include "common.hpp"
@@ -173,9 +173,9 @@ __global__ __launch_bounds__(512, 1) void recur_i8_kernel(const u32x4* __restric
 // a step costs 10 us however few rows there are, so the rows have to fill half of the chip.  Measured (us, one launch per step / this):
 // 1024 wide: 8192 members x 64 steps 983 / 732, 4096 x 32 346 / 342, 2500 x 32 312 / 337; 896: 4096 x 32 328 / 304;
 // 768: 5000 x 16 173 / 113; 640: 300 x 16 129 / 91; 512: 8192 x 32 243 / 127; 272: 2076 x 36 262 / 98; 256: 100 x 64 367 / 81.
-bool recur_i8_applies(int d_out, int d_in, int64_t rows, int steps)
+bool recur_i8_applies(int d_out, int d_in, int64_t rows, int steps, int compute_units)
 {
-    return d_out == d_in && d_in % 16 == 0 && steps >= 4 && (d_in <= 768 || (d_in <= 1024 && rows >= 4096));
+    return d_out == d_in && d_in % 16 == 0 && steps >= 4 && (d_in <= 768 || (d_in <= 1024 && rows >= (int64_t)RECUR_ROWS * compute_units / 2));
 }
 
 egg_status launch_recur_i8(eggroll_ctx* c, const int8_t* A, const int8_t* B, int anti, int64_t rows, int d, int int_bound, int corr_shift,
@@ -209,8 +209,9 @@ egg_status launch_recur_i8(eggroll_ctx* c, const int8_t* A, const int8_t* B, int
     }
     // (k blocks kept and in flight, measured at 1024 / 768 wide: kept ones are worth more than depth -- 3 + 4: 870 us for 8192 members
     // x 64 steps, 4 + 3: 798, 5 + 2: 727 to 740, 6 + 1: 732 and the best with few rows; 7 + 2 spills 56 registers: 783)
-    if (nb <= 8) EGG_RECUR_D(1, 8, 1)
-    if (nb <= 16) EGG_RECUR_D(2, 16, 1)
+    static_assert(512 * 127 * 127 < (1 << 23), "up to 512 wide the product always fits");
+    if (nb <= 8) EGG_RECUR(1, 8, 1, true)
+    if (nb <= 16) EGG_RECUR(2, 16, 1, true)
     if (nb <= 24) EGG_RECUR_D(3, 10, 2)
     EGG_RECUR_D(4, 6, 1)
 #undef EGG_RECUR_D

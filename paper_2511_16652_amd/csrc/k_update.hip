@@ -734,15 +734,17 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
     Operand P{(const char*)c->pack_a.p, 16, (int64_t)s.d_out * 16, s.d_out};
     Operand Q{(const char*)(b_panel ? B_cache : c->pack_b.p), 16, (int64_t)s.d_in * 16, s.d_in};
     UpdArgs ea{G, W, fnorm, s.d_out, s.d_in, scale, lr, accumulate, w_dtype == EGG_BF16 ? 1 : 0};
-    if (const int small = small_tile(s.d_in, s.d_out)) {
+    if (const int small = small_tile(s.d_in, s.d_out, c->compute_units)) {
         return bf ? launch_upd_small<MmaF16>(c, "update_gemm_f16_small", Q, P, (int)kgroups, small, ea)
                   : launch_upd_small<MmaF32>(c, "update_gemm_f32", Q, P, (int)kgroups, small, ea);
     }
     if (bf) {
-        const int64_t big_tiles = ((s.d_out + 255) / 256) * (int64_t)((s.d_in + 255) / 256);
-        if (big_tiles > BIG_TILES_ABOVE) return launch_upd_gemm16<256, 256, 2, 4, false>(c, "update_gemm_f16", Q, P, (int)kgroups, ea);
+        if (big_tiles(s.d_in, s.d_out, c->compute_units)) return launch_upd_gemm16<256, 256, 2, 4, false>(c, "update_gemm_f16", Q, P, (int)kgroups, ea);
         if (((s.d_out + 127) / 128) * (int64_t)((s.d_in + 127) / 128) <= c->compute_units)
             return launch_upd_gemm16<128, 128, 2, 2, true>(c, "update_gemm_f16_small", Q, P, (int)kgroups, ea);
+        // one to two 128 x 128 tiles per CU: 32x32 blocks, stores entry by entry.  The 16x16 form with two workgroups per CU is better
+        // at middling K and worse at both ends (whole updates, us, this / that): 3072 x 2048, K = 8192 175 / 166, 32768 662 / 682;
+        // 4096 x 2048, K = 256 23.7 / 26.0, 4096 114 / 107; 3000 x 2700, K = 2000 75 / 75.
         return launch_upd_gemm<MmaF16, 128, 128, 2, 2>(c, "update_gemm_f16_small", P, Q, (int)kgroups, ea);
     }
     if (narrow_f32_tiles(s.d_out, s.d_in, c->compute_units)) return launch_upd_gemm<MmaF32, 128, 64, 2, 2>(c, "update_gemm_f32", P, Q, (int)kgroups, ea);
