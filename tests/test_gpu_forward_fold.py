@@ -78,6 +78,16 @@ def test_folded_layer(ctx, case, sigma):
     assert torch.isfinite(Y.float()).all() and (err <= tol).all(), (err - tol).max()
 
 
+@pytest.mark.parametrize("shape", [(132, 72, 9, 17), (1028, 72, 30, 17), (2052, 72, 26, 100), (4096, 64, 62, 51), (4096, 72, 62, 51)])
+@pytest.mark.parametrize("rank", [1, 4, 8])
+@pytest.mark.parametrize("gelu,resid", [(0, 0), (1, 0), (0, 1), (1, 1)])
+def test_every_form(ctx, shape, rank, gelu, resid):
+    """Each width of the lanes' factors with each activation and residual, in each of the folding kernels."""
+    d_out, d_in, N, S = shape
+    for sigma in (0.0, 0.7) if rank == 1 else (0.7,):
+        test_folded_layer(ctx, (d_out, d_in, N, S, rank, 0, gelu, resid), sigma)
+
+
 @pytest.mark.parametrize("d_out,d_in,N,S", [(64, 64, 3, 15), (64, 64, 2, 100), (260, 72, 9, 31), (1028, 64, 37, 16), (4096, 64, 130, 64), (4096, 72, 84, 100)])
 @pytest.mark.parametrize("rank", [1, 2, 4, 8, 16])
 def test_an_infinite_projection(ctx, d_out, d_in, N, S, rank):

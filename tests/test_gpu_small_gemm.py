@@ -37,6 +37,8 @@ def factors(ctx, key, ids, n, rank, which, tdt, code):
     ("bf16", 520, 64, 33, 16, 2, 0),        # 17 x 17 tiles of 32
     ("bf16", 1028, 64, 33, 16, 2, 0),       # 33 x 17: past the 32 form; one stage of K
     ("bf16", 1028, 136, 33, 16, 4, 0), ("bf16", 1028, 200, 33, 16, 8, 0), ("bf16", 1028, 256, 33, 16, 1, 0),   # two, three and four stages
+    ("bf16", 1028, 512, 550, 2, 1, 1), ("bf16", 4100, 64, 1025, 2, 1, 1), ("bf16", 4100, 64, 2050, 1, 4, 0), ("bf16", 4100, 64, 2050, 1, 8, 1),   # past them all, fewer
+    ("bf16", 4100, 72, 683, 3, 16, 0), ("bf16", 3076, 64, 4100, 1, 8, 0), ("bf16", 3076, 72, 1367, 3, 16, 0),   # than 15 rows: 128, 256 x 128 and 256 tiles
     ("bf16", 1028, 328, 33, 16, 1, 0), ("bf16", 1028, 392, 33, 16, 1, 0), ("bf16", 1028, 456, 33, 16, 1, 0),   # five, six, seven
 ])
 def test_small_forward(ctx, dtype, d_out, d_in, N, S, rank, cache):
@@ -119,7 +121,7 @@ def test_bf16_rows_do_not_depend_on_the_call(ctx, d_out, d_in, S, rank, members,
 
 
 @pytest.mark.parametrize("d_out,d_in,N,S,rank,anti,cache", [
-    (2044, 140, 1000, 1, 1, 0, 1), (2044, 140, 1000, 1, 1, 1, 0), (2044, 68, 333, 3, 4, 0, 0), (2044, 36, 60, 16, 16, 0, 1),   # 128 x 64 tiles
+    (2044, 140, 1000, 1, 1, 0, 1), (2044, 140, 1000, 1, 1, 1, 0), (2044, 68, 333, 3, 4, 0, 0), (2044, 68, 500, 2, 1, 0, 1), (2044, 68, 333, 3, 8, 0, 0), (2044, 36, 60, 16, 16, 0, 1),   # 128 x 64 tiles
     (2044, 140, 2046, 1, 1, 1, 0), (2044, 140, 2047, 1, 1, 0, 1), (2044, 68, 681, 3, 2, 0, 0), (2044, 36, 60, 33, 8, 0, 0), (2044, 68, 510, 2, 16, 1, 0)])
 @pytest.mark.parametrize("form", ["plain", "gelu", "residual", "both"])
 def test_f32_tiles(ctx, d_out, d_in, N, S, rank, anti, cache, form):
