@@ -352,7 +352,10 @@ int64_t eggroll_int_threshold(double alpha, int64_t n_terms, double noise_std);
  * model independently (Alg. 1; Sec. 4.1) and evaluates all members in one batched pass (Sec. 4.2); the two
  * model families below are the synthetic stand-ins this library is measured on.  Everything is bf16,
  * row-major, member-major rows; a population is walked in chunks of `chunk_members` members (0 = a default
- * of about 2^18 rows per chunk), which changes neither noise nor results.  Activations of one chunk live in
+ * of about 2^18 rows per chunk), which changes neither noise nor results -- with one exception: at rank 1 with
+ * rows_per_member a multiple of 64, chunks of at least 192 up-projection tiles of 256 x 256 form the down-projection's
+ * projections in the order of eggroll_perturbed_forward_chained, so a chunk on the other side of that line (a short last
+ * one, say) can differ by flipped bf16 roundings.  Activations of one chunk live in
  * the context's scratch.
  *
  * Unperturbed glue (identical in the perturbed and the sigma = 0 pass); d a multiple of 8:
