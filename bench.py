@@ -45,10 +45,13 @@ def parse():
     return a
 
 
-def profiled_traffic(workload, markers):
+FORWARD_EPILOGUES = ("LeanEpi", "FoldEpi", "FoldSmallEpi", "FwdRowEpi")  # what tells a forward GEMM's kernel from the update's
+
+
+def profiled_traffic(workload, core, names=("",)):
     """HBM bytes per launch of the dominant kernel as rocprofv3 counted them (FETCH_SIZE + WRITE_SIZE, scaled by kernels of
     known traffic in the same profile): the traffic table of profiles/<workload>_kernels.md, rows of the kernels whose name
-    holds every marker, averaged over their dispatches.  None when no such profile is in the tree."""
+    holds `core` and one of `names`, averaged over their dispatches.  None when no profile in the tree has such a row."""
     path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", "%s_kernels.md" % workload)
     if not os.path.exists(path):
         return None
@@ -59,7 +62,7 @@ def profiled_traffic(workload, markers):
             in_table = True
         elif line.startswith("## "):
             in_table = False
-        elif in_table and line.startswith("|") and all(m in line for m in markers):
+        elif in_table and line.startswith("|") and core in line and any(n in line for n in names):
             cells = [c.strip() for c in line.strip().strip("|").split("|")]
             try:
                 n, b = int(cells[1]), int(cells[-1])
@@ -281,7 +284,7 @@ def decoder_workload(args):
                         "step_frac_of_bf16_peak": (fwd_flops + upd_flops) / t_step["median"] / 1e12 / peak},
         "roofline": {"bound": "mfma", "kernel": "forward_gemm_bf16 (all %d launches of one step)" % gemm["launches"],
                      "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
-                     "traffic": profiled_traffic("cfg5", ("MmaBf16", "Epi"))},
+                     "traffic": profiled_traffic("cfg5", "MmaBf16", FORWARD_EPILOGUES)},
         "measured_ceilings": ceil,
         "mean_token_loglik": loglik_mean,
         "kernels": kernels,
@@ -418,7 +421,7 @@ def mlp_stack_workload(args):
                         "step_frac_of_bf16_peak": (fwd_flops + upd_flops) / t_step["median"] / 1e12 / peak},
         "roofline": {"bound": "mfma", "kernel": "forward_gemm_bf16 (all %d launches of one step)" % gemm["launches"],
                      "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
-                     "traffic": profiled_traffic("cfg4", ("MmaBf16", "Epi"))},
+                     "traffic": profiled_traffic("cfg4", "MmaBf16", FORWARD_EPILOGUES)},
         "measured_ceilings": ceil,
         "kernels": kernels,
     }
@@ -619,7 +622,7 @@ def linear_workload(args):
         "measured_ceilings": measured_ceilings(),
         "roofline": {"bound": "mfma", "kernel": gemm_name, "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak,
-                     "traffic": profiled_traffic(args.workload, ("MmaBf16" if wl.dtype == "bf16" else "MmaF32", "Epi"))},
+                     "traffic": profiled_traffic(args.workload, "MmaBf16" if wl.dtype == "bf16" else "MmaF32", FORWARD_EPILOGUES)},
         "update_roofline": {"bound": "mfma", "kernel": upd_name, "achieved": upd_tflops, "peak": peak,
                             "unit": "TFLOP/s", "frac": upd_tflops / peak},
         "kernels": kernels,
@@ -751,7 +754,7 @@ def int8_workload(args):
         "roofline": {"bound": "mfma", "kernel": "forward_recur_i8", "achieved": achieved,
                      "peak": roofline.MFMA_PEAK_TFLOPS["i8"], "unit": "TOP/s",
                      "frac": achieved / roofline.MFMA_PEAK_TFLOPS["i8"],
-                     "traffic": profiled_traffic(args.workload, ("recur_i8_kernel",))},
+                     "traffic": profiled_traffic(args.workload, "recur_i8_kernel")},
         "kernels": kernels,
         "integer_update": {"ms": 1e3 * t_upd, "TOP/s": ops / t_upd / 1e12, "threshold": tau, "kernels": uk},
     }
