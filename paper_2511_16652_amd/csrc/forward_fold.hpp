@@ -39,8 +39,9 @@ __device__ __forceinline__ void gelu_bf16_grade4(float (&y)[4])
 }
 
 // The parts of the N products c t that a fold's K-slots hold: the nearest bf16 values or what they leave, which together are c t to about
-// 2^-17.  (The correction is at most of the size of the layer's output, whose own rounding to bf16 is 2^-9; over the ranks and row
-// counts of the layer tests the error against 64 bits is the same as with the correction in fp32.)
+// 2^-17; the layer's output is rounded to bf16, 2^-9, behind it.  Measured against 64 bits over ranks 1 to 16, 16 to 200 rows per member,
+// 512 x 512 and 1024 -> 2048 (relative 2-norm, 1.66e-3 throughout), the correction folded / in fp32: at sigma = 0.001 the same in
+// seven digits, at sigma = 0.5, where the correction is of the output's size, larger by 1.2e-6 of itself (2.4e-6 at most).
 // A finite c t that would round to infinity takes the largest bf16 value, and an infinite one leaves nothing (inf - inf is NaN): the
 // products with the factors are then those of c t itself.  The operations are written out, none is left to contraction: a member's
 // bits are the same in every kernel that folds.
