@@ -131,11 +131,12 @@ struct MmaF32Blk16 {
     }
 };
 
-// Products with more 256 x 256 tiles than half of the CUs take them: up to there, four times as many tiles of 128 x 128 fit two
-// workgroups on each CU at once; beyond, they need a second wave where one of the large tiles still does.  Measured between 128 and
-// 192 tiles on 256 CUs (us, 128 x 128 / 256 x 256): forward 2048 x 8192, 5760 rows 240 / 215; 3072^2, 3000 rows (S = 1) 119 / 105;
-// 2048^2, 4608 rows 69.4 / 63.6; update 4096 x 2560, K = 4096 153 / 128.
-inline bool big_tiles(int64_t M, int64_t N, int compute_units) { return ((M + 255) / 256) * ((N + 255) / 256) > compute_units / 2; }
+// Store-only forward layers and updates take 256 x 256 tiles where those of 128 x 128 would be more than two for each CU: up to there
+// they are all at work at once, two workgroups to a CU, and waste less on ragged edges; beyond, they need a second wave where one of
+// the large tiles still does.  Measured on 256 CUs (us, 128 x 128 / 256 x 256).  Beyond two per CU: forward 2048 x 8192, 5760 rows 240 / 215;
+// 2048^2, 4608 rows 69.4 / 63.6; update 4096 x 2560, K = 4096 153 / 128.  Up to it, 129 to 224 of the large ones: forward 2304 -> 576,
+// 10880 rows 63.9 / 72.6; 2048 -> 2100, 3700 rows 55.3 / 68.1; 2048 -> 128, 57344 rows 92.4 / 103; update 576 x 10800, K = 4096 126 / 148.
+inline bool big_tiles(int64_t M, int64_t N, int compute_units) { return ((M + 127) / 128) * ((N + 127) / 128) > 2 * (int64_t)compute_units; }
 
 // fp32 products are bound by the MFMAs of the busiest CU: 128 x 64 tiles where they leave it less to do than 128 x 128 tiles.
 // Measured (us, 128 x 128 / 128 x 64): forward 1024 x 2048, 8255 rows (520 tiles on 256 CUs) 422 / 378; update 3000 x 2000, K = 1000

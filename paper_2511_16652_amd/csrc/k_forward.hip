@@ -570,58 +570,52 @@ static egg_status launch_forward_t(eggroll_ctx* c, const StreamKey& ka, const eg
     FwdArgs ea{ka, (uint32_t)(s.member_begin / anti), S, s.d_out, make_fast_div((uint32_t)S), sigma / sqrtf((float)s.rank),
                (int)act, yd == EGG_BF16 ? 1 : 0, Y, t, A_buf, 0, resid, nullptr, nullptr};
     if constexpr (BF16) {
-        const bool big = big_tiles(s.d_out, R, c->compute_units);
-        // bf16 out and no correction, or one that 16 neighbouring rows share among at most two members: folded into the
-        // accumulators, store-only epilogue.  The parked form below is the faster one where it applies (big tiles, S a multiple
-        // of 64, whole K stages).
-        const bool parked = big && kchunks % 8 == 0 && (ea.c == 0.f || (!REGEN && RANK <= 8 && S % 64 == 0));
-        if (!next && yd == EGG_BF16 && !parked && (ea.c == 0.f || (!REGEN && ea.S >= FOLD_MIN_ROWS)))
-            return launch_forward_fold(c, FoldLayer{ea.S, s.d_out, s.d_in, s.rank, R, ea.c, act == EGG_ACT_GELU, W, X, A_buf, resid, Y, t});
-        // (the correction per output, here and in the general epilogue: the same bits for any number of rows)
-        if (!next && small16(s.d_out, R, c->compute_units) && (REGEN || ea.S < FOLD_MIN_ROWS))
-            return launch_gemm_small16<Epi>(c, P, Q, kchunks, ea);
-        if (big) {
-            // bf16 out and nothing left to correct in the epilogue (unperturbed, or the correction folds into the
-            // accumulators): the store-only epilogue with the activation and the residual fixed at compile time
-            const bool folded = !REGEN && RANK <= 8 && ea.c != 0.f && S % 64 == 0;
-            if (next) {
-                // the fused next-layer projection exists in one form: rank 1, 2 or 4 (the next layer's too), folded correction,
-                // GELU, no residual
-                if constexpr (!REGEN && (RANK == 1 || RANK == 2 || RANK == 4)) {
-                    if (forward_fuses_next_projection(s, EGG_BF16, yd, sigma, act, resid != nullptr)) {
-                        const int slabs = (s.d_out + 127) / 128;
-                        egg_status st = reserve(c, c->proj_part, (size_t)slabs * R * RANK * sizeof(float));
-                        if (st != EGG_OK) return st;
-                        ea.next_B = next->B;
-                        ea.next_part = (float*)c->proj_part.p;
-                        st = launch_gemm_persistent<MmaBf16Blk16, 256, 256, 2, 4, LeanEpi<RANK, LEAN_ON | LEAN_GELU | LEAN_PROJ>>(
-                            c, "forward_gemm_bf16", P, Q, kchunks, ea);
-                        if (st != EGG_OK) return st;
-                        return launch_sum_slabs(c, (const float*)c->proj_part.p, slabs, R * RANK, next->t);
-                    }
+        if (next) {
+            // the fused next-layer projection exists in one form: rank 1, 2 or 4 (the next layer's too), folded correction,
+            // GELU, no residual
+            if constexpr (!REGEN && (RANK == 1 || RANK == 2 || RANK == 4)) {
+                if (forward_fuses_next_projection(s, EGG_BF16, yd, sigma, act, resid != nullptr)) {
+                    const int slabs = (s.d_out + 127) / 128;
+                    egg_status st = reserve(c, c->proj_part, (size_t)slabs * R * RANK * sizeof(float));
+                    if (st != EGG_OK) return st;
+                    ea.next_B = next->B;
+                    ea.next_part = (float*)c->proj_part.p;
+                    st = launch_gemm_persistent<MmaBf16Blk16, 256, 256, 2, 4, LeanEpi<RANK, LEAN_ON | LEAN_GELU | LEAN_PROJ>>(
+                        c, "forward_gemm_bf16", P, Q, kchunks, ea);
+                    if (st != EGG_OK) return st;
+                    return launch_sum_slabs(c, (const float*)c->proj_part.p, slabs, R * RANK, next->t);
                 }
-                return fail(c, EGG_EINVAL, "this layer cannot form the next layer's projections (ask forward_fuses_next_projection first)");
             }
-            if (yd == EGG_BF16 && (ea.c == 0.f || folded) && kchunks % 8 == 0) {
-                constexpr int LR = (REGEN || RANK > 8) ? 1 : RANK;
+            return fail(c, EGG_EINVAL, "this layer cannot form the next layer's projections (ask forward_fuses_next_projection first)");
+        }
+        // bf16 out and no correction, or one that 16 neighbouring rows share among at most two members: folded into the
+        // accumulators, store-only epilogue with the activation and the residual fixed at compile time.  The parked form is the
+        // faster one where it applies (big tiles, S a multiple of 64, whole K stages).
+        if (yd == EGG_BF16 && (ea.c == 0.f || (!REGEN && ea.S >= FOLD_MIN_ROWS))) {
+            const bool parked = big_tiles(s.d_out, R, c->compute_units) && kchunks % 8 == 0 && (ea.c == 0.f || (RANK <= 8 && S % 64 == 0));
+            if (!parked)
+                return launch_forward_fold(c, FoldLayer{ea.S, s.d_out, s.d_in, s.rank, R, ea.c, act == EGG_ACT_GELU, W, X, A_buf, resid, Y, t});
+            constexpr int LR = (REGEN || RANK > 8) ? 1 : RANK;
 #define EGG_LEAN(L) \
     return launch_gemm_persistent<MmaBf16Blk16, 256, 256, 2, 4, LeanEpi<LR, L>>(c, "forward_gemm_bf16", P, Q, kchunks, ea)
-                switch ((act == EGG_ACT_GELU ? LEAN_GELU : 0) | (resid ? LEAN_RESID : 0)) {
-                    case 0: EGG_LEAN(LEAN_ON);
-                    case LEAN_GELU: EGG_LEAN(LEAN_ON | LEAN_GELU);
-                    case LEAN_RESID: EGG_LEAN(LEAN_ON | LEAN_RESID);
-                    default: EGG_LEAN(LEAN_ON | LEAN_GELU | LEAN_RESID);
-                }
-#undef EGG_LEAN
+            switch ((act == EGG_ACT_GELU ? LEAN_GELU : 0) | (resid ? LEAN_RESID : 0)) {
+                case 0: EGG_LEAN(LEAN_ON);
+                case LEAN_GELU: EGG_LEAN(LEAN_ON | LEAN_GELU);
+                case LEAN_RESID: EGG_LEAN(LEAN_ON | LEAN_RESID);
+                default: EGG_LEAN(LEAN_ON | LEAN_GELU | LEAN_RESID);
             }
-            ea.pair_share = pairs;
-            return launch_gemm<MmaBf16Blk16, 256, 256, 2, 4, Epi>(c, "forward_gemm_bf16", P, Q, kchunks, ea);
+#undef EGG_LEAN
         }
-        if (next) return fail(c, EGG_EINVAL, "this layer cannot form the next layer's projections (ask forward_fuses_next_projection first)");
+        // The correction per output (the same bits for any number of rows).  This epilogue is longer than a tile of 128 x 128 hides, so
+        // the large tile pays earlier than in big_tiles: from more of them than half of the CUs, whatever of them is ragged (us,
+        // 128 x 128 / 256 x 256: 3700 rows of 2048 -> 2100, S = 1 88.0 / 81.6; 3 rows per member at rank 4 100 / 93; 57344 of 2048 -> 104 250 / 231).
+        if (small16(s.d_out, R, c->compute_units) && (REGEN || ea.S < FOLD_MIN_ROWS)) return launch_gemm_small16<Epi>(c, P, Q, kchunks, ea);
+        ea.pair_share = pairs;
+        if (((s.d_out + 255) / 256) * ((R + 255) / 256) > c->compute_units / 2)
+            return launch_gemm<MmaBf16Blk16, 256, 256, 2, 4, Epi>(c, "forward_gemm_bf16", P, Q, kchunks, ea);
         // few rows against a large layer (the paper's own benchmark shape, batch 1024 on 8192 x 8192): tall
         // tiles keep one workgroup per CU busy where 256 x 256 tiles would leave half the chip idle
         const int64_t tall_tiles = ((s.d_out + 255) / 256) * ((R + 127) / 128);
-        ea.pair_share = pairs;
         if (tall_tiles >= 192) {
             return launch_gemm<MmaBf16Blk16, 256, 128, 4, 2, Epi>(c, "forward_gemm_bf16_tall", P, Q, kchunks, ea);
         }
