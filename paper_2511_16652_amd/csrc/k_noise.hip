@@ -89,15 +89,18 @@ struct NoisePiece {
     uint32_t first_wg;    // first workgroup of the vector
     u32x4_t* out;
 };
-constexpr int NOISE_JOBS = 20;
+// Room for 20 vectors, or for 2: the host copies a launch's arguments, and a kilobyte of them is felt in a small call (attention of 16
+// members x 16 heads x 64 x 32 with the one vector of factors it needs, three launches: 13.1 us a call with room for 20, 12.4 for 2).
+constexpr int NOISE_JOBS = 20, NOISE_JOBS_FEW = 2;
+template <int JOBS>
 struct NoisePieces {
     int count;
-    NoisePiece job[NOISE_JOBS];
+    NoisePiece job[JOBS];
 };
 
-template <int MODE>
+template <int MODE, int JOBS>
 __global__ __launch_bounds__(256) void noise_pieces_kernel(uint32_t member_begin, IntMap im, const int8_t* __restrict__ table,
-                                                           NoisePieces jobs)
+                                                           NoisePieces<JOBS> jobs)
 {
     constexpr int BPP = (MODE == NM_BF16 || MODE == NM_I8_TABLE) ? 4 : 2;  // Threefry blocks per piece
     int j = 0;
@@ -190,17 +193,27 @@ egg_status launch_noise_jobs(eggroll_ctx* c, const NoiseJob* jobs, int count, ui
     const int per_piece = dist == EGG_RAW ? 4 : (table || dist == EGG_UNIFORM_INT ? 16 : (dtype == EGG_F32 ? 4 : 8));  // values
     const IntMap im = make_int_map(dist == EGG_UNIFORM_INT && !table ? int_bound : 0);
     const int8_t* tab = (const int8_t*)c->norm_tab.p;
-    NoisePieces np{};
+    NoisePieces<NOISE_JOBS> np{};
     uint32_t wgs = 0;
     auto flush = [&]() -> egg_status {
         if (np.count == 0) return EGG_OK;
         KernelScope ks(c, "noise_gen");
         const dim3 g(wgs), b(256);
-        if (dist == EGG_RAW) hipLaunchKernelGGL(noise_pieces_kernel<NM_RAW>, g, b, 0, c->stream, member_begin, im, tab, np);
-        else if (table) hipLaunchKernelGGL(noise_pieces_kernel<NM_I8_TABLE>, g, b, 0, c->stream, member_begin, im, tab, np);
-        else if (dist == EGG_UNIFORM_INT) hipLaunchKernelGGL(noise_pieces_kernel<NM_I8>, g, b, 0, c->stream, member_begin, im, tab, np);
-        else if (dtype == EGG_F32) hipLaunchKernelGGL(noise_pieces_kernel<NM_F32>, g, b, 0, c->stream, member_begin, im, tab, np);
-        else hipLaunchKernelGGL(noise_pieces_kernel<NM_BF16>, g, b, 0, c->stream, member_begin, im, tab, np);
+        auto launch = [&](auto jobs_c, const auto& args) {
+            constexpr int JOBS = decltype(jobs_c)::value;
+            if (dist == EGG_RAW) hipLaunchKernelGGL((noise_pieces_kernel<NM_RAW, JOBS>), g, b, 0, c->stream, member_begin, im, tab, args);
+            else if (table) hipLaunchKernelGGL((noise_pieces_kernel<NM_I8_TABLE, JOBS>), g, b, 0, c->stream, member_begin, im, tab, args);
+            else if (dist == EGG_UNIFORM_INT) hipLaunchKernelGGL((noise_pieces_kernel<NM_I8, JOBS>), g, b, 0, c->stream, member_begin, im, tab, args);
+            else if (dtype == EGG_F32) hipLaunchKernelGGL((noise_pieces_kernel<NM_F32, JOBS>), g, b, 0, c->stream, member_begin, im, tab, args);
+            else hipLaunchKernelGGL((noise_pieces_kernel<NM_BF16, JOBS>), g, b, 0, c->stream, member_begin, im, tab, args);
+        };
+        if (np.count <= NOISE_JOBS_FEW) {
+            NoisePieces<NOISE_JOBS_FEW> few{np.count, {}};
+            for (int q = 0; q < np.count; ++q) few.job[q] = np.job[q];
+            launch(std::integral_constant<int, NOISE_JOBS_FEW>{}, few);
+        } else {
+            launch(std::integral_constant<int, NOISE_JOBS>{}, np);
+        }
         np.count = 0;
         wgs = 0;
         return check_hip(c, hipGetLastError(), "noise_gen launch");
