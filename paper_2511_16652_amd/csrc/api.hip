@@ -132,8 +132,31 @@ egg_status forward_linear(eggroll_ctx* c, egg_key key, const egg_shape& shape, e
             if (s != EGG_OK) return s;
             t = (float*)c->t_buf.p;
         }
-        s = launch_project(c, make_stream_key(key.seed, key.step, key.layer, 1), shape, io_dtype, X, t, B_cache, panel);
-        if (s != EGG_OK) return s;
+        const StreamKey ka = make_stream_key(key.seed, key.step, key.layer, 0), kb = make_stream_key(key.seed, key.step, key.layer, 1);
+        // few members with many rows: their rows go to several workgroups, and the factors are drawn for all of them in one launch
+        // (with A, which that layer needs as well); the entry point that allocates nothing has no place for them but the caller's cache
+        const ProjectSplit split = project_split(c, shape, io_dtype, B_cache || !t_fixed);
+        void* B = B_cache;
+        if (split.ready) {
+            const int anti = shape.antithetic ? 2 : 1, esz = io_dtype == EGG_BF16 ? 2 : 4;
+            const int64_t ids = shape.member_count / anti, na = (int64_t)shape.d_out * shape.rank, nb = (int64_t)shape.d_in * shape.rank;
+            if (!B) {
+                if ((s = reserve(c, c->b_buf, (size_t)(ids * nb) * esz)) != EGG_OK) return s;
+                B = c->b_buf.p;
+            }
+            NoiseJob jobs[2] = {{kb, nb, B}, {ka, na, A_cache}};
+            const bool draw_A = A_cache || !A_ready;
+            if (draw_A && !A_cache) {
+                if ((s = reserve(c, c->a_buf, (size_t)(ids * na) * esz)) != EGG_OK) return s;
+                jobs[1].out = c->a_buf.p;
+            }
+            if ((s = launch_noise_jobs(c, jobs, draw_A ? 2 : 1, (uint32_t)(shape.member_begin / anti), ids, io_dtype, EGG_NORMAL, 0)) != EGG_OK) return s;
+            if (draw_A) {
+                A_ready = jobs[1].out;
+                A_cache = nullptr;
+            }
+        }
+        if ((s = launch_project(c, kb, shape, io_dtype, X, t, B, panel, split)) != EGG_OK) return s;
     }
     return launch_forward_gemm(c, make_stream_key(key.seed, key.step, key.layer, 0), shape, io_dtype, y_dtype, sigma, act, W, X, Y,
                                t, A_cache, resid, next, A_ready);

@@ -140,8 +140,15 @@ struct NoiseJob {
 };
 egg_status launch_noise_jobs(eggroll_ctx* c, const NoiseJob* jobs, int count, uint32_t member_begin, int64_t members, egg_dtype dtype,
                              egg_dist dist, int int_bound);
+// How the rows of a member (of a pair) are shared among workgroups of the projection pass: `parts` of `rows` each.  ready: B_cache holds
+// the factors already (otherwise every workgroup draws its member's, and fills B_cache if there is one).
+struct ProjectSplit {
+    int parts, rows;
+    bool ready;
+};
+ProjectSplit project_split(const eggroll_ctx* c, const egg_shape& s, egg_dtype io, bool ready);
 egg_status launch_project(eggroll_ctx* c, const StreamKey& kb, const egg_shape& s, egg_dtype io, const void* X,
-                          float* t, void* B_cache, bool panel);
+                          float* t, void* B_cache, bool panel, const ProjectSplit& split);
 // A layer whose output feeds the next perturbed layer directly (up-projection -> down-projection) can form that
 // layer's projections (same rank, 1, 2 or 4) in its own epilogue, from the bf16 values it stores: B = the next layer's
 // factors [member][d_out][rank] bf16, t = where the projections [rows][rank] go.  Supported where

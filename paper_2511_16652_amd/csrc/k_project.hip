@@ -2,14 +2,16 @@
 // (Sec. 4.2: for r = 1 "a batch of N vector-vector dot products of length d_in"; the B x r
 // intermediate of the arithmetic-intensity appendix).  One workgroup per member: B_i is regenerated
 // once into LDS (and optionally kept in the caller's cache), then the member's S rows are streamed
-// against it, one wave per row.  HBM-bound on X for large S, integer-ALU bound (noise) for S = 1.
+// against it, one wave per row (members with many rows share them among several workgroups, project_split).  HBM-bound on X for large S, integer-ALU bound (noise) for S = 1.
 // With antithetic pairs a workgroup owns a pair: the factors are generated once for its 2S rows.
 #include "common.hpp"
+#include <algorithm>
 
 namespace egg {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// The rows of a member are shared among blockIdx.y workgroups, part_rows (a multiple of 4) to each; with READY its factors stand in B_cache.
 // d_in is walked in panels of `panel` columns (a multiple of the 16-byte chunk, all of d_in when B_i fits the LDS budget):
 // per panel B_i[k0 .. k0 + panel) is regenerated into LDS and the member's rows are streamed against it; with more than
 // one panel the partial sums are carried in t itself (a row is always handled by the same wave).
@@ -21,14 +23,15 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // 64 x 64 of 2048, rank 8: 143 / 109; 1024 -> 1024, 256 x 16, rank 8: 30.7 / 29.1.
 // Below rank 8, and with one row to a wave, the loop over rows one at a time is as fast or faster (the registers of the deeper
 // form cost more waves than its loads hide: 64 rows of 2048 at rank 4 74.6 us against 68.3).
-template <bool BF16, int RANK, int NR>
-__global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t member_begin, int S, int anti_rows, int d_in, int panel,
-                                                      const void* __restrict__ X, float* __restrict__ t,
+template <bool BF16, int RANK, int NR, bool READY>
+__global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t member_begin, int S_all, int part_rows, int anti_rows, int d_in,
+                                                      int panel, const void* __restrict__ X, float* __restrict__ t,
                                                       void* __restrict__ B_cache)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x;
     const int64_t ml = blockIdx.x;  // local member
+    const int s_first = (int)blockIdx.y * part_rows, S = min(S_all, s_first + part_rows);
     const uint32_t member = member_begin + (uint32_t)ml;
     constexpr int EPC = BF16 ? 8 : 4;  // elements per 16-byte chunk of X (d_in is a multiple of it)
     // bf16 with more than one rank term: the panel sits in LDS rank-major ([l][column]), so that a 16-byte read holds the
@@ -37,6 +40,18 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
     constexpr bool TRANSPOSED = BF16 && RANK >= 2;
     const int lane = tid & 63, wave = tid >> 6;
     constexpr int U = 2;  // chunks of a row per step (NR > 1)
+    constexpr int BLOCKS_PER_PIECE = TRANSPOSED ? 8 : BF16 ? 4 : 2;
+    // columns 8 c8 .. 8 c8 + 7 of rank terms l and l + 1, a word per column -> the rank-major panel of kn columns
+    auto put_columns = [&](int c8, int l, int kn, const uint32_t (&pk)[8]) __attribute__((always_inline)) {
+        u32x4 r0, r1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            r0[e] = (pk[2 * e] & 0xFFFFu) | (pk[2 * e + 1] << 16);
+            r1[e] = (pk[2 * e] >> 16) | (pk[2 * e + 1] & 0xFFFF0000u);
+        }
+        *(u32x4*)((uint16_t*)smem + (int64_t)l * kn + c8 * 8) = r0;
+        *(u32x4*)((uint16_t*)smem + (int64_t)(l + 1) * kn + c8 * 8) = r1;
+    };
 
     for (int k0 = 0; k0 < d_in; k0 += panel) {
         const int kn = min(panel, d_in - k0);     // columns of this panel
@@ -46,22 +61,38 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
         auto load = [&](int s0, int ch0, uint4 (&x)[NR][U]) __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < NR; ++j) {
-                const int64_t row = ml * S + min(s0 + 4 * j, S - 1);
+                const int64_t row = ml * S_all + min(s0 + 4 * j, S - 1);
                 const uint4* xr = (const uint4*)((const char*)X + (row * (int64_t)d_in + k0) * (BF16 ? 2 : 4));
 #pragma unroll
                 for (int u = 0; u < U; ++u) x[j][u] = xr[min(ch0 + lane + 64 * u, chunks - 1)];
             }
         };
         uint4 xn[NR][U];
-        if constexpr (NR > 1) load(wave, 0, xn);
+        if constexpr (NR > 1) load(s_first + wave, 0, xn);
         const int n = kn * RANK;                  // even: d_in and panel are multiples of 4
         const int first = k0 * RANK;              // flat index of the panel's first factor entry (even)
         if (k0) __syncthreads();                  // every wave is done with the previous panel
         // ---- phase 1: B_i panel -> LDS (storage dtype), optional cache ---------------------------
+        if constexpr (READY) {
+            if constexpr (TRANSPOSED) {
+                // as below: 8 columns of two neighbouring rank terms, one word each
+                constexpr int LP = RANK / 2;
+                const uint32_t* const src = (const uint32_t*)B_cache + (ml * (int64_t)d_in * RANK + first) / 2;
+                for (int i = tid; i < (kn >> 3) * LP; i += 256) {
+                    const int c8 = i / LP, l = (i % LP) * 2;
+                    uint32_t pk[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) pk[e] = src[((c8 * 8 + e) * RANK + l) >> 1];
+                    put_columns(c8, l, kn, pk);
+                }
+            } else {
+                const uint4* const src = (const uint4*)((const char*)B_cache + (ml * (int64_t)d_in * RANK + first) * (BF16 ? 2 : 4));
+                for (int i = tid; i < n / EPC; i += 256) ((uint4*)smem)[i] = src[i];
+            }
+        } else
         // A thread expands several independent Threefry blocks and writes 16-byte pieces.
         // Where that would leave half of the threads without a piece, each expands one block at a time instead (512 columns at rank 1:
         // 64 pieces; the pass over 1618 antithetic pairs 5.7 us by pieces, 5.0 so).
-        constexpr int BLOCKS_PER_PIECE = TRANSPOSED ? 8 : BF16 ? 4 : 2;
         if ((n >> 1) <= 128 * BLOCKS_PER_PIECE) {
             for (int i = tid; i < (n >> 1); i += 256) {
                 const int gb = (first >> 1) + i;
@@ -101,14 +132,7 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
                     pk[e] = pack_bf16x2(z0, z1);
                     if (B_cache) ((uint32_t*)B_cache)[ml * (int64_t)((d_in * RANK) >> 1) + gb] = pk[e];
                 }
-                u32x4 r0, r1;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    r0[e] = (pk[2 * e] & 0xFFFFu) | (pk[2 * e + 1] << 16);
-                    r1[e] = (pk[2 * e] >> 16) | (pk[2 * e + 1] & 0xFFFF0000u);
-                }
-                *(u32x4*)((uint16_t*)smem + (int64_t)l * kn + c8 * 8) = r0;
-                *(u32x4*)((uint16_t*)smem + (int64_t)(l + 1) * kn + c8 * 8) = r1;
+                put_columns(c8, l, kn, pk);
             }
         } else {
             constexpr int BPP = BF16 ? 4 : 2;     // blocks per 16-byte piece of the flat vector
@@ -136,7 +160,7 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
         // ---- phase 2: one wave per row ------------------------------------------------------------
         // the sums of a row over the wave's lanes
         auto finish = [&](int s, float (&a)[RANK]) __attribute__((always_inline)) {
-            const int64_t row = ml * S + s;
+            const int64_t row = ml * S_all + s;
 #pragma unroll
             for (int l = 0; l < RANK; ++l) {
                 const float v = wave_sum(a[l]);  // (at rank 1 the order of the normalisation pass, which forms the same projections)
@@ -149,8 +173,8 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
             }
         };
       if constexpr (NR == 1) {
-        for (int s = wave; s < S; s += 4) {
-            const int64_t row = ml * S + s;
+        for (int s = s_first + wave; s < S; s += 4) {
+            const int64_t row = ml * S_all + s;
             const uint4* xr = (const uint4*)((const char*)X + (row * (int64_t)d_in + k0) * (BF16 ? 2 : 4));
             float acc[RANK];
 #pragma unroll
@@ -211,7 +235,7 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
             finish(s, acc);
         }
       } else {
-        for (int s0 = wave; s0 < S; s0 += 4 * NR) {
+        for (int s0 = s_first + wave; s0 < S; s0 += 4 * NR) {
             float acc[NR][RANK];
 #pragma unroll
             for (int j = 0; j < NR; ++j)
@@ -472,9 +496,11 @@ __global__ __launch_bounds__(512) void project_row8_kernel(StreamKey kb, uint32_
     if (tid < 8 && g * 8 + tid < members) t[g * 8 + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
 }
 
+constexpr int64_t PANEL_BYTES = 128 * 1024;  // B_i of a member in LDS, at most
+
 template <bool BF16>
 static egg_status launch_project_t(eggroll_ctx* c, const StreamKey& kb, const egg_shape& shape, const void* X, float* t,
-                                   void* B_cache, bool panel)
+                                   void* B_cache, bool panel, const ProjectSplit& split)
 {
     if (panel && B_cache) {
         if (!BF16 || shape.rank != 1 || shape.rows_per_member != 1 || shape.antithetic)
@@ -493,12 +519,12 @@ static egg_status launch_project_t(eggroll_ctx* c, const StreamKey& kb, const eg
         s.member_count /= 2;
         s.rows_per_member *= 2;
     }
-    // B_i panels of at most 128 KB in LDS: all of d_in when it fits, else the largest multiple of 64 columns
+    // all of d_in when its panel fits, else the largest multiple of 64 columns
     const int esz = BF16 ? 2 : 4;
     int kpanel = s.d_in;
-    if ((size_t)s.d_in * s.rank * esz > 128 * 1024) kpanel = (int)(128 * 1024 / ((size_t)s.rank * esz)) / 64 * 64;
+    if ((int64_t)s.d_in * s.rank * esz > PANEL_BYTES) kpanel = (int)(PANEL_BYTES / (s.rank * esz)) / 64 * 64;
     const size_t lds = (size_t)kpanel * s.rank * esz;
-    const dim3 g((unsigned)s.member_count), b(256);
+    const dim3 g((unsigned)s.member_count, (unsigned)split.parts), b(256);  // (at most four parts to a CU)
     if (s.member_count > 0x7FFFFFFF) return fail(c, EGG_EUNSUPPORTED, "too many members in one call");
     const uint32_t mb = (uint32_t)s.member_begin;
     if (s.rank == 1 && s.rows_per_member == 1) {
@@ -519,22 +545,22 @@ static egg_status launch_project_t(eggroll_ctx* c, const StreamKey& kb, const eg
     }
     // (rank 8 and 16) rows of a wave at once: four, or two, where the repeats this makes are at most an eighth of the rows (with more
     // the loop over single rows is level or faster: 5, 6, 9, 17 and 33 rows by 1 to 3 %)
-    const int S = s.rows_per_member;
+    const int S = std::min(s.rows_per_member, split.rows);
     auto fits = [&](int k) { return (int64_t)(S + 4 * k - 1) / (4 * k) * (4 * k) * 8 <= (int64_t)S * 9; };
     const int nr = fits(4) ? 4 : fits(2) ? 2 : 1;
 #define EGG_LAUNCH_PROJECT(R)                                                                                        \
     {                                                                                                                \
-        auto kern = project_kernel<BF16, R, 1>;                                                                      \
+        auto kern = split.ready ? project_kernel<BF16, R, 1, true> : project_kernel<BF16, R, 1, false>;              \
         if constexpr (R >= 8) {                                                                                      \
-            if (nr == 4) kern = project_kernel<BF16, R, 4>;                                                          \
-            if (nr == 2) kern = project_kernel<BF16, R, 2>;                                                          \
+            if (nr == 4) kern = split.ready ? project_kernel<BF16, R, 4, true> : project_kernel<BF16, R, 4, false>;  \
+            if (nr == 2) kern = split.ready ? project_kernel<BF16, R, 2, true> : project_kernel<BF16, R, 2, false>;  \
         }                                                                                                            \
         if (lds > 48 * 1024) {                                                                                       \
             egg_status st = ensure_dynamic_lds(c, (const void*)kern, (size_t)lds, "project smem attr"); \
             if (st != EGG_OK) return st;                                                                             \
         }                                                                                                            \
         KernelScope ks(c, "project");                                                                                \
-        hipLaunchKernelGGL(kern, g, b, lds, c->stream, kb, mb, s.rows_per_member, anti_rows, s.d_in, kpanel, X, t, B_cache);            \
+        hipLaunchKernelGGL(kern, g, b, lds, c->stream, kb, mb, s.rows_per_member, split.rows, anti_rows, s.d_in, kpanel, X, t, B_cache); \
     }
     switch (s.rank) {
         case 1: EGG_LAUNCH_PROJECT(1) break;
@@ -547,11 +573,36 @@ static egg_status launch_project_t(eggroll_ctx* c, const StreamKey& kb, const eg
     return check_hip(c, hipGetLastError(), "project launch");
 }
 
-egg_status launch_project(eggroll_ctx* c, const StreamKey& kb, const egg_shape& s, egg_dtype io, const void* X,
-                          float* t, void* B_cache, bool panel)
+// One workgroup per member leaves the chip idle where members are few and their rows many, so a member's rows are shared among as many
+// workgroups as make four to a CU, or two where there are more than half as many members as CUs (a row still belongs to one wave, and its
+// additions keep their order).  Every workgroup holds the whole panel of factors in LDS, which is drawn once by the noise kernel and
+// read back (drawing it again in each cost as much as the rows: 4096 columns of rank 8 are 11 us); so that a part's rows are worth that,
+// it has 8 rows or more, 16 where the panel is longer than 32 KB, 32 where it is walked in pieces or members are not that few.  Without a place for the factors they are
+// drawn by every workgroup, one to a CU.  Whole calls of bf16 layers with 256 outputs, one workgroup per member / this (us): 22 x 128 rows
+// of 8192, rank 1, pairs 175 / 74; 22 x 128 of 5664, rank 8 140 / 68; 25 x 178 of 400, rank 8 53 / 18; 109 x 20 of 1024, rank 16 38 / 30;
+// 105 x 100 of 768, rank 1 35 / 20; 256 x 64 of 2048, rank 4 42.7 / 41.7.  Beyond: 300 x 40 of 512, rank 1 in four parts 19.9 / 17.6,
+// but 400 x 64 of 2048, rank 4 56 / 63; and 256 x 16 of 1024, rank 8 in two parts of 8 23.6 / 25.4.
+ProjectSplit project_split(const eggroll_ctx* c, const egg_shape& shape, egg_dtype io, bool ready)
 {
-    return io == EGG_BF16 ? launch_project_t<true>(c, kb, s, X, t, B_cache, panel)
-                          : launch_project_t<false>(c, kb, s, X, t, B_cache, panel);
+    const int64_t ids = shape.antithetic ? shape.member_count / 2 : shape.member_count;
+    const int S = shape.antithetic ? 2 * shape.rows_per_member : shape.rows_per_member;
+    const ProjectSplit whole{1, S, false};
+    const bool few = 2 * ids <= c->compute_units;
+    const int64_t want = (int64_t)c->compute_units * (!ready ? 1 : few ? 4 : 2);
+    if (shape.rows_per_member == 1 || ids <= 0 || 2 * ids > want) return whole;
+    const int64_t panel = (int64_t)shape.d_in * shape.rank * (io == EGG_BF16 ? 2 : 4);
+    const int least = few && panel <= 32 * 1024 ? 8 : few && panel <= PANEL_BYTES ? 16 : 32;
+    const int64_t per = want / ids;
+    const int rows = std::max((int)((S + per - 1) / per + 3) / 4 * 4, least);
+    if (rows >= S) return whole;
+    return ProjectSplit{(S + rows - 1) / rows, rows, ready};
+}
+
+egg_status launch_project(eggroll_ctx* c, const StreamKey& kb, const egg_shape& s, egg_dtype io, const void* X,
+                          float* t, void* B_cache, bool panel, const ProjectSplit& split)
+{
+    return io == EGG_BF16 ? launch_project_t<true>(c, kb, s, X, t, B_cache, panel, split)
+                          : launch_project_t<false>(c, kb, s, X, t, B_cache, panel, split);
 }
 
 }  // namespace egg
