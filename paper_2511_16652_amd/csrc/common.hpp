@@ -247,6 +247,21 @@ egg_status launch_embed_i8(eggroll_ctx* c, egg_key key, const egg_shape& s, int 
 egg_status launch_egg_forward_i8(eggroll_ctx* c, egg_key key, const egg_shape& s, int L, int int_bound, int corr_shift, int T,
                                  const egg_model_i8& P, const uint8_t* tokens, const int8_t* S_in, int8_t* S_out,
                                  int8_t* logits);
+// the whole forward pass in one kernel at D = 256 (k_egg_fused.hip); factors: per layer A and B of Wf, Uf, Wh, Uh, then A1, B1, A2, B2,
+// fD bytes an array of D values per id and f4D one of 4 D
+struct EggFusedModel {
+    const int8_t *embA, *embB, *headA, *headB, *factors;
+    int64_t fD, f4D;
+    int8_t* weights;  // scratch, egg_fused_weight_bytes(L)
+    const uint8_t* tokens;
+    const int8_t* S_in;
+    int8_t *S_out, *logits;
+    int64_t rows;
+    int L, T, anti, corr_shift, out_shift;
+};
+bool egg_fused_applies(int D, int int_bound, int corr_shift, int out_shift);
+size_t egg_fused_weight_bytes(int L);
+egg_status launch_egg_fused(eggroll_ctx* c, const EggFusedModel& m, int int_bound, const egg_model_i8& P);
 egg_status launch_loglik_i8(eggroll_ctx* c, int64_t rows, const int8_t* logits, const uint8_t* targets, int accumulate, int32_t* out);
 // integer updates of several matrices of one population
 struct I8UpdateJob {

@@ -74,6 +74,22 @@ struct MmaF16 {
         c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
     }
 };
+// Stores and no-return atomics issued from inline asm, for the row-streaming kernels of the integer model.  The compiler's waitcnt
+// pass treats vmcnt as in-order only while nothing but loads is pending; one store it knows of turns every
+// later use of a loaded register into s_waitcnt vmcnt(0), which would drain the loads of later blocks at
+// each epilogue.  Operations it does not know of can only make its counted waits stricter (they occupy
+// counter slots), never weaker.  What is stored so is read back by its own lane alone, if at all.
+__device__ __forceinline__ void store16_untracked(void* p, const u32x4& v)
+{
+    // the two wait states cover the hazard between a store of more than 64 bits and a VALU write of its data
+    // registers, which the compiler's hazard recognizer handles for its own stores but cannot see inside asm
+    asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
+}
+__device__ __forceinline__ void atomic_add_untracked(int* p, int v)
+{
+    asm volatile("global_atomic_add %0, %1, off" ::"v"(p), "v"(v) : "memory");
+}
+
 struct MmaI8 {
     static constexpr int MFMA_PER_MMA = 1;
     static constexpr int BLK = 32;

@@ -263,6 +263,7 @@ egg_status launch_embed_i8(eggroll_ctx* c, egg_key key, const egg_shape& s, int 
     return launch_embed(c, emb, tokens, A, B, Y, rows, D, anti, corr_shift);
 }
 
+// At D = 256 all of it is one kernel (k_egg_fused.hip); what follows is the general form.
 // Scratch of one forward call: the rank-1 factors of all 6 L + 2 perturbed parameters (generated once per
 // call: a member's perturbation is fixed while it is evaluated, Alg. 1), the activations of one time
 // step, and a second copy of the recurrent state to ping-pong with S_out.
@@ -277,13 +278,16 @@ egg_status launch_egg_forward_i8(eggroll_ctx* c, egg_key key, const egg_shape& s
     const uint32_t first_id = (uint32_t)(anti ? s.member_begin / 2 : s.member_begin);
     const int os_d = 4 + ilog2(D) / 2, os_4d = os_d + 1;   // 16 sqrt(n) as a shift, n = D and 4 D
     auto pad = [](size_t b) { return (b + 255) & ~size_t(255); };
-    const size_t fD = pad((size_t)ids * D), f4D = pad((size_t)ids * 4 * D), f256 = pad((size_t)ids * 256);
+    const size_t id_pad = (size_t)ids + 127;   // (the fused kernel reads whole workgroups, of up to 128 ids)
+    const size_t fD = pad(id_pad * D), f4D = pad(id_pad * 4 * D), f256 = pad(id_pad * 256);
     const size_t act = pad((size_t)rows * D), dots = pad((size_t)rows * sizeof(int));
     const size_t per_layer = 8 * fD + 2 * (f4D + fD);
+    const bool fused = egg_fused_applies(D, int_bound, corr_shift, os_d);
     const size_t n_dots = 4 + 2 * (size_t)L;   // u.B_Wf, u.B_Wh, f^.B_Uh, one for the MLP and the head; s.B_Uf twice per layer
     const size_t total = 2 * (f256 + fD) + (size_t)L * per_layer   // factors
-                         + 7 * act + 4 * act                        // y, u, y', a1, a3, f, f^; MLP hidden
-                         + n_dots * dots + (T > 1 ? (size_t)L * act : 0);
+                         + (fused ? egg_fused_weight_bytes(L)
+                                  : 7 * act + 4 * act               // y, u, y', a1, a3, f, f^; MLP hidden
+                                        + n_dots * dots + (T > 1 ? (size_t)L * act : 0));
     egg_status st;
     if ((st = reserve(c, c->gru, total)) != EGG_OK) return st;
     char* p = (char*)c->gru.p;
@@ -314,6 +318,14 @@ egg_status launch_egg_forward_i8(eggroll_ctx* c, egg_key key, const egg_shape& s
         gen(base + 5, 1, 4 * D, F[i].B2);
     }
     if ((st = launch_noise_jobs(c, noise.data(), (int)noise.size(), first_id, ids, EGG_I8, EGG_UNIFORM_INT, int_bound)) != EGG_OK) return st;
+    if (fused) {
+        EggFusedModel m{};
+        m.embA = embA; m.embB = embB; m.headA = headA; m.headB = headB; m.factors = L ? F[0].A[0] : nullptr; m.fD = (int64_t)fD; m.f4D = (int64_t)f4D;
+        m.weights = take(egg_fused_weight_bytes(L));
+        m.tokens = tokens; m.S_in = S_in; m.S_out = S_out; m.logits = logits;
+        m.rows = rows; m.L = L; m.T = T; m.anti = anti; m.corr_shift = corr_shift; m.out_shift = os_d;
+        return launch_egg_fused(c, m, int_bound, P);
+    }
     int8_t *y = take(act), *u = take(act), *yp = take(act), *a1 = take(act), *a3 = take(act), *f = take(act), *fh = take(act);
     int8_t* hid = take(4 * act);
     int* dot[4];

@@ -121,22 +121,6 @@ struct I8Args {
     int8_t* g_out2;
 };
 
-// Stores and no-return atomics issued from inline asm, for the row-streaming kernel.  The compiler's waitcnt
-// pass treats vmcnt as in-order only while nothing but loads is pending; one store it knows of turns every
-// later use of a loaded register into s_waitcnt vmcnt(0), which would drain the loads of later blocks at
-// each epilogue.  Operations it does not know of can only make its counted waits stricter (they occupy
-// counter slots), never weaker.  Nothing in the kernel reads these locations back.
-__device__ __forceinline__ void store16_untracked(void* p, const u32x4& v)
-{
-    // the two wait states cover the hazard between a store of more than 64 bits and a VALU write of its data
-    // registers, which the compiler's hazard recognizer handles for its own stores but cannot see inside asm
-    asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
-}
-__device__ __forceinline__ void atomic_add_untracked(int* p, int v)
-{
-    asm volatile("global_atomic_add %0, %1, off" ::"v"(p), "v"(v) : "memory");
-}
-
 // MODE < 0: gate mode and next-dot accumulation are read from the arguments at run time (general core).
 // MODE >= 0: both are compile-time constants (gate = MODE & 3, next-dot = MODE >> 2), which strips the other
 // variants' code and their uniform branches from a kernel whose time goes into issuing the epilogue.  These
