@@ -129,71 +129,68 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(Operand P, Operand Q
     }
 }
 
-// The same for the bf16 forward layer, whose outputs must not depend on how many rows a call has (a population may be walked in
-// chunks): K is not split, every output is the one ascending chain of 16x16x32 MFMAs that the large tiles run.  A workgroup owns
-// 32 x 32 outputs, a wave a 16 x 16 block of them over all of K, its fragments straight from memory, two batches of eight k-steps
-// in flight; the chain itself is short (16 cycles a step).
-// Epi: struct Args; Epi(const Args&); extra<MT>(acc, m0, n0, lane, n_rows) adds to the block's accumulators; apply4 as above.
-template <class MT, class Epi>
-__global__ __launch_bounds__(256, 2) void gemm_small16_kernel(Operand P, Operand Q, int kchunks, int tiles_m, typename Epi::Args ea)
+// Products of few tiles that have to keep K whole (a layer's outputs must not depend on how many rows a call has): a workgroup of four waves
+// to a tile of 32 x 32 or 64 x 64, a wave to a quarter of it, four stages of K in flight through LDS, several workgroups to a CU.  Every
+// output is the one ascending chain of MFMAs that the large tiles run.  What bounds such a product is the latency of its loads and how
+// many CUs share them: tiles of 128 leave most CUs empty, fragments straight from memory waited for every eighth k-step (us, whole layers
+// at rank 2, before / 32 / 64: 328 outputs of 8192, 64 rows 72 / 27 / 38, 1580 rows 73 / 48 / 43, 2816 rows 75 / 57 / 58; 2048 x 2048, 512 rows
+// 25.7 / 20.5 / 18.2, 1024 rows 26.3 / 30.8 / 23.4; 1696 of 5664, 512 rows 57 / 52 / 34; one row per member 1024 x 1024, 486 rows at rank 1 21.4
+// / 9.4 / 11.0; 2048 of 4096, 900 rows at rank 4 65 / 61 / 46).  So: 32 up to two tiles a CU, 64 up to one, 32 again up to four
+// (ragged shapes), 64 up to two where there are outputs enough that rows are not read from memory alone (256 outputs of 2048, 4800 rows
+// 27.8 in tiles of 128 / 32.6; 328 of 8192, 4800 rows 81 / 104).  0: larger tiles.
+inline int deep_tile(int64_t M, int64_t N, int compute_units)
 {
-    static_assert(MT::BLK == 16, "16x16 MFMA blocks");
-    constexpr int U = 8;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int m0 = (int)(blockIdx.x % tiles_m) * 32 + (wave & 1) * 16, n0 = (int)(blockIdx.x / tiles_m) * 32 + (wave >> 1) * 16;
-    if (m0 >= P.rows || n0 >= Q.rows) return;  // (no barrier in this kernel)
-    const int fr = lane & 15, fc = lane >> 4;  // a k-step is four 16-byte chunks
-    const char* pa = P.base + (int64_t)min(m0 + fr, P.rows - 1) * P.row_stride;  // rows past the end re-read the last one
-    const char* qa = Q.base + (int64_t)min(n0 + fr, Q.rows - 1) * Q.row_stride;
-    typename MT::acc_t acc;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] = 0;
-    struct Batch {
-        u32x4 a[U], b[U];
-    };
-    auto load = [&](Batch& f, int s) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t c = min((s + u) * 4 + fc, kchunks - 1);  // unconditional, from a clamped chunk
-            f.a[u] = *(const u32x4*)(pa + c * P.kc_stride);
-            f.b[u] = *(const u32x4*)(qa + c * Q.kc_stride);
-        }
-    };
-    auto mul = [&](Batch& f, int s, bool tail) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (tail) {
-                const bool in = (s + u) * 4 + fc < kchunks;
-                f.a[u] = in ? f.a[u] : u32x4{0u, 0u, 0u, 0u};
-                f.b[u] = in ? f.b[u] : u32x4{0u, 0u, 0u, 0u};
-            }
-            MT::mma(f.a[u], f.b[u], acc);
-        }
-    };
-    const int steps = (kchunks + 3) / 4;
-    Batch f0, f1;
-    load(f0, 0);
-    int s = 0;
-    for (; (s + 2 * U) * 4 <= kchunks; s += 2 * U) {  // two whole batches: nothing to mask
-        load(f1, s + U);
-        mul(f0, s, false);
-        load(f0, s + 2 * U);  // (past the end: clamped, and masked below or never used)
-        mul(f1, s + U, false);
-    }
-    for (; s < steps; s += U) {
-        load(f1, s + U);
-        mul(f0, s, true);
-        f0 = f1;
-    }
-    Epi epi(ea);
-    epi.template extra<MT>(acc, m0, n0, lane, Q.rows);
-    const int m = m0 + fc * 4, n = n0 + fr;
-    const float v[4] = {acc[0], acc[1], acc[2], acc[3]};
-    if (m < P.rows && n < Q.rows) epi.apply4(m, n, v);
+    const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32), t64 = ((M + 63) / 64) * ((N + 63) / 64), cu = compute_units;
+    if (t32 <= 2 * cu) return 32;
+    if (t64 <= cu) return 64;
+    if (t32 <= 4 * cu) return 32;
+    return t64 <= 2 * cu && M >= 512 ? 64 : 0;
 }
-// Up to one tile of 32 x 32 per CU the bf16 layer takes it (us, this kernel / 128 x 128 tiles): 16 rows per member 256 x 64 x 4096
-// 41 / 46, 512 x 512 x 1024 19.7 / 20.6 (1024 x 512 x 1024: 28 / 21); one row per member 512 x 256 x 1024 14 / 24.
-inline bool small16(int64_t M, int64_t N, int compute_units) { return ((M + 31) / 32) * ((N + 31) / 32) <= compute_units; }
+
+// An epilogue for 4 outputs of a row (extra, apply4) applied straight from the accumulators, for the kernel of one small tile per workgroup
+template <class Row>
+struct DirectEpi {
+    typedef float value_t;
+    typedef typename Row::Args Args;
+    const Row row;
+    static constexpr __host__ __device__ int lds_per_wave(int) { return 0; }
+    __device__ __forceinline__ DirectEpi(const Args& a, char*, int) : row(a) {}
+    template <int MB, int NB>
+    __device__ __forceinline__ void prefetch(int, int, int, int) {}
+    template <class MT, int MB, int NB>
+    __device__ __forceinline__ void extra_mma(typename MT::acc_t (&acc)[MB][NB], int m0, int n0, int lane, int n_rows)
+    {
+        static_for<0, MB>([&](auto ic) __attribute__((always_inline)) {
+            static_for<0, NB>([&](auto jc) __attribute__((always_inline)) {
+                constexpr int i = decltype(ic)::value, j = decltype(jc)::value;
+                row.template extra<MT>(acc[i][j], m0 + i * 16, n0 + j * 16, lane, n_rows);
+            });
+        });
+    }
+    template <int J>
+    __device__ __forceinline__ void column_at(int, bool) {}
+    template <int I, int J>
+    __device__ __forceinline__ void store4_at(int m, int n, const float (&v)[4], bool valid, int) const
+    {
+        if (valid && m < row.a.d_out) row.apply4(m, n, v);
+    }
+    template <int W>
+    __device__ __forceinline__ void flush(int, int, int) {}
+};
+
+template <class MT, class Row, int T>
+egg_status launch_gemm_deep(eggroll_ctx* c, const char* name, const Operand& P, const Operand& Q, int kchunks, const typename Row::Args& ea)
+{
+    auto kern = gemm_nt_deep_kernel<MT, T, T, 2, 2, false, DirectEpi<Row>>;
+    const int tiles_m = (P.rows + T - 1) / T, tiles_n = (Q.rows + T - 1) / T;
+    const size_t lds = 2 * gemm_lds_bytes<T, T>();
+    if (!operand_offsets_fit(P, T) || !operand_offsets_fit(Q, T)) return fail(c, EGG_EUNSUPPORTED, "operand strides too large for 32-bit tile offsets");
+    const egg_status st = ensure_dynamic_lds(c, (const void*)kern, lds, "gemm smem attr");
+    if (st != EGG_OK) return st;
+    KernelScope ks(c, shaped_name(c, name, P.rows, kchunks * (Row::IS_BF16 ? 8 : 4)));
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(256), lds, c->stream, P, Q, kchunks, tiles_m, tiles_n,
+                       (const char*)c->zero_page.p, c->conservative_waits ? 1 : 0, ea);
+    return check_hip(c, hipGetLastError(), name);
+}
 
 }  // namespace egg

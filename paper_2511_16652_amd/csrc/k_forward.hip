@@ -421,61 +421,12 @@ struct FwdRowEpi {
     }
 };
 
-// A parked epilogue applied straight from the accumulators, for the kernel of one small tile per workgroup
-template <class Row>
-struct DirectEpi {
-    typedef float value_t;
-    typedef FwdArgs Args;
-    const Row row;
-    static constexpr __host__ __device__ int lds_per_wave(int) { return 0; }
-    __device__ __forceinline__ DirectEpi(const Args& a, char*, int) : row(a) {}
-    template <int MB, int NB>
-    __device__ __forceinline__ void prefetch(int, int, int, int) {}
-    template <class MT, int MB, int NB>
-    __device__ __forceinline__ void extra_mma(typename MT::acc_t (&)[MB][NB], int, int, int, int) {}
-    template <int J>
-    __device__ __forceinline__ void column_at(int, bool) {}
-    template <int I, int J>
-    __device__ __forceinline__ void store4_at(int m, int n, const float (&v)[4], bool valid, int) const
-    {
-        if (valid && m < row.a.d_out) row.apply4(m, n, v);
-    }
-    template <int W>
-    __device__ __forceinline__ void flush(int, int, int) {}
-};
-
 // fp32 products of up to four tiles of 32 x 32 per CU: a workgroup a tile, a wave a 16 x 16 block of it over all of K, four stages of K
 // in flight.  K stays whole, so that a row does not depend on how many rows the call has.  Measured (whole calls with 4 rows per
 // member at rank 1, us, 128 x 64 and 128 x 128 tiles / this): 256 x 64 x 256 18.5 / 14.1, x 2048 77.8 / 27.0; 512 x 512 x 1024 44.9 / 19.0;
 // 1024 x 1024 x 1024 46.5 / 35.5; beyond the line, 1400 x 1000 x 1024 46.8 / 47.8, 2048 x 1024 x 1024 47.3 / 60.0.  (K split over the
 // four waves of a tile, its partial sums added through LDS, was 13.8, 27.2, 19.7 and 39.2.)
 static bool deep_f32_tiles(int64_t M, int64_t N, int compute_units) { return ((M + 31) / 32) * ((N + 31) / 32) <= 4 * (int64_t)compute_units; }
-
-template <class Row>
-static egg_status launch_gemm_f32_deep(eggroll_ctx* c, const Operand& P, const Operand& Q, int kchunks, const FwdArgs& ea)
-{
-    constexpr int T = 32;
-    auto kern = gemm_nt_deep_kernel<MmaF32Blk16, T, T, 2, 2, false, DirectEpi<Row>>;
-    const int tiles_m = (P.rows + T - 1) / T, tiles_n = (Q.rows + T - 1) / T;
-    const size_t lds = 2 * gemm_lds_bytes<T, T>();
-    if (!operand_offsets_fit(P, T) || !operand_offsets_fit(Q, T)) return fail(c, EGG_EUNSUPPORTED, "operand strides too large for 32-bit tile offsets");
-    const egg_status st = ensure_dynamic_lds(c, (const void*)kern, lds, "gemm smem attr");
-    if (st != EGG_OK) return st;
-    KernelScope ks(c, shaped_name(c, "forward_gemm_f32", P.rows, kchunks * 4));
-    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(256), lds, c->stream, P, Q, kchunks, tiles_m, tiles_n,
-                       (const char*)c->zero_page.p, c->conservative_waits ? 1 : 0, ea);
-    return check_hip(c, hipGetLastError(), "forward_gemm_f32");
-}
-
-// bf16, for the products that small16 names
-template <class Epi>
-static egg_status launch_gemm_small16(eggroll_ctx* c, const Operand& P, const Operand& Q, int kchunks, const FwdArgs& ea)
-{
-    const int tm = (P.rows + 31) / 32, tn = (Q.rows + 31) / 32;
-    KernelScope ks(c, shaped_name(c, "forward_gemm_bf16_small", P.rows, kchunks * 8));
-    hipLaunchKernelGGL((gemm_small16_kernel<MmaBf16Blk16, Epi>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
-    return check_hip(c, hipGetLastError(), "forward_gemm_bf16_small");
-}
 
 template <class MT, int BM, int BN, int WM, int WN, class Epi>
 static egg_status launch_gemm(eggroll_ctx* c, const char* name, const Operand& P, const Operand& Q, int kchunks,
@@ -609,7 +560,9 @@ static egg_status launch_forward_t(eggroll_ctx* c, const StreamKey& ka, const eg
         // The correction per output (the same bits for any number of rows).  This epilogue is longer than a tile of 128 x 128 hides, so
         // the large tile pays earlier than in big_tiles: from more of them than half of the CUs, whatever of them is ragged (us,
         // 128 x 128 / 256 x 256: 3700 rows of 2048 -> 2100, S = 1 88.0 / 81.6; 3 rows per member at rank 4 100 / 93; 57344 of 2048 -> 104 250 / 231).
-        if (small16(s.d_out, R, c->compute_units) && (REGEN || ea.S < FOLD_MIN_ROWS)) return launch_gemm_small16<Epi>(c, P, Q, kchunks, ea);
+        const int deep = deep_tile(s.d_out, R, c->compute_units);
+        if (deep == 32) return launch_gemm_deep<MmaBf16Blk16, Epi, 32>(c, "forward_gemm_bf16_small", P, Q, kchunks, ea);
+        if (deep == 64) return launch_gemm_deep<MmaBf16Blk16, Epi, 64>(c, "forward_gemm_bf16_small", P, Q, kchunks, ea);
         ea.pair_share = pairs;
         if (((s.d_out + 255) / 256) * ((R + 255) / 256) > c->compute_units / 2)
             return launch_gemm<MmaBf16Blk16, 256, 256, 2, 4, Epi>(c, "forward_gemm_bf16", P, Q, kchunks, ea);
@@ -623,7 +576,7 @@ static egg_status launch_forward_t(eggroll_ctx* c, const StreamKey& ka, const eg
     } else {
         if (next) return fail(c, EGG_EINVAL, "this layer cannot form the next layer's projections (ask forward_fuses_next_projection first)");
         // (every form runs the same chain of products, k ascending: a row is the same bits for any number of rows)
-        if (deep_f32_tiles(s.d_out, R, c->compute_units)) return launch_gemm_f32_deep<Epi>(c, P, Q, kchunks, ea);
+        if (deep_f32_tiles(s.d_out, R, c->compute_units)) return launch_gemm_deep<MmaF32Blk16, Epi, 32>(c, "forward_gemm_f32", P, Q, kchunks, ea);
         ea.pair_share = pairs;
         if (narrow_f32_tiles(s.d_out, R, c->compute_units)) return launch_gemm<MmaF32, 128, 64, 2, 2, Epi>(c, "forward_gemm_f32", P, Q, kchunks, ea);
         return launch_gemm<MmaF32, 128, 128, 2, 2, Epi>(c, "forward_gemm_f32", P, Q, kchunks, ea);

@@ -181,6 +181,7 @@ template <int AW, int LEAN>
 struct FoldSmallEpi {
     typedef float value_t;
     typedef FoldArgs Args;
+    static constexpr bool IS_BF16 = true;
     const Args a;
     __device__ __forceinline__ FoldSmallEpi(const Args& a_) : a(a_) {}
     template <class MT>
@@ -255,12 +256,9 @@ template <int AW, int LEAN>
 static egg_status launch_fold_aw(eggroll_ctx* c, const Operand& P, const Operand& Q, int kchunks, const FoldArgs& ea)
 {
     // 256 x 256 tiles or four times as many of 128 x 128, two workgroups per CU or, where that leaves CUs empty, one.  K that is not made of whole stages takes the loaders with the zero page.
-    if (small16(P.rows, Q.rows, c->compute_units)) {
-        const int tm = (P.rows + 31) / 32, tn = (Q.rows + 31) / 32;
-        KernelScope ks(c, shaped_name(c, "forward_gemm_bf16_small", P.rows, kchunks * 8));
-        hipLaunchKernelGGL((gemm_small16_kernel<MmaBf16Blk16, FoldSmallEpi<AW, LEAN>>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
-        return check_hip(c, hipGetLastError(), "forward_gemm_bf16_small");
-    }
+    const int deep = deep_tile(P.rows, Q.rows, c->compute_units);
+    if (deep == 32) return launch_gemm_deep<MmaBf16Blk16, FoldSmallEpi<AW, LEAN>, 32>(c, "forward_gemm_bf16_small", P, Q, kchunks, ea);
+    if (deep == 64) return launch_gemm_deep<MmaBf16Blk16, FoldSmallEpi<AW, LEAN>, 64>(c, "forward_gemm_bf16_small", P, Q, kchunks, ea);
     if (big_tiles(P.rows, Q.rows, c->compute_units)) {
         if constexpr (AW > 0)  // (whole stages and nothing to correct: the parked form's kernel)
             if (kchunks % 8 == 0) return launch_fold_t<256, 256, 2, 4, 1, false, AW, LEAN>(c, "forward_gemm_bf16", P, Q, kchunks, ea);
