@@ -147,6 +147,22 @@ struct MmaF32Blk16 {
     }
 };
 
+// fp32 panels as two fp16 parts each, hi = the nearest fp16 value, lo = what it leaves: a stage of 8 chunks holds the hi parts of 32 k-values and
+// then their lo parts, 4 bytes a value as in fp32, and a pair of fragments is multiplied three times (lo lo is below 2^-24 of the product).
+// Three 16x16x32 MFMAs take 48 cycles where fp32 takes 256.
+struct MmaF16Split {
+    static constexpr int MFMA_PER_MMA = 1;
+    static constexpr int BLK = 16;
+    static constexpr bool SPLIT = true;
+    typedef f32x4 acc_t;
+    static __device__ __forceinline__ u32x4 arrange(const u32x4& x) { return x; }
+    static __device__ __forceinline__ void mma(const u32x4& a, const u32x4& b, acc_t& c) { MmaF16Blk16::mma(a, b, c); }
+};
+template <class MT, class = void>
+struct is_split : std::false_type {};
+template <class MT>
+struct is_split<MT, std::void_t<decltype(MT::SPLIT)>> : std::true_type {};
+
 // Store-only forward layers and updates take 256 x 256 tiles where those of 128 x 128 would be more than two for each CU: up to there
 // they are all at work at once, two workgroups to a CU, and waste less on ragged edges; beyond, they need a second wave where one of
 // the large tiles still does.  Measured on 256 CUs (us, 128 x 128 / 256 x 256).  Beyond two per CU: forward 2048 x 8192, 5760 rows 240 / 215;
@@ -807,7 +823,7 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P,
     const int64_t pstep = 8 * P.kc_stride, qstep = 8 * Q.kc_stride;
     const int KT = (kchunks + 7) >> 3;
 
-    constexpr int KSTEPS = 2, CPS = 4;
+    constexpr int KSTEPS = 2, CPS = 4, PRODUCTS = is_split<MT>::value ? 3 : KSTEPS;
     const int frow = lane & (BLK - 1);
     const int fsw = (frow >> 1) & 7;
     constexpr int BLK_STEP = KMAJOR ? BLK * 16 : BLK * PITCH;
@@ -844,6 +860,14 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P,
         for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[i][j][e] = 0;
+    // the products of hi with lo parts in accumulators of their own: a rounding of theirs is 2^-12 of one beside the hi parts' sum
+    typename MT::acc_t cross[is_split<MT>::value ? MB : 1][is_split<MT>::value ? NB : 1];
+    if constexpr (is_split<MT>::value) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) cross[i][j] = acc[i][j];
+    }
     u32x4 fa[2][KSTEPS][MB], fb[2][KSTEPS][NB];
 
     // the barrier without the memory fence of __syncthreads(), which would wait for every load in flight: what it orders is the
@@ -869,14 +893,20 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P,
         EGG_DEEP_BARRIER(IN_FLIGHT) /* stage KT_ + 1 has landed; every wave holds stage KT_ in registers */     \
         if (LOAD4) issue((KT_) + DEPTH);                                                                       \
         if (NEXT) EGG_DEEP_READ((SET) ^ 1, (KT_) + 1)                                                          \
-        _Pragma("unroll") for (int ks = 0; ks < KSTEPS; ++ks)                                                  \
+        /* products of k-steps (0, 0), (1, 1); of parts (hi, hi), (hi, lo), (lo, hi) */                       \
+        _Pragma("unroll") for (int ks = 0; ks < PRODUCTS; ++ks)                                                \
         {                                                                                                      \
-            _Pragma("unroll") for (int i = 0; i < MB; ++i) fa[SET][ks][i] = MT::arrange(fa[SET][ks][i]);       \
-            _Pragma("unroll") for (int j = 0; j < NB; ++j) fb[SET][ks][j] = MT::arrange(fb[SET][ks][j]);       \
+            const int ka_ = is_split<MT>::value ? ks >> 1 : ks, kb_ = is_split<MT>::value ? ks & 1 : ks;        \
+            _Pragma("unroll") for (int i = 0; i < MB; ++i) fa[SET][ka_][i] = MT::arrange(fa[SET][ka_][i]);     \
+            _Pragma("unroll") for (int j = 0; j < NB; ++j) fb[SET][kb_][j] = MT::arrange(fb[SET][kb_][j]);     \
             _Pragma("unroll") for (int i = 0; i < MB; ++i)                                                     \
-                _Pragma("unroll") for (int j = 0; j < NB; ++j) MT::mma(fa[SET][ks][i], fb[SET][ks][j], acc[i][j]); \
+                _Pragma("unroll") for (int j = 0; j < NB; ++j)                                                 \
+                {                                                                                              \
+                    if constexpr (is_split<MT>::value) MT::mma(fa[SET][ka_][i], fb[SET][kb_][j], ks ? cross[i][j] : acc[i][j]); \
+                    else MT::mma(fa[SET][ka_][i], fb[SET][kb_][j], acc[i][j]);                                 \
+                }                                                                                              \
         }                                                                                                      \
-        _Pragma("unroll") for (int r_ = 0; r_ < KSTEPS * MB * NB * MT::MFMA_PER_MMA; ++r_)                     \
+        _Pragma("unroll") for (int r_ = 0; r_ < PRODUCTS * MB * NB * MT::MFMA_PER_MMA; ++r_)                     \
         {                                                                                                      \
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                 \
             if ((NEXT) && r_ < KSTEPS * (MB + NB)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);          \
@@ -925,6 +955,12 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P,
 #undef EGG_ITER_DEEP
 #undef EGG_DEEP_READ
 #undef EGG_DEEP_BARRIER
+    if constexpr (is_split<MT>::value) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[i][j] += cross[i][j];
+    }
     Epi epi(ea, lds + DEPTH * STAGE_BYTES + wave * Epi::lds_per_wave(WTM), lane);
     epi.template prefetch<MB, NB>(m0 + wm * WTM, n0 + wn * WTN, lane, Q.rows);
     epi.template extra_mma<MT, MB, NB>(acc, m0 + wm * WTM, n0 + wn * WTN, lane, Q.rows);

@@ -9,7 +9,7 @@
 // 2^-25 it becomes zero -- about 5e-5 of N(0,1) draws, each contributing an absolute error <= 2^-25 to a product
 // of typical size 1.  The A panel holds (f_i / fnorm) a with |f_i / fnorm| <= 1, so members whose |f_i| is far
 // below max|f| lose relative precision the same way: the error per term is bounded by 2^-25 max|f|, i.e. it is
-// relative to the largest fitness, not to f_i.  fp32 factors stay fp32.  No atomics: each G entry has one owner
+// relative to the largest fitness, not to f_i.  fp32 factors stay fp32, or (MmaF16Split) are two fp16 parts of 22 bits and more.  No atomics: each G entry has one owner
 // and a fixed summation order, so the result is run-to-run identical.
 #include "common.hpp"
 #include "gemm_core.hpp"
@@ -228,6 +228,7 @@ __global__ __launch_bounds__(256) void pack_r1_kernel(const void* __restrict__ s
 // other kernel: bf16 factors times f_i / fnorm as the pack pass rounds them to fp16; fp32 factors stay fp32.
 //   rank 1:  a thread owns one column pair of EPC consecutive members -- one Threefry block per member -- and writes the two
 //            finished 16-byte chunks, which are neighbours in the panel;
+//   (parts: 8 kappa, a chunk of hi and one of lo parts for each column)
 //   rank >= 2: a thread owns one chunk, EPC consecutive kappa = i r + l of one column: EPC / 2 blocks.
 // The blocks of a thread are independent chains.  Vector-ALU bound: about 87 issue slots per block and the conversion.
 // Measured at 16384 members x (8192 + 2048) x rank 4 (bf16): 926 us (744 are the generator's issue slots); noise kernel
@@ -251,10 +252,29 @@ struct GenPackArgs {
 };
 constexpr int INLINE_NORM_MEMBERS = 1024;  // up to here the maximum over the fitness costs a workgroup less than a launch does
 
-template <bool BF16, int RANK>
+// how a panel holds its values: fp16 of bf16 factors; fp32; or (fp32 factors) two fp16 parts of 2^SPLIT_EXP times the value, the hi parts of 32 kappa
+// in four chunks, then their lo parts in four
+enum PanelForm { PANEL_F16, PANEL_F32, PANEL_SPLIT };
+constexpr int SPLIT_EXP = 12;   // factors are below 6 in magnitude, and so are those of the A panel: f_i / fnorm is 1 at most
+
+// the parts of v; an infinite one (an infinite fitness) goes into lo, where its products with the other panel's hi parts keep their
+// signs (its hi times a lo part would not), and a finite one too large (beside an infinite fitness) is cut to the largest
+__device__ __forceinline__ void split_f16(float v, _Float16& hi, _Float16& lo)
+{
+    const float x = v * (float)(1 << SPLIT_EXP);
+    hi = (_Float16)x;
+    lo = (_Float16)(x - (float)hi);
+    if (fabsf(x) > 65504.f) {
+        hi = __builtin_isinf(v) ? (_Float16)0.f : (_Float16)__builtin_copysignf(65504.f, v);
+        lo = __builtin_isinf(v) ? (_Float16)v : (_Float16)0.f;
+    }
+}
+
+template <PanelForm FORM, int RANK>
 __global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
 {
-    constexpr int EPC = BF16 ? 8 : 4;
+    constexpr bool BF16 = FORM == PANEL_F16;
+    constexpr int EPC = FORM == PANEL_F32 ? 4 : 8;
     const GenPackJob& J = g.job[blockIdx.x >= g.job[1].first_wg ? 1 : 0];
     const bool fit = J.fitness != nullptr;
     float finv = 1.f;
@@ -320,7 +340,7 @@ __global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
                 c0[w] = __builtin_bit_cast(uint32_t, a);
                 c1[w] = __builtin_bit_cast(uint32_t, b);
             }
-        } else {
+        } else if constexpr (FORM == PANEL_F32) {
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
                 c0[w] = __float_as_uint(lo[w]);
@@ -328,10 +348,30 @@ __global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
             }
         }
         u32x4* o = J.out + kg * J.d + 2 * u;
+        if constexpr (FORM == PANEL_SPLIT) {
+            u32x4 l0, l1;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                h2 h, l;
+                _Float16 p, q;
+                split_f16(lo[2 * w], p, q); h[0] = p; l[0] = q;
+                split_f16(lo[2 * w + 1], p, q); h[1] = p; l[1] = q;
+                c0[w] = __builtin_bit_cast(uint32_t, h);
+                l0[w] = __builtin_bit_cast(uint32_t, l);
+                split_f16(hi[2 * w], p, q); h[0] = p; l[0] = q;
+                split_f16(hi[2 * w + 1], p, q); h[1] = p; l[1] = q;
+                c1[w] = __builtin_bit_cast(uint32_t, h);
+                l1[w] = __builtin_bit_cast(uint32_t, l);
+            }
+            o = J.out + (kg + (kg & ~int64_t(3))) * J.d + 2 * u;
+            o[(int64_t)4 * J.d] = l0;
+            o[(int64_t)4 * J.d + 1] = l1;
+        }
         o[0] = c0;
         o[1] = c1;
     } else {
         constexpr int NB = EPC / 2;
+        u32x4 o_lo;
         float fs[NB];
 #pragma unroll
         for (int b = 0; b < NB; ++b) fs[b] = fs_of((kg * EPC + 2 * b) / RANK);
@@ -367,17 +407,30 @@ __global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
                 p[0] = (_Float16)z0;
                 p[1] = (_Float16)z1;
                 o[b] = __builtin_bit_cast(uint32_t, p);
+            } else if constexpr (FORM == PANEL_SPLIT) {
+                h2 h, l;
+                _Float16 p, q;
+                split_f16(z0, p, q); h[0] = p; l[0] = q;
+                split_f16(z1, p, q); h[1] = p; l[1] = q;
+                o[b] = __builtin_bit_cast(uint32_t, h);
+                o_lo[b] = __builtin_bit_cast(uint32_t, l);
             } else {
                 o[2 * b] = __float_as_uint(z0);
                 o[2 * b + 1] = __float_as_uint(z1);
             }
         }
-        J.out[kg * J.d + u] = o;
+        if constexpr (FORM == PANEL_SPLIT) {
+            u32x4* const to = J.out + (kg + (kg & ~int64_t(3))) * J.d + u;
+            to[0] = o;
+            to[(int64_t)4 * J.d] = o_lo;
+        } else {
+            J.out[kg * J.d + u] = o;
+        }
     }
 }
 
 // panels of the A and (out_b != NULL) the B factors
-static egg_status launch_gen_pack(eggroll_ctx* c, bool bf, const StreamKey& ka, const StreamKey& kb, const egg_shape& s, const float* fitness,
+static egg_status launch_gen_pack(eggroll_ctx* c, PanelForm form, const StreamKey& ka, const StreamKey& kb, const egg_shape& s, const float* fitness,
                                   float* fnorm, bool inline_norm, int64_t kgroups, void* out_a, void* out_b)
 {
     const int ua = s.rank == 1 ? s.d_out / 2 : s.d_out, ub = s.rank == 1 ? s.d_in / 2 : s.d_in;
@@ -404,7 +457,9 @@ static egg_status launch_gen_pack(eggroll_ctx* c, bool bf, const StreamKey& ka, 
         case 8: EGG_GEN_PACK(B, 8);   \
         default: EGG_GEN_PACK(B, 16); \
     }
-        if (bf) EGG_GEN_PACK_RANKS(true) else EGG_GEN_PACK_RANKS(false)
+        if (form == PANEL_F16) EGG_GEN_PACK_RANKS(PANEL_F16)
+        else if (form == PANEL_F32) EGG_GEN_PACK_RANKS(PANEL_F32)
+        else EGG_GEN_PACK_RANKS(PANEL_SPLIT)
 #undef EGG_GEN_PACK_RANKS
 #undef EGG_GEN_PACK
         const egg_status st = check_hip(c, hipGetLastError(), "update_pack launch");
@@ -420,6 +475,7 @@ struct UpdArgs {
     int d_out, d_in;
     float scale, lr;
     int accumulate, w_bf16;
+    float unit;  // a power of two: what a product of the panels' values stands for (UpdEpi16)
 };
 
 // MBLK: row blocks (of 32) per wave tile.  G is row-major [d_out][d_in] and a column n is one k: the 32 lanes of a
@@ -536,7 +592,7 @@ struct UpdEpi16 {
 #pragma unroll
             for (int it = 0; it < PASSES; ++it) {
                 const int64_t idx = at(it, in);
-                float v[4] = {scale * g[it].x, scale * g[it].y, scale * g[it].z, scale * g[it].w};
+                float v[4] = {scale * (a.unit * g[it].x), scale * (a.unit * g[it].y), scale * (a.unit * g[it].z), scale * (a.unit * g[it].w)};
                 if (a.accumulate) { v[0] += old[it].x; v[1] += old[it].y; v[2] += old[it].z; v[3] += old[it].w; }
                 if (!in) continue;
                 *(float4*)(a.G + idx) = make_float4(v[0], v[1], v[2], v[3]);
@@ -552,7 +608,7 @@ struct UpdEpi16 {
                 const int j = nb0 + c / WTM, k = mw0 + c % WTM;
                 if (j >= n_rows || k >= a.d_in) continue;
                 const int64_t idx = (int64_t)j * a.d_in + k;
-                float v = scale * *(const float*)(stage + (c / WTM) * P + (c % WTM) * 4);
+                float v = scale * (a.unit * *(const float*)(stage + (c / WTM) * P + (c % WTM) * 4));
                 if (a.accumulate) v += a.G[idx];
                 a.G[idx] = v;
                 if (a.W && a.w_bf16) {
@@ -628,7 +684,7 @@ static egg_status launch_upd_small(eggroll_ctx* c, const char* name, const Opera
 }
 
 // DEEP: one tile per CU with four stages in flight
-template <int BM, int BN, int WM, int WN, bool DEEP>
+template <class MT, int BM, int BN, int WM, int WN, bool DEEP>
 static egg_status launch_upd_gemm16(eggroll_ctx* c, const char* name, const Operand& P, const Operand& Q, int kchunks, const UpdArgs& ea)
 {
     typedef UpdEpi16<BM / WM> Epi;
@@ -638,13 +694,13 @@ static egg_status launch_upd_gemm16(eggroll_ctx* c, const char* name, const Oper
     const size_t lds = DEEP ? 2 * stages + epi : std::max(stages, epi);
     const dim3 g((unsigned)(tiles_m * tiles_n)), b(WM * WN * 64);
     if constexpr (DEEP) {
-        auto kern = gemm_nt_deep_kernel<MmaF16Blk16, BM, BN, WM, WN, true, Epi>;
+        auto kern = gemm_nt_deep_kernel<MT, BM, BN, WM, WN, true, Epi>;
         const egg_status st = ensure_dynamic_lds(c, (const void*)kern, lds, "gemm smem attr");
         if (st != EGG_OK) return st;
         KernelScope ks(c, name);
         hipLaunchKernelGGL(kern, g, b, lds, c->stream, P, Q, kchunks, tiles_m, tiles_n, (const char*)c->zero_page.p, c->conservative_waits ? 1 : 0, ea);
     } else {
-        auto kern = gemm_nt_kernel<MmaF16Blk16, BM, BN, WM, WN, true, Epi>;
+        auto kern = gemm_nt_kernel<MT, BM, BN, WM, WN, true, Epi>;
         const egg_status st = ensure_dynamic_lds(c, (const void*)kern, lds, "gemm smem attr");
         if (st != EGG_OK) return st;
         KernelScope ks(c, name);
@@ -671,6 +727,19 @@ static egg_status launch_upd_gemm(eggroll_ctx* c, const char* name, const Operan
     return check_hip(c, hipGetLastError(), name);
 }
 
+// fp32 factors generated for the call go into panels of two fp16 parts each (split_f16), multiplied by fp16 MFMAs: where the tiles of 32 x 32
+// are more than two to a CU, from 192 kappa on.  A fp32 MFMA takes 256 cycles for what three of those do in 48; what bounds the contraction then is
+// the rate at which a CU loads (32 KB for 32 kappa of a 128 x 128 tile).  Whole updates, us, fp32 MFMAs / 64 x 64 / 128 x 128 tiles of
+// parts: 1024 x 1024, K = 1024 41 / 25 / 38, 8000 220 / 106 / 185; 2048 x 2048, K = 300 39.5 / 27.5 / 28.7, 2048 161 / 83 / 77; 3280 x 1960,
+// K = 2048 287 / 152 / 122; 4096 x 4096, K = 8000 2094 / 1054 / 831.  Fewer tiles: 512 x 512, K = 300 11.5 / 13.8, 2048 35 / 34.
+// Error against 64 bits, relative 2-norm, fp32 MFMAs / parts: 1024 x 1024 (K split over four waves) K = 64 1.25e-7 / 1.36e-7, 192 1.57e-7 / 1.49e-7,
+// 700 2.64e-7 / 2.22e-7; 2048 x 2048 K = 192 2.58e-7 / 1.48e-7, 700 4.7e-7 / 2.2e-7, 8000 1.61e-6 / 5.9e-7.
+// (A caller's caches may hold any values: their updates stay on fp32 MFMAs.)
+static bool split_update(int64_t M, int64_t N, int64_t K, int compute_units)
+{
+    return ((M + 31) / 32) * ((N + 31) / 32) > 2 * (int64_t)compute_units && K >= 192;
+}
+
 egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& kb, const egg_shape& s,
                          egg_dtype noise_dtype, const float* fitness, float scale, int accumulate, float* G, void* W,
                          egg_dtype w_dtype, float lr, const void* A_cache, const void* B_cache, bool b_panel)
@@ -678,7 +747,12 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
     const bool bf = noise_dtype == EGG_BF16;
     const int esz = bf ? 2 : 4, epc = bf ? 8 : 4;
     const int64_t K = s.member_count * (int64_t)s.rank;
-    const int64_t kgroups = (K + epc - 1) / epc;
+    // Without caches the factors are generated straight into the panels (a rank-1 work item is a column pair: an odd width goes
+    // through the noise kernel and the pack pass, like the caches).
+    const bool gen_packed = !A_cache && (s.rank > 1 || (s.d_out % 2 == 0 && s.d_in % 2 == 0));
+    const bool split = !bf && gen_packed && split_update(s.d_out, s.d_in, K, c->compute_units);
+    // chunks of a panel; in parts, two for 8 kappa, whole stages of 32
+    const int64_t kgroups = split ? (K + 31) / 32 * 8 : (K + epc - 1) / epc;
     if (kgroups > 0x7FFFFFFF) return fail(c, EGG_EUNSUPPORTED, "population * rank too large");
     egg_status st;
 
@@ -687,16 +761,13 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
     if ((st = reserve(c, c->pack_a, (size_t)kgroups * s.d_out * 16)) != EGG_OK) return st;
     // b_panel: the caller's B_cache already is the packed panel (written by the forward pass); only A is generated
     if (!b_panel && (st = reserve(c, c->pack_b, (size_t)kgroups * s.d_in * 16)) != EGG_OK) return st;
-    // Without caches the factors are generated straight into the panels (a rank-1 work item is a column pair: an odd width goes
-    // through the noise kernel and the pack pass, like the caches).
-    const bool gen_packed = !A_cache && (s.rank > 1 || (s.d_out % 2 == 0 && s.d_in % 2 == 0));
     const bool inline_norm = gen_packed && s.member_count <= INLINE_NORM_MEMBERS;
     if (!inline_norm) {
         KernelScope ks(c, "fitness_norm");
         hipLaunchKernelGGL(fitness_norm_kernel, dim3(1), dim3(1024), 0, c->stream, fitness, s.member_count, fnorm);
     }
     if (gen_packed) {
-        if ((st = launch_gen_pack(c, bf, ka, kb, s, fitness, fnorm, inline_norm, kgroups, c->pack_a.p, b_panel ? nullptr : c->pack_b.p)) != EGG_OK) return st;
+        if ((st = launch_gen_pack(c, bf ? PANEL_F16 : split ? PANEL_SPLIT : PANEL_F32, ka, kb, s, fitness, fnorm, inline_norm, split ? kgroups / 2 : kgroups, c->pack_a.p, b_panel ? nullptr : c->pack_b.p)) != EGG_OK) return st;
     } else {
         // factors in [member][d][r] layout: the caller's caches, or regenerated into scratch
         const void* A_src = A_cache;
@@ -733,15 +804,20 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
 
     Operand P{(const char*)c->pack_a.p, 16, (int64_t)s.d_out * 16, s.d_out};
     Operand Q{(const char*)(b_panel ? B_cache : c->pack_b.p), 16, (int64_t)s.d_in * 16, s.d_in};
-    UpdArgs ea{G, W, fnorm, s.d_out, s.d_in, scale, lr, accumulate, w_dtype == EGG_BF16 ? 1 : 0};
+    UpdArgs ea{G, W, fnorm, s.d_out, s.d_in, scale, lr, accumulate, w_dtype == EGG_BF16 ? 1 : 0, split ? ldexpf(1.f, -2 * SPLIT_EXP) : 1.f};
+    if (split) {
+        if (((s.d_out + 63) / 64) * (int64_t)((s.d_in + 63) / 64) <= 2 * c->compute_units)
+            return launch_upd_gemm16<MmaF16Split, 64, 64, 2, 2, true>(c, "update_gemm_f32", Q, P, (int)kgroups, ea);
+        return launch_upd_gemm16<MmaF16Split, 128, 128, 2, 2, true>(c, "update_gemm_f32", Q, P, (int)kgroups, ea);
+    }
     if (const int small = small_tile(s.d_in, s.d_out, c->compute_units)) {
         return bf ? launch_upd_small<MmaF16>(c, "update_gemm_f16_small", Q, P, (int)kgroups, small, ea)
                   : launch_upd_small<MmaF32>(c, "update_gemm_f32", Q, P, (int)kgroups, small, ea);
     }
     if (bf) {
-        if (big_tiles(s.d_in, s.d_out, c->compute_units)) return launch_upd_gemm16<256, 256, 2, 4, false>(c, "update_gemm_f16", Q, P, (int)kgroups, ea);
+        if (big_tiles(s.d_in, s.d_out, c->compute_units)) return launch_upd_gemm16<MmaF16Blk16, 256, 256, 2, 4, false>(c, "update_gemm_f16", Q, P, (int)kgroups, ea);
         if (((s.d_out + 127) / 128) * (int64_t)((s.d_in + 127) / 128) <= c->compute_units)
-            return launch_upd_gemm16<128, 128, 2, 2, true>(c, "update_gemm_f16_small", Q, P, (int)kgroups, ea);
+            return launch_upd_gemm16<MmaF16Blk16, 128, 128, 2, 2, true>(c, "update_gemm_f16_small", Q, P, (int)kgroups, ea);
         // one to two 128 x 128 tiles per CU: 32x32 blocks, stores entry by entry.  The 16x16 form with two workgroups per CU is better
         // at middling K and worse at both ends (whole updates, us, this / that): 3072 x 2048, K = 8192 175 / 166, 32768 662 / 682;
         // 4096 x 2048, K = 256 23.7 / 26.0, 4096 114 / 107; 3000 x 2700, K = 2000 75 / 75.
