@@ -673,17 +673,16 @@ struct UpdSmallEpi {
     }
 };
 
-template <class MT>
-static egg_status launch_upd_small(eggroll_ctx* c, const char* name, const Operand& P, const Operand& Q, int kchunks, int tile, const UpdArgs& ea)
+template <class MT, int T>
+static egg_status launch_upd_small(eggroll_ctx* c, const char* name, const Operand& P, const Operand& Q, int kchunks, const UpdArgs& ea)
 {
-    const int tm = (P.rows + tile - 1) / tile, tn = (Q.rows + tile - 1) / tile;
+    const int tm = (P.rows + T - 1) / T, tn = (Q.rows + T - 1) / T;
     KernelScope ks(c, name);
-    if (tile == 32) hipLaunchKernelGGL((gemm_small_kernel<MT, 32, UpdSmallEpi>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
-    else hipLaunchKernelGGL((gemm_small_kernel<MT, 64, UpdSmallEpi>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
+    hipLaunchKernelGGL((gemm_small_kernel<MT, T, UpdSmallEpi>), dim3((unsigned)(tm * tn)), dim3(256), 0, c->stream, P, Q, kchunks, tm, ea);
     return check_hip(c, hipGetLastError(), name);
 }
 
-// DEEP: one tile per CU with four stages in flight
+// DEEP: four stages in flight, a workgroup a tile
 template <class MT, int BM, int BN, int WM, int WN, bool DEEP>
 static egg_status launch_upd_gemm16(eggroll_ctx* c, const char* name, const Operand& P, const Operand& Q, int kchunks, const UpdArgs& ea)
 {
@@ -810,10 +809,18 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
             return launch_upd_gemm16<MmaF16Split, 64, 64, 2, 2, true>(c, "update_gemm_f32", Q, P, (int)kgroups, ea);
         return launch_upd_gemm16<MmaF16Split, 128, 128, 2, 2, true>(c, "update_gemm_f32", Q, P, (int)kgroups, ea);
     }
-    if (const int small = small_tile(s.d_in, s.d_out, c->compute_units)) {
-        return bf ? launch_upd_small<MmaF16>(c, "update_gemm_f16_small", Q, P, (int)kgroups, small, ea)
-                  : launch_upd_small<MmaF32>(c, "update_gemm_f32", Q, P, (int)kgroups, small, ea);
+    const int small = small_tile(s.d_in, s.d_out, c->compute_units);
+    if (bf && small) {
+        // four stages of K in flight through LDS (whole updates, us, K split over the waves of a tile / this): tiles of 32 256 x 256, K = 2048 17.9 / 15.3,
+        // 8000 37.7 / 30.2, 1024 x 512, K = 1024 15.0 / 13.2; tiles of 64 1024 x 1024, K = 300 13.2 / 12.1, 2320 x 608, K = 300 16.2 / 14.5, 8000
+        // 104 / 103.  With one tile of 64 to a CU deeper K is better split: 1024 x 1024, K = 1024 16.1 / 16.6, 8000 58 / 61.
+        if (small == 32) return launch_upd_gemm16<MmaF16Blk16, 32, 32, 2, 2, true>(c, "update_gemm_f16_small", Q, P, (int)kgroups, ea);
+        const int64_t t64 = ((s.d_out + 63) / 64) * (int64_t)((s.d_in + 63) / 64);
+        if (t64 > c->compute_units || K <= 512) return launch_upd_gemm16<MmaF16Blk16, 64, 64, 2, 2, true>(c, "update_gemm_f16_small", Q, P, (int)kgroups, ea);
+        return launch_upd_small<MmaF16, 64>(c, "update_gemm_f16_small", Q, P, (int)kgroups, ea);
     }
+    if (small == 32) return launch_upd_small<MmaF32, 32>(c, "update_gemm_f32", Q, P, (int)kgroups, ea);
+    if (small) return launch_upd_small<MmaF32, 64>(c, "update_gemm_f32", Q, P, (int)kgroups, ea);
     if (bf) {
         if (big_tiles(s.d_in, s.d_out, c->compute_units)) return launch_upd_gemm16<MmaF16Blk16, 256, 256, 2, 4, false>(c, "update_gemm_f16", Q, P, (int)kgroups, ea);
         if (((s.d_out + 127) / 128) * (int64_t)((s.d_in + 127) / 128) <= c->compute_units)
