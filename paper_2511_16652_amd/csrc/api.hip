@@ -136,27 +136,27 @@ egg_status forward_linear(eggroll_ctx* c, egg_key key, const egg_shape& shape, e
         // few members with many rows: their rows go to several workgroups, and the factors are drawn for all of them in one launch
         // (with A, which that layer needs as well); the entry point that allocates nothing has no place for them but the caller's cache
         const ProjectSplit split = project_split(c, shape, io_dtype, B_cache || !t_fixed);
-        void* B = B_cache;
-        if (split.ready) {
-            const int anti = shape.antithetic ? 2 : 1, esz = io_dtype == EGG_BF16 ? 2 : 4;
-            const int64_t ids = shape.member_count / anti, na = (int64_t)shape.d_out * shape.rank, nb = (int64_t)shape.d_in * shape.rank;
-            if (!B) {
-                if ((s = reserve(c, c->b_buf, (size_t)(ids * nb) * esz)) != EGG_OK) return s;
-                B = c->b_buf.p;
-            }
-            NoiseJob jobs[2] = {{kb, nb, B}, {ka, na, A_cache}};
-            const bool draw_A = A_cache || !A_ready;
-            if (draw_A && !A_cache) {
-                if ((s = reserve(c, c->a_buf, (size_t)(ids * na) * esz)) != EGG_OK) return s;
-                jobs[1].out = c->a_buf.p;
-            }
-            if ((s = launch_noise_jobs(c, jobs, draw_A ? 2 : 1, (uint32_t)(shape.member_begin / anti), ids, io_dtype, EGG_NORMAL, 0)) != EGG_OK) return s;
-            if (draw_A) {
-                A_ready = jobs[1].out;
-                A_cache = nullptr;
-            }
+        const int anti = shape.antithetic ? 2 : 1, esz = io_dtype == EGG_BF16 ? 2 : 4;
+        const int64_t ids = shape.member_count / anti;
+        NoiseJob jobs[2] = {{kb, (int64_t)shape.d_in * shape.rank, B_cache}, {ka, (int64_t)shape.d_out * shape.rank, A_cache}};
+        const bool draw_A = !forward_regenerates(shape, sigma, A_cache) && (A_cache || !A_ready);
+        if (split.ready && !B_cache) {
+            if ((s = reserve(c, c->b_buf, (size_t)(ids * jobs[0].n) * esz)) != EGG_OK) return s;
+            jobs[0].out = c->b_buf.p;
         }
-        if ((s = launch_project(c, kb, shape, io_dtype, X, t, B, panel, split)) != EGG_OK) return s;
+        if (draw_A && !A_cache) {
+            if ((s = reserve(c, c->a_buf, (size_t)(ids * jobs[1].n) * esz)) != EGG_OK) return s;
+            jobs[1].out = c->a_buf.p;
+        }
+        NoisePiece along;
+        const bool with_A = draw_A && !split.ready && normal_pieces(jobs[1], ids, io_dtype, along) && project_draws_along(c, shape, io_dtype, split, along);
+        if (split.ready && (s = launch_noise_jobs(c, jobs, draw_A ? 2 : 1, (uint32_t)(shape.member_begin / anti), ids, io_dtype, EGG_NORMAL, 0)) != EGG_OK)
+            return s;
+        if (draw_A && (split.ready || with_A)) {
+            A_ready = jobs[1].out;
+            A_cache = nullptr;
+        }
+        if ((s = launch_project(c, kb, shape, io_dtype, X, t, jobs[0].out, panel, split, with_A ? &along : nullptr)) != EGG_OK) return s;
     }
     return launch_forward_gemm(c, make_stream_key(key.seed, key.step, key.layer, 0), shape, io_dtype, y_dtype, sigma, act, W, X, Y,
                                t, A_cache, resid, next, A_ready);
@@ -196,8 +196,7 @@ egg_status checked_forward(eggroll_ctx* c, egg_key key, const egg_shape* shape, 
             return fail(c, EGG_EUNSUPPORTED, "rows * rank = %lld exceeds the static scratch of %zu values", (long long)R * shape->rank,
                         t_capacity);
         // the one other scratch user of this path: factors materialised for S > 1 or rank > 1 go to the caller's cache
-        const bool regen = sigma == 0.0f || (shape->rank == 1 && shape->rows_per_member == 1 && !(shape->antithetic && A_cache));
-        if (!regen && !A_cache)
+        if (!forward_regenerates(*shape, sigma, A_cache) && !A_cache)
             return fail(c, EGG_EINVAL, "more than one row per member or rank > 1 materialises A_i: pass A_cache (this entry point does not allocate)");
     }
     if (t_in && B_cache) return fail(c, EGG_EINVAL, "given projections skip the pass that would fill B_cache: pass one or the other");

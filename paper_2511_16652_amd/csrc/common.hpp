@@ -140,6 +140,8 @@ struct NoiseJob {
 };
 egg_status launch_noise_jobs(eggroll_ctx* c, const NoiseJob* jobs, int count, uint32_t member_begin, int64_t members, egg_dtype dtype,
                              egg_dist dist, int int_bound);
+// normals that another kernel draws along with its own work: false where the vectors are not made of whole 16-byte pieces
+bool normal_pieces(const NoiseJob& job, int64_t members, egg_dtype dtype, NoisePiece& out);
 // How the rows of a member (of a pair) are shared among workgroups of the projection pass: `parts` of `rows` each.  ready: B_cache holds
 // the factors already (otherwise every workgroup draws its member's, and fills B_cache if there is one).
 struct ProjectSplit {
@@ -148,7 +150,9 @@ struct ProjectSplit {
 };
 ProjectSplit project_split(const eggroll_ctx* c, const egg_shape& s, egg_dtype io, bool ready);
 egg_status launch_project(eggroll_ctx* c, const StreamKey& kb, const egg_shape& s, egg_dtype io, const void* X,
-                          float* t, void* B_cache, bool panel, const ProjectSplit& split);
+                          float* t, void* B_cache, bool panel, const ProjectSplit& split, const NoisePiece* along = nullptr);
+// the projection pass can draw these vectors as well, in workgroups of its own
+bool project_draws_along(const eggroll_ctx* c, const egg_shape& s, egg_dtype io, const ProjectSplit& split, const NoisePiece& along);
 // A layer whose output feeds the next perturbed layer directly (up-projection -> down-projection) can form that
 // layer's projections (same rank, 1, 2 or 4) in its own epilogue, from the bf16 values it stores: B = the next layer's
 // factors [member][d_out][rank] bf16, t = where the projections [rows][rank] go.  Supported where
@@ -157,6 +161,11 @@ struct NextProjection {
     const void* B;
     float* t;
 };
+// one row per member at rank 1 (a kept cache of pairs apart): the epilogue draws the factors A itself
+inline bool forward_regenerates(const egg_shape& s, float sigma, const void* A_cache)
+{
+    return sigma == 0.f || (s.rank == 1 && s.rows_per_member == 1 && !(s.antithetic && A_cache));
+}
 bool forward_fuses_next_projection(const egg_shape& s, egg_dtype io, egg_dtype yd, float sigma, egg_act act, bool resid);
 // A_ready: the factors A that eggroll_noise_gen would write for this layer, already drawn by the caller (NULL: drawn here)
 egg_status launch_forward_gemm(eggroll_ctx* c, const StreamKey& ka, const egg_shape& s, egg_dtype io, egg_dtype yd,

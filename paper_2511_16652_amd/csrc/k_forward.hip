@@ -590,7 +590,7 @@ egg_status launch_forward_gemm(eggroll_ctx* c, const StreamKey& ka, const egg_sh
     const bool bf = io == EGG_BF16;
     // rank 1 with one row per member (or the unperturbed pass): regenerate in the epilogue
     // (with antithetic pairs a kept cache has one entry per pair, not per row: that goes the materialised way)
-    if (sigma == 0.f || (s.rank == 1 && s.rows_per_member == 1 && !(s.antithetic && A_cache))) {
+    if (forward_regenerates(s, sigma, A_cache)) {
         return bf ? launch_forward_t<true, 1, true>(c, ka, s, yd, sigma, act, W, X, Y, t, A_cache, resid, next)
                   : launch_forward_t<false, 1, true>(c, ka, s, yd, sigma, act, W, X, Y, t, A_cache, resid, next);
     }

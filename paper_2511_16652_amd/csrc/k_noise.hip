@@ -6,8 +6,6 @@
 
 namespace egg {
 
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
 enum NoiseMode { NM_F32 = 0, NM_BF16 = 1, NM_I8 = 2, NM_RAW = 3, NM_I8_TABLE = 4 };
 
 template <int MODE>
@@ -82,13 +80,6 @@ __global__ __launch_bounds__(256) void noise_gen_kernel(StreamKey key, uint32_t 
 // 64-bit division that the general kernel spends on every block, which was as long as the generator itself.
 // Several vectors of the same members (the factors of a layer's matrices) go out in one launch: a workgroup looks up its
 // vector by its number.  Vector-ALU bound.
-struct NoisePiece {
-    StreamKey key;
-    FastDiv per_member;   // pieces per member
-    uint32_t total;       // pieces
-    uint32_t first_wg;    // first workgroup of the vector
-    u32x4_t* out;
-};
 // Room for 20 vectors, or for 2: the host copies a launch's arguments, and a kilobyte of them is felt in a small call (attention of 16
 // members x 16 heads x 64 x 32 with the one vector of factors it needs, three launches: 13.1 us a call with room for 20, 12.4 for 2).
 constexpr int NOISE_JOBS = 20, NOISE_JOBS_FEW = 2;
@@ -110,26 +101,15 @@ __global__ __launch_bounds__(256) void noise_pieces_kernel(uint32_t member_begin
     if (i >= J.total) return;
     const uint32_t m = fast_div(J.per_member, i);
     const uint32_t blk = (i - m * J.per_member.d) * BPP;
+    if constexpr (MODE == NM_BF16 || MODE == NM_F32) {
+        J.out[i] = normal_piece<MODE == NM_BF16>(J.key, member_begin + m, blk);
+        return;
+    }
     uint32_t w[2 * BPP];
 #pragma unroll
     for (int b = 0; b < BPP; ++b) noise_words(J.key, member_begin + m, blk + b, w[2 * b], w[2 * b + 1]);
     uint32_t o[4];
-    if constexpr (MODE == NM_BF16) {
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            float z0, z1;
-            normal_pair<false>(w[2 * b], w[2 * b + 1], z0, z1);
-            o[b] = pack_bf16x2(z0, z1);
-        }
-    } else if constexpr (MODE == NM_F32) {
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            float z0, z1;
-            normal_pair<true>(w[2 * b], w[2 * b + 1], z0, z1);
-            o[2 * b] = __float_as_uint(z0);
-            o[2 * b + 1] = __float_as_uint(z1);
-        }
-    } else if constexpr (MODE == NM_RAW) {
+    if constexpr (MODE == NM_RAW) {
 #pragma unroll
         for (int b = 0; b < 4; ++b) o[b] = w[b];
     } else if constexpr (MODE == NM_I8_TABLE) {
@@ -141,7 +121,7 @@ __global__ __launch_bounds__(256) void noise_pieces_kernel(uint32_t member_begin
 #pragma unroll
         for (int b = 0; b < 4; ++b) o[b] = int4_from_word(im, w[b]);
     }
-    J.out[i] = u32x4_t{o[0], o[1], o[2], o[3]};
+    J.out[i] = noise_x4{o[0], o[1], o[2], o[3]};
 }
 
 static egg_status launch_noise_general(eggroll_ctx* c, const StreamKey& k, uint32_t member_begin, int64_t members, int64_t n,
@@ -180,6 +160,22 @@ egg_status ensure_normal_table(eggroll_ctx* c)
     const egg_status st = reserve(c, c->norm_tab, 65536);
     if (st != EGG_OK) return st;
     return check_hip(c, hipMemcpy(c->norm_tab.p, h.data(), 65536, hipMemcpyHostToDevice), "upload of the integer normal table");
+}
+
+// whole pieces, 32-bit piece numbers (the exact division needs them below 2^31): everything else goes value by value
+static bool whole_pieces(const NoiseJob& J, int per_piece, int64_t members)
+{
+    const int64_t ppm = J.n / per_piece;
+    return J.n % per_piece == 0 && aligned16(J.out) && ppm < (int64_t(1) << 31) && members <= ((int64_t(1) << 31) - 256) / std::max<int64_t>(ppm, 1);
+}
+
+bool normal_pieces(const NoiseJob& J, int64_t members, egg_dtype dtype, NoisePiece& out)
+{
+    const int per_piece = dtype == EGG_F32 ? 4 : 8;
+    if (J.n <= 0 || members <= 0 || !whole_pieces(J, per_piece, members)) return false;
+    const uint32_t ppm = (uint32_t)(J.n / per_piece);
+    out = NoisePiece{J.key, make_fast_div(ppm), (uint32_t)(members * ppm), 0, (noise_x4*)J.out};
+    return true;
 }
 
 egg_status launch_noise_jobs(eggroll_ctx* c, const NoiseJob* jobs, int count, uint32_t member_begin, int64_t members, egg_dtype dtype,
@@ -222,8 +218,7 @@ egg_status launch_noise_jobs(eggroll_ctx* c, const NoiseJob* jobs, int count, ui
     for (int q = 0; q < count; ++q) {
         const NoiseJob& J = jobs[q];
         const int64_t ppm = J.n / per_piece;
-        // whole pieces, 32-bit piece numbers (the exact division needs them below 2^31): everything else goes value by value
-        if (J.n % per_piece || !aligned16(J.out) || ppm >= (int64_t(1) << 31) || members > ((int64_t(1) << 31) - 256) / std::max<int64_t>(ppm, 1)) {
+        if (!whole_pieces(J, per_piece, members)) {
             if ((st = launch_noise_general(c, J.key, member_begin, members, J.n, dtype, dist, int_bound, J.out)) != EGG_OK) return st;
             continue;
         }
@@ -231,7 +226,7 @@ egg_status launch_noise_jobs(eggroll_ctx* c, const NoiseJob* jobs, int count, ui
         const uint32_t total = (uint32_t)(members * ppm), n_wg = (total + 255u) / 256u;
         if (np.count == NOISE_JOBS || wgs > 0x7FFFFFFFu - n_wg)
             if ((st = flush()) != EGG_OK) return st;
-        np.job[np.count++] = NoisePiece{J.key, make_fast_div((uint32_t)ppm), total, wgs, (u32x4_t*)J.out};
+        np.job[np.count++] = NoisePiece{J.key, make_fast_div((uint32_t)ppm), total, wgs, (noise_x4*)J.out};
         wgs += n_wg;
     }
     return flush();

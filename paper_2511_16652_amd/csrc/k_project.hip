@@ -11,6 +11,16 @@ namespace egg {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// workgroups past the members': 256 pieces each of the vectors drawn along (project_draws_along)
+template <bool BF16>
+__device__ __forceinline__ void draw_along(const NoisePiece& J, uint32_t member_begin)
+{
+    const uint32_t i = (blockIdx.x - J.first_wg) * 256u + threadIdx.x;
+    if (i >= J.total) return;
+    const uint32_t m = fast_div(J.per_member, i);
+    J.out[i] = normal_piece<BF16>(J.key, member_begin + m, (i - m * J.per_member.d) * (BF16 ? 4 : 2));
+}
+
 // The rows of a member are shared among blockIdx.y workgroups, part_rows (a multiple of 4) to each; with READY its factors stand in B_cache.
 // d_in is walked in panels of `panel` columns (a multiple of the 16-byte chunk, all of d_in when B_i fits the LDS budget):
 // per panel B_i[k0 .. k0 + panel) is regenerated into LDS and the member's rows are streamed against it; with more than
@@ -26,8 +36,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 template <bool BF16, int RANK, int NR, bool READY>
 __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t member_begin, int S_all, int part_rows, int anti_rows, int d_in,
                                                       int panel, const void* __restrict__ X, float* __restrict__ t,
-                                                      void* __restrict__ B_cache)
+                                                      void* __restrict__ B_cache, NoisePiece along)
 {
+    if (blockIdx.x >= along.first_wg) return draw_along<BF16>(along, member_begin);
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x;
     const int64_t ml = blockIdx.x;  // local member
@@ -361,8 +372,9 @@ __global__ __launch_bounds__(256) void project_row_kernel(StreamKey kb, uint32_t
 // 64 in the LDS form.
 template <bool BF16, int RANK, int NR>
 __global__ __launch_bounds__(256) void project_rows_rank_kernel(StreamKey kb, uint32_t member_begin, int d_in, const void* __restrict__ X,
-                                                                float* __restrict__ t, void* __restrict__ B_cache)
+                                                                float* __restrict__ t, void* __restrict__ B_cache, NoisePiece along)
 {
+    if (blockIdx.x >= along.first_wg) return draw_along<BF16>(along, member_begin);
     constexpr int EPP = BF16 ? 8 : 4, BPP = EPP / 2;
     constexpr int NL = RANK < EPP ? RANK : EPP;         // rank terms a thread meets
     constexpr int PPC = RANK > EPP ? RANK / EPP : 1;    // pieces per column
@@ -500,7 +512,7 @@ constexpr int64_t PANEL_BYTES = 128 * 1024;  // B_i of a member in LDS, at most
 
 template <bool BF16>
 static egg_status launch_project_t(eggroll_ctx* c, const StreamKey& kb, const egg_shape& shape, const void* X, float* t,
-                                   void* B_cache, bool panel, const ProjectSplit& split)
+                                   void* B_cache, bool panel, const ProjectSplit& split, const NoisePiece* with)
 {
     if (panel && B_cache) {
         if (!BF16 || shape.rank != 1 || shape.rows_per_member != 1 || shape.antithetic)
@@ -524,8 +536,11 @@ static egg_status launch_project_t(eggroll_ctx* c, const StreamKey& kb, const eg
     int kpanel = s.d_in;
     if ((int64_t)s.d_in * s.rank * esz > PANEL_BYTES) kpanel = (int)(PANEL_BYTES / (s.rank * esz)) / 64 * 64;
     const size_t lds = (size_t)kpanel * s.rank * esz;
-    const dim3 g((unsigned)s.member_count, (unsigned)split.parts), b(256);  // (at most four parts to a CU)
     if (s.member_count > 0x7FFFFFFF) return fail(c, EGG_EUNSUPPORTED, "too many members in one call");
+    NoisePiece along{};
+    if (with) along = *with;
+    along.first_wg = (uint32_t)s.member_count;  // (past the grid without them)
+    const dim3 g((unsigned)s.member_count + (along.total + 255u) / 256u, (unsigned)split.parts), b(256);  // (at most four parts to a CU)
     const uint32_t mb = (uint32_t)s.member_begin;
     if (s.rank == 1 && s.rows_per_member == 1) {
         KernelScope ks(c, "project");
@@ -536,8 +551,8 @@ static egg_status launch_project_t(eggroll_ctx* c, const StreamKey& kb, const eg
         KernelScope ks(c, "project");
 #define EGG_ROWS(R)                                                                                                                       \
     if (s.rank == R) {                                                                                                                    \
-        if (shape.antithetic) hipLaunchKernelGGL((project_rows_rank_kernel<BF16, R, 2>), g, b, 0, c->stream, kb, mb, s.d_in, X, t, B_cache); \
-        else hipLaunchKernelGGL((project_rows_rank_kernel<BF16, R, 1>), g, b, 0, c->stream, kb, mb, s.d_in, X, t, B_cache);               \
+        if (shape.antithetic) hipLaunchKernelGGL((project_rows_rank_kernel<BF16, R, 2>), g, b, 0, c->stream, kb, mb, s.d_in, X, t, B_cache, along); \
+        else hipLaunchKernelGGL((project_rows_rank_kernel<BF16, R, 1>), g, b, 0, c->stream, kb, mb, s.d_in, X, t, B_cache, along);               \
     }
         EGG_ROWS(2) EGG_ROWS(4) EGG_ROWS(8) EGG_ROWS(16)
 #undef EGG_ROWS
@@ -560,7 +575,7 @@ static egg_status launch_project_t(eggroll_ctx* c, const StreamKey& kb, const eg
             if (st != EGG_OK) return st;                                                                             \
         }                                                                                                            \
         KernelScope ks(c, "project");                                                                                \
-        hipLaunchKernelGGL(kern, g, b, lds, c->stream, kb, mb, s.rows_per_member, split.rows, anti_rows, s.d_in, kpanel, X, t, B_cache); \
+        hipLaunchKernelGGL(kern, g, b, lds, c->stream, kb, mb, s.rows_per_member, split.rows, anti_rows, s.d_in, kpanel, X, t, B_cache, along); \
     }
     switch (s.rank) {
         case 1: EGG_LAUNCH_PROJECT(1) break;
@@ -598,11 +613,25 @@ ProjectSplit project_split(const eggroll_ctx* c, const egg_shape& shape, egg_dty
     return ProjectSplit{(S + rows - 1) / rows, rows, ready};
 }
 
-egg_status launch_project(eggroll_ctx* c, const StreamKey& kb, const egg_shape& s, egg_dtype io, const void* X,
-                          float* t, void* B_cache, bool panel, const ProjectSplit& split)
+// The factors A that the layer needs beside the projections do not depend on them: they are drawn in the same launch, by workgroups
+// after the members'.  A launch of its own cost 3 us of the host's time and the chip ran empty before and after it.  Whole calls of bf16 layers
+// (us, apart / along): 256 -> 256, 256 members x 4 rows, rank 4 13.0 / 9.1; 1024 -> 1024, 256 x 16, rank 8 27.6 / 24.0; 8192 -> 8192, 1024 x 1,
+// rank 4 246.0 / 240.2; 1024 -> 1024, 4096 x 4, rank 16 243 / 237.  They take the LDS of the members' workgroups though, so where that leaves
+// one workgroup on a CU, only up to four times the CUs of them: 8192 -> 2048, 64 x 16, rank 8 84.7 / 81.7, but 1000 x 4 267 / 272 and fp32
+// 2048 -> 2048, 512 x 4, rank 16 263 / 293.  Rows in several parts have their factors, A too, from a launch before.
+bool project_draws_along(const eggroll_ctx* c, const egg_shape& shape, egg_dtype io, const ProjectSplit& split, const NoisePiece& along)
 {
-    return io == EGG_BF16 ? launch_project_t<true>(c, kb, s, X, t, B_cache, panel, split)
-                          : launch_project_t<false>(c, kb, s, X, t, B_cache, panel, split);
+    const int64_t ids = shape.antithetic ? shape.member_count / 2 : shape.member_count, wgs = (along.total + 255u) / 256u;
+    if (split.parts > 1 || ids + wgs >= int64_t(1) << 24) return false;  // (2^32 threads to a launch)
+    const int64_t lds = shape.rows_per_member == 1 && shape.rank > 1 ? 0 : (int64_t)shape.d_in * shape.rank * (io == EGG_BF16 ? 2 : 4);
+    return lds <= PANEL_BYTES / 2 || wgs <= 4 * (int64_t)c->compute_units;
+}
+
+egg_status launch_project(eggroll_ctx* c, const StreamKey& kb, const egg_shape& s, egg_dtype io, const void* X,
+                          float* t, void* B_cache, bool panel, const ProjectSplit& split, const NoisePiece* along)
+{
+    return io == EGG_BF16 ? launch_project_t<true>(c, kb, s, X, t, B_cache, panel, split, along)
+                          : launch_project_t<false>(c, kb, s, X, t, B_cache, panel, split, along);
 }
 
 }  // namespace egg

@@ -182,4 +182,38 @@ __device__ __forceinline__ float bf16_hi(uint32_t packed) { return __uint_as_flo
 // round an fp32 value to the nearest bf16 and return it as fp32
 __device__ __forceinline__ float round_bf16(float f) { return bf16_lo(pack_bf16x2(f, 0.f)); }
 
+typedef uint32_t noise_x4 __attribute__((ext_vector_type(4)));
+
+// 16 bytes of a factor vector: 8 normals in bf16 from the four blocks at blk, or 4 in fp32 from two
+template <bool BF16>
+__device__ __forceinline__ noise_x4 normal_piece(const StreamKey& k, uint32_t member, uint32_t blk)
+{
+    constexpr int BPP = BF16 ? 4 : 2;
+    uint32_t w[2 * BPP];
+#pragma unroll
+    for (int b = 0; b < BPP; ++b) noise_words(k, member, blk + b, w[2 * b], w[2 * b + 1]);
+    noise_x4 o;
+#pragma unroll
+    for (int b = 0; b < BPP; ++b) {
+        float z0, z1;
+        normal_pair<!BF16>(w[2 * b], w[2 * b + 1], z0, z1);
+        if constexpr (BF16) {
+            o[b] = pack_bf16x2(z0, z1);
+        } else {
+            o[2 * b] = __float_as_uint(z0);
+            o[2 * b + 1] = __float_as_uint(z1);
+        }
+    }
+    return o;
+}
+
+// vectors of one length, one per member and back to back, as 16-byte pieces: workgroup first_wg + g draws pieces 256 g .. 256 g + 255
+struct NoisePiece {
+    StreamKey key;
+    FastDiv per_member;   // pieces per member
+    uint32_t total;       // pieces
+    uint32_t first_wg;
+    noise_x4* out;
+};
+
 }  // namespace egg
