@@ -270,45 +270,40 @@ __device__ __forceinline__ void split_f16(float v, _Float16& hi, _Float16& lo)
     }
 }
 
+// 2^ceil(log2(max|f|)) over at most INLINE_NORM_MEMBERS members, found by the 256 threads of a workgroup
+__device__ __forceinline__ float workgroup_norm(const float* __restrict__ fitness, int64_t members)
+{
+    __shared__ float red[4];
+    float m = 0.f;
+#pragma unroll
+    for (int k = 0; k < INLINE_NORM_MEMBERS / 256; ++k) m = fmaxf(m, fabsf(fitness[min((int64_t)(k * 256 + threadIdx.x), members - 1)]));
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    return fitness_pow2(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
+}
+
+// what a thread draws: EPC kappa of one column, of the pair 2u and 2u + 1 at rank 1, and their lo parts
 template <PanelForm FORM, int RANK>
-__global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
+struct PanelChunks {
+    static constexpr int COLS = RANK == 1 ? 2 : 1;
+    u32x4 hi[COLS], lo[FORM == PANEL_SPLIT ? COLS : 1];
+};
+template <PanelForm FORM, int RANK>
+__device__ __forceinline__ PanelChunks<FORM, RANK> draw_chunks(const StreamKey& key, uint32_t member_begin, int64_t members,
+                                                               const float* __restrict__ fitness, float finv, int64_t kg, int u)
 {
     constexpr bool BF16 = FORM == PANEL_F16;
     constexpr int EPC = FORM == PANEL_F32 ? 4 : 8;
-    const GenPackJob& J = g.job[blockIdx.x >= g.job[1].first_wg ? 1 : 0];
-    const bool fit = J.fitness != nullptr;
-    float finv = 1.f;
-    if (fit) {
-        if (g.fnorm) {
-            finv = g.fnorm[1];
-        } else {
-            __shared__ float red[4];
-            float m = 0.f;
-#pragma unroll
-            for (int k = 0; k < INLINE_NORM_MEMBERS / 256; ++k) m = fmaxf(m, fabsf(J.fitness[min((int64_t)(k * 256 + threadIdx.x), g.members - 1)]));
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-            __syncthreads();
-            const float p = fitness_pow2(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
-            finv = 1.f / p;
-            if (blockIdx.x == 0 && threadIdx.x == 0) {
-                g.fnorm_out[0] = p;
-                g.fnorm_out[1] = finv;
-            }
-        }
-    }
-    const uint32_t i = (blockIdx.x - J.first_wg) * 256u + threadIdx.x;
-    if (i >= J.total) return;
-    const uint32_t q = fast_div(J.div, i);
-    const int u = (int)(i - q * J.div.d);
-    const int64_t kg = J.kg0 + q;
+    const bool fit = fitness != nullptr;
+    PanelChunks<FORM, RANK> out;
     typedef _Float16 h2 __attribute__((ext_vector_type(2)));
     // fitness of a member of this K group (members past the end count with 0: their entries of the A panel are zero)
     auto fs_of = [&](int64_t m) __attribute__((always_inline)) {
         if (!fit) return 1.f;
-        const float v = J.fitness[min(m, g.members - 1)];  // unconditional, from a clamped index
-        return m < g.members ? v * finv : 0.f;
+        const float v = fitness[min(m, members - 1)];  // unconditional, from a clamped index
+        return m < members ? v * finv : 0.f;
     };
     if constexpr (RANK == 1) {
         float lo[EPC], hi[EPC];  // columns 2u and 2u + 1 of the members
@@ -318,7 +313,7 @@ __global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
 #pragma unroll
         for (int e = 0; e < EPC; ++e) {
             uint32_t w0, w1;
-            noise_words(J.key, g.member_begin + (uint32_t)(kg * EPC + e), (uint32_t)u, w0, w1);
+            noise_words(key, member_begin + (uint32_t)(kg * EPC + e), (uint32_t)u, w0, w1);
             normal_pair<!BF16>(w0, w1, lo[e], hi[e]);
             if constexpr (BF16) {
                 const uint32_t pk = pack_bf16x2(lo[e], hi[e]);  // the factors are bf16 values
@@ -347,7 +342,6 @@ __global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
                 c1[w] = __float_as_uint(hi[w]);
             }
         }
-        u32x4* o = J.out + kg * J.d + 2 * u;
         if constexpr (FORM == PANEL_SPLIT) {
             u32x4 l0, l1;
 #pragma unroll
@@ -363,12 +357,11 @@ __global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
                 c1[w] = __builtin_bit_cast(uint32_t, h);
                 l1[w] = __builtin_bit_cast(uint32_t, l);
             }
-            o = J.out + (kg + (kg & ~int64_t(3))) * J.d + 2 * u;
-            o[(int64_t)4 * J.d] = l0;
-            o[(int64_t)4 * J.d + 1] = l1;
+            out.lo[0] = l0;
+            out.lo[1] = l1;
         }
-        o[0] = c0;
-        o[1] = c1;
+        out.hi[0] = c0;
+        out.hi[1] = c1;
     } else {
         constexpr int NB = EPC / 2;
         u32x4 o_lo;
@@ -382,7 +375,7 @@ __global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
             const int64_t m = kappa / RANK;
             const int l = (int)(kappa - m * RANK);
             uint32_t w0, w1;
-            noise_words(J.key, g.member_begin + (uint32_t)m, ((uint32_t)u * RANK + l) >> 1, w0, w1);
+            noise_words(key, member_begin + (uint32_t)m, ((uint32_t)u * RANK + l) >> 1, w0, w1);
             float z0, z1;
             normal_pair<!BF16>(w0, w1, z0, z1);
             if constexpr (BF16) {
@@ -419,13 +412,41 @@ __global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
                 o[2 * b + 1] = __float_as_uint(z1);
             }
         }
-        if constexpr (FORM == PANEL_SPLIT) {
-            u32x4* const to = J.out + (kg + (kg & ~int64_t(3))) * J.d + u;
-            to[0] = o;
-            to[(int64_t)4 * J.d] = o_lo;
+        if constexpr (FORM == PANEL_SPLIT) out.lo[0] = o_lo;
+        out.hi[0] = o;
+    }
+    return out;
+}
+
+template <PanelForm FORM, int RANK>
+__global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
+{
+    const GenPackJob& J = g.job[blockIdx.x >= g.job[1].first_wg ? 1 : 0];
+    float finv = 1.f;
+    if (J.fitness) {
+        if (g.fnorm) {
+            finv = g.fnorm[1];
         } else {
-            J.out[kg * J.d + u] = o;
+            const float p = workgroup_norm(J.fitness, g.members);
+            finv = 1.f / p;
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                g.fnorm_out[0] = p;
+                g.fnorm_out[1] = finv;
+            }
         }
+    }
+    const uint32_t i = (blockIdx.x - J.first_wg) * 256u + threadIdx.x;
+    if (i >= J.total) return;
+    const uint32_t q = fast_div(J.div, i);
+    const int u = (int)(i - q * J.div.d);
+    const int64_t kg = J.kg0 + q;
+    typedef PanelChunks<FORM, RANK> Chunks;
+    const Chunks ch = draw_chunks<FORM, RANK>(J.key, g.member_begin, g.members, J.fitness, finv, kg, u);
+    u32x4* const o = J.out + (FORM == PANEL_SPLIT ? kg + (kg & ~int64_t(3)) : kg) * J.d + Chunks::COLS * u;
+#pragma unroll
+    for (int c = 0; c < Chunks::COLS; ++c) {
+        o[c] = ch.hi[c];
+        if constexpr (FORM == PANEL_SPLIT) o[(int64_t)4 * J.d + c] = ch.lo[c];
     }
 }
 
@@ -632,6 +653,7 @@ struct UpdSmallEpi {
     const Args a;
     float scale;
     __device__ __forceinline__ UpdSmallEpi(const Args& a_) : a(a_) { scale = a.scale * a.fnorm[0]; }
+    __device__ __forceinline__ UpdSmallEpi(const Args& a_, float norm) : a(a_) { scale = a.scale * norm; }
     __device__ __forceinline__ void apply4(int m, int n, const float (&v)[4])
     {
         const int64_t at = (int64_t)n * a.d_in + m;
@@ -672,6 +694,109 @@ struct UpdSmallEpi {
         }
     }
 };
+
+// The whole update of a small population in one kernel: a workgroup draws the 32 columns of both panels that its 32 x 32 tile of G needs
+// into LDS and multiplies them there.  Drawing a panel again for every tile beside it costs less than a second launch there (3 us; each
+// thread draws K / 8 blocks).  The bits are those of the kernels that multiply packed panels of this size.
+struct UpdDrawArgs {
+    StreamKey ka, kb;
+    uint32_t member_begin;
+    int64_t members;
+    const float* fitness;
+    int kgroups, tiles_m;  // K groups in whole steps
+};
+template <PanelForm FORM, int RANK>
+__global__ __launch_bounds__(256) void upd_draw_kernel(UpdDrawArgs g, UpdArgs ea)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    static_assert(FORM != PANEL_SPLIT, "few tiles are not split");
+    typedef PanelChunks<FORM, RANK> Chunks;
+    constexpr int PER = 32 / Chunks::COLS;
+    u32x4* const panel = (u32x4*)smem;  // [B, A][kgroups][32]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m0 = (int)(blockIdx.x % g.tiles_m) * 32, n0 = (int)(blockIdx.x / g.tiles_m) * 32;  // k, j of G
+    const float norm = workgroup_norm(g.fitness, g.members);
+    const float finv = 1.f / norm;
+    const int items = g.kgroups * PER;
+    // columns past the end are drawn as well (any entries of the stream) and not stored
+    for (int i = tid; i < 2 * items; i += 256) {
+        const bool a = i >= items;
+        const int it = a ? i - items : i, kg = it / PER, u = it % PER;
+        const Chunks ch = draw_chunks<FORM, RANK>(a ? g.ka : g.kb, g.member_begin, g.members, a ? g.fitness : nullptr, finv, kg, (a ? n0 : m0) / Chunks::COLS + u);
+#pragma unroll
+        for (int c = 0; c < Chunks::COLS; ++c) panel[(a ? g.kgroups * 32 : 0) + kg * 32 + u * Chunks::COLS + c] = ch.hi[c];
+    }
+    __syncthreads();
+    UpdSmallEpi epi(ea, norm);
+    const u32x4 *const P = panel, *const Q = panel + g.kgroups * 32;
+    if constexpr (FORM == PANEL_F16) {
+        // a wave to a quarter of the tile, K ascending: the bits of the deep kernel
+        const int r = lane & 15, q = lane >> 4, mb = (wave & 1) * 16, nb = (wave >> 1) * 16;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int c = q; c < g.kgroups; c += 4) MmaF16Blk16::mma(P[c * 32 + mb + r], Q[c * 32 + nb + r], acc);
+        const float v[4] = {acc[0], acc[1], acc[2], acc[3]};
+        const int m = m0 + mb + 4 * q, n = n0 + nb + r;
+        if (m < ea.d_in && n < ea.d_out) epi.apply4(m, n, v);
+    } else {
+        // a wave to a quarter of K, the partial tiles added through LDS: the bits of gemm_small_kernel
+        constexpr int PITCH = 32 * 4 + 16;
+        const int fr = lane & 31, fc = lane >> 5;
+        const int steps = g.kgroups / 2, per = (steps + 3) / 4;
+        const int s0 = min(wave * per, steps), s1 = min(s0 + per, steps);
+        f32x16 acc;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+        for (int s = s0; s < s1; ++s) MmaF32::mma(P[(2 * s + fc) * 32 + fr], Q[(2 * s + fc) * 32 + fr], acc);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *(f32x4*)(smem + (wave * 32 + fr) * PITCH + (q * 8 + fc * 4) * 4) = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+        __syncthreads();
+        const int col = tid / 8, row = (tid % 8) * 4, m = m0 + row, n = n0 + col;
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const f32x4 x = *(const f32x4*)(smem + (w * 32 + col) * PITCH + row * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] += x[e];
+        }
+        if (m < ea.d_in && n < ea.d_out) epi.apply4(m, n, v);
+    }
+}
+
+// Where: for up to two tiles of 32 x 32 a CU and populations of up to 64 kappa, 128 in bf16 where a tile is alone on its CU.  Whole updates (us,
+// two kernels / this): bf16 256 x 256, K = 64 9.1 / 5.4, 128 9.1 / 6.7, 192 8.0 / 8.6; 1024 x 512 (512 tiles), K = 64 9.3 / 6.7, 128 9.3 / 9.8; fp32 256 x
+// 256, K = 64 9.2 / 6.0, 128 9.1 / 8.9 (rank 16 9.1 / 9.8); 1024 x 512, K = 64 9.5 / 7.8, 128 10.2 / 12.2.
+static bool draws_in_place(const egg_shape& s, bool bf, int compute_units)
+{
+    const int64_t tiles = ((s.d_out + 31) / 32) * (int64_t)((s.d_in + 31) / 32);
+    if (tiles > 2 * (int64_t)compute_units || s.member_count > INLINE_NORM_MEMBERS) return false;
+    return s.member_count * (int64_t)s.rank <= (bf && tiles <= compute_units ? 128 : 64);
+}
+
+static egg_status launch_upd_draw(eggroll_ctx* c, bool bf, const StreamKey& ka, const StreamKey& kb, const egg_shape& s, const float* fitness, const UpdArgs& ea)
+{
+    const int64_t K = s.member_count * (int64_t)s.rank;
+    const int kgroups = bf ? (int)((K + 31) / 32) * 4 : (int)((K + 7) / 8) * 2;
+    const int tm = (s.d_in + 31) / 32, tn = (s.d_out + 31) / 32;
+    const UpdDrawArgs g{ka, kb, (uint32_t)s.member_begin, s.member_count, fitness, kgroups, tm};
+    const size_t lds = std::max<size_t>((size_t)kgroups * 2 * 32 * 16, bf ? 0 : 4 * 32 * (32 * 4 + 16));
+    KernelScope ks(c, "update_gemm_drawn");
+#define EGG_UPD_DRAW(F, R) hipLaunchKernelGGL((upd_draw_kernel<F, R>), dim3((unsigned)(tm * tn)), dim3(256), lds, c->stream, g, ea); break
+#define EGG_UPD_DRAW_RANKS(F)         \
+    switch (s.rank) {                 \
+        case 1: EGG_UPD_DRAW(F, 1);   \
+        case 2: EGG_UPD_DRAW(F, 2);   \
+        case 4: EGG_UPD_DRAW(F, 4);   \
+        case 8: EGG_UPD_DRAW(F, 8);   \
+        default: EGG_UPD_DRAW(F, 16); \
+    }
+    if (bf) EGG_UPD_DRAW_RANKS(PANEL_F16)
+    else EGG_UPD_DRAW_RANKS(PANEL_F32)
+#undef EGG_UPD_DRAW_RANKS
+#undef EGG_UPD_DRAW
+    return check_hip(c, hipGetLastError(), "update_gemm_drawn launch");
+}
 
 template <class MT, int T>
 static egg_status launch_upd_small(eggroll_ctx* c, const char* name, const Operand& P, const Operand& Q, int kchunks, const UpdArgs& ea)
@@ -755,6 +880,8 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
     if (kgroups > 0x7FFFFFFF) return fail(c, EGG_EUNSUPPORTED, "population * rank too large");
     egg_status st;
 
+    if (gen_packed && !b_panel && draws_in_place(s, bf, c->compute_units))
+        return launch_upd_draw(c, bf, ka, kb, s, fitness, UpdArgs{G, W, nullptr, s.d_out, s.d_in, scale, lr, accumulate, w_dtype == EGG_BF16 ? 1 : 0, 1.f});
     if ((st = reserve(c, c->fnorm, 256)) != EGG_OK) return st;
     float* fnorm = (float*)c->fnorm.p;
     if ((st = reserve(c, c->pack_a, (size_t)kgroups * s.d_out * 16)) != EGG_OK) return st;
