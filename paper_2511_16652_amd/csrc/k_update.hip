@@ -4,6 +4,7 @@
 // Two steps: (1) a pack pass turns the [member][d][r] factors (the forward's caches, or freshly
 // regenerated ones) into K-packed panels -- 16-byte chunks of consecutive kappa for one column --
 // with the fitness folded into the A panel; (2) the MFMA NT core contracts the panels over K.
+// Small populations do both in one kernel (upd_draw_kernel).
 // bf16 factors are packed as fp16 (11 significant bits instead of 8 for f_i*a): a bf16 value of magnitude
 // >= 2^-14 is exact in fp16; below that it lands on fp16's subnormal grid (absolute error <= 2^-25) and below
 // 2^-25 it becomes zero -- about 5e-5 of N(0,1) draws, each contributing an absolute error <= 2^-25 to a product
@@ -231,7 +232,7 @@ __global__ __launch_bounds__(256) void pack_r1_kernel(const void* __restrict__ s
 //   (parts: 8 kappa, a chunk of hi and one of lo parts for each column)
 //   rank >= 2: a thread owns one chunk, EPC consecutive kappa = i r + l of one column: EPC / 2 blocks.
 // The blocks of a thread are independent chains.  Vector-ALU bound: about 87 issue slots per block and the conversion.
-// Measured at 16384 members x (8192 + 2048) x rank 4 (bf16): 926 us (744 are the generator's issue slots); noise kernel
+// Measured at 16384 members x (8192 + 2048) x rank 4 (bf16): 906 us (744 are the generator's issue slots); noise kernel
 // 2 x 640 us + pack pass 2 x 240 us before.
 struct GenPackJob {
     StreamKey key;
@@ -290,18 +291,18 @@ struct PanelChunks {
     static constexpr int COLS = RANK == 1 ? 2 : 1;
     u32x4 hi[COLS], lo[FORM == PANEL_SPLIT ? COLS : 1];
 };
-template <PanelForm FORM, int RANK>
+// (FIT, the A panel: times the fitness; fixed at compile time, as a branch in the code of both panels the pass of 16384 members x (8192 + 2048) x rank 4 took 923 us, 906 so)
+template <PanelForm FORM, int RANK, bool FIT>
 __device__ __forceinline__ PanelChunks<FORM, RANK> draw_chunks(const StreamKey& key, uint32_t member_begin, int64_t members,
                                                                const float* __restrict__ fitness, float finv, int64_t kg, int u)
 {
     constexpr bool BF16 = FORM == PANEL_F16;
     constexpr int EPC = FORM == PANEL_F32 ? 4 : 8;
-    const bool fit = fitness != nullptr;
     PanelChunks<FORM, RANK> out;
     typedef _Float16 h2 __attribute__((ext_vector_type(2)));
     // fitness of a member of this K group (members past the end count with 0: their entries of the A panel are zero)
     auto fs_of = [&](int64_t m) __attribute__((always_inline)) {
-        if (!fit) return 1.f;
+        if constexpr (!FIT) return 1.f;
         const float v = fitness[min(m, members - 1)];  // unconditional, from a clamped index
         return m < members ? v * finv : 0.f;
     };
@@ -320,7 +321,7 @@ __device__ __forceinline__ PanelChunks<FORM, RANK> draw_chunks(const StreamKey& 
                 lo[e] = bf16_lo(pk);
                 hi[e] = bf16_hi(pk);
             }
-            if (fit) {
+            if constexpr (FIT) {
                 lo[e] *= fs[e];
                 hi[e] *= fs[e];
             }
@@ -384,14 +385,14 @@ __device__ __forceinline__ PanelChunks<FORM, RANK> draw_chunks(const StreamKey& 
                 z1 = bf16_hi(pk);
             }
             if constexpr (BF16 && RANK < 16) {
-                if (fit) {
+                if constexpr (FIT) {
                     h2 p;
                     p[0] = f16_product(z0, fs[b]);
                     p[1] = f16_product(z1, fs[b]);
                     o[b] = __builtin_bit_cast(uint32_t, p);
                     continue;
                 }
-            } else if (fit) {
+            } else if constexpr (FIT) {
                 z0 *= fs[b];
                 z1 *= fs[b];
             }
@@ -441,7 +442,8 @@ __global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
     const int u = (int)(i - q * J.div.d);
     const int64_t kg = J.kg0 + q;
     typedef PanelChunks<FORM, RANK> Chunks;
-    const Chunks ch = draw_chunks<FORM, RANK>(J.key, g.member_begin, g.members, J.fitness, finv, kg, u);
+    const Chunks ch = J.fitness ? draw_chunks<FORM, RANK, true>(J.key, g.member_begin, g.members, J.fitness, finv, kg, u)
+                                : draw_chunks<FORM, RANK, false>(J.key, g.member_begin, g.members, nullptr, 1.f, kg, u);
     u32x4* const o = J.out + (FORM == PANEL_SPLIT ? kg + (kg & ~int64_t(3)) : kg) * J.d + Chunks::COLS * u;
 #pragma unroll
     for (int c = 0; c < Chunks::COLS; ++c) {
@@ -723,7 +725,8 @@ __global__ __launch_bounds__(256) void upd_draw_kernel(UpdDrawArgs g, UpdArgs ea
     for (int i = tid; i < 2 * items; i += 256) {
         const bool a = i >= items;
         const int it = a ? i - items : i, kg = it / PER, u = it % PER;
-        const Chunks ch = draw_chunks<FORM, RANK>(a ? g.ka : g.kb, g.member_begin, g.members, a ? g.fitness : nullptr, finv, kg, (a ? n0 : m0) / Chunks::COLS + u);
+        const Chunks ch = a ? draw_chunks<FORM, RANK, true>(g.ka, g.member_begin, g.members, g.fitness, finv, kg, n0 / Chunks::COLS + u)
+                            : draw_chunks<FORM, RANK, false>(g.kb, g.member_begin, g.members, nullptr, 1.f, kg, m0 / Chunks::COLS + u);
 #pragma unroll
         for (int c = 0; c < Chunks::COLS; ++c) panel[(a ? g.kgroups * 32 : 0) + kg * 32 + u * Chunks::COLS + c] = ch.hi[c];
     }
