@@ -185,7 +185,7 @@ egg_status eggroll_perturbed_forward_chained(eggroll_ctx* ctx, egg_key key, cons
  * The forward pass then costs one more write of the panel, and the update neither regenerates nor repacks B;
  * A is regenerated from the key (its panel carries the fitness, which the forward pass cannot know).
  * Supported for bf16, rank 1, one row per member, not antithetic; other shapes return EGG_EUNSUPPORTED when
- * a B_cache is passed.  Results of both calls are bit-identical to those of the default layout.
+ * a B_cache is passed, before any work is enqueued.  Results of both calls are bit-identical to those of the default layout.
  */
 typedef enum { EGG_CACHE_ROWS = 0, EGG_CACHE_PANEL = 1 } egg_cache_layout;
 egg_status eggroll_set_cache_layout(eggroll_ctx* ctx, egg_cache_layout layout);

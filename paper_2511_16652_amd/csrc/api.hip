@@ -199,6 +199,9 @@ egg_status checked_forward(eggroll_ctx* c, egg_key key, const egg_shape* shape, 
         if (!forward_regenerates(*shape, sigma, A_cache) && !A_cache)
             return fail(c, EGG_EINVAL, "more than one row per member or rank > 1 materialises A_i: pass A_cache (this entry point does not allocate)");
     }
+    // (before anything is enqueued: the factors of other shapes, in the default layout, are larger than the panel)
+    if (panel && B_cache && (io_dtype != EGG_BF16 || shape->rank != 1 || shape->rows_per_member != 1 || shape->antithetic))
+        return fail(c, EGG_EUNSUPPORTED, "the panel cache layout needs bf16, rank 1, one row per member, no antithetic pairs");
     if (t_in && B_cache) return fail(c, EGG_EINVAL, "given projections skip the pass that would fill B_cache: pass one or the other");
     if (want_next) {
         if (!t_next) return fail(c, EGG_EINVAL, "t_next must be non-NULL");

@@ -514,9 +514,7 @@ template <bool BF16>
 static egg_status launch_project_t(eggroll_ctx* c, const StreamKey& kb, const egg_shape& shape, const void* X, float* t,
                                    void* B_cache, bool panel, const ProjectSplit& split, const NoisePiece* with)
 {
-    if (panel && B_cache) {
-        if (!BF16 || shape.rank != 1 || shape.rows_per_member != 1 || shape.antithetic)
-            return fail(c, EGG_EUNSUPPORTED, "the panel cache layout needs bf16, rank 1, one row per member, no antithetic pairs");
+    if (panel && B_cache) {  // (bf16, rank 1, one row per member, no pairs: checked_forward)
         const int64_t groups = (shape.member_count + 7) / 8;
         if (groups > 0x7FFFFFFF) return fail(c, EGG_EUNSUPPORTED, "too many members in one call");
         KernelScope ks(c, "project");

@@ -178,6 +178,36 @@ def test_panel_cache_layout_is_bit_identical(d_out, d_in, N, mb):
         assert (panel[-1, :, N % 8:] == 0).all()
 
 
+@pytest.mark.parametrize("dtype,N,S,rank,anti", [("bf16", 64, 64, 4, 0), ("bf16", 64, 64, 1, 0), ("f32", 64, 64, 1, 0), ("bf16", 64, 1, 2, 0), ("bf16", 64, 1, 1, 1),
+                                                 ("f32", 64, 1, 1, 0), ("bf16", 16, 256, 16, 1)])
+@pytest.mark.parametrize("entry", ["plain", "noalloc", "add"])
+def test_panel_cache_refused_untouched(dtype, N, S, rank, anti, entry):
+    """Shapes that have no panel are refused before anything is written: neither the panel of the documented size nor what lies behind it, as
+    far as the factors in the default layout would reach, nor Y."""
+    import torch
+    d_out, d_in = 256, 2048
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator("cuda").manual_seed(2)
+    W, X = (torch.randn(s, generator=g, device="cuda").to(tdt) for s in ((d_out, d_in), (N * S, d_in)))
+    Y = torch.full((N * S, d_out), 7.0, dtype=tdt, device="cuda")
+    assert (N + 7) // 8 * d_in * 16 < N * d_in * rank * 4
+    B = torch.full((N * d_in * rank * 4,), 0xA5, dtype=torch.uint8, device="cuda")   # the panel is its first ceil(N / 8) d_in 16 bytes
+    c = eb.Context(0)
+    try:
+        c.eggroll_set_cache_layout(eb.EGG_CACHE_PANEL)
+        args = (eb.make_key(9, 2, 3), eb.make_shape(0, N, S, d_out, d_in, rank, anti), 0.05, eb.EGG_ACT_NONE, W, X)
+        forward = {"plain": c.eggroll_perturbed_forward, "noalloc": c.eggroll_perturbed_forward_noalloc, "add": c.eggroll_perturbed_forward_add}[entry]
+        # (without allocation, layers that materialise A need a cache for it, which the panel layout has not: invalid before it is unsupported)
+        code = eb.EGG_EINVAL if entry == "noalloc" and (S > 1 or rank > 1) else eb.EGG_EUNSUPPORTED
+        with pytest.raises(eb.EggrollError) as e:
+            forward(*args, *((Y.clone(),) if entry == "add" else ()), Y, None, B)
+        assert e.value.status == code
+        torch.cuda.synchronize()
+    finally:
+        c.close()
+    assert bool((B == 0xA5).all()) and bool((Y == 7.0).all())
+
+
 def test_rank_convergence_on_the_device(ctx):
     """The O(1/r) statement of Sec. "Rank Analysis" through the device path: fitness cos(<U, W_i>) from the
     perturbed forward (fp32, one row per member, x = v so that y_i = W_i v), the update from eggroll_update, for
