@@ -192,7 +192,7 @@ egg_status eggroll_set_cache_layout(eggroll_ctx* ctx, egg_cache_layout layout);
 
 /*
  * Diagnostic switch.  The row-streaming integer matmul (used at d_in = 256) and the kernel of products whose tiles leave compute
- * units empty (fp32 and bf16 layers, bf16 updates) keep loads in flight across their loop iterations and wait for them by count;
+ * units empty (layers and updates, fp32 and bf16) keep loads in flight across their loop iterations and wait for them by count;
  * with on != 0 they wait for every outstanding load instead (slower, no assumption about how many loads are in flight).  Results
  * are identical in both forms; tests hold one against the other.
  */
@@ -314,7 +314,9 @@ egg_status eggroll_egg_update_i8(eggroll_ctx* ctx, egg_key key, const egg_shape*
  * G: fp32 [d_out][d_in].  fitness: fp32 [member_count], used as given (centring / z-scoring /
  * ranking is the caller's shaping).  noise_dtype: EGG_BF16 or EGG_F32 -- the precision the forward
  * pass evaluated the factors in.  A_cache/B_cache: the side outputs of the forward (or of
- * eggroll_noise_gen); NULL = regenerate from the key.
+ * eggroll_noise_gen); NULL = regenerate from the key.  In EGG_F32 regenerated factors may be multiplied as three bf16 parts
+ * each, which hold all their bits (larger matrices and populations): G is then rounded in another order than from caches and
+ * agrees with that to fp32 rounding, not in bits.
  * If W != NULL:  W[j][k] += lr * G[j][k], rounded to w_dtype (EGG_BF16 or EGG_F32), after G is final.
  * rows_per_member is ignored.
  */

@@ -147,21 +147,25 @@ struct MmaF32Blk16 {
     }
 };
 
-// fp32 panels as two fp16 parts each, hi = the nearest fp16 value, lo = what it leaves: a stage of 8 chunks holds the hi parts of 32 k-values and
-// then their lo parts, 4 bytes a value as in fp32, and a pair of fragments is multiplied three times (lo lo is below 2^-24 of the product).
-// Three 16x16x32 MFMAs take 48 cycles where fp32 takes 256.
-struct MmaF16Split {
+// fp32 panels as three bf16 parts a value, hi, mid and lo, each the nearest to what those before it leave: all 24 bits of it, with fp32's range.
+// A stage of 12 chunks holds the hi parts of 32 k-values, then their mid parts, then lo.  Of the nine products of parts three are left out, mid lo and lo mid,
+// each at most 2^-24 of the whole product, and lo lo (of normal pairs 2^-27 of it together in the mean square; with the two of them in as well a single
+// product's error is 1 % less, 3.61e-8 for 3.65e-8).  Six 16x16x32 MFMAs take 96 cycles where fp32 takes 256.
+struct MmaF32Split {
     static constexpr int MFMA_PER_MMA = 1;
     static constexpr int BLK = 16;
     static constexpr bool SPLIT = true;
     typedef f32x4 acc_t;
+    // parts of either side, smallest products first
+    static constexpr int PRODUCTS = 6, PA[PRODUCTS] = {1, 0, 2, 0, 1, 0}, PB[PRODUCTS] = {1, 2, 0, 1, 0, 0};
     static __device__ __forceinline__ u32x4 arrange(const u32x4& x) { return x; }
-    static __device__ __forceinline__ void mma(const u32x4& a, const u32x4& b, acc_t& c) { MmaF16Blk16::mma(a, b, c); }
+    static __device__ __forceinline__ void mma(const u32x4& a, const u32x4& b, acc_t& c) { MmaBf16Blk16::mma(a, b, c); }
 };
 template <class MT, class = void>
 struct is_split : std::false_type {};
 template <class MT>
 struct is_split<MT, std::void_t<decltype(MT::SPLIT)>> : std::true_type {};
+constexpr int SPLIT_CHUNKS = 12, SPLIT_STAGES = 3;  // chunks of a stage in parts; stages in LDS (128 x 128 tiles: 144 KB)
 
 // Store-only forward layers and updates take 256 x 256 tiles where those of 128 x 128 would be more than two for each CU: up to there
 // they are all at work at once, two workgroups to a CU, and waste less on ragged edges; beyond, they need a second wave where one of
@@ -208,10 +212,11 @@ __device__ __forceinline__ void tile_coords(int pid, int tiles_m, int tiles_n, i
 typedef __attribute__((address_space(3))) void egg_lds_void;
 typedef __attribute__((address_space(1))) const void egg_glb_void;
 // TAIL = false: the caller guarantees that K is a whole number of stages (no zero-page redirection, and the
-// chunk numbers need not be kept).
-template <int ROWS, int NT, bool KMAJOR, bool TAIL = true>
+// chunk numbers need not be kept).  CHUNKS: of a stage (other than 8: K-packed operands only).
+template <int ROWS, int NT, bool KMAJOR, bool TAIL = true, int CHUNKS = 8>
 struct DmaLoader {
-    static constexpr int L = ROWS * 8 / NT;
+    static_assert(CHUNKS == 8 || KMAJOR, "row-major stages have 128 bytes a row");
+    static constexpr int L = ROWS * CHUNKS / NT;
     uint32_t off[L];
     int chunk[TAIL ? L : 1];
     __device__ __forceinline__ void init(const Operand& o, int row0, int tid)
@@ -241,9 +246,9 @@ struct DmaLoader {
 };
 
 // Largest per-lane byte offset the loader forms must fit 32 bits (checked on the host).
-inline bool operand_offsets_fit(const Operand& o, int tile_rows)
+inline bool operand_offsets_fit(const Operand& o, int tile_rows, int stage_chunks = 8)
 {
-    return (int64_t)tile_rows * o.row_stride + 8 * o.kc_stride < (int64_t(1) << 32);
+    return (int64_t)tile_rows * o.row_stride + stage_chunks * o.kc_stride < (int64_t(1) << 32);
 }
 
 template <int BM, int BN>
@@ -801,29 +806,32 @@ constexpr int vm_lds_imm(int n) { return 0x0070 | (n & 15) | ((n >> 4) << 14); }
 // about 65 bytes/ns, the rate the chip reaches per CU with all of them loading): 128 x 128 stages take 0.57 us, 0.66 in the
 // two-stage loop.  Layers of 1024 x 2048 rows, 1024 -> .. (us, before / now): K = 256 16.8 / 15.7, 1024 24.3 / 22.9, 4096 51.3 / 49.2.
 // fp32 runs it on 32 x 32 tiles, several workgroups to a CU (k_forward.hip): there the MFMAs are the bound, 256 cycles a stage.
+// fp32 in parts (MmaF32Split): three stages of 12 chunks, 48 KB each for 128 x 128 tiles, 0.7 us at that rate; their MFMAs take 0.64.
 // K-packed or row-major operands; epilogues as in the persistent kernel.  wait_all: the context's diagnostic switch, every wait of the
 // main loop is for everything.
 template <class MT, int BM, int BN, int WM, int WN, bool KMAJOR, class Epi>
 __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P, Operand Q, int kchunks, int tiles_m, int tiles_n,
                                                                  const char* zero_page, int wait_all, typename Epi::Args ea)
 {
-    constexpr int NT = WM * WN * 64, DEPTH = 4;
+    constexpr bool SPLIT = is_split<MT>::value;
+    static_assert(!SPLIT || KMAJOR, "parts are panels");
+    constexpr int NT = WM * WN * 64, DEPTH = SPLIT ? SPLIT_STAGES : 4;
     constexpr int WTM = BM / WM, WTN = BN / WN;
     constexpr int BLK = MT::BLK;
     static_assert(BLK == 16, "written for the 16x16x32 form");
     constexpr int MB = WTM / BLK, NB = WTN / BLK;
-    constexpr int PITCH = 128;
+    constexpr int CHUNKS = SPLIT ? SPLIT_CHUNKS : 8, PITCH = CHUNKS * 16;
     constexpr int STAGE_BYTES = (BM + BN) * PITCH;
-    static_assert(BM * 8 % NT == 0 && BN * 8 % NT == 0, "tile shape");
+    static_assert(BM * CHUNKS % NT == 0 && BN * CHUNKS % NT == 0, "tile shape");
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM, wn = wave / WM;
-    const int64_t pstep = 8 * P.kc_stride, qstep = 8 * Q.kc_stride;
-    const int KT = (kchunks + 7) >> 3;
+    const int64_t pstep = CHUNKS * P.kc_stride, qstep = CHUNKS * Q.kc_stride;
+    const int KT = (kchunks + CHUNKS - 1) / CHUNKS;
 
-    constexpr int KSTEPS = 2, CPS = 4, PRODUCTS = is_split<MT>::value ? 3 : KSTEPS;
+    constexpr int CPS = 4, KSTEPS = CHUNKS / CPS;   // (of a split stage: its parts)
     const int frow = lane & (BLK - 1);
     const int fsw = (frow >> 1) & 7;
     constexpr int BLK_STEP = KMAJOR ? BLK * 16 : BLK * PITCH;
@@ -842,16 +850,16 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P,
     const int m0 = tm * BM, n0 = tn * BN;
     const char* pb = P.base + (int64_t)m0 * P.row_stride;
     const char* qb = Q.base + (int64_t)n0 * Q.row_stride;
-    DmaLoader<BM, NT, KMAJOR> lp;
-    DmaLoader<BN, NT, KMAJOR> lq;
+    DmaLoader<BM, NT, KMAJOR, !SPLIT, CHUNKS> lp;  // (panels of parts are made of whole stages)
+    DmaLoader<BN, NT, KMAJOR, !SPLIT, CHUNKS> lq;
     lp.init(P, m0, tid);
     lq.init(Q, n0, tid);
-    constexpr int LOADS = DmaLoader<BM, NT, KMAJOR>::L + DmaLoader<BN, NT, KMAJOR>::L;  // of a wave per stage
+    constexpr int LOADS = decltype(lp)::L + decltype(lq)::L;  // of a wave per stage
     static_assert((DEPTH - 1) * LOADS < 64, "the counter holds the loads in flight");
     auto issue = [&](int kt) __attribute__((always_inline)) {
-        char* dst = lds + (kt & (DEPTH - 1)) * STAGE_BYTES;
-        lp.load(pb + (int64_t)kt * pstep, kt * 8, kchunks, zero_page, dst, wave);
-        lq.load(qb + (int64_t)kt * qstep, kt * 8, kchunks, zero_page, dst + BM * PITCH, wave);
+        char* dst = lds + (uint32_t)kt % DEPTH * STAGE_BYTES;
+        lp.load(pb + (int64_t)kt * pstep, kt * CHUNKS, kchunks, zero_page, dst, wave);
+        lq.load(qb + (int64_t)kt * qstep, kt * CHUNKS, kchunks, zero_page, dst + BM * PITCH, wave);
     };
     typename MT::acc_t acc[MB][NB];
 #pragma unroll
@@ -860,9 +868,9 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P,
         for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[i][j][e] = 0;
-    // the products of hi with lo parts in accumulators of their own: a rounding of theirs is 2^-12 of one beside the hi parts' sum
-    typename MT::acc_t cross[is_split<MT>::value ? MB : 1][is_split<MT>::value ? NB : 1];
-    if constexpr (is_split<MT>::value) {
+    // all products but those of hi parts in accumulators of their own: a rounding of theirs is 2^-8 of one beside the hi parts' sum
+    typename MT::acc_t cross[SPLIT ? MB : 1][SPLIT ? NB : 1];
+    if constexpr (SPLIT) {
 #pragma unroll
         for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -880,43 +888,56 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P,
     asm volatile("" ::: "memory");
 #define EGG_DEEP_READ(SET, KT_)                                                                                \
     {                                                                                                          \
-        const char* st_ = lds + ((KT_) & (DEPTH - 1)) * STAGE_BYTES;                                           \
+        const char* st_ = lds + (uint32_t)(KT_) % DEPTH * STAGE_BYTES;                                         \
         _Pragma("unroll") for (int ks = 0; ks < KSTEPS; ++ks)                                                  \
         {                                                                                                      \
             _Pragma("unroll") for (int j = 0; j < NB; ++j) fb[SET][ks][j] = *(const u32x4*)(st_ + b_base + foffb[ks] + j * BLK_STEP); \
             _Pragma("unroll") for (int i = 0; i < MB; ++i) fa[SET][ks][i] = *(const u32x4*)(st_ + a_base + foffa[ks] + i * BLK_STEP); \
         }                                                                                                      \
     }
+    // the products of a stage whose fragments are in set SET
+    auto products = [&](auto set_) __attribute__((always_inline)) {
+        constexpr int SET = decltype(set_)::value;
+        if constexpr (SPLIT) {
+            // (block rows outermost: the next stage's fragments of one take the place of those done with)
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int p = 0; p < MT::PRODUCTS; ++p)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) MT::mma(fa[SET][MT::PA[p]][i], fb[SET][MT::PB[p]][j], p == MT::PRODUCTS - 1 ? acc[i][j] : cross[i][j]);
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < KSTEPS; ++ks) {
+#pragma unroll
+                for (int i = 0; i < MB; ++i) fa[SET][ks][i] = MT::arrange(fa[SET][ks][i]);
+#pragma unroll
+                for (int j = 0; j < NB; ++j) fb[SET][ks][j] = MT::arrange(fb[SET][ks][j]);
+#pragma unroll
+                for (int i = 0; i < MB; ++i)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) MT::mma(fa[SET][ks][i], fb[SET][ks][j], acc[i][j]);
+            }
+        }
+    };
     // stage KT_, its fragments in set SET; IN_FLIGHT: stages issued after stage KT_ + 1 that may still be under way
 #define EGG_ITER_DEEP(KT_, SET, NEXT, LOAD4, IN_FLIGHT)                                                        \
     {                                                                                                          \
         EGG_DEEP_BARRIER(IN_FLIGHT) /* stage KT_ + 1 has landed; every wave holds stage KT_ in registers */     \
         if (LOAD4) issue((KT_) + DEPTH);                                                                       \
         if (NEXT) EGG_DEEP_READ((SET) ^ 1, (KT_) + 1)                                                          \
-        /* products of k-steps (0, 0), (1, 1); of parts (hi, hi), (hi, lo), (lo, hi) */                       \
-        _Pragma("unroll") for (int ks = 0; ks < PRODUCTS; ++ks)                                                \
-        {                                                                                                      \
-            const int ka_ = is_split<MT>::value ? ks >> 1 : ks, kb_ = is_split<MT>::value ? ks & 1 : ks;        \
-            _Pragma("unroll") for (int i = 0; i < MB; ++i) fa[SET][ka_][i] = MT::arrange(fa[SET][ka_][i]);     \
-            _Pragma("unroll") for (int j = 0; j < NB; ++j) fb[SET][kb_][j] = MT::arrange(fb[SET][kb_][j]);     \
-            _Pragma("unroll") for (int i = 0; i < MB; ++i)                                                     \
-                _Pragma("unroll") for (int j = 0; j < NB; ++j)                                                 \
-                {                                                                                              \
-                    if constexpr (is_split<MT>::value) MT::mma(fa[SET][ka_][i], fb[SET][kb_][j], ks ? cross[i][j] : acc[i][j]); \
-                    else MT::mma(fa[SET][ka_][i], fb[SET][kb_][j], acc[i][j]);                                 \
-                }                                                                                              \
-        }                                                                                                      \
-        _Pragma("unroll") for (int r_ = 0; r_ < PRODUCTS * MB * NB * MT::MFMA_PER_MMA; ++r_)                     \
+        products(std::integral_constant<int, SET>{});                                                          \
+        constexpr int MFMAS = (SPLIT ? 6 : KSTEPS) * MB * NB * MT::MFMA_PER_MMA;                               \
+        _Pragma("unroll") for (int r_ = 0; r_ < MFMAS; ++r_)                                                   \
         {                                                                                                      \
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                 \
             if ((NEXT) && r_ < KSTEPS * (MB + NB)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);          \
         }                                                                                                      \
     }
-    issue(0);
-    if (KT > 1) issue(1);
-    if (KT > 2) issue(2);
-    if (KT > 3) issue(3);
-    if (KT > 3) { EGG_DEEP_BARRIER(3) }
+#pragma unroll
+    for (int q = 0; q < DEPTH; ++q)
+        if (q < KT) issue(q);
+    if (KT >= DEPTH) { EGG_DEEP_BARRIER(DEPTH - 1) }
     else { EGG_DEEP_BARRIER(0) }
     EGG_DEEP_READ(0, 0)
     int kt = 0;
@@ -936,14 +957,14 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P,
         }
     }
     // the last stages, nothing more to issue: KT - 2 - kt stages are under way beyond stage kt + 1
-    const int left = KT - kt;  // 1 .. 4
-    if (left == 4) {
+    const int left = KT - kt;  // 1 .. DEPTH
+    if (DEPTH == 4 && left == 4) {
         EGG_ITER_DEEP(kt, 0, true, false, 2)
         EGG_ITER_DEEP(kt + 1, 1, true, false, 1)
         EGG_ITER_DEEP(kt + 2, 0, true, false, 0)
         EGG_ITER_DEEP(kt + 3, 1, false, false, 0)
     } else if (left == 3) {
-        EGG_ITER_DEEP(kt, 0, true, false, 0)
+        EGG_ITER_DEEP(kt, 0, true, false, DEPTH == 3 ? 1 : 0)
         EGG_ITER_DEEP(kt + 1, 1, true, false, 0)
         EGG_ITER_DEEP(kt + 2, 0, false, false, 0)
     } else if (left == 2) {
@@ -955,13 +976,14 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_nt_deep_kernel(Operand P,
 #undef EGG_ITER_DEEP
 #undef EGG_DEEP_READ
 #undef EGG_DEEP_BARRIER
-    if constexpr (is_split<MT>::value) {
+    if constexpr (SPLIT) {
 #pragma unroll
         for (int i = 0; i < MB; ++i)
 #pragma unroll
             for (int j = 0; j < NB; ++j) acc[i][j] += cross[i][j];
     }
-    Epi epi(ea, lds + DEPTH * STAGE_BYTES + wave * Epi::lds_per_wave(WTM), lane);
+    // (every wave had the last stage in registers at the last barrier: where the LDS has no room behind them, the slices lie over the stages)
+    Epi epi(ea, lds + (SPLIT ? 0 : DEPTH * STAGE_BYTES) + wave * Epi::lds_per_wave(WTM), lane);
     epi.template prefetch<MB, NB>(m0 + wm * WTM, n0 + wn * WTN, lane, Q.rows);
     epi.template extra_mma<MT, MB, NB>(acc, m0 + wm * WTM, n0 + wn * WTN, lane, Q.rows);
     static_for<0, NB>([&](auto jc) __attribute__((always_inline)) {

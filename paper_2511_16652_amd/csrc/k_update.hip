@@ -10,7 +10,8 @@
 // 2^-25 it becomes zero -- about 5e-5 of N(0,1) draws, each contributing an absolute error <= 2^-25 to a product
 // of typical size 1.  The A panel holds (f_i / fnorm) a with |f_i / fnorm| <= 1, so members whose |f_i| is far
 // below max|f| lose relative precision the same way: the error per term is bounded by 2^-25 max|f|, i.e. it is
-// relative to the largest fitness, not to f_i.  fp32 factors stay fp32, or (MmaF16Split) are two fp16 parts of 22 bits and more.  No atomics: each G entry has one owner
+// relative to the largest fitness, not to f_i.  fp32 factors stay fp32, or (MmaF32Split) are three bf16
+// parts each, which hold all their 24 bits.  No atomics: each G entry has one owner
 // and a fixed summation order, so the result is run-to-run identical.
 #include "common.hpp"
 #include "gemm_core.hpp"
@@ -229,7 +230,7 @@ __global__ __launch_bounds__(256) void pack_r1_kernel(const void* __restrict__ s
 // other kernel: bf16 factors times f_i / fnorm as the pack pass rounds them to fp16; fp32 factors stay fp32.
 //   rank 1:  a thread owns one column pair of EPC consecutive members -- one Threefry block per member -- and writes the two
 //            finished 16-byte chunks, which are neighbours in the panel;
-//   (parts: 8 kappa, a chunk of hi and one of lo parts for each column)
+//   (parts: 8 kappa, a chunk of hi, mid and lo parts each for each column)
 //   rank >= 2: a thread owns one chunk, EPC consecutive kappa = i r + l of one column: EPC / 2 blocks.
 // The blocks of a thread are independent chains.  Vector-ALU bound: about 87 issue slots per block and the conversion.
 // Measured at 16384 members x (8192 + 2048) x rank 4 (bf16): 906 us (744 are the generator's issue slots); noise kernel
@@ -253,21 +254,37 @@ struct GenPackArgs {
 };
 constexpr int INLINE_NORM_MEMBERS = 1024;  // up to here the maximum over the fitness costs a workgroup less than a launch does
 
-// how a panel holds its values: fp16 of bf16 factors; fp32; or (fp32 factors) two fp16 parts of 2^SPLIT_EXP times the value, the hi parts of 32 kappa
-// in four chunks, then their lo parts in four
+// how a panel holds its values: fp16 of bf16 factors; fp32; or (fp32 factors) three bf16 parts a value, the hi parts of 32 kappa in four chunks, then their
+// mid parts in four, then lo
 enum PanelForm { PANEL_F16, PANEL_F32, PANEL_SPLIT };
-constexpr int SPLIT_EXP = 12;   // factors are below 6 in magnitude, and so are those of the A panel: f_i / fnorm is 1 at most
 
-// the parts of v; an infinite one (an infinite fitness) goes into lo, where its products with the other panel's hi parts keep their
-// signs (its hi times a lo part would not), and a finite one too large (beside an infinite fitness) is cut to the largest
-__device__ __forceinline__ void split_f16(float v, _Float16& hi, _Float16& lo)
+// parts of one value beyond the largest bf16 one (an infinite fitness, or one that counts as that beside it).  An infinite one goes into lo, whose
+// products are those with the other panel's hi parts alone and keep their signs (hi times a mid part would not).
+__device__ __forceinline__ void split_large(float v, float (&part)[3])
 {
-    const float x = v * (float)(1 << SPLIT_EXP);
-    hi = (_Float16)x;
-    lo = (_Float16)(x - (float)hi);
-    if (fabsf(x) > 65504.f) {
-        hi = __builtin_isinf(v) ? (_Float16)0.f : (_Float16)__builtin_copysignf(65504.f, v);
-        lo = __builtin_isinf(v) ? (_Float16)v : (_Float16)0.f;
+    constexpr float MOST = 3.3895313892515355e38f;  // 2^127 (2 - 2^-7)
+    part[0] = part[1] = 0.f;
+    part[2] = v;
+    if (!__builtin_isinf(v)) {
+        part[0] = fabsf(v) > MOST ? __builtin_copysignf(MOST, v) : round_bf16(v);
+        part[1] = round_bf16(v - part[0]);
+        part[2] = v - part[0] - part[1];
+    }
+}
+// the parts of a and b, a word each
+__device__ __forceinline__ void split_bf16(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo)
+{
+    hi = pack_bf16x2(a, b);
+    const float a1 = a - bf16_lo(hi), b1 = b - bf16_hi(hi);
+    mid = pack_bf16x2(a1, b1);
+    lo = pack_bf16x2(a1 - bf16_lo(mid), b1 - bf16_hi(mid));
+    if (fmaxf(fabsf(a), fabsf(b)) > 3.38e38f) {
+        float p[3], q[3];
+        split_large(a, p);
+        split_large(b, q);
+        hi = pack_bf16x2(p[0], q[0]);
+        mid = pack_bf16x2(p[1], q[1]);
+        lo = pack_bf16x2(p[2], q[2]);
     }
 }
 
@@ -285,11 +302,12 @@ __device__ __forceinline__ float workgroup_norm(const float* __restrict__ fitnes
     return fitness_pow2(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
 }
 
-// what a thread draws: EPC kappa of one column, of the pair 2u and 2u + 1 at rank 1, and their lo parts
+// what a thread draws: EPC kappa of one column, of the pair 2u and 2u + 1 at rank 1, and their mid and lo parts
 template <PanelForm FORM, int RANK>
 struct PanelChunks {
     static constexpr int COLS = RANK == 1 ? 2 : 1;
-    u32x4 hi[COLS], lo[FORM == PANEL_SPLIT ? COLS : 1];
+    static constexpr int PARTS = FORM == PANEL_SPLIT ? 3 : 1;
+    u32x4 c[PARTS][COLS];
 };
 // (FIT, the A panel: times the fitness; fixed at compile time, as a branch in the code of both panels the pass of 16384 members x (8192 + 2048) x rank 4 took 923 us, 906 so)
 template <PanelForm FORM, int RANK, bool FIT>
@@ -344,28 +362,22 @@ __device__ __forceinline__ PanelChunks<FORM, RANK> draw_chunks(const StreamKey& 
             }
         }
         if constexpr (FORM == PANEL_SPLIT) {
-            u32x4 l0, l1;
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
-                h2 h, l;
-                _Float16 p, q;
-                split_f16(lo[2 * w], p, q); h[0] = p; l[0] = q;
-                split_f16(lo[2 * w + 1], p, q); h[1] = p; l[1] = q;
-                c0[w] = __builtin_bit_cast(uint32_t, h);
-                l0[w] = __builtin_bit_cast(uint32_t, l);
-                split_f16(hi[2 * w], p, q); h[0] = p; l[0] = q;
-                split_f16(hi[2 * w + 1], p, q); h[1] = p; l[1] = q;
-                c1[w] = __builtin_bit_cast(uint32_t, h);
-                l1[w] = __builtin_bit_cast(uint32_t, l);
+                uint32_t p[3];
+                split_bf16(lo[2 * w], lo[2 * w + 1], p[0], p[1], p[2]);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) out.c[q][0][w] = p[q];
+                split_bf16(hi[2 * w], hi[2 * w + 1], p[0], p[1], p[2]);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) out.c[q][1][w] = p[q];
             }
-            out.lo[0] = l0;
-            out.lo[1] = l1;
+        } else {
+            out.c[0][0] = c0;
+            out.c[0][1] = c1;
         }
-        out.hi[0] = c0;
-        out.hi[1] = c1;
     } else {
         constexpr int NB = EPC / 2;
-        u32x4 o_lo;
         float fs[NB];
 #pragma unroll
         for (int b = 0; b < NB; ++b) fs[b] = fs_of((kg * EPC + 2 * b) / RANK);
@@ -402,19 +414,16 @@ __device__ __forceinline__ PanelChunks<FORM, RANK> draw_chunks(const StreamKey& 
                 p[1] = (_Float16)z1;
                 o[b] = __builtin_bit_cast(uint32_t, p);
             } else if constexpr (FORM == PANEL_SPLIT) {
-                h2 h, l;
-                _Float16 p, q;
-                split_f16(z0, p, q); h[0] = p; l[0] = q;
-                split_f16(z1, p, q); h[1] = p; l[1] = q;
-                o[b] = __builtin_bit_cast(uint32_t, h);
-                o_lo[b] = __builtin_bit_cast(uint32_t, l);
+                uint32_t p[3];
+                split_bf16(z0, z1, p[0], p[1], p[2]);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) out.c[q][0][b] = p[q];
             } else {
                 o[2 * b] = __float_as_uint(z0);
                 o[2 * b + 1] = __float_as_uint(z1);
             }
         }
-        if constexpr (FORM == PANEL_SPLIT) out.lo[0] = o_lo;
-        out.hi[0] = o;
+        if constexpr (FORM != PANEL_SPLIT) out.c[0][0] = o;
     }
     return out;
 }
@@ -444,12 +453,11 @@ __global__ __launch_bounds__(256) void gen_pack_kernel(GenPackArgs g)
     typedef PanelChunks<FORM, RANK> Chunks;
     const Chunks ch = J.fitness ? draw_chunks<FORM, RANK, true>(J.key, g.member_begin, g.members, J.fitness, finv, kg, u)
                                 : draw_chunks<FORM, RANK, false>(J.key, g.member_begin, g.members, nullptr, 1.f, kg, u);
-    u32x4* const o = J.out + (FORM == PANEL_SPLIT ? kg + (kg & ~int64_t(3)) : kg) * J.d + Chunks::COLS * u;
+    u32x4* const o = J.out + (FORM == PANEL_SPLIT ? (kg >> 2) * SPLIT_CHUNKS + (kg & 3) : kg) * J.d + Chunks::COLS * u;
 #pragma unroll
-    for (int c = 0; c < Chunks::COLS; ++c) {
-        o[c] = ch.hi[c];
-        if constexpr (FORM == PANEL_SPLIT) o[(int64_t)4 * J.d + c] = ch.lo[c];
-    }
+    for (int q = 0; q < Chunks::PARTS; ++q)
+#pragma unroll
+        for (int c = 0; c < Chunks::COLS; ++c) o[(int64_t)4 * q * J.d + c] = ch.c[q][c];
 }
 
 // panels of the A and (out_b != NULL) the B factors
@@ -498,7 +506,6 @@ struct UpdArgs {
     int d_out, d_in;
     float scale, lr;
     int accumulate, w_bf16;
-    float unit;  // a power of two: what a product of the panels' values stands for (UpdEpi16)
 };
 
 // MBLK: row blocks (of 32) per wave tile.  G is row-major [d_out][d_in] and a column n is one k: the 32 lanes of a
@@ -615,7 +622,7 @@ struct UpdEpi16 {
 #pragma unroll
             for (int it = 0; it < PASSES; ++it) {
                 const int64_t idx = at(it, in);
-                float v[4] = {scale * (a.unit * g[it].x), scale * (a.unit * g[it].y), scale * (a.unit * g[it].z), scale * (a.unit * g[it].w)};
+                float v[4] = {scale * g[it].x, scale * g[it].y, scale * g[it].z, scale * g[it].w};
                 if (a.accumulate) { v[0] += old[it].x; v[1] += old[it].y; v[2] += old[it].z; v[3] += old[it].w; }
                 if (!in) continue;
                 *(float4*)(a.G + idx) = make_float4(v[0], v[1], v[2], v[3]);
@@ -631,7 +638,7 @@ struct UpdEpi16 {
                 const int j = nb0 + c / WTM, k = mw0 + c % WTM;
                 if (j >= n_rows || k >= a.d_in) continue;
                 const int64_t idx = (int64_t)j * a.d_in + k;
-                float v = scale * (a.unit * *(const float*)(stage + (c / WTM) * P + (c % WTM) * 4));
+                float v = scale * *(const float*)(stage + (c / WTM) * P + (c % WTM) * 4);
                 if (a.accumulate) v += a.G[idx];
                 a.G[idx] = v;
                 if (a.W && a.w_bf16) {
@@ -728,7 +735,7 @@ __global__ __launch_bounds__(256) void upd_draw_kernel(UpdDrawArgs g, UpdArgs ea
         const Chunks ch = a ? draw_chunks<FORM, RANK, true>(g.ka, g.member_begin, g.members, g.fitness, finv, kg, n0 / Chunks::COLS + u)
                             : draw_chunks<FORM, RANK, false>(g.kb, g.member_begin, g.members, nullptr, 1.f, kg, m0 / Chunks::COLS + u);
 #pragma unroll
-        for (int c = 0; c < Chunks::COLS; ++c) panel[(a ? g.kgroups * 32 : 0) + kg * 32 + u * Chunks::COLS + c] = ch.hi[c];
+        for (int c = 0; c < Chunks::COLS; ++c) panel[(a ? g.kgroups * 32 : 0) + kg * 32 + u * Chunks::COLS + c] = ch.c[0][c];
     }
     __syncthreads();
     UpdSmallEpi epi(ea, norm);
@@ -810,15 +817,17 @@ static egg_status launch_upd_small(eggroll_ctx* c, const char* name, const Opera
     return check_hip(c, hipGetLastError(), name);
 }
 
-// DEEP: four stages in flight, a workgroup a tile
+// DEEP: four stages in flight (parts: three), a workgroup a tile
 template <class MT, int BM, int BN, int WM, int WN, bool DEEP>
 static egg_status launch_upd_gemm16(eggroll_ctx* c, const char* name, const Operand& P, const Operand& Q, int kchunks, const UpdArgs& ea)
 {
     typedef UpdEpi16<BM / WM> Epi;
     const int tiles_m = (P.rows + BM - 1) / BM, tiles_n = (Q.rows + BN - 1) / BN;
     const size_t stages = gemm_lds_bytes<BM, BN>(), epi = (size_t)WM * WN * Epi::lds_per_wave(BM / WM);
-    if (!operand_offsets_fit(P, BM) || !operand_offsets_fit(Q, BN)) return fail(c, EGG_EUNSUPPORTED, "operand strides too large for 32-bit tile offsets");
-    const size_t lds = DEEP ? 2 * stages + epi : std::max(stages, epi);
+    constexpr int CHUNKS = is_split<MT>::value ? SPLIT_CHUNKS : 8;
+    if (!operand_offsets_fit(P, BM, CHUNKS) || !operand_offsets_fit(Q, BN, CHUNKS)) return fail(c, EGG_EUNSUPPORTED, "operand strides too large for 32-bit tile offsets");
+    const size_t lds = is_split<MT>::value ? (size_t)SPLIT_STAGES * SPLIT_CHUNKS * 16 * (BM + BN) : DEEP ? 2 * stages + epi : std::max(stages, epi);
+    static_assert(!is_split<MT>::value || (DEEP && WM * WN * Epi::lds_per_wave(BM / WM) <= SPLIT_CHUNKS * 16 * (BM + BN)), "the slices of the epilogue over a stage");
     const dim3 g((unsigned)(tiles_m * tiles_n)), b(WM * WN * 64);
     if constexpr (DEEP) {
         auto kern = gemm_nt_deep_kernel<MT, BM, BN, WM, WN, true, Epi>;
@@ -854,17 +863,20 @@ static egg_status launch_upd_gemm(eggroll_ctx* c, const char* name, const Operan
     return check_hip(c, hipGetLastError(), name);
 }
 
-// fp32 factors generated for the call go into panels of two fp16 parts each (split_f16), multiplied by fp16 MFMAs: where the tiles of 32 x 32
-// are more than two to a CU, from 192 kappa on.  A fp32 MFMA takes 256 cycles for what three of those do in 48; what bounds the contraction then is
-// the rate at which a CU loads (32 KB for 32 kappa of a 128 x 128 tile).  Whole updates, us, fp32 MFMAs / 64 x 64 / 128 x 128 tiles of
-// parts: 1024 x 1024, K = 1024 41 / 25 / 38, 8000 220 / 106 / 185; 2048 x 2048, K = 300 39.5 / 27.5 / 28.7, 2048 161 / 83 / 77; 3280 x 1960,
-// K = 2048 287 / 152 / 122; 4096 x 4096, K = 8000 2094 / 1054 / 831.  Fewer tiles: 512 x 512, K = 300 11.5 / 13.8, 2048 35 / 34.
-// Error against 64 bits, relative 2-norm, fp32 MFMAs / parts: 1024 x 1024 (K split over four waves) K = 64 1.25e-7 / 1.36e-7, 192 1.57e-7 / 1.49e-7,
-// 700 2.64e-7 / 2.22e-7; 2048 x 2048 K = 192 2.58e-7 / 1.48e-7, 700 4.7e-7 / 2.2e-7, 8000 1.61e-6 / 5.9e-7.
+// fp32 factors generated for the call go into panels of three bf16 parts each (split_bf16), multiplied by bf16 MFMAs, where the tiles of 32 x 32 are more
+// than two to a CU: from 192 kappa in tiles of 64 x 64, up to two of them to a CU, and beyond that from 512 in tiles of 128 x 128.  A fp32 MFMA takes 256
+// cycles for what six of those do in 96; against that stand panels half as long again, 48 KB for 32 kappa of a 128 x 128 tile, and, of so large tiles, a
+// nearly empty last wave.  Whole updates, us, fp32 MFMAs / parts: 64 x 64: 1024 x 736, K = 192 15.6 / 13.6, 1400 x 1400, K = 192 22.7 / 17.7, 1000 59.4 /
+// 40.8; 1024 x 1024, K = 1024 40 / 31, 8000 216 / 144.  128 x 128: 2048 x 2048, K = 192 26.5 / 28.6, 384 41.0 / 38.0, 2048 161 / 108, 8000 568 / 366; 2100 x
+// 2100, K = 192 32.6 / 42.5, 384 54.2 / 57.6; 4096 x 4096, K = 512 152 / 122, 1024 283 / 204, 8000 2067 / 1380.  Fewer tiles are bound by latency.
+// Error against 64 bits, relative 2-norm, fp32 MFMAs / parts: all members with a fitness, 1024 x 1024, K = 192 1.30e-7 / 0.90e-7, 700 2.38e-7 / 1.72e-7, 2048 x
+// 2048, K = 700 4.8e-7 / 1.7e-7, 8000 1.60e-6 / 0.57e-6; fitness over eight decades, 700 1.09e-7 / 0.55e-7; sixteen members with one 6.8e-8 / 4.8e-8, four 5.1e-8 /
+// 4.0e-8, a single one 3.6e-8 / 3.7e-8.
 // (A caller's caches may hold any values: their updates stay on fp32 MFMAs.)
 static bool split_update(int64_t M, int64_t N, int64_t K, int compute_units)
 {
-    return ((M + 31) / 32) * ((N + 31) / 32) > 2 * (int64_t)compute_units && K >= 192;
+    const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32), t64 = ((M + 63) / 64) * ((N + 63) / 64), two = 2 * (int64_t)compute_units;
+    return t32 > two && K >= (t64 <= two ? 192 : 512) && std::max(M, N) <= 1 << 24;  // (offsets into a stage in 32 bits)
 }
 
 egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& kb, const egg_shape& s,
@@ -877,26 +889,42 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
     // Without caches the factors are generated straight into the panels (a rank-1 work item is a column pair: an odd width goes
     // through the noise kernel and the pack pass, like the caches).
     const bool gen_packed = !A_cache && (s.rank > 1 || (s.d_out % 2 == 0 && s.d_in % 2 == 0));
-    const bool split = !bf && gen_packed && split_update(s.d_out, s.d_in, K, c->compute_units);
-    // chunks of a panel; in parts, two for 8 kappa, whole stages of 32
-    const int64_t kgroups = split ? (K + 31) / 32 * 8 : (K + epc - 1) / epc;
+    bool split = !bf && gen_packed && split_update(s.d_out, s.d_in, K, c->compute_units);
+    int64_t kgroups = (K + epc - 1) / epc;  // chunks of a panel
     if (kgroups > 0x7FFFFFFF) return fail(c, EGG_EUNSUPPORTED, "population * rank too large");
     egg_status st;
 
     if (gen_packed && !b_panel && draws_in_place(s, bf, c->compute_units))
-        return launch_upd_draw(c, bf, ka, kb, s, fitness, UpdArgs{G, W, nullptr, s.d_out, s.d_in, scale, lr, accumulate, w_dtype == EGG_BF16 ? 1 : 0, 1.f});
+        return launch_upd_draw(c, bf, ka, kb, s, fitness, UpdArgs{G, W, nullptr, s.d_out, s.d_in, scale, lr, accumulate, w_dtype == EGG_BF16 ? 1 : 0});
     if ((st = reserve(c, c->fnorm, 256)) != EGG_OK) return st;
     float* fnorm = (float*)c->fnorm.p;
-    if ((st = reserve(c, c->pack_a, (size_t)kgroups * s.d_out * 16)) != EGG_OK) return st;
     // b_panel: the caller's B_cache already is the packed panel (written by the forward pass); only A is generated
-    if (!b_panel && (st = reserve(c, c->pack_b, (size_t)kgroups * s.d_in * 16)) != EGG_OK) return st;
+    auto reserve_panels = [&](int64_t chunks) {
+        const egg_status a = reserve(c, c->pack_a, (size_t)chunks * s.d_out * 16);
+        return a != EGG_OK || b_panel ? a : reserve(c, c->pack_b, (size_t)chunks * s.d_in * 16);
+    };
+    if (split) {
+        // three chunks for 8 kappa, whole stages of 32; where there is no memory for them, fp32 panels take two thirds of it
+        const int64_t chunks = (K + 31) / 32 * SPLIT_CHUNKS;
+        const eggroll_ctx::Buf held = c->pack_a;
+        const size_t retired = c->retired.size();
+        split = chunks <= 0x7FFFFFFF && reserve_panels(chunks) == EGG_OK;
+        if (split) {
+            kgroups = chunks;
+        } else if (c->pack_a.p != held.p) {  // the first panel was to be had, the second not: nothing has used it yet
+            (void)hipFree(c->pack_a.p);
+            c->pack_a = held;
+            c->retired.resize(retired);
+        }
+    }
+    if (!split && (st = reserve_panels(kgroups)) != EGG_OK) return st;
     const bool inline_norm = gen_packed && s.member_count <= INLINE_NORM_MEMBERS;
     if (!inline_norm) {
         KernelScope ks(c, "fitness_norm");
         hipLaunchKernelGGL(fitness_norm_kernel, dim3(1), dim3(1024), 0, c->stream, fitness, s.member_count, fnorm);
     }
     if (gen_packed) {
-        if ((st = launch_gen_pack(c, bf ? PANEL_F16 : split ? PANEL_SPLIT : PANEL_F32, ka, kb, s, fitness, fnorm, inline_norm, split ? kgroups / 2 : kgroups, c->pack_a.p, b_panel ? nullptr : c->pack_b.p)) != EGG_OK) return st;
+        if ((st = launch_gen_pack(c, bf ? PANEL_F16 : split ? PANEL_SPLIT : PANEL_F32, ka, kb, s, fitness, fnorm, inline_norm, split ? kgroups / 3 : kgroups, c->pack_a.p, b_panel ? nullptr : c->pack_b.p)) != EGG_OK) return st;
     } else {
         // factors in [member][d][r] layout: the caller's caches, or regenerated into scratch
         const void* A_src = A_cache;
@@ -933,11 +961,11 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
 
     Operand P{(const char*)c->pack_a.p, 16, (int64_t)s.d_out * 16, s.d_out};
     Operand Q{(const char*)(b_panel ? B_cache : c->pack_b.p), 16, (int64_t)s.d_in * 16, s.d_in};
-    UpdArgs ea{G, W, fnorm, s.d_out, s.d_in, scale, lr, accumulate, w_dtype == EGG_BF16 ? 1 : 0, split ? ldexpf(1.f, -2 * SPLIT_EXP) : 1.f};
+    UpdArgs ea{G, W, fnorm, s.d_out, s.d_in, scale, lr, accumulate, w_dtype == EGG_BF16 ? 1 : 0};
     if (split) {
         if (((s.d_out + 63) / 64) * (int64_t)((s.d_in + 63) / 64) <= 2 * c->compute_units)
-            return launch_upd_gemm16<MmaF16Split, 64, 64, 2, 2, true>(c, "update_gemm_f32", Q, P, (int)kgroups, ea);
-        return launch_upd_gemm16<MmaF16Split, 128, 128, 2, 2, true>(c, "update_gemm_f32", Q, P, (int)kgroups, ea);
+            return launch_upd_gemm16<MmaF32Split, 64, 64, 2, 2, true>(c, "update_gemm_f32", Q, P, (int)kgroups, ea);
+        return launch_upd_gemm16<MmaF32Split, 128, 128, 2, 2, true>(c, "update_gemm_f32", Q, P, (int)kgroups, ea);
     }
     const int small = small_tile(s.d_in, s.d_out, c->compute_units);
     if (bf && small) {

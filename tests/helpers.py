@@ -1,4 +1,6 @@
 """Shared helpers of the GPU parity tests: tolerance metric and tensor marshalling."""
+import contextlib
+
 import numpy as np
 
 from paper_2511_16652_amd import inputs
@@ -63,3 +65,24 @@ def to_numpy(t):
 def storage_round(a, dtype):
     a = np.asarray(a, dtype=np.float32)
     return inputs.round_to_bf16(a) if dtype == "bf16" else a
+
+
+@contextlib.contextmanager
+def memory_left(bytes_left):
+    """Holds device memory until about `bytes_left` (to 16 MB) of it are free."""
+    import torch
+    torch.cuda.empty_cache()
+    fill, piece = [], 32 << 30
+    try:
+        while piece >= 16 << 20:
+            if torch.cuda.mem_get_info()[0] - piece < bytes_left:
+                piece //= 2
+                continue
+            try:
+                fill.append(torch.empty(piece, dtype=torch.uint8, device="cuda"))
+            except torch.cuda.OutOfMemoryError:
+                piece //= 2
+        yield
+    finally:
+        fill.clear()
+        torch.cuda.empty_cache()
