@@ -8,7 +8,7 @@
 // bf16 factors are packed as fp16 (11 significant bits instead of 8 for f_i*a): a bf16 value of magnitude
 // >= 2^-14 is exact in fp16; below that it lands on fp16's subnormal grid (absolute error <= 2^-25) and below
 // 2^-25 it becomes zero -- about 5e-5 of N(0,1) draws, each contributing an absolute error <= 2^-25 to a product
-// of typical size 1.  The A panel holds (f_i / fnorm) a with |f_i / fnorm| <= 1, so members whose |f_i| is far
+// of typical size 1.  The A panel holds (f_i / fnorm) a with |f_i / fnorm| <= 1 (below 2 beyond 2^127), so members whose |f_i| is far
 // below max|f| lose relative precision the same way: the error per term is bounded by 2^-25 max|f|, i.e. it is
 // relative to the largest fitness, not to f_i.  fp32 factors stay fp32, or (MmaF32Split) are three bf16
 // parts each, which hold all their 24 bits.  No atomics: each G entry has one owner
@@ -19,19 +19,19 @@
 
 namespace egg {
 
-// 2^ceil(log2(max|f|)) of the maximum, 1 where that is zero or not finite
+// 2^ceil(log2(max|f|)) of the maximum, 2^127 at most (2^128 is infinite), 1 where the maximum is zero or infinite
 __device__ __forceinline__ float fitness_pow2(float mx)
 {
     float p = 1.f;
-    if (mx > 0.f && mx < 3.0e38f) {
+    if (mx > 0.f && !__builtin_isinf(mx)) {
         int e;
         (void)frexpf(mx, &e);  // mx = frac * 2^e, frac in [0.5, 1)
-        p = ldexpf(1.f, e);
+        p = ldexpf(1.f, min(e, 127));
     }
     return p;
 }
 
-// fnorm[0] = 2^ceil(log2(max|f|)) (1 if all zero), fnorm[1] = 1/fnorm[0].  Folding f/fnorm[0] into the
+// fnorm[0] = 2^ceil(log2(max|f|)) (fitness_pow2), fnorm[1] = 1/fnorm[0].  Folding f/fnorm[0] into the
 // fp16 panel and fnorm[0] into the epilogue scale is exact (a power of two) and keeps f_i*a inside
 // the fp16 range whatever the magnitude of the fitness values.
 __global__ __launch_bounds__(1024) void fitness_norm_kernel(const float* __restrict__ f, int64_t n, float* __restrict__ fnorm)
@@ -258,7 +258,7 @@ constexpr int INLINE_NORM_MEMBERS = 1024;  // up to here the maximum over the fi
 // mid parts in four, then lo
 enum PanelForm { PANEL_F16, PANEL_F32, PANEL_SPLIT };
 
-// parts of one value beyond the largest bf16 one (an infinite fitness, or one that counts as that beside it).  An infinite one goes into lo, whose
+// parts of one value beyond the largest bf16 one (an infinite fitness, or one of that size beside it).  An infinite one goes into lo, whose
 // products are those with the other panel's hi parts alone and keep their signs (hi times a mid part would not).
 __device__ __forceinline__ void split_large(float v, float (&part)[3])
 {

@@ -208,6 +208,31 @@ def test_panel_cache_refused_untouched(dtype, N, S, rank, anti, entry):
     assert bool((B == 0xA5).all()) and bool((Y == 7.0).all())
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d_out,d_in,N", [(256, 256, 64), (256, 256, 300), (1024, 736, 200), (2048, 1028, 600), (2048, 2052, 1040), (4096, 2052, 64)])
+@pytest.mark.parametrize("size", [1.6e38, 1.8e38, 2.9e38, 3.01e38, 3.2e38, 3.4e38, 1e-37])
+@pytest.mark.parametrize("cached", [False, True])
+def test_fitness_at_the_ends_of_the_range(ctx, dtype, d_out, d_in, N, size, cached):
+    """A finite fitness next to the largest value of its type: G is right wherever it is in range, and infinite beyond it.  And next to the smallest.
+    Bounds: a rounding of 2^-24 of the terms' sizes for each term and two more; bf16 factors are panels of fp16, 2^-11 for f a, 2^-10 with the rest.
+    And the smallest fp32 value."""
+    import torch
+    code, tdt = (eb.EGG_F32, torch.float32) if dtype == "f32" else (eb.EGG_BF16, torch.bfloat16)
+    key, shape = eb.make_key(3, 1, 9), eb.make_shape(0, N, 1, d_out, d_in, 1)
+    f = torch.randn(N, generator=torch.Generator("cuda").manual_seed(1), device="cuda") * (size * 1e-9)   # (together 1e-7 of it and less)
+    f[7], f[11] = size, -size / 4
+    A, B = (torch.empty((N, d, 1), dtype=tdt, device="cuda") for d in (d_out, d_in))
+    ctx.eggroll_noise_gen(key, shape, code, eb.EGG_NORMAL, 0, A, B)
+    G = torch.zeros((d_out, d_in), device="cuda")
+    ctx.eggroll_update(key, shape, code, f, 1.0, 0, G, None, 0.0, *((A, B) if cached else (None, None)))
+    a, b = A[:, :, 0].double() * f.double()[:, None], B[:, :, 0].double()
+    want, terms = a.t().contiguous() @ b, a.abs().t().contiguous() @ b.abs()
+    fits, over = terms < 3.38e38, want.abs() > 3.45e38 * (1 if dtype == "f32" else 1.002)
+    assert fits.float().mean() > 0.5
+    assert ((G.double() - want).abs()[fits] <= ((N + 2) * 2.0 ** -24 if dtype == "f32" else 2.0 ** -10) * (terms[fits] + size * 1e-6) + 2.0 ** -149).all()
+    assert torch.equal(G[over], torch.sign(want[over]).float() * float("inf"))
+
+
 def test_rank_convergence_on_the_device(ctx):
     """The O(1/r) statement of Sec. "Rank Analysis" through the device path: fitness cos(<U, W_i>) from the
     perturbed forward (fp32, one row per member, x = v so that y_i = W_i v), the update from eggroll_update, for
