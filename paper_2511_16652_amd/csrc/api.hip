@@ -58,6 +58,17 @@ egg_status reserve(eggroll_ctx* c, eggroll_ctx::Buf& b, size_t bytes)
     return EGG_OK;
 }
 
+bool try_reserve(eggroll_ctx* c, eggroll_ctx::Buf& b, size_t bytes)
+{
+    if (b.bytes >= bytes) return true;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return reserve(c, b, bytes) == EGG_OK;
+}
+
 egg_status ensure_dynamic_lds(eggroll_ctx* c, const void* kern, size_t bytes, const char* what)
 {
     static std::mutex mu;
@@ -135,18 +146,18 @@ egg_status forward_linear(eggroll_ctx* c, egg_key key, const egg_shape& shape, e
         const StreamKey ka = make_stream_key(key.seed, key.step, key.layer, 0), kb = make_stream_key(key.seed, key.step, key.layer, 1);
         // few members with many rows: their rows go to several workgroups, and the factors are drawn for all of them in one launch
         // (with A, which that layer needs as well); the entry point that allocates nothing has no place for them but the caller's cache
-        const ProjectSplit split = project_split(c, shape, io_dtype, B_cache || !t_fixed);
+        ProjectSplit split = project_split(c, shape, io_dtype, B_cache || !t_fixed);
         const int anti = shape.antithetic ? 2 : 1, esz = io_dtype == EGG_BF16 ? 2 : 4;
         const int64_t ids = shape.member_count / anti;
         NoiseJob jobs[2] = {{kb, (int64_t)shape.d_in * shape.rank, B_cache}, {ka, (int64_t)shape.d_out * shape.rank, A_cache}};
         const bool draw_A = !forward_regenerates(shape, sigma, A_cache) && (A_cache || !A_ready);
-        if (split.ready && !B_cache) {
-            if ((s = reserve(c, c->b_buf, (size_t)(ids * jobs[0].n) * esz)) != EGG_OK) return s;
-            jobs[0].out = c->b_buf.p;
-        }
         if (draw_A && !A_cache) {
             if ((s = reserve(c, c->a_buf, (size_t)(ids * jobs[1].n) * esz)) != EGG_OK) return s;
             jobs[1].out = c->a_buf.p;
+        }
+        if (split.ready && !B_cache) {
+            if (try_reserve(c, c->b_buf, (size_t)(ids * jobs[0].n) * esz)) jobs[0].out = c->b_buf.p;
+            else split = project_split(c, shape, io_dtype, false);  // no memory for the factors: every workgroup draws its member's
         }
         NoisePiece along;
         const bool with_A = draw_A && !split.ready && normal_pieces(jobs[1], ids, io_dtype, along) && project_draws_along(c, shape, io_dtype, split, along);

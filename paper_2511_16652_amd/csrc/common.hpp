@@ -93,6 +93,9 @@ __device__ __forceinline__ float wave_sum(float x)
 egg_status fail(eggroll_ctx* c, egg_status s, const char* fmt, ...);
 egg_status check_hip(eggroll_ctx* c, hipError_t e, const char* what);
 egg_status reserve(eggroll_ctx* c, eggroll_ctx::Buf& b, size_t bytes);
+// scratch that a call is faster with and can do without: false where there is no memory for it, or a capture, which an allocation would
+// end, is under way
+bool try_reserve(eggroll_ctx* c, eggroll_ctx::Buf& b, size_t bytes);
 
 // RAII bracket: records events around one kernel launch when profiling is on
 struct KernelScope {

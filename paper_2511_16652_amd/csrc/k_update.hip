@@ -898,17 +898,12 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
         return launch_upd_draw(c, bf, ka, kb, s, fitness, UpdArgs{G, W, nullptr, s.d_out, s.d_in, scale, lr, accumulate, w_dtype == EGG_BF16 ? 1 : 0});
     if ((st = reserve(c, c->fnorm, 256)) != EGG_OK) return st;
     float* fnorm = (float*)c->fnorm.p;
-    // b_panel: the caller's B_cache already is the packed panel (written by the forward pass); only A is generated
-    auto reserve_panels = [&](int64_t chunks) {
-        const egg_status a = reserve(c, c->pack_a, (size_t)chunks * s.d_out * 16);
-        return a != EGG_OK || b_panel ? a : reserve(c, c->pack_b, (size_t)chunks * s.d_in * 16);
-    };
     if (split) {
         // three chunks for 8 kappa, whole stages of 32; where there is no memory for them, fp32 panels take two thirds of it
         const int64_t chunks = (K + 31) / 32 * SPLIT_CHUNKS;
         const eggroll_ctx::Buf held = c->pack_a;
         const size_t retired = c->retired.size();
-        split = chunks <= 0x7FFFFFFF && reserve_panels(chunks) == EGG_OK;
+        split = chunks <= 0x7FFFFFFF && try_reserve(c, c->pack_a, (size_t)chunks * s.d_out * 16) && try_reserve(c, c->pack_b, (size_t)chunks * s.d_in * 16);
         if (split) {
             kgroups = chunks;
         } else if (c->pack_a.p != held.p) {  // the first panel was to be had, the second not: nothing has used it yet
@@ -917,7 +912,9 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
             c->retired.resize(retired);
         }
     }
-    if (!split && (st = reserve_panels(kgroups)) != EGG_OK) return st;
+    if ((st = reserve(c, c->pack_a, (size_t)kgroups * s.d_out * 16)) != EGG_OK) return st;
+    // b_panel: the caller's B_cache already is the packed panel (written by the forward pass); only A is generated
+    if (!b_panel && (st = reserve(c, c->pack_b, (size_t)kgroups * s.d_in * 16)) != EGG_OK) return st;
     const bool inline_norm = gen_packed && s.member_count <= INLINE_NORM_MEMBERS;
     if (!inline_norm) {
         KernelScope ks(c, "fitness_norm");

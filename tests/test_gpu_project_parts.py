@@ -7,6 +7,7 @@ import math
 
 import pytest
 
+from helpers import memory_left
 from paper_2511_16652_amd import binding as eb
 
 pytestmark = pytest.mark.gpu
@@ -61,3 +62,73 @@ def test_parts_are_the_same_bits(ctx, dtype, d_in, N, S, rank, anti):
     rms = ref.square().mean(1, keepdim=True).sqrt()
     tol = 1e-5 * (ref.abs() + rms) if dtype == "f32" else 2.0 ** -8 * ref.abs() + 1e-4 * (rms + corr.abs().amax(1, keepdim=True))
     assert ((Y.double() - ref).abs() <= tol).all()
+
+
+def test_little_memory():
+    """Where there is no memory for the factors drawn beforehand every workgroup draws its member's: the same bits."""
+    import torch
+    d_out, d_in, N, S, rank = 32, 1 << 21, 16, 64, 16   # factors B of 1 GB
+    g = torch.Generator("cuda").manual_seed(4)
+    W, X = ((torch.randn((n, d_in), generator=g, device="cuda") * 1e-3).to(torch.bfloat16) for n in (d_out, N * S))
+
+    def forward():
+        Y = torch.empty((N * S, d_out), dtype=torch.bfloat16, device="cuda")
+        c = eb.Context(0)
+        try:
+            c.eggroll_perturbed_forward(eb.make_key(1, 2, 3), eb.make_shape(0, N, S, d_out, d_in, rank), 0.5, eb.EGG_ACT_NONE, W, X, Y)
+            torch.cuda.synchronize()
+        finally:
+            c.close()
+        return Y
+
+    want = forward()
+    with memory_left(700 << 20):
+        got = forward()
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("call", ["forward", "update"])
+def test_scratch_to_be_had_only_outside_a_capture(call):
+    """Calls whose faster form wants scratch that no call before them needed run in a capture all the same, without it."""
+    import torch
+    d, rank, S = 1024, 4, 64
+    few, many = (24, 800) if call == "forward" else (224, 240)   # (the larger call leaves scratch for all but the faster form)
+    g = torch.Generator("cuda").manual_seed(4)
+    stream = torch.cuda.Stream()
+    ctx = eb.Context(0, stream=stream)
+    key = eb.make_key(1, 2, 3)
+    if call == "forward":
+        W, X = ((torch.randn((n, d), generator=g, device="cuda")).to(torch.bfloat16) for n in (d, many * S))
+        out = torch.zeros((many * S, d), dtype=torch.bfloat16, device="cuda")
+
+        def run(c, n):
+            c.eggroll_perturbed_forward(key, eb.make_shape(0, n, S, d, d, rank), 0.5, eb.EGG_ACT_NONE, W, X, out)
+    else:
+        f, out = torch.randn(many, generator=g, device="cuda"), torch.zeros((d, d), device="cuda")
+        A, B = (torch.zeros((many, d, 1), device="cuda") for _ in range(2))
+
+        def run(c, n, *caches):
+            c.eggroll_update(key, eb.make_shape(0, n, 1, d, d, 1), eb.EGG_F32, f, 1.0, 0, out, None, 0.0, *caches)
+
+    other = eb.Context(0, stream=stream)
+    with torch.cuda.stream(stream):
+        run(other, few)                             # (the reference; code is loaded outside the capture)
+        want = out.clone()
+        run(ctx, many, *((A, B) if call == "update" else ()))
+    torch.cuda.synchronize()
+    generation = ctx.eggroll_scratch_generation()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        run(ctx, few)
+    assert ctx.eggroll_scratch_generation() == generation
+    for _ in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        if call == "forward":
+            assert torch.equal(out[:few * S], want[:few * S])
+        else:
+            assert (out - want).norm() <= 1e-6 * want.norm()   # (fp32 products for those of parts)
+    ctx.close()
+    other.close()
