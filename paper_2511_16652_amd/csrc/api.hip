@@ -132,6 +132,7 @@ egg_status forward_linear(eggroll_ctx* c, egg_key key, const egg_shape& shape, e
     const bool panel = c->cache_layout == EGG_CACHE_PANEL;
     const int64_t R = shape.member_count * (int64_t)shape.rows_per_member;
     float* t = nullptr;
+    const bool regenerate = forward_regenerates(shape, sigma, A_cache);
     if (sigma != 0.0f && t_ready) {
         t = const_cast<float*>(t_ready);  // the producer of X already formed the projections
     } else if (sigma != 0.0f) {
@@ -150,7 +151,7 @@ egg_status forward_linear(eggroll_ctx* c, egg_key key, const egg_shape& shape, e
         const int anti = shape.antithetic ? 2 : 1, esz = io_dtype == EGG_BF16 ? 2 : 4;
         const int64_t ids = shape.member_count / anti;
         NoiseJob jobs[2] = {{kb, (int64_t)shape.d_in * shape.rank, B_cache}, {ka, (int64_t)shape.d_out * shape.rank, A_cache}};
-        const bool draw_A = !forward_regenerates(shape, sigma, A_cache) && (A_cache || !A_ready);
+        const bool draw_A = !regenerate && (A_cache || !A_ready);
         if (draw_A && !A_cache) {
             if ((s = reserve(c, c->a_buf, (size_t)(ids * jobs[1].n) * esz)) != EGG_OK) return s;
             jobs[1].out = c->a_buf.p;
@@ -170,7 +171,7 @@ egg_status forward_linear(eggroll_ctx* c, egg_key key, const egg_shape& shape, e
         if ((s = launch_project(c, kb, shape, io_dtype, X, t, jobs[0].out, panel, split, with_A ? &along : nullptr)) != EGG_OK) return s;
     }
     return launch_forward_gemm(c, make_stream_key(key.seed, key.step, key.layer, 0), shape, io_dtype, y_dtype, sigma, act, W, X, Y,
-                               t, A_cache, resid, next, A_ready);
+                               t, regenerate, A_cache, resid, next, A_ready);
 }
 
 // validation shared by the forward entry points; t_fixed != NULL: the projections go to that buffer of t_capacity

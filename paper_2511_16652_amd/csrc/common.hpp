@@ -170,10 +170,11 @@ inline bool forward_regenerates(const egg_shape& s, float sigma, const void* A_c
     return sigma == 0.f || (s.rank == 1 && s.rows_per_member == 1 && !(s.antithetic && A_cache));
 }
 bool forward_fuses_next_projection(const egg_shape& s, egg_dtype io, egg_dtype yd, float sigma, egg_act act, bool resid);
-// A_ready: the factors A that eggroll_noise_gen would write for this layer, already drawn by the caller (NULL: drawn here)
+// regenerate: forward_regenerates of the call (A_cache may since have become A_ready); A_ready: the factors A that eggroll_noise_gen would write for
+// this layer, already drawn by the caller (NULL: drawn here)
 egg_status launch_forward_gemm(eggroll_ctx* c, const StreamKey& ka, const egg_shape& s, egg_dtype io, egg_dtype yd,
                                float sigma, egg_act act, const void* W, const void* X, void* Y, const float* t,
-                               void* A_cache, const void* resid = nullptr, const NextProjection* next = nullptr, const void* A_ready = nullptr);
+                               bool regenerate, void* A_cache, const void* resid, const NextProjection* next, const void* A_ready);
 egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& kb, const egg_shape& s,
                          egg_dtype noise_dtype, const float* fitness, float scale, int accumulate, float* G, void* W,
                          egg_dtype w_dtype, float lr, const void* A_cache, const void* B_cache, bool b_panel);

@@ -585,12 +585,12 @@ static egg_status launch_forward_t(eggroll_ctx* c, const StreamKey& ka, const eg
 
 egg_status launch_forward_gemm(eggroll_ctx* c, const StreamKey& ka, const egg_shape& s, egg_dtype io, egg_dtype yd,
                                float sigma, egg_act act, const void* W, const void* X, void* Y, const float* t,
-                               void* A_cache, const void* resid, const NextProjection* next, const void* A_ready)
+                               bool regenerate, void* A_cache, const void* resid, const NextProjection* next, const void* A_ready)
 {
     const bool bf = io == EGG_BF16;
     // rank 1 with one row per member (or the unperturbed pass): regenerate in the epilogue
     // (with antithetic pairs a kept cache has one entry per pair, not per row: that goes the materialised way)
-    if (forward_regenerates(s, sigma, A_cache)) {
+    if (regenerate) {
         return bf ? launch_forward_t<true, 1, true>(c, ka, s, yd, sigma, act, W, X, Y, t, A_cache, resid, next)
                   : launch_forward_t<false, 1, true>(c, ka, s, yd, sigma, act, W, X, Y, t, A_cache, resid, next);
     }

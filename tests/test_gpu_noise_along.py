@@ -26,6 +26,9 @@ def ctx():
     ("bf16", 8, 72, 1, 2, 1, False), ("bf16", 12, 72, 301, 3, 2, False), ("bf16", 24, 64, 85, 1, 16, False), ("bf16", 100, 520, 6, 1, 2, True),
     ("bf16", 1028, 264, 513, 1, 4, False), ("bf16", 200, 264, 514, 5, 8, True), ("bf16", 64, 72, 2, 1, 1, True),
     ("bf16", 2048, 8712, 256, 2, 4, False), ("bf16", 2056, 8712, 256, 2, 4, False),  # the most, and more, beside 70 KB of LDS
+    # pairs of one row at rank 1, whose A is read back from a cache and drawn again without one: both factors along, A apart, tiles of 32, 64, 128 and 256
+    ("bf16", 100, 72, 300, 1, 1, True), ("bf16", 1032, 264, 600, 1, 1, True), ("bf16", 2056, 520, 1100, 1, 1, True), ("bf16", 4104, 264, 4200, 1, 1, True),
+    ("f32", 72, 68, 300, 1, 1, True), ("f32", 1028, 260, 1100, 1, 1, True), ("f32", 2052, 260, 2100, 1, 1, True),
     ("f32", 4, 64, 300, 2, 1, False), ("f32", 36, 68, 258, 1, 2, True), ("f32", 260, 2052, 515, 3, 16, False), ("f32", 132, 128, 600, 4, 4, True),
 ])
 def test_the_factors_are_the_entry_points(ctx, dtype, d_out, d_in, N, S, rank, anti):
