@@ -208,7 +208,7 @@ __device__ __forceinline__ void tile_coords(int pid, int tiles_m, int tiles_n, i
 //   K-packed operands  (KMAJOR = true) : row idx % ROWS of chunk idx / ROWS;
 //                                        64 lanes read 64 consecutive rows of one chunk plane: 1 KB.
 // Addresses are a wave-uniform 64-bit base (tile origin + K offset, kept in scalar registers) plus a
-// loop-invariant 32-bit per-lane offset.
+// loop-invariant per-lane offset: of 32 bits, or of 64 in tiles of 32 rows, which take rows of any length.
 typedef __attribute__((address_space(3))) void egg_lds_void;
 typedef __attribute__((address_space(1))) const void egg_glb_void;
 // TAIL = false: the caller guarantees that K is a whole number of stages (no zero-page redirection, and the
@@ -217,7 +217,8 @@ template <int ROWS, int NT, bool KMAJOR, bool TAIL = true, int CHUNKS = 8>
 struct DmaLoader {
     static_assert(CHUNKS == 8 || KMAJOR, "row-major stages have 128 bytes a row");
     static constexpr int L = ROWS * CHUNKS / NT;
-    uint32_t off[L];
+    typedef std::conditional_t<ROWS <= 32, uint64_t, uint32_t> offset_t;
+    offset_t off[L];
     int chunk[TAIL ? L : 1];
     __device__ __forceinline__ void init(const Operand& o, int row0, int tid)
     {
@@ -228,7 +229,7 @@ struct DmaLoader {
             const int ch = KMAJOR ? idx / ROWS : (idx & 7) ^ ((row >> 1) & 7);
             if constexpr (TAIL) chunk[it] = ch;
             const int rl = min(row, o.rows - 1 - row0);  // rows past the end re-read the last valid row
-            off[it] = (uint32_t)((int64_t)rl * o.row_stride + (int64_t)ch * o.kc_stride);
+            off[it] = (offset_t)((int64_t)rl * o.row_stride + (int64_t)ch * o.kc_stride);
         }
     }
     // chunks past the end of K (only possible in the last stage) read the zero page instead
@@ -245,7 +246,7 @@ struct DmaLoader {
     }
 };
 
-// Largest per-lane byte offset the loader forms must fit 32 bits (checked on the host).
+// Largest per-lane byte offset the loader forms must fit 32 bits (checked on the host; not for tiles of 32 rows).
 inline bool operand_offsets_fit(const Operand& o, int tile_rows, int stage_chunks = 8)
 {
     return (int64_t)tile_rows * o.row_stride + stage_chunks * o.kc_stride < (int64_t(1) << 32);

@@ -184,7 +184,8 @@ egg_status launch_gemm_deep(eggroll_ctx* c, const char* name, const Operand& P, 
     auto kern = gemm_nt_deep_kernel<MT, T, T, 2, 2, false, DirectEpi<Row>>;
     const int tiles_m = (P.rows + T - 1) / T, tiles_n = (Q.rows + T - 1) / T;
     const size_t lds = 2 * gemm_lds_bytes<T, T>();
-    if (!operand_offsets_fit(P, T) || !operand_offsets_fit(Q, T)) return fail(c, EGG_EUNSUPPORTED, "operand strides too large for 32-bit tile offsets");
+    // (bf16 rows of any length in tiles of 32; fp32 rows of 32 M values and more are refused in every tile)
+    if (!(T == 32 && Row::IS_BF16) && (!operand_offsets_fit(P, T) || !operand_offsets_fit(Q, T))) return fail(c, EGG_EUNSUPPORTED, "operand strides too large for 32-bit tile offsets");
     const egg_status st = ensure_dynamic_lds(c, (const void*)kern, lds, "gemm smem attr");
     if (st != EGG_OK) return st;
     KernelScope ks(c, shaped_name(c, name, P.rows, kchunks * (Row::IS_BF16 ? 8 : 4)));

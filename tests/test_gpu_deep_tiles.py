@@ -61,3 +61,26 @@ def test_few_tiles(ctx, d_out, d_in, N, S, rank, anti, form):
     ref = pre if form == "plain" else 0.5 * pre * (1 + torch.erf(pre * math.sqrt(0.5)))
     ref = ref + R[:N * S].double() if form == "both" else ref
     assert ((Y.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-4 * (1 + pre.square().mean(1, keepdim=True).sqrt())).all()
+
+
+@pytest.mark.parametrize("sigma", [0.0, 0.5])
+def test_rows_of_more_than_32_bits_of_offset(ctx, sigma):
+    """A layer of a few outputs takes rows of any length: the last of these begins 4.4 GB behind the first."""
+    import torch
+    d_out, d_in, N = 32, (1 << 26) + (1 << 22) + 8, 2
+    bf, key = torch.bfloat16, eb.make_key(1, 2, 3)
+    g = torch.Generator("cuda").manual_seed(8)
+    W, X = (torch.randn((n, d_in), generator=g, device="cuda", dtype=bf) for n in (d_out, N))
+    Y = torch.full((N, d_out), float("nan"), dtype=bf, device="cuda")
+    assert (d_out - 1) * d_in * 2 > 1 << 32
+    ctx.eggroll_perturbed_forward(key, eb.make_shape(0, N, 1, d_out, d_in, 1), sigma, eb.EGG_ACT_NONE, W, X, Y)
+    A, B = (torch.empty((N, d, 1), dtype=bf, device="cuda") for d in (d_out, d_in))
+    ctx.eggroll_noise_gen(key, eb.make_shape(0, N, 1, d_out, d_in, 1), eb.EGG_BF16, eb.EGG_NORMAL, 0, A, B)
+    ref, t, step = torch.zeros((N, d_out), dtype=torch.float64, device="cuda"), torch.zeros((N, 1), dtype=torch.float64, device="cuda"), 1 << 22
+    for k in range(0, d_in, step):
+        x = X[:, k:k + step].double()
+        ref += x @ W[:, k:k + step].double().t().contiguous()
+        t += (x * B[:, k:k + step, 0].double()).sum(1, keepdim=True)
+    ref += sigma * t * A[:, :, 0].double()
+    # one rounding, and an fp32 sum of 2^21 steps that rounds at the size of the whole: 2^-24 sqrt(2^21) of its deviation, ten times
+    assert ((Y.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-3 * d_in ** 0.5 * (1 + sigma)).all()
