@@ -1,7 +1,7 @@
 """GPU: bf16 layers of few tiles, in 32 x 32 and 64 x 64 tiles with four stages of K in flight, on both sides of each line of the rule between
 them (on 256 CUs), with ragged K, rows and outputs.
 
-A call's rows are the same bits as in a call of eight times the members, which runs in large tiles; and one rounding from 64 bits, 2^-8 (plus what GELU's polynomial and the folded correction leave, 1e-4 of
+A call's rows are the same bits as in a call of sixteen times the members, which runs in tiles of 128 and more; and one rounding from 64 bits, 2^-8 (plus what GELU's polynomial and the folded correction leave, 1e-4 of
 the row's rms)."""
 import math
 
@@ -35,7 +35,8 @@ def test_few_tiles(ctx, d_out, d_in, N, S, rank, anti, form):
     import torch
     g = torch.Generator("cuda").manual_seed(d_in)
     bf = torch.bfloat16
-    many, sigma, key = 8 * N, 0.5, eb.make_key(1, 2, 3)
+    many, sigma, key = 16 * N, 0.5, eb.make_key(1, 2, 3)
+    assert -(-d_out // 64) * -(-many * S // 64) > 512
     W = (torch.randn((d_out, d_in), generator=g, device="cuda") * d_in ** -0.5).to(bf)
     X, R = (torch.randn((many * S, d), generator=g, device="cuda").to(bf) for d in (d_in, d_out))
 
