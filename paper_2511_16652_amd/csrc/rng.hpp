@@ -111,44 +111,30 @@ __host__ __device__ __forceinline__ uint32_t fast_div(const FastDiv& f, uint32_t
 }
 
 // byte -> integer on {-b..b}: m = 2b+1, q = 256/m; byte < q*m ? byte/q - b : 0.
-// qm = q*m and the reciprocal multiplier are precomputed on the host (see IntMap).
+// In 16 bits, in both halves of a word: (byte * mul2 + add2) >> shift2 is byte / q below q m and more than 2 b from there on.
 struct IntMap {
-    int bound;
-    uint32_t q, qm, magic;  // byte / q == (byte * magic) >> 16 for byte < 256
-    // the same in 16 bits, in both halves of a word: (byte * mul2 + add2) >> shift2 is byte / q below qm and more than 2 bound from there on
     uint32_t mul2, add2, shift2, bound2;
 };
 
 inline IntMap make_int_map(int bound)
 {
-    IntMap m;
-    m.bound = bound;
-    const uint32_t mm = 2u * (uint32_t)bound + 1u;
-    m.q = 256u / mm;
-    m.qm = m.q * mm;
-    m.magic = (65536u + m.q - 1u) / m.q;  // ceil(2^16 / q): exact for all byte < 256 (checked on the host)
-    m.mul2 = m.add2 = m.shift2 = 0;
+    const uint32_t m = 2u * (uint32_t)bound + 1u, q = 256u / m;
+    IntMap map{0, 0, 0, (uint32_t)bound * 0x10001u};
     // 2^s / q rounded up, or rounded down and applied to byte + 1: one of them does for every bound up to 127
-    for (uint32_t s = 0; s < 16 && !m.mul2; ++s)
-        for (uint32_t up = 0; up < 2 && !m.mul2; ++up) {
-            const uint32_t mul = up ? (1u << s) / m.q : ((1u << s) + m.q - 1u) / m.q, add = up ? mul : 0u;
+    for (uint32_t s = 0; s < 16 && !map.mul2; ++s)
+        for (uint32_t up = 0; up < 2 && !map.mul2; ++up) {
+            const uint32_t mul = up ? (1u << s) / q : ((1u << s) + q - 1u) / q, add = up ? mul : 0u;
             bool exact = mul && mul * 255u + add <= 65535u;
             for (uint32_t x = 0; x < 256 && exact; ++x) {
                 const uint32_t v = (x * mul + add) >> s;
-                exact = x < m.qm ? v == x / m.q : v > 2u * (uint32_t)bound;
+                exact = x < q * m ? v == x / q : v > 2u * (uint32_t)bound;
             }
-            if (exact) m.mul2 = mul * 0x10001u, m.add2 = add * 0x10001u, m.shift2 = s * 0x10001u;
+            if (exact) map.mul2 = mul * 0x10001u, map.add2 = add * 0x10001u, map.shift2 = s * 0x10001u;
         }
-    m.bound2 = (uint32_t)bound * 0x10001u;
-    return m;
+    return map;
 }
 
-__host__ __device__ __forceinline__ int int_from_byte(const IntMap& m, uint32_t byte)
-{
-    return byte < m.qm ? (int)((byte * m.magic) >> 16) - m.bound : 0;
-}
-
-// four packed int8 values from one word, two bytes at a time in 16 bits: a byte at or past qm has a quotient above 2 bound.  About
+// four packed int8 values from one word, two bytes at a time in 16 bits: a byte at or past q m has a quotient above 2 bound.  About
 // 15 instructions; byte by byte it was 32, beside the 67 of the generator for two words.
 __device__ __forceinline__ uint32_t int4_from_word(const IntMap& m, uint32_t w)
 {
