@@ -263,7 +263,7 @@ egg_status launch_embed_i8(eggroll_ctx* c, egg_key key, const egg_shape& s, int 
     return launch_embed(c, emb, tokens, A, B, Y, rows, D, anti, corr_shift);
 }
 
-// At D = 256 all of it is one kernel (k_egg_fused.hip); what follows is the general form.
+// At D = 256 all of it is one kernel (k_egg_fused.hip) where the shifts can be folded; what follows is the general form.
 // Scratch of one forward call: the rank-1 factors of all 6 L + 2 perturbed parameters (generated once per
 // call: a member's perturbation is fixed while it is evaluated, Alg. 1), the activations of one time
 // step, and a second copy of the recurrent state to ping-pong with S_out.
@@ -278,11 +278,11 @@ egg_status launch_egg_forward_i8(eggroll_ctx* c, egg_key key, const egg_shape& s
     const uint32_t first_id = (uint32_t)(anti ? s.member_begin / 2 : s.member_begin);
     const int os_d = 4 + ilog2(D) / 2, os_4d = os_d + 1;   // 16 sqrt(n) as a shift, n = D and 4 D
     auto pad = [](size_t b) { return (b + 255) & ~size_t(255); };
-    const size_t id_pad = (size_t)ids + 127;   // (the fused kernel reads whole workgroups, of up to 128 ids)
+    const bool fused = egg_fused_applies(D, int_bound, corr_shift, os_d);
+    const size_t id_pad = (size_t)ids + (fused ? 127 : 0);   // (it reads whole workgroups, of up to 128 ids)
     const size_t fD = pad(id_pad * D), f4D = pad(id_pad * 4 * D), f256 = pad(id_pad * 256);
     const size_t act = pad((size_t)rows * D), dots = pad((size_t)rows * sizeof(int));
     const size_t per_layer = 8 * fD + 2 * (f4D + fD);
-    const bool fused = egg_fused_applies(D, int_bound, corr_shift, os_d);
     const size_t n_dots = 4 + 2 * (size_t)L;   // u.B_Wf, u.B_Wh, f^.B_Uh, one for the MLP and the head; s.B_Uf twice per layer
     const size_t total = 2 * (f256 + fD) + (size_t)L * per_layer   // factors
                          + (fused ? egg_fused_weight_bytes(L)

@@ -1,5 +1,5 @@
-"""GPU: products too small for the chip-filling tiles (updates: 32 and 64 tiles with K split over four waves; bf16 layers: 32 tiles from
-memory, one 128 x 128 tile per CU with four stages in flight; fp32 layers: 32 tiles with four stages in flight), at the edges of their
+"""GPU: products too small for the chip-filling tiles (fp32 updates: 32 and 64 tiles with K split over four waves; bf16 updates and layers: 32 and 64 tiles,
+and one 128 x 128 tile per CU, with four stages in flight; fp32 layers: 32 tiles with four stages in flight), at the edges of their
 K ranges and of the rule between them, and the tiles that follow them.
 
 References in 64 bits from the library's own factors; fp32: 1e-5 of |value| + rms (sums of up to 2064 products in another order);
@@ -35,7 +35,7 @@ def factors(ctx, key, ids, n, rank, which, tdt, code):
     ("f32", 1028, 132, 260, 2, 1, 0),       # 33 x 17 tiles of 32
     ("bf16", 4, 8, 1, 1, 1, 0), ("bf16", 36, 24, 33, 1, 1, 1), ("bf16", 100, 520, 9, 3, 4, 0), ("bf16", 132, 2056, 5, 7, 16, 0),
     ("bf16", 520, 64, 33, 16, 2, 0),        # 17 x 17 tiles of 32
-    ("bf16", 1028, 64, 33, 16, 2, 0),       # 33 x 17: past the 32 form; one stage of K
+    ("bf16", 1028, 64, 33, 16, 2, 0),       # 33 x 17 of them, 17 x 9 of 64; one stage of K
     ("bf16", 1028, 136, 33, 16, 4, 0), ("bf16", 1028, 200, 33, 16, 8, 0), ("bf16", 1028, 256, 33, 16, 1, 0),   # two, three and four stages
     ("bf16", 1028, 512, 550, 2, 1, 1), ("bf16", 4100, 64, 1025, 2, 1, 1), ("bf16", 4100, 64, 2050, 1, 4, 0), ("bf16", 4100, 64, 2050, 1, 8, 1),   # past them all, fewer
     ("bf16", 4100, 72, 683, 3, 16, 0), ("bf16", 3076, 64, 4100, 1, 8, 0), ("bf16", 3076, 72, 1367, 3, 16, 0),   # than 15 rows: 128, 256 x 128 and 256 tiles
