@@ -262,6 +262,7 @@ enum PanelForm { PANEL_F16, PANEL_F32, PANEL_SPLIT };
 // products are those with the other panel's hi parts alone and keep their signs (hi times a mid part would not).
 __device__ __forceinline__ void split_large(float v, float (&part)[3])
 {
+#pragma clang fp contract(off)
     constexpr float MOST = 3.3895313892515355e38f;  // 2^127 (2 - 2^-7)
     part[0] = part[1] = 0.f;
     part[2] = v;
@@ -271,13 +272,15 @@ __device__ __forceinline__ void split_large(float v, float (&part)[3])
         part[2] = v - part[0] - part[1];
     }
 }
-// the parts of a and b, a word each
-__device__ __forceinline__ void split_bf16(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo)
+// the parts of a + ea and b + eb, a word each; ea, eb: what rounding a and b to 24 bits left (0 for values that are fp32).  Without contraction: a is a
+// product, of the generator or with the fitness, and a - hi would be formed from it unrounded, the parts of another factor than the fp32 one.
+__device__ __forceinline__ void split_bf16(float a, float b, float ea, float eb, uint32_t& hi, uint32_t& mid, uint32_t& lo)
 {
+#pragma clang fp contract(off)
     hi = pack_bf16x2(a, b);
     const float a1 = a - bf16_lo(hi), b1 = b - bf16_hi(hi);
     mid = pack_bf16x2(a1, b1);
-    lo = pack_bf16x2(a1 - bf16_lo(mid), b1 - bf16_hi(mid));
+    lo = pack_bf16x2(a1 - bf16_lo(mid) + ea, b1 - bf16_hi(mid) + eb);
     if (fmaxf(fabsf(a), fabsf(b)) > 3.38e38f) {
         float p[3], q[3];
         split_large(a, p);
@@ -326,6 +329,7 @@ __device__ __forceinline__ PanelChunks<FORM, RANK> draw_chunks(const StreamKey& 
     };
     if constexpr (RANK == 1) {
         float lo[EPC], hi[EPC];  // columns 2u and 2u + 1 of the members
+        float elo[EPC], ehi[EPC];  // (parts: what rounding f a left of it)
         float fs[EPC];
 #pragma unroll
         for (int e = 0; e < EPC; ++e) fs[e] = fs_of(kg * EPC + e);
@@ -339,9 +343,15 @@ __device__ __forceinline__ PanelChunks<FORM, RANK> draw_chunks(const StreamKey& 
                 lo[e] = bf16_lo(pk);
                 hi[e] = bf16_hi(pk);
             }
+            elo[e] = ehi[e] = 0.f;
             if constexpr (FIT) {
+                const float z0 = lo[e], z1 = hi[e];
                 lo[e] *= fs[e];
                 hi[e] *= fs[e];
+                if constexpr (FORM == PANEL_SPLIT) {
+                    elo[e] = fmaf(z0, fs[e], -lo[e]);
+                    ehi[e] = fmaf(z1, fs[e], -hi[e]);
+                }
             }
         }
         u32x4 c0, c1;
@@ -365,10 +375,10 @@ __device__ __forceinline__ PanelChunks<FORM, RANK> draw_chunks(const StreamKey& 
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
                 uint32_t p[3];
-                split_bf16(lo[2 * w], lo[2 * w + 1], p[0], p[1], p[2]);
+                split_bf16(lo[2 * w], lo[2 * w + 1], elo[2 * w], elo[2 * w + 1], p[0], p[1], p[2]);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) out.c[q][0][w] = p[q];
-                split_bf16(hi[2 * w], hi[2 * w + 1], p[0], p[1], p[2]);
+                split_bf16(hi[2 * w], hi[2 * w + 1], ehi[2 * w], ehi[2 * w + 1], p[0], p[1], p[2]);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) out.c[q][1][w] = p[q];
             }
@@ -404,9 +414,16 @@ __device__ __forceinline__ PanelChunks<FORM, RANK> draw_chunks(const StreamKey& 
                     o[b] = __builtin_bit_cast(uint32_t, p);
                     continue;
                 }
-            } else if constexpr (FIT) {
-                z0 *= fs[b];
-                z1 *= fs[b];
+            }
+            float e0 = 0.f, e1 = 0.f;
+            if constexpr (FIT && !(BF16 && RANK < 16)) {
+                const float p0 = z0 * fs[b], p1 = z1 * fs[b];
+                if constexpr (FORM == PANEL_SPLIT) {
+                    e0 = fmaf(z0, fs[b], -p0);
+                    e1 = fmaf(z1, fs[b], -p1);
+                }
+                z0 = p0;
+                z1 = p1;
             }
             if constexpr (BF16) {
                 h2 p;
@@ -415,7 +432,7 @@ __device__ __forceinline__ PanelChunks<FORM, RANK> draw_chunks(const StreamKey& 
                 o[b] = __builtin_bit_cast(uint32_t, p);
             } else if constexpr (FORM == PANEL_SPLIT) {
                 uint32_t p[3];
-                split_bf16(z0, z1, p[0], p[1], p[2]);
+                split_bf16(z0, z1, e0, e1, p[0], p[1], p[2]);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) out.c[q][0][b] = p[q];
             } else {
@@ -869,9 +886,9 @@ static egg_status launch_upd_gemm(eggroll_ctx* c, const char* name, const Operan
 // nearly empty last wave.  Whole updates, us, fp32 MFMAs / parts: 64 x 64: 1024 x 736, K = 192 15.6 / 13.6, 1400 x 1400, K = 192 22.7 / 17.7, 1000 59.4 /
 // 40.8; 1024 x 1024, K = 1024 40 / 31, 8000 216 / 144.  128 x 128: 2048 x 2048, K = 192 26.5 / 28.6, 384 41.0 / 38.0, 2048 161 / 108, 8000 568 / 366; 2100 x
 // 2100, K = 192 32.6 / 42.5, 384 54.2 / 57.6; 4096 x 4096, K = 512 152 / 122, 1024 283 / 204, 8000 2067 / 1380.  Fewer tiles are bound by latency.
-// Error against 64 bits, relative 2-norm, fp32 MFMAs / parts: all members with a fitness, 1024 x 1024, K = 192 1.30e-7 / 0.90e-7, 700 2.38e-7 / 1.72e-7, 2048 x
-// 2048, K = 700 4.8e-7 / 1.7e-7, 8000 1.60e-6 / 0.57e-6; fitness over eight decades, 700 1.09e-7 / 0.55e-7; sixteen members with one 6.8e-8 / 4.8e-8, four 5.1e-8 /
-// 4.0e-8, a single one 3.6e-8 / 3.7e-8.
+// Error against 64 bits, relative 2-norm, fp32 MFMAs / parts: all members with a fitness, 1024 x 1024, K = 192 1.32e-7 / 0.88e-7, 700 2.41e-7 / 1.69e-7, 2048 x
+// 2048, K = 700 4.8e-7 / 1.7e-7, 8000 1.60e-6 / 0.57e-6; fitness over eight decades, 700 1.10e-7 / 0.49e-7; sixteen members with one 7.8e-8 / 4.2e-8, four 4.4e-8 /
+// 3.0e-8, a single one 3.6e-8 / 2.6e-8 (fp32 rounds it at f a and at the end, parts hold f a to 2^-27 and round at the end).
 // (A caller's caches may hold any values: their updates stay on fp32 MFMAs.)
 static bool split_update(int64_t M, int64_t N, int64_t K, int compute_units)
 {
