@@ -278,7 +278,8 @@ typedef struct {
  * (both may be NULL when layers == 0); logits: int8 [steps][member_count][256].  Scratch held by the
  * context: about (18 layers + 2) D + 512 bytes per noise id for the factors, and either 11 D + 4 (4 + 2 layers) bytes per
  * member for one step's activations and dot products and, when steps > 1, one more copy of the state, or, at D = 256 with shifts
- * and noise whose products fit 32 bits (corr_shift 4 and bounds to 120, say), 786432 bytes per layer for the weights in another order.  Bit-exact.
+ * and noise whose products fit 32 bits (corr_shift 4 and bounds to 120, say), 786432 bytes per layer for the weights in another order
+ * (and factors of 127 ids more; where that is not to be had, the former).  Bit-exact.
  */
 egg_status eggroll_egg_forward_i8(eggroll_ctx* ctx, egg_key key, const egg_shape* shape, int layers, int int_bound,
                                   int corr_shift, int steps, const egg_model_i8* model, const uint8_t* tokens,

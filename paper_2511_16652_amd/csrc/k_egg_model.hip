@@ -278,18 +278,21 @@ egg_status launch_egg_forward_i8(eggroll_ctx* c, egg_key key, const egg_shape& s
     const uint32_t first_id = (uint32_t)(anti ? s.member_begin / 2 : s.member_begin);
     const int os_d = 4 + ilog2(D) / 2, os_4d = os_d + 1;   // 16 sqrt(n) as a shift, n = D and 4 D
     auto pad = [](size_t b) { return (b + 255) & ~size_t(255); };
-    const bool fused = egg_fused_applies(D, int_bound, corr_shift, os_d);
-    const size_t id_pad = (size_t)ids + (fused ? 127 : 0);   // (it reads whole workgroups, of up to 128 ids)
-    const size_t fD = pad(id_pad * D), f4D = pad(id_pad * 4 * D), f256 = pad(id_pad * 256);
     const size_t act = pad((size_t)rows * D), dots = pad((size_t)rows * sizeof(int));
-    const size_t per_layer = 8 * fD + 2 * (f4D + fD);
     const size_t n_dots = 4 + 2 * (size_t)L;   // u.B_Wf, u.B_Wh, f^.B_Uh, one for the MLP and the head; s.B_Uf twice per layer
-    const size_t total = 2 * (f256 + fD) + (size_t)L * per_layer   // factors
-                         + (fused ? egg_fused_weight_bytes(L)
-                                  : 7 * act + 4 * act               // y, u, y', a1, a3, f, f^; MLP hidden
-                                        + n_dots * dots + (T > 1 ? (size_t)L * act : 0));
+    size_t fD, f4D, f256;
+    auto scratch = [&](bool one_kernel) {
+        const size_t id_pad = (size_t)ids + (one_kernel ? 127 : 0);   // (it reads whole workgroups, of up to 128 ids)
+        fD = pad(id_pad * D); f4D = pad(id_pad * 4 * D); f256 = pad(id_pad * 256);
+        return 2 * (f256 + fD) + (size_t)L * (10 * fD + 2 * f4D)          // factors
+               + (one_kernel ? egg_fused_weight_bytes(L)
+                             : 7 * act + 4 * act                          // y, u, y', a1, a3, f, f^; MLP hidden
+                                   + n_dots * dots + (T > 1 ? (size_t)L * act : 0));
+    };
+    // (few members of many layers need less scratch pass by pass: where that of the one kernel is not to be had)
+    const bool fused = egg_fused_applies(D, int_bound, corr_shift, os_d) && try_reserve(c, c->gru, scratch(true));
     egg_status st;
-    if ((st = reserve(c, c->gru, total)) != EGG_OK) return st;
+    if ((st = reserve(c, c->gru, scratch(fused))) != EGG_OK) return st;
     char* p = (char*)c->gru.p;
     auto take = [&](size_t b) { char* q = p; p += b; return (int8_t*)q; };
     // all factors of the call in a few launches (twenty vectors each) instead of one for each of 12 L + 4 vectors

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import oracle
+from helpers import memory_left
 from paper_2511_16652_amd import binding as eb
 
 pytestmark = pytest.mark.gpu
@@ -46,3 +47,30 @@ def test_bit_exact(ctx, L, N, T, mb, anti, bound, cs):
     want, S_want = oracle.egg_forward_i8(SEED, STEP, LAYER, mb, N, D, L, b, cs, P, tok, S, antithetic=bool(anti))
     assert (S_out.cpu().numpy() == S_want).all()
     assert (logits.cpu().numpy() == want).all()
+
+
+def test_little_memory():
+    """The one kernel reads whole workgroups of factors and a copy of the weights in another order (here 550 MB, pass by pass 4 MB): without memory for
+    them the call runs pass by pass, the same bits."""
+    import torch
+    L, N = 400, 2
+    g = torch.Generator("cuda").manual_seed(1)
+    i8 = lambda *s: torch.randint(-40, 41, s, generator=g, device="cuda", dtype=torch.int8)  # noqa: E731
+    P = {"emb": i8(256, D), "ln1": i8(L, D), "gru_w": i8(L, 4, D, D), "gru_b": i8(L, 2, D), "ln2": i8(L, D), "mlp1": i8(L, 4 * D, D), "mlp2": i8(L, D, 4 * D),
+         "ln_out": i8(D), "head": i8(256, D)}
+    tok, S = torch.tensor([[3, 200]], dtype=torch.uint8, device="cuda"), i8(L, N, D)
+
+    def forward():
+        S_out, logits = torch.empty_like(S), torch.empty((1, N, 256), dtype=torch.int8, device="cuda")
+        c = eb.Context(0)
+        try:
+            c.eggroll_egg_forward_i8(eb.make_key(SEED, STEP, LAYER), eb.make_shape(0, N, 1, D, D, 1), L, 8, 4, 1, P, tok, S, S_out, logits)
+            torch.cuda.synchronize()
+        finally:
+            c.close()
+        return S_out, logits
+
+    want = forward()
+    with memory_left(300 << 20):
+        got = forward()
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
