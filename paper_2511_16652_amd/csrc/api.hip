@@ -145,13 +145,16 @@ egg_status forward_linear(eggroll_ctx* c, egg_key key, const egg_shape& shape, e
             t = (float*)c->t_buf.p;
         }
         const StreamKey ka = make_stream_key(key.seed, key.step, key.layer, 0), kb = make_stream_key(key.seed, key.step, key.layer, 1);
-        // few members with many rows: their rows go to several workgroups, and the factors are drawn for all of them in one launch
-        // (with A, which that layer needs as well); the entry point that allocates nothing has no place for them but the caller's cache
-        ProjectSplit split = project_split(c, shape, io_dtype, B_cache || !t_fixed);
         const int anti = shape.antithetic ? 2 : 1, esz = io_dtype == EGG_BF16 ? 2 : 4;
         const int64_t ids = shape.member_count / anti;
         NoiseJob jobs[2] = {{kb, (int64_t)shape.d_in * shape.rank, B_cache}, {ka, (int64_t)shape.d_out * shape.rank, A_cache}};
         const bool draw_A = !regenerate && (A_cache || !A_ready);
+        // few members with many rows: their rows go to several workgroups, and the factors are drawn for all of them in one launch
+        // (with A, which that layer needs as well); the entry point that allocates nothing has no place for them but the caller's cache.
+        // A that is not made of whole pieces (rank 1, 8 not a divisor of d_out) would be a launch of its own beside B's (us, so / every workgroup draws its member's B:
+        // 6 members x 16 rows, 16 -> 380 14.7 / 12.0; 64 x 64, 1024 -> 132 15.1 / 13.6; 22 x 128, 4096 -> 260 28.6 / 27.4).
+        const bool together = !draw_A || jobs[1].n % (16 / esz) == 0;
+        ProjectSplit split = project_split(c, shape, io_dtype, together && (B_cache || !t_fixed));
         if (draw_A && !A_cache) {
             if ((s = reserve(c, c->a_buf, (size_t)(ids * jobs[1].n) * esz)) != EGG_OK) return s;
             jobs[1].out = c->a_buf.p;

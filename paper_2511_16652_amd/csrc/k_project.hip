@@ -42,6 +42,7 @@ __global__ __launch_bounds__(256) void project_kernel(StreamKey kb, uint32_t mem
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x;
     const int64_t ml = blockIdx.x;  // local member
+    if (!READY && blockIdx.y) B_cache = nullptr;  // (the first part fills it)
     const int s_first = (int)blockIdx.y * part_rows, S = min(S_all, s_first + part_rows);
     const uint32_t member = member_begin + (uint32_t)ml;
     constexpr int EPC = BF16 ? 8 : 4;  // elements per 16-byte chunk of X (d_in is a multiple of it)
