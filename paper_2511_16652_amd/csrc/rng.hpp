@@ -6,6 +6,7 @@
 // key is wave-uniform, so the key schedule lives in scalar registers.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <array>
 #include <stdint.h>
 
 namespace egg {
@@ -116,22 +117,30 @@ struct IntMap {
     uint32_t mul2, add2, shift2, bound2;
 };
 
+// (bound <= 127; the search takes about a microsecond, which every launch of the generator paid: all of them once in a process)
 inline IntMap make_int_map(int bound)
 {
-    const uint32_t m = 2u * (uint32_t)bound + 1u, q = 256u / m;
-    IntMap map{0, 0, 0, (uint32_t)bound * 0x10001u};
-    // 2^s / q rounded up, or rounded down and applied to byte + 1: one of them does for every bound up to 127
-    for (uint32_t s = 0; s < 16 && !map.mul2; ++s)
-        for (uint32_t up = 0; up < 2 && !map.mul2; ++up) {
-            const uint32_t mul = up ? (1u << s) / q : ((1u << s) + q - 1u) / q, add = up ? mul : 0u;
-            bool exact = mul && mul * 255u + add <= 65535u;
-            for (uint32_t x = 0; x < 256 && exact; ++x) {
-                const uint32_t v = (x * mul + add) >> s;
-                exact = x < q * m ? v == x / q : v > 2u * (uint32_t)bound;
-            }
-            if (exact) map.mul2 = mul * 0x10001u, map.add2 = add * 0x10001u, map.shift2 = s * 0x10001u;
+    static const std::array<IntMap, 128> maps = [] {
+        std::array<IntMap, 128> all{};
+        for (uint32_t b = 0; b < 128; ++b) {
+            const uint32_t m = 2u * b + 1u, q = 256u / m;
+            IntMap& map = all[b];
+            map.bound2 = b * 0x10001u;
+            // 2^s / q rounded up, or rounded down and applied to byte + 1: one of them does for every bound up to 127
+            for (uint32_t s = 0; s < 16 && !map.mul2; ++s)
+                for (uint32_t up = 0; up < 2 && !map.mul2; ++up) {
+                    const uint32_t mul = up ? (1u << s) / q : ((1u << s) + q - 1u) / q, add = up ? mul : 0u;
+                    bool exact = mul && mul * 255u + add <= 65535u;
+                    for (uint32_t x = 0; x < 256 && exact; ++x) {
+                        const uint32_t v = (x * mul + add) >> s;
+                        exact = x < q * m ? v == x / q : v > 2u * b;
+                    }
+                    if (exact) map.mul2 = mul * 0x10001u, map.add2 = add * 0x10001u, map.shift2 = s * 0x10001u;
+                }
         }
-    return map;
+        return all;
+    }();
+    return maps[bound];
 }
 
 // four packed int8 values from one word, two bytes at a time in 16 bits: a byte at or past q m has a quotient above 2 bound.  About
