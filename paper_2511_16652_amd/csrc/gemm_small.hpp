@@ -1,5 +1,5 @@
 // NT contractions for products too small to fill the chip with the tiles of gemm_core.hpp:  C[m][n] = sum_k P[m][k] Q[n][k], in two forms: K split over the
-// waves of a tile (fp32 updates of few tiles, and bf16 ones of one 64 x 64 tile to a CU with deep K), and, at the end, the tiles with four stages of K in LDS
+// waves of a tile (fp32 updates of few tiles, and bf16 ones of 64 x 64 tiles with deep K), and, at the end, the tiles with four stages of K in LDS
 // that keep K whole (layers; the updates that run them are chosen in k_update.hip).
 //
 // gemm_small_kernel: a workgroup owns a T x T tile (T = 32 or 64) and its four waves split K: each takes a quarter of it over the whole tile,
@@ -15,7 +15,7 @@ namespace egg {
 
 // Tile of a small update of M x N, in whichever of the two forms; 0 where the tiles of 128 and more do better.  Measured over 256 .. 4096 rows and
 // columns and K of 64 .. 4096 on 256 CUs (us, gemm_small_kernel in bf16 against those; the lines lie where the last listed shape still gains; the tiles with four
-// stages, which bf16 takes now but for one case, are faster than it and so gain up to the same lines at least):
+// stages, which bf16 takes now but for deep K, are faster than it and so gain up to the same lines at least):
 //   32: up to two tiles per CU   256 x 256 x 4096: 26 / 56
 //   64: up to two tiles per CU   2048 x 1024 x 4096: 57 / 68 (2048 x 2048: 86 / 78)
 inline int small_tile(int64_t M, int64_t N, int compute_units)

@@ -985,10 +985,15 @@ egg_status launch_update(eggroll_ctx* c, const StreamKey& ka, const StreamKey& k
     if (bf && small) {
         // four stages of K in flight through LDS (whole updates, us, K split over the waves of a tile / this): tiles of 32 256 x 256, K = 2048 17.9 / 15.3,
         // 8000 37.7 / 30.2, 1024 x 512, K = 1024 15.0 / 13.2; tiles of 64 1024 x 1024, K = 300 13.2 / 12.1, 2320 x 608, K = 300 16.2 / 14.5, 8000
-        // 104 / 103.  With one tile of 64 to a CU deeper K is better split: 1024 x 1024, K = 1024 16.1 / 16.6, 8000 58 / 61.
+        // 104 / 103.  With one tile of 64 to a CU deeper K is better split: 1024 x 1024, K = 1024 16.1 / 16.6, 8000 58 / 61.  So it is from 1.75 tiles to a CU on where the
+        // tiles of a row of G are 16, 24 .. and each of the 8 XCDs, workgroups going round them, keeps to the same two or more of its columns: 512 x 4096, K = 1500
+        // 30.9 / 32.4, 2000 37 / 42, 6000 75 / 79; 2048 x 1024, K = 2000 34.5 / 35.5, 4096 53.0 / 54.9; 1024 x 2048, K = 4096 50.7 / 51.5.  Otherwise: 4096 x 512 (8 tiles a
+        // row), K = 2000 44.0 / 42.6, 8000 126 / 102; 1472 x 1344 (21), K = 2000 38.5 / 33.2; 1280 x 1024 (1.25 to a CU), K = 2000 31.2 / 30.6.
         if (small == 32) return launch_upd_gemm16<MmaF16Blk16, 32, 32, 2, 2, true>(c, "update_gemm_f16_small", Q, P, (int)kgroups, ea);
         const int64_t t64 = ((s.d_out + 63) / 64) * (int64_t)((s.d_in + 63) / 64);
-        if (t64 > c->compute_units || K <= 512) return launch_upd_gemm16<MmaF16Blk16, 64, 64, 2, 2, true>(c, "update_gemm_f16_small", Q, P, (int)kgroups, ea);
+        const int row64 = (s.d_in + 63) / 64;
+        const bool split_k = t64 <= c->compute_units ? K > 512 : K > 1024 && row64 >= 16 && row64 % 8 == 0 && 4 * t64 >= 7 * (int64_t)c->compute_units;
+        if (!split_k) return launch_upd_gemm16<MmaF16Blk16, 64, 64, 2, 2, true>(c, "update_gemm_f16_small", Q, P, (int)kgroups, ea);
         return launch_upd_small<MmaF16, 64>(c, "update_gemm_f16_small", Q, P, (int)kgroups, ea);
     }
     if (small == 32) return launch_upd_small<MmaF32, 32>(c, "update_gemm_f32", Q, P, (int)kgroups, ea);

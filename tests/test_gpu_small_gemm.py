@@ -210,3 +210,26 @@ def test_counted_waits_equal_waits_for_everything(ctx, kind, stages):
                 ctx.eggroll_set_conservative_waits(0)
             res.append(Y)
         assert torch.equal(res[0], res[1]) and torch.isfinite(res[0].float()).all()
+
+
+@pytest.mark.parametrize("d_out,d_in,N,rank", [
+    (2048, 1024, 1024, 1), (2048, 1024, 1025, 1), (1980, 1012, 515, 2),    # both sides of K = 1024 beside 16 tiles a row, ragged
+    (512, 4096, 257, 4), (4096, 512, 1025, 1), (1472, 1344, 1025, 1), (1728, 1024, 1025, 1), (1792, 1024, 1025, 1),   # 64, 8 and 21 tiles a row; 432 tiles and 448
+])
+def test_bf16_update_of_deep_K(ctx, d_out, d_in, N, rank):
+    """Tiles of 64 x 64 with K whole or split over the waves.  f a is rounded to fp16 once, 2^-11 of a term at most, uniformly: 2^-12 of the terms' norm with room to
+    spare for the fp32 sums (1e-6); a single entry six times that."""
+    import torch
+    key, shape = eb.make_key(1, 2, 3), eb.make_shape(0, N, 1, d_out, d_in, rank)
+    A, B = (torch.empty((N, d, rank), dtype=torch.bfloat16, device="cuda") for d in (d_out, d_in))
+    ctx.eggroll_noise_gen(key, shape, eb.EGG_BF16, eb.EGG_NORMAL, 0, A, B)
+    f = torch.randn(N, generator=torch.Generator("cuda").manual_seed(N), device="cuda")
+    G, Gc = (torch.full((d_out, d_in), float("nan"), device="cuda") for _ in range(2))
+    ctx.eggroll_update(key, shape, eb.EGG_BF16, f, 1.0, 0, G)
+    ctx.eggroll_update(key, shape, eb.EGG_BF16, f, 1.0, 0, Gc, None, 0.0, A, B)
+    assert torch.equal(G, Gc)
+    a, b = (F.double().transpose(1, 2).reshape(N * rank, -1) for F in (A, B))
+    a = a * f.double().repeat_interleave(rank)[:, None]
+    ref, s = a.t().contiguous() @ b, (a.square().t().contiguous() @ b.square()).sqrt()
+    err = (G.double() - ref).abs()
+    assert err.norm() <= 2.0 ** -12 * s.norm() and (err <= 6 * 2.0 ** -12 * s).all()
