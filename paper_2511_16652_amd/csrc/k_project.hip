@@ -617,13 +617,15 @@ ProjectSplit project_split(const eggroll_ctx* c, const egg_shape& shape, egg_dty
 // (us, apart / along): 256 -> 256, 256 members x 4 rows, rank 4 13.0 / 9.1; 1024 -> 1024, 256 x 16, rank 8 27.6 / 24.0; 8192 -> 8192, 1024 x 1,
 // rank 4 246.0 / 240.2; 1024 -> 1024, 4096 x 4, rank 16 243 / 237.  They take the LDS of the members' workgroups though, so where that leaves
 // one workgroup on a CU, only up to four times the CUs of them: 8192 -> 2048, 64 x 16, rank 8 84.7 / 81.7, but 1000 x 4 267 / 272 and fp32
-// 2048 -> 2048, 512 x 4, rank 16 263 / 293.  Rows in several parts have their factors, A too, from a launch before.
+// 2048 -> 2048, 512 x 4, rank 16 263 / 293.  Where it leaves two of them, fp32 factors, whose normals take longer chains of instructions, only up to 80 times: 1024 -> 2048, 600 x 4,
+// rank 16 (75 times) 210 / 205, 1000 x 2 (125 times) 188 / 197, 4096 x 2 676 / 727; in bf16 they are level at 256 times and gain below.  Rows in several parts have their factors, A too, from a launch before.
 bool project_draws_along(const eggroll_ctx* c, const egg_shape& shape, egg_dtype io, const ProjectSplit& split, const NoisePiece& along)
 {
     const int64_t ids = shape.antithetic ? shape.member_count / 2 : shape.member_count, wgs = (along.total + 255u) / 256u;
     if (split.parts > 1 || ids + wgs >= int64_t(1) << 24) return false;  // (2^32 threads to a launch)
     const int64_t lds = shape.rows_per_member == 1 && shape.rank > 1 ? 0 : (int64_t)shape.d_in * shape.rank * (io == EGG_BF16 ? 2 : 4);
-    return lds <= PANEL_BYTES / 2 || wgs <= 4 * (int64_t)c->compute_units;
+    const int64_t most = lds > PANEL_BYTES / 2 ? 4 : io == EGG_F32 && 3 * lds > 160 * 1024 ? 80 : wgs;
+    return wgs <= most * c->compute_units;
 }
 
 egg_status launch_project(eggroll_ctx* c, const StreamKey& kb, const egg_shape& s, egg_dtype io, const void* X,

@@ -31,6 +31,7 @@ def ctx():
     ("f32", 72, 68, 300, 1, 1, True), ("f32", 1028, 260, 1100, 1, 1, True), ("f32", 2052, 260, 2100, 1, 1, True),
     # few members with many rows and A of half pieces: each of several workgroups draws its member's B, the first fills the cache
     ("bf16", 380, 16, 6, 16, 1, False), ("bf16", 100, 24, 2, 17, 1, False), ("bf16", 20, 4104, 4, 40, 1, True), ("bf16", 4, 66000, 3, 70, 1, False),
+    ("f32", 2048, 1024, 640, 2, 16, False), ("f32", 2052, 1024, 640, 2, 16, False),   # the same beside 64 KB, in fp32
     ("f32", 4, 64, 300, 2, 1, False), ("f32", 36, 68, 258, 1, 2, True), ("f32", 260, 2052, 515, 3, 16, False), ("f32", 132, 128, 600, 4, 4, True),
 ])
 def test_the_factors_are_the_entry_points(ctx, dtype, d_out, d_in, N, S, rank, anti):
